@@ -3,12 +3,12 @@
 // gather of the input tile and the scatter (or scatter-add, Sec. 3.4) of the output block
 // happen inside the same kernel, so the tile stacks never reach HBM.
 //
-// Two kernels here, two more behind conv16_try / conv3_try (conv16.hip: 3x3 stride 1 on tiles whose sides are
-// multiples of 16 with 32 or 64 input channels; conv3.hip: every other 3x3 case the matrix cores can take), which
-// are asked first:
+// Two kernels here, three more behind conv16_try / conv3_try (conv16.hip: 3x3 stride 1 on tiles whose sides are
+// multiples of 16 with 32 or 64 input channels; conv3.hip: every other 3x3 case the 16-bit matrix instructions can
+// take) and conv_f32_try (conv_f32.hip: fp32 arithmetic, for float32 and for channel counts the 16-bit kernels do not
+// take), which are asked first:
 //   conv_direct  any shape, any of f32/bf16/f16: one thread per output element, fp32 FMA chain.
-//                Used for f32 (there is no fp32 MFMA worth using at these sizes) and for channel
-//                counts the MFMA path does not take.
+//                Left for tiles so wide that the rows of 64 output pixels do not fit LDS (from about 1100 pixels).
 //   conv_mfma    bf16/f16 with Cin % 8 == 0 and Cout % 8 == 0, kernel sizes other than 3x3 (and 3x3 tiles too
 //                large for the other kernels' LDS plans): implicit GEMM on the matrix cores.
 //                Per workgroup: up to 256 output pixels x 64 output channels, fp32 accumulators in
@@ -33,7 +33,7 @@ __global__ __launch_bounds__(256) void conv_direct(ConvParams p) {
     typedef typename Elem<DT>::T T;
     const T *in = (const T *)p.in;
     T *out = (T *)p.out;
-    const T *w = (const T *)p.w;  // HWIO
+    const T *w = (const T *)p.w;  // fma_weight_index
     const int nact = min(*p.count, p.cap);
     const uint32_t per_tile = (uint32_t)p.oh * p.ow * p.Cout;
     const FastDiv div_cout = p.div_cv;  // reused: divides by Cout in this kernel
@@ -63,8 +63,9 @@ __global__ __launch_bounds__(256) void conv_direct(ConvParams p) {
                     } else {
                         src = in + (((size_t)b * p.th + yy) * p.tw + xx) * p.Cin;
                     }
-                    const T *wp = w + ((size_t)(r * p.kw + t) * p.Cin) * p.Cout + o;
-                    for (int c = 0; c < p.Cin; ++c) acc = fmaf(Elem<DT>::load(src + c), Elem<DT>::load(wp + (size_t)c * p.Cout), acc);
+                    for (int c = 0; c < p.Cin; ++c)
+                        acc = fmaf(Elem<DT>::load(src + c),
+                                   Elem<DT>::load(w + fma_weight_index(r * p.kw + t, c, o, p.kh * p.kw, (p.Cin + 7) >> 3)), acc);
                 }
             if (p.relu) acc = fmaxf(acc, 0.f);
             if (FUSED) {
@@ -151,12 +152,19 @@ __global__ void pack_mfma32_weights(const T *__restrict__ w, T *__restrict__ pac
     }
 }
 
+// fp32 order (fma_weight_index), for float32 and for 16-bit types of widths the matrix kernels above do not take
 template <typename T>
-__global__ void copy_weights(const T *__restrict__ w, T *__restrict__ packed, size_t total, int taps, int Cin, int Cout,
-                             int transposed) {
+__global__ void pack_fma_weights(const T *__restrict__ w, T *__restrict__ packed, size_t total, int taps, int Cin, int Cout,
+                                 int transposed) {
+    const int C8 = (Cin + 7) >> 3;
     for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (size_t)gridDim.x * blockDim.x) {
-        const int o = (int)(idx % Cout), c = (int)((idx / Cout) % Cin), tap = (int)(idx / ((size_t)Cout * Cin));
-        packed[idx] = w[weight_index(tap, c, o, taps, Cin, Cout, transposed)];
+        const int lane = (int)(idx >> 1) & 63;
+        const size_t rest = idx >> 7;
+        const int tap = (int)(rest % taps);
+        const int c = (int)((rest / taps) % C8) * 8 + (lane >> 4) * 2 + (int)(idx & 1), o = (int)(rest / taps / C8) * 16 + (lane & 15);
+        T v = 0;
+        if (c < Cin && o < Cout) v = w[weight_index(tap, c, o, taps, Cin, Cout, transposed)];
+        packed[idx] = v;
     }
 }
 
@@ -356,7 +364,7 @@ static size_t packed_elems(sbnet_dtype dt, int kh, int kw, int Cin, int Cout) {
         const size_t CinP = ((size_t)Cin + 31) / 32 * 32, CoutP = ((size_t)Cout + 63) / 64 * 64;
         return 2 * (size_t)kh * kw * CinP * CoutP;      // 16x16x32 operand order, then 32x32x16 operand order
     }
-    return (size_t)kh * kw * Cin * Cout;
+    return (size_t)kh * kw * (((size_t)Cin + 7) / 8 * 8) * (((size_t)Cout + 15) / 16 * 16);   // fma_weight_index
 }
 
 static sbnet_status check_conv_shape(const char *who, sbnet_dtype dt, int cap, int th, int tw, int Cin, int kh,
@@ -388,6 +396,7 @@ static sbnet_status run_conv(const char *who, sbnet_dtype dt, ConvParams &p, hip
     if (conv3_try(dt, FUSED, p, s, &st16, who)) return st16;
 
     if (!use_mfma(dt, p.Cin, p.Cout)) {
+        if (conv_f32_try(dt, FUSED, p, s, &st16, who)) return st16;
         p.div_cv = make_fastdiv(p.Cout);
         const long long per_tile = M * p.Cout;
         dim3 grid((unsigned)((per_tile + 255) / 256 > 64 ? 64 : (per_tile + 255) / 256), (unsigned)(p.cap > 4096 ? 4096 : p.cap));
@@ -468,10 +477,10 @@ static sbnet_status pack_entry(const char *who, const void *w_hwio, sbnet_dtype 
         hipLaunchKernelGGL(pack_mfma32_weights<uint16_t>, dim3(grid), dim3(256), 0, s, (const uint16_t *)w_hwio,
                            (uint16_t *)w_packed + elems / 2, kh * kw, Cin, Cout, CinP, ngroups, transposed);
     } else if (dtype == SBNET_F32) {
-        hipLaunchKernelGGL(copy_weights<uint32_t>, dim3(grid), dim3(256), 0, s, (const uint32_t *)w_hwio,
+        hipLaunchKernelGGL(pack_fma_weights<uint32_t>, dim3(grid), dim3(256), 0, s, (const uint32_t *)w_hwio,
                            (uint32_t *)w_packed, elems, kh * kw, Cin, Cout, transposed);
     } else {
-        hipLaunchKernelGGL(copy_weights<uint16_t>, dim3(grid), dim3(256), 0, s, (const uint16_t *)w_hwio,
+        hipLaunchKernelGGL(pack_fma_weights<uint16_t>, dim3(grid), dim3(256), 0, s, (const uint16_t *)w_hwio,
                            (uint16_t *)w_packed, elems, kh * kw, Cin, Cout, transposed);
     }
     return launch_status(who);

@@ -144,6 +144,14 @@ __device__ __forceinline__ void buf_store16(__amdgpu_buffer_rsrc_t r, uint32_t o
 bool conv16_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t s, sbnet_status *st, const char *who);
 // the same decision without a launch (p.oh, p.ow set)
 bool conv16_accepts(sbnet_dtype dt, bool fused, const ConvParams &p);
+// conv_f32.hip: the same contract for fp32 arithmetic (float32 of any width, 16-bit types of widths the others do not take);
+// p.oh, p.ow, p.div_ow, p.div_tw set.  Weights in the order of fma_weight_index.
+bool conv_f32_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t s, sbnet_status *st, const char *who);
+// Packed order of those weights: [o / 16][c / 8][tap][lane][2], lane = (c % 8) / 2 * 16 + o % 16, element c % 2 (the operand
+// order of v_mfma_f32_16x16x4_f32), zero where c >= Cin or o >= Cout.
+__host__ __device__ __forceinline__ size_t fma_weight_index(int tap, int c, int o, int taps, int C8) {
+    return (((size_t)(o >> 4) * C8 + (c >> 3)) * taps + tap) * 128 + (((c & 7) >> 1) * 16 + (o & 15)) * 2 + (c & 1);
+}
 // conv3.hip: the same contract for the LDS-tiled 3x3 kernel (any stride, tile size and channel counts that are multiples of 8).
 bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t s, sbnet_status *st, const char *who);
 

@@ -412,6 +412,53 @@ def test_sparse_bn_apply_and_backward(H, W, C, bo, N, dtype, relu):
         assert torch.equal(dx, dx2) and torch.equal(dgam, dgam2) and torch.equal(dbet, dbet2)
 
 
+# --------------------------------------------------------------------------- fp32 convolution
+F32_CONV_CASES = [
+    # H, W, Cin, Cout, k, s, bo, N, dtype: items are 64 output pixels x up to 64 channels, chunks whole groups of 8 channels
+    (24, 20, 1, 1, 3, 1, 8, 1, "f32"),       # the smallest: one channel in, one out
+    (33, 41, 3, 17, 3, 1, 16, 2, "f32"),     # scalar staging, a second block of output channels with one channel
+    (30, 30, 24, 24, 3, 1, 15, 1, "f32"),    # 225 pixels: a last pass of 33, rows that straddle passes
+    (40, 36, 46, 38, 3, 1, 12, 1, "f32"),    # six groups of 8 channels, the last one partial
+    (36, 36, 64, 80, 3, 1, 16, 1, "f32"),    # several chunks and two output groups of three blocks, the last one empty
+    (20, 20, 132, 64, 3, 1, 10, 1, "f32"),   # many chunks
+    (26, 26, 12, 20, 5, 2, 4, 1, "f32"),     # 25 taps, stride 2
+    (16, 150, 8, 16, 1, 1, 100, 1, "f32"),   # 1x1, output rows longer than a pass
+    (32, 32, 5, 9, 3, 2, 8, 2, "bf16"),      # widths the 16-bit kernels do not take
+    (32, 32, 16, 21, 3, 1, 8, 1, "f16"),
+    (8, 1400, 4, 4, 3, 1, 1300, 1, "f32"),   # rows too wide for LDS: the one-thread-per-element kernel
+]
+
+
+@pytest.mark.parametrize("H,W,Cin,Cout,k,s,bo,N,dtype", F32_CONV_CASES)
+def test_fp32_convolution_unfused_and_fused(H, W, Cin, Cout, k, s, bo, N, dtype):
+    """fp32 products and sums of up to 25 * 132 terms: rounding of the sum below 2^-24 * sqrt(3300) * 3 = 1e-5 of the
+    result's RMS with random signs; 16-bit results one rounding more (the tolerances of CONV_TOL)."""
+    step("fp32 conv %s" % ((H, W, Cin, Cout, k, s, bo, N, dtype),))
+    r = gen.rng_for(12, H * 1000 + W + Cin)
+    g_in, g_out, Ho, Wo = sb.geometry(H, W, k, s, bo)
+    x = gen.activations(r, (N, H, W, Cin), dtype)
+    w = gen.conv_weights(r, k, k, Cin, Cout, dtype)
+    b = gen.bias_vector(r, Cout)
+    y0 = gen.activations(r, (N, Ho, Wo, Cout), dtype)
+    tol = 1e-5 if dtype == "f32" else CONV_TOL[dtype]
+    wp = sb.pack_weights(to_dev(w, dtype))
+    for dens in (0.0, 1.0) if bo > 1000 else (0.0, 0.02, 1.0):
+        mask = (r.random((N, Ho, Wo)) < dens).astype(np.float32)
+        idx = orc.reduce_mask(mask, ogeom(g_out))
+        d_idx, d_cnt = dev_indices(idx, len(idx) + 2)
+        for add, relu in ((False, True), (True, False)):
+            y = to_dev(y0, dtype)
+            sb.sparse_conv(to_dev(x, dtype), d_idx, d_cnt, g_in, g_out, wp, torch.from_numpy(b).cuda(), y, stride=s, relu=relu, add=add)
+            ref = orc.sparse_conv_tiled(x, idx, ogeom(g_in), ogeom(g_out), w, b, y0, relu=relu, add=add, stride=s)
+            assert_close(to_host(y), ref, tol, "fused add=%d" % add)
+        if not len(idx):
+            continue
+        tiles = sb.sparse_gather(to_dev(x, dtype), d_idx, d_cnt, g_in)
+        out = sb.conv_on_tiles(tiles, d_cnt, wp, torch.from_numpy(b).cuda(), stride=s, relu=False)[:len(idx)]
+        ref = orc.conv_valid(to_host(tiles)[:len(idx)], w, b, stride=s)
+        assert_close(to_host(out), ref, tol, "unfused")
+
+
 # --------------------------------------------------------------------------- convolution on tiles
 CONV_CASES = [
     # B, th, tw, Cin, Cout, k, s, dtype, relu, bias
