@@ -4,10 +4,16 @@
 // gather and needs no kernel of its own.)
 //
 // The paper adds with atomics.  Here the sum is pulled instead of pushed: a small map from block coordinates to
-// the block's position in the index list is built first (two tiny kernels), then every cell of the block grid
-// (bstride_h x bstride_w pixels) looks up the at most (R+1)^2 tiles that can cover it, R = ceil((bsize - bstride) /
-// bstride), and each of its pixels adds their contributions in ascending (by, bx) order, in fp32, onto dx, rounding
-// once.  No atomics, results do not depend on scheduling, every dx vector is read and written once, whole vectors.
+// the block's position in the index list is built first, then every pixel's contributions are added in ascending
+// (by, bx) order, in fp32, onto dx, rounding once.  No atomics, results do not depend on scheduling, every dx vector
+// is read and written once, whole vectors.  Two kernels do that:
+//   gb_tiles       tiles that reach over at most one following block per axis (any 3x3, blocks of at least half the
+//                  kernel otherwise): work items are pieces of active tiles; a pixel that several tiles cover belongs
+//                  to the first of them.
+//   gb_cells       tiles that reach further, and dense lists of small cells: work items are cells of the block grid
+//                  (bstride_h x bstride_w pixels), each looking up the at most (R+1)^2 tiles that can cover it,
+//                  R = ceil((bsize - bstride) / bstride).
+// gb_either holds both and lets the device-side count pick.
 #include "tile_add.h"
 
 namespace sbnet {
@@ -101,12 +107,13 @@ __device__ __forceinline__ void make_vec(uint4 &v, const uint32_t *w) { v = make
 __device__ __forceinline__ void make_vec(uint2 &v, const uint32_t *w) { v = make_uint2(w[0], w[1]); }
 __device__ __forceinline__ void make_vec(uint32_t &v, const uint32_t *w) { v = w[0]; }
 
-// RM: largest reach (in cells) this instantiation handles; U vectors per thread are processed together, all of
+// U vectors per thread are processed together, all of
 // their loads (tile gradients and dx) issued before the first is used: a thread's memory round trips overlap
 // instead of adding up (more than two at a time was measured slower: fewer workgroups fit a CU).
+// RM: largest reach in cells.
 template <typename V, int DT, int RM, int U>
-__global__ __launch_bounds__(kGbThreads) void gb_accumulate(V *__restrict__ dx, const V *__restrict__ dtiles,
-                                                            const int32_t *__restrict__ map, GbParams p) {
+__device__ __forceinline__ void gb_cells(V *__restrict__ dx, const V *__restrict__ dtiles, const int32_t *__restrict__ map,
+                                         const GbParams &p) {
     constexpr int NW = Words<V>::N, NA = Acc<DT>::N;
     constexpr int NT = (RM + 1) * (RM + 1);
     const uint32_t ncells = (uint32_t)p.N * p.cells_h * p.cells_w;
@@ -181,23 +188,151 @@ __global__ __launch_bounds__(kGbThreads) void gb_accumulate(V *__restrict__ dx, 
     }
 }
 
+// Piece `seg` of active tile b.  Every pixel of the tile looks which neighbouring tiles cover it too (at most one
+// vertically, one horizontally and their diagonal); the first existing one in (by, bx) order owns the pixel and adds all
+// of them, so what an owner adds after its own value comes in ascending order by itself.
+// Bound by HBM (tile gradients read once, dx read and written once).  A cell per workgroup, as in gb_cells, left most
+// workgroups without work and the others with a chain of up to sixteen memory round trips.
+template <typename V, int DT, int U>
+__device__ __forceinline__ void gb_tiles(V *__restrict__ dx, const V *__restrict__ dtiles,
+                                         const int32_t *__restrict__ map, const int32_t *__restrict__ indices, uint32_t nact,
+                                         int segs, uint32_t piece, const FastDiv &div_segs, const FastDiv &div_tr, const GbParams &p) {
+    constexpr int NW = Words<V>::N, NA = Acc<DT>::N;
+    // the first item's block is requested beside the count (past the count, and the list, it is not used)
+    uint32_t b = min(fdiv(blockIdx.x, div_segs), (uint32_t)p.cap - 1u);
+    int n = indices[3 * b], by = indices[3 * b + 1], bx = indices[3 * b + 2];
+    const uint32_t items = nact * (uint32_t)segs;
+    const int ovh = p.g.bsize_h - p.g.bstride_h, ovw = p.g.bsize_w - p.g.bstride_w;
+    for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
+        if (item != blockIdx.x) {
+            b = fdiv(item, div_segs);
+            n = indices[3 * b]; by = indices[3 * b + 1]; bx = indices[3 * b + 2];
+        }
+        const uint32_t seg = item - b * (uint32_t)segs;
+        if (n < 0 || n >= p.N || by < 0 || by >= p.g.bcount_h || bx < 0 || bx >= p.g.bcount_w) continue;
+        int nb[9];                                                // list positions of the 3 x 3 blocks around b, -1: none
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            const int y = by + t / 3 - 1, x = bx + t % 3 - 1;
+            const bool ok = y >= 0 && y < p.g.bcount_h && x >= 0 && x < p.g.bcount_w;
+            const int e = map[(n * p.g.bcount_h + min(max(y, 0), p.g.bcount_h - 1)) * p.g.bcount_w + min(max(x, 0), p.g.bcount_w - 1)];
+            nb[t] = ok ? e : -1;
+        }
+        const int py0 = p.g.boffset_h + by * p.g.bstride_h, px0 = p.g.boffset_w + bx * p.g.bstride_w;
+        const uint32_t v_hi = min((seg + 1) * piece, p.tile_vecs);
+        for (uint32_t v0 = seg * piece + threadIdx.x; v0 < v_hi; v0 += kGbThreads * U) {
+            V own[U], old[U], more[U][3];
+            size_t o[U];
+            uint32_t use[U];                                          // bit 3: owned; bits 0..2: more[u][0..2] adds
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t v = v0 + u * kGbThreads;
+                const uint32_t i = fdiv(v, div_tr), rem = v - i * p.tile_row_vecs;
+                const uint32_t j = fdiv(rem, p.div_pv), k = rem - j * p.pix_vecs;
+                const int yy = py0 + (int)i, xx = px0 + (int)j;
+                const bool live = v < v_hi && yy >= 0 && yy < p.H && xx >= 0 && xx < p.W;
+                // the other tile row / column over this pixel: -1 the one before, +1 the one after, 0 none
+                const int dy = (int)i < ovh ? -1 : (int)i >= p.g.bstride_h ? 1 : 0;
+                const int dxc = (int)j < ovw ? -1 : (int)j >= p.g.bstride_w ? 1 : 0;
+                const int th = dxc < 0 ? nb[3] : dxc > 0 ? nb[5] : -1;
+                const int tv = dy < 0 ? nb[1] : dy > 0 ? nb[7] : -1;
+                const int td = dy < 0 ? (dxc < 0 ? nb[0] : dxc > 0 ? nb[2] : -1) : dy > 0 ? (dxc < 0 ? nb[6] : dxc > 0 ? nb[8] : -1) : -1;
+                // a tile in front of b owns the pixel: left in the same row, anything in the row before
+                const bool mine = live && !(dxc < 0 && th >= 0) && !(dy < 0 && (tv >= 0 || td >= 0));
+                o[u] = (((size_t)n * p.H + yy) * p.W + xx) * p.pix_vecs + k;
+                const int oh = -dxc * p.g.bstride_w * (int)p.pix_vecs, ov = -dy * p.g.bstride_h * (int)p.tile_row_vecs;
+                // the row after: the tile further left first
+                const bool left = dxc < 0;
+                const int t1 = left ? td : tv, t2 = left ? tv : td, o1 = left ? oh + ov : ov, o2 = left ? ov : oh + ov;
+                use[u] = mine ? 8u | (th >= 0 ? 1u : 0u) | (t1 >= 0 ? 2u : 0u) | (t2 >= 0 ? 4u : 0u) : 0u;
+                if (mine) {
+                    own[u] = dtiles[(size_t)b * p.tile_vecs + v];
+                    old[u] = dx[o[u]];
+                    if (th >= 0) more[u][0] = dtiles[(size_t)th * p.tile_vecs + (v + oh)];
+                    if (t1 >= 0) more[u][1] = dtiles[(size_t)t1 * p.tile_vecs + (v + o1)];
+                    if (t2 >= 0) more[u][2] = dtiles[(size_t)t2 * p.tile_vecs + (v + o2)];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (!use[u]) continue;
+                float acc[NW * NA];
+#pragma unroll
+                for (int i = 0; i < NW * NA; ++i) acc[i] = 0.f;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) Acc<DT>::add(acc + w * NA, word_of(own[u], w));
+#pragma unroll
+                for (int t = 0; t < 3; ++t)
+                    if (use[u] >> t & 1) {
+#pragma unroll
+                        for (int w = 0; w < NW; ++w) Acc<DT>::add(acc + w * NA, word_of(more[u][t], w));
+                    }
+                uint32_t out[NW];
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    Acc<DT>::add(acc + w * NA, word_of(old[u], w));
+                    out[w] = Acc<DT>::pack(acc + w * NA);
+                }
+                V res;
+                make_vec(res, out);
+                dx[o[u]] = res;
+            }
+        }
+    }
+}
+
+// Tiles of small cells (at most 2048 vectors: 64 channels on 16 x 16 blocks) whose list holds at least half of the blocks run
+// cell by cell, where no pixel of a halo is visited twice; all others tile by tile.  bf16, 16 x 16 blocks (old = cells only):
+//   800 x 704 x 64     5 % of the blocks 15.2 -> 9.1 us, 10 % 17.4 -> 10.3, 30 % 25.1 -> 20.5; 50 % cells 29.5, tiles 30.2;
+//                      100 % cells 43.2, tiles 44.2 (8 x 8 blocks: 10 % 20.7 -> 11.9; 50 % 32.3 / 34.1; 100 % 48.2 / 55.0)
+//   400 x 352 x 256    10 % 31.4 -> 9.8, 30 % 39.8 -> 19.3, 100 % 47.4 -> 41.6 (32 x 32 blocks: 10 % 99.8 -> 9.5)
+template <typename V, int DT, int U>
+__global__ __launch_bounds__(kGbThreads, 5) void gb_either(V *__restrict__ dx, const V *__restrict__ dtiles,
+                                                        const int32_t *__restrict__ map, const int32_t *__restrict__ indices,
+                                                        const int32_t *__restrict__ count, int cells_from, int segs, uint32_t piece,
+                                                        FastDiv div_segs, FastDiv div_tr, GbParams p) {
+    const int nact = min(*count, p.cap);
+    if (nact >= cells_from) gb_cells<V, DT, 1, 2>(dx, dtiles, map, p);
+    else gb_tiles<V, DT, U>(dx, dtiles, map, indices, (uint32_t)nact, segs, piece, div_segs, div_tr, p);
+}
+
 template <typename V, int DT>
-static void launch_gb(void *dx, const void *dtiles, const int32_t *map, const GbParams &p, hipStream_t s) {
-    const long long ncells = (long long)p.N * p.cells_h * p.cells_w;
+__global__ __launch_bounds__(kGbThreads) void gb_far(V *__restrict__ dx, const V *__restrict__ dtiles,
+                                                     const int32_t *__restrict__ map, GbParams p) {
+    gb_cells<V, DT, kGbMaxR, 2>(dx, dtiles, map, p);
+}
+
+template <typename V, int DT>
+static void launch_gb(void *dx, const void *dtiles, const int32_t *map, const int32_t *indices, const int32_t *count,
+                      const GbParams &p, hipStream_t s) {
+    constexpr int U = 3;                                         // vectors per thread in flight
+    const long long ncells = (long long)p.N * p.cells_h * p.cells_w, nblocks = (long long)p.N * p.g.bcount_h * p.g.bcount_w;
+    // pieces of a tile: one step of a workgroup each, a tile that is little more than one step whole
+    const int segs = p.tile_vecs <= 4 * kGbThreads ? 1 : (int)((p.tile_vecs + kGbThreads * U - 1) / (kGbThreads * U));
+    const uint32_t piece = (p.tile_vecs + segs - 1) / segs;
+    const long long items = (long long)p.cap * segs;
+    if (p.R_h <= 1 && p.R_w <= 1 && items < (1LL << 31)) {
+        // a cell that is one step of a workgroup, all of them resident at once, needs no list: one memory round trip less
+        // (83 x 192 x 32 x 2, 8 x 8 blocks, 37 active: 6.0 us against 7.0)
+        const bool tiny = p.cell_vecs <= 2 * kGbThreads && ncells <= 1024;
+        const int cells_from = tiny ? 0 : p.cell_vecs <= 2048 ? (int)((nblocks * 5 + 7) / 8) : 0x7fffffff;
+        const int gt = tiny ? 1 : (int)(items < 4096 ? items : 4096);
+        const int gc = p.cap >= cells_from ? (int)(ncells < 16384 ? ncells : 16384) : 1;
+        hipLaunchKernelGGL((gb_either<V, DT, U>), dim3(gt > gc ? gt : gc), dim3(kGbThreads), 0, s, (V *)dx, (const V *)dtiles, map,
+                           indices, count, cells_from, segs, piece, make_fastdiv(segs), make_fastdiv(p.tile_row_vecs), p);
+        return;
+    }
     const int grid = (int)(ncells < 16384 ? ncells : 16384);
-    if (p.R_h <= 1 && p.R_w <= 1)
-        hipLaunchKernelGGL((gb_accumulate<V, DT, 1, 2>), dim3(grid), dim3(kGbThreads), 0, s, (V *)dx, (const V *)dtiles, map, p);
-    else
-        hipLaunchKernelGGL((gb_accumulate<V, DT, kGbMaxR, 2>), dim3(grid), dim3(kGbThreads), 0, s, (V *)dx, (const V *)dtiles, map, p);
+    hipLaunchKernelGGL((gb_far<V, DT>), dim3(grid), dim3(kGbThreads), 0, s, (V *)dx, (const V *)dtiles, map, p);
 }
 
 template <int DT>
-static sbnet_status dispatch_gb(int vec_bytes, void *dx, const void *dtiles, const int32_t *map, const GbParams &p,
-                                hipStream_t s) {
+static sbnet_status dispatch_gb(int vec_bytes, void *dx, const void *dtiles, const int32_t *map, const int32_t *indices,
+                                const int32_t *count, const GbParams &p, hipStream_t s) {
     switch (vec_bytes) {
-        case 16: launch_gb<uint4, DT>(dx, dtiles, map, p, s); break;
-        case 8: launch_gb<uint2, DT>(dx, dtiles, map, p, s); break;
-        case 4: launch_gb<uint32_t, DT>(dx, dtiles, map, p, s); break;
+        case 16: launch_gb<uint4, DT>(dx, dtiles, map, indices, count, p, s); break;
+        case 8: launch_gb<uint2, DT>(dx, dtiles, map, indices, count, p, s); break;
+        case 4: launch_gb<uint32_t, DT>(dx, dtiles, map, indices, count, p, s); break;
         default: return fail(SBNET_EUNSUPPORTED, "sbnet_sparse_gather_backward: a pixel's channels must fill 4-byte words");
     }
     return launch_status("sbnet_sparse_gather_backward");
@@ -264,7 +399,7 @@ extern "C" sbnet_status sbnet_sparse_gather_backward(const void *dtiles, sbnet_d
         hipLaunchKernelGGL(gb_map_fill, dim3((cap + 255) / 256 > 1024 ? 1024 : (cap + 255) / 256), dim3(256), 0, s, map, indices,
                            count, cap, N, g->bcount_h, g->bcount_w);
     }
-    if (dtype == SBNET_F32) return dispatch_gb<SBNET_F32>(vec, dx, dtiles, map, p, s);
-    if (dtype == SBNET_BF16) return dispatch_gb<SBNET_BF16>(vec, dx, dtiles, map, p, s);
-    return dispatch_gb<SBNET_F16>(vec, dx, dtiles, map, p, s);
+    if (dtype == SBNET_F32) return dispatch_gb<SBNET_F32>(vec, dx, dtiles, map, indices, count, p, s);
+    if (dtype == SBNET_BF16) return dispatch_gb<SBNET_BF16>(vec, dx, dtiles, map, indices, count, p, s);
+    return dispatch_gb<SBNET_F16>(vec, dx, dtiles, map, indices, count, p, s);
 }

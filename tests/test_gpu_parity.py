@@ -334,6 +334,36 @@ def test_gather_backward(H, W, C, k, s, bo, N, dtype):
         assert torch.equal(dx, dx2)
 
 
+# One kernel runs tile by tile (below five eighths of the blocks, or cells of more than 2048 vectors) or cell by cell
+@pytest.mark.parametrize("H,W,C,k,s,bo,N,dtype", [
+    (70, 90, 64, 3, 1, 16, 2, "bf16"),     # 2592 vectors a tile: four pieces, ragged blocks
+    (50, 66, 260, 3, 1, 8, 1, "f32"),      # 4160 vectors a cell: tile by tile at every share
+    (66, 66, 26, 3, 1, 24, 1, "f16"),      # 4-byte words, 13 per pixel
+    (61, 53, 128, 3, 2, 8, 1, "f16"),      # strided geometry: tile 17, stride 16
+    (64, 48, 64, 5, 1, 16, 1, "bf16"),     # halo 2
+    (130, 130, 64, 3, 1, 8, 2, "bf16"),    # 800 vectors a tile: one piece of two steps
+])
+def test_gather_backward_by_tiles_and_by_cells(H, W, C, k, s, bo, N, dtype):
+    step("gather_backward by tiles / cells %s" % ((H, W, C, k, s, bo, N, dtype),))
+    r = gen.rng_for(8, H * 1000 + W + C + 1)
+    g_in, _, _, _ = sb.geometry(H, W, k, s, bo)
+    dx0 = gen.activations(r, (N, H, W, C), dtype)
+    every = np.stack(np.meshgrid(np.arange(N), np.arange(g_in.bcount_h), np.arange(g_in.bcount_w), indexing="ij"), -1).reshape(-1, 3)
+    for share in (0.15, 0.5, 0.8, 1.0):
+        idx = every[np.sort(r.permutation(len(every))[:max(1, int(share * len(every)))])].astype(np.int32)
+        d_idx, d_cnt = dev_indices(idx, len(idx) + 2)
+        t = gen.activations(r, (len(idx) + 2, g_in.bsize_h, g_in.bsize_w, C), dtype)
+        dx = to_dev(dx0, dtype)
+        sb.sparse_gather_backward(to_dev(t, dtype), d_idx, d_cnt, g_in, dx)
+        ref = orc.gather_backward(t[:len(idx)], idx, ogeom(g_in), dx0)
+        got = to_host(dx)
+        # an fp32 sum of at most five terms, then one rounding: half a unit of the result's last place plus the sum's
+        # rounding, four times 2^-24 of the terms' magnitude (below 16)
+        half = {"f32": 2.0 ** -24, "bf16": 2.0 ** -9, "f16": 2.0 ** -12}[dtype]
+        assert (np.abs(got - ref) <= 1.001 * half * np.abs(ref) * 2 + 4 * 16 * 2.0 ** -24).all()
+        assert np.array_equal(got[ref == dx0], dx0[ref == dx0])
+
+
 @pytest.mark.parametrize("H,W,C,bo,N,dtype", [(48, 80, 64, 16, 2, "bf16"), (37, 29, 40, 4, 2, "f16"), (64, 64, 16, 8, 1, "f32"),
                                               (33, 47, 256, 16, 1, "bf16"), (70, 70, 96, 32, 1, "f32")])
 def test_sparse_bn_stats(H, W, C, bo, N, dtype):
