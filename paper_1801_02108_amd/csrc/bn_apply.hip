@@ -4,15 +4,21 @@
 //
 //   bn_apply        y = act(gamma (x - mean) / sqrt(var + eps) + beta) on the pixels of the listed blocks that lie
 //                   inside the image; every other pixel of y is left as it is.
-//   bn_bwd_partial  with z = gamma xhat + beta, g = dy (or dy where z > 0 when the forward call applied a ReLU):
-//                   per (block, channel) the sums of g and of g xhat, reduced through LDS.
-//   bn_bwd_combine  per channel: dbeta = sum g, dgamma = sum g xhat over the blocks (every thread a strided subset in
-//                   list order, then a fixed tree: no atomics, the same bits every run), and the pixel count.
+//   bn_bwd_partial  with z = gamma xhat + beta, g = dy (or dy where z > 0 when the forward call applied a ReLU): per
+//                   (row, channel) the sums of g and of g xhat, a row being the pieces that one workgroup walks.
+//   bn_bwd_combine  per channel: dbeta = sum g, dgamma = sum g xhat over the rows (every thread a strided subset in
+//                   order, then a fixed tree: no atomics, the same bits every run), and the pixel count.
 //   bn_bwd_dx       dx = gamma / sqrt(var + eps) * (g - dbeta / n - xhat dgamma / n): the gradient of training-mode
 //                   normalisation whose mean and variance are the statistics of these same n pixels.
 //
-// All four walk (block, slab of 128 bytes of channels per pixel) items with 8 lanes per pixel strip, as the statistics
-// kernel does; arithmetic in fp32, one rounding to the storage type.
+// Work items are (block, piece of 128 pixels, slab of 128 bytes of channels per pixel), with 8 lanes per pixel strip;
+// arithmetic in fp32, one rounding to the storage type.  What bounds them is HBM (the active blocks read, and written, once
+// per kernel); what kept them from it was the address unit: 32 four-byte coefficient loads per thread and item took as long
+// as the pixels.  The coefficients of all channels now pass through LDS, one channel per thread, once per workgroup, and
+// partial sums leave a workgroup once (up to 1024 rows of them), not once per block.  bf16, before -> now:
+//   800 x 704 x 64, 880 blocks of 16 x 16 (28.8 MB per tensor): apply 19.5 -> 11.9 us (4.8 TB/s), partial 18.4 -> 13.4,
+//     combine 4.9 -> 3.9, dx 26.8 -> 18.6 (4.6 TB/s); a large copy runs at 5.1
+//   844 x 494 x 64, 3746 blocks of 8 x 8 (30.7 MB): 37.3 -> 12.9, 36.3 -> 13.1, 8.5 -> 3.9, 58.8 -> 18.4 us
 #include "bn_common.h"
 
 namespace sbnet {
@@ -24,71 +30,80 @@ struct BnAffine {
     int relu;
 };
 
-// origin of block b's window and this thread's place in the slab
-struct BnPlace {
-    int y0, x0, npx, c0;
-    bool chan_ok;
-    long long base;
+constexpr int kBnCoef = 512;                  // channels whose coefficients one pass through LDS holds
+
+// Per-channel coefficients in LDS, NC arrays of kBnCoef floats.  load() fills channels [c_lo, c_lo + kBnCoef) by all threads of
+// the workgroup (barriers around it), get() reads a thread's EPV consecutive channels.
+template <int NC>
+struct BnCoefs {
+    float (*lds)[kBnCoef];
+    int c_lo;
+    template <typename F>
+    __device__ __forceinline__ void load(int first, int C, F f) {
+        c_lo = first;
+        for (int c = threadIdx.x; c < kBnCoef && first + c < C; c += kBnThreads) {
+            float v[NC];
+            f(first + c, v);
+#pragma unroll
+            for (int i = 0; i < NC; ++i) lds[i][c] = v[i];
+        }
+        __syncthreads();
+    }
+    template <int EPV>
+    __device__ __forceinline__ void get(int i, int c0, float *v) const {
+        const int at = min(max(c0 - c_lo, 0), kBnCoef - EPV);     // lanes past the channel count read, and do not use, some value
+#pragma unroll
+        for (int e = 0; e < EPV; e += 4) {
+            const float4 t = *(const float4 *)&lds[i][at + e];
+            v[e] = t.x; v[e + 1] = t.y; v[e + 2] = t.z; v[e + 3] = t.w;
+        }
+    }
 };
 
-template <int EPV>
-__device__ __forceinline__ BnPlace bn_place(uint32_t b, int slab, int k, const int32_t *indices, const BnParams &p) {
-    BnPlace w;
-    const int n = indices[3 * b], by = indices[3 * b + 1], bx = indices[3 * b + 2];
-    w.y0 = p.g.boffset_h + by * p.g.bstride_h;
-    w.x0 = p.g.boffset_w + bx * p.g.bstride_w;
-    const int ylo = max(w.y0, 0), yhi = min(w.y0 + p.g.bsize_h, p.H), xlo = max(w.x0, 0), xhi = min(w.x0 + p.g.bsize_w, p.W);
-    w.npx = max(yhi - ylo, 0) * max(xhi - xlo, 0);
-    w.c0 = slab * p.cs + k * EPV;
-    w.chan_ok = w.c0 < p.C;
-    w.base = (long long)n * p.H * p.W * p.pix_vecs + (long long)(slab * (p.cs / EPV) + k);
-    return w;
+__device__ __forceinline__ void bn_affine_of(const BnAffine &a, int c, float *v) {
+    v[0] = a.mean[c];
+    v[1] = 1.0f / sqrtf(a.var[c] + a.eps);
+    v[2] = a.gamma ? a.gamma[c] : 1.f;
+    v[3] = a.beta ? a.beta[c] : 0.f;
 }
 
-// vector index of pixel q of the block (row-major inside the window), or -1 outside the image / the block
-__device__ __forceinline__ long long bn_pixel(const BnPlace &w, int q, const BnParams &p) {
-    const int i = (int)fdiv((uint32_t)q, p.div_w), j = q - i * p.g.bsize_w;
-    const int yy = w.y0 + i, xx = w.x0 + j;
-    if (!w.chan_ok || q >= p.hw || yy < 0 || yy >= p.H || xx < 0 || xx >= p.W) return -1;
-    return w.base + ((long long)yy * p.W + xx) * p.pix_vecs;
-}
-
-template <int EPV>
-__device__ __forceinline__ void bn_coeffs(const BnAffine &a, const BnPlace &w, int C, float *mean, float *rstd, float *gam,
-                                          float *bet) {
-#pragma unroll
-    for (int e = 0; e < EPV; ++e) {
-        const int c = w.c0 + e;
-        const bool ok = w.chan_ok && c < C;
-        mean[e] = ok ? a.mean[c] : 0.f;
-        rstd[e] = ok ? 1.0f / sqrtf(a.var[c] + a.eps) : 0.f;
-        gam[e] = ok ? (a.gamma ? a.gamma[c] : 1.f) : 0.f;
-        bet[e] = ok ? (a.beta ? a.beta[c] : 0.f) : 0.f;
-    }
-}
+// the slabs of an item range are walked in groups whose channels fit the LDS copy: group gi holds slabs [gi * per, ...)
+__device__ __forceinline__ int bn_group_slabs(const BnParams &p) { return kBnCoef / p.cs; }
 
 template <int DT>
 __global__ __launch_bounds__(kBnThreads) void bn_apply(const uint4 *x, uint4 *y,                       // y may be x
                                                        const int32_t *__restrict__ indices, const int32_t *__restrict__ count,
-                                                       BnParams p, BnAffine a) {
+                                                       int pieces, FastDiv div_pieces, BnParams p, BnAffine a) {
     constexpr int EPV = BnElem<DT>::EPV;
+    __shared__ __align__(16) float cf[4][kBnCoef];
     const int nact = min(*count, p.cap);
-    const uint32_t items = (uint32_t)nact * (uint32_t)p.slabs;
     const int pg = threadIdx.x >> 3, k = threadIdx.x & 7;
-    for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
-        const uint32_t b = fdiv(item, p.div_slabs);
-        const BnPlace w = bn_place<EPV>(b, (int)(item - b * p.slabs), k, indices, p);
-        float mean[EPV], rstd[EPV], gam[EPV], bet[EPV];
-        bn_coeffs<EPV>(a, w, p.C, mean, rstd, gam, bet);
-        for (int q0 = pg; q0 < p.hw; q0 += 32 * 4) {
+    for (int s0 = 0; s0 < p.slabs; s0 += bn_group_slabs(p)) {
+        const int ns = min(bn_group_slabs(p), p.slabs - s0);
+        const uint32_t items = (uint32_t)nact * (uint32_t)(ns * pieces);
+        BnBlock blk = bn_block(indices, fdiv(blockIdx.x, div_pieces) / (uint32_t)ns, p.cap);
+        BnCoefs<4> co = {cf, 0};
+        if (s0) __syncthreads();
+        co.load(s0 * p.cs, p.C, [&](int c, float *v) { bn_affine_of(a, c, v); });
+        for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
+            const uint32_t bs = fdiv(item, div_pieces);           // (block, slab of the group)
+            const int piece = (int)(item - bs * pieces);
+            const uint32_t b = ns == 1 ? bs : bs / (uint32_t)ns;
+            const int slab = s0 + (int)(bs - b * ns);
+            if (item != blockIdx.x) blk = bn_block(indices, b, p.cap);
+            const BnPlace w = bn_place<EPV>(blk, slab, k, p);
             long long at[4];
             uint4 v[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                at[u] = bn_pixel(w, q0 + 32 * u, p);
-                v[u] = make_uint4(0, 0, 0, 0);
+                at[u] = bn_pixel(w, piece * kBnPiece + pg + 32 * u, p);
                 if (at[u] >= 0) v[u] = x[at[u]];
             }
+            float mean[EPV], rstd[EPV], gam[EPV], bet[EPV];
+            co.get<EPV>(0, w.c0, mean);
+            co.get<EPV>(1, w.c0, rstd);
+            co.get<EPV>(2, w.c0, gam);
+            co.get<EPV>(3, w.c0, bet);
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 if (at[u] >= 0) {
@@ -106,102 +121,125 @@ __global__ __launch_bounds__(kBnThreads) void bn_apply(const uint4 *x, uint4 *y,
     }
 }
 
-// workspace layout: float part[cap][C][2] (sum g, sum g xhat), float cnt[cap], float ntot
+// workspace layout: float part[rows][C][2] (sum g, sum g xhat), at cnt float cnt[rows], ntot; rows = gridDim.x / slabs <= cap
 template <int DT>
 __global__ __launch_bounds__(kBnThreads) void bn_bwd_partial(const uint4 *__restrict__ x, const uint4 *__restrict__ dy,
                                                              const int32_t *__restrict__ indices,
                                                              const int32_t *__restrict__ count, float *__restrict__ part,
-                                                             float *__restrict__ cnt, BnParams p, BnAffine a) {
-    constexpr int EPV = BnElem<DT>::EPV;
-    __shared__ float red[2][32][8 * EPV + 1];
-    const int nact = min(*count, p.cap);
-    const uint32_t items = (uint32_t)nact * (uint32_t)p.slabs;
+                                                             float *__restrict__ cnt, int pieces, FastDiv div_pieces,
+                                                             BnParams p, BnAffine a) {
+    constexpr int EPV = BnElem<DT>::EPV, NCH = 8 * EPV;
+    __shared__ __align__(16) float cf[4][NCH];
+    __shared__ float red[2][32][NCH + 1];
+    __shared__ int redn[32];
     const int pg = threadIdx.x >> 3, k = threadIdx.x & 7;
-    for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
-        const uint32_t b = fdiv(item, p.div_slabs);
-        const int slab = (int)(item - b * p.slabs);
-        const BnPlace w = bn_place<EPV>(b, slab, k, indices, p);
-        float mean[EPV], rstd[EPV], gam[EPV], bet[EPV], s1[EPV], s2[EPV];
-        bn_coeffs<EPV>(a, w, p.C, mean, rstd, gam, bet);
+    const uint32_t row = fdiv(blockIdx.x, p.div_slabs), rows = fdiv(gridDim.x, p.div_slabs);
+    const int slab = (int)(blockIdx.x - row * p.slabs);
+    if (threadIdx.x < NCH && slab * p.cs + (int)threadIdx.x < p.C) {
+        float v[4];
+        bn_affine_of(a, slab * p.cs + threadIdx.x, v);
 #pragma unroll
-        for (int e = 0; e < EPV; ++e) s1[e] = s2[e] = 0.f;
-        for (int q0 = pg; q0 < p.hw; q0 += 32 * 2) {
-            long long at[2];
-            uint4 vx[2], vg[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                at[u] = bn_pixel(w, q0 + 32 * u, p);
-                vx[u] = vg[u] = make_uint4(0, 0, 0, 0);
-                if (at[u] >= 0) {
-                    vx[u] = x[at[u]];
-                    vg[u] = dy[at[u]];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-                if (at[u] >= 0) {
-                    float f[EPV], g[EPV];
-                    BnElem<DT>::unpack(vx[u], f);
-                    BnElem<DT>::unpack(vg[u], g);
-#pragma unroll
-                    for (int e = 0; e < EPV; ++e) {
-                        const float xh = (f[e] - mean[e]) * rstd[e];
-                        const float ge = (a.relu && !(fmaf(gam[e], xh, bet[e]) > 0.f)) ? 0.f : g[e];
-                        s1[e] += ge;
-                        s2[e] = fmaf(ge, xh, s2[e]);
-                    }
-                }
-        }
-#pragma unroll
-        for (int e = 0; e < EPV; ++e) {
-            red[0][pg][k * EPV + e] = s1[e];
-            red[1][pg][k * EPV + e] = s2[e];
-        }
-        __syncthreads();
-        if (threadIdx.x < 8 * EPV) {
-            const int c = slab * p.cs + threadIdx.x;
-            float t1 = 0.f, t2 = 0.f;
-            for (int gq = 0; gq < 32; ++gq) {
-                t1 += red[0][gq][threadIdx.x];
-                t2 += red[1][gq][threadIdx.x];
-            }
-            if (c < p.C) {
-                part[((size_t)b * p.C + c) * 2] = t1;
-                part[((size_t)b * p.C + c) * 2 + 1] = t2;
-            }
-            if (slab == 0 && threadIdx.x == 0) cnt[b] = (float)w.npx;
-        }
-        __syncthreads();
+        for (int i = 0; i < 4; ++i) cf[i][threadIdx.x] = v[i];
     }
+    BnBlock blk = bn_block(indices, fdiv(row, div_pieces), p.cap);
+    const uint32_t items = (uint32_t)min(*count, p.cap) * (uint32_t)pieces;
+    if (row >= items) return;
+    __syncthreads();
+    float mean[EPV], rstd[EPV], gam[EPV], bet[EPV], s1[EPV], s2[EPV];
+#pragma unroll
+    for (int e = 0; e < EPV; ++e) {
+        mean[e] = cf[0][k * EPV + e]; rstd[e] = cf[1][k * EPV + e];
+        gam[e] = cf[2][k * EPV + e]; bet[e] = cf[3][k * EPV + e];
+        s1[e] = s2[e] = 0.f;
+    }
+    int npx = 0;
+    for (uint32_t item = row; item < items; item += rows) {
+        const uint32_t b = fdiv(item, div_pieces);
+        const BnPlace w = bn_place<EPV>(blk, slab, k, p);
+        blk = bn_block(indices, fdiv(item + rows, div_pieces), p.cap);        // the next item's
+        const int q0 = (int)(item - b * pieces) * kBnPiece + pg;
+        long long at[4];
+        uint4 vx[4], vg[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            at[u] = bn_pixel(w, q0 + 32 * u, p);
+            if (at[u] >= 0) {
+                vx[u] = x[at[u]];
+                vg[u] = dy[at[u]];
+                ++npx;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (at[u] >= 0) {
+                float f[EPV], g[EPV];
+                BnElem<DT>::unpack(vx[u], f);
+                BnElem<DT>::unpack(vg[u], g);
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    const float xh = (f[e] - mean[e]) * rstd[e];
+                    const float ge = (a.relu && !(fmaf(gam[e], xh, bet[e]) > 0.f)) ? 0.f : g[e];
+                    s1[e] += ge;
+                    s2[e] = fmaf(ge, xh, s2[e]);
+                }
+            }
+    }
+    float t1, t2;
+    const float n = bn_reduce<EPV>(red, redn, s1, s2, npx, &t1, &t2);
+    const int c = slab * p.cs + threadIdx.x;
+    if (threadIdx.x < NCH && c < p.C) {
+        part[((size_t)row * p.C + c) * 2] = t1;
+        part[((size_t)row * p.C + c) * 2 + 1] = t2;
+    }
+    if (slab == 0 && threadIdx.x == 0) cnt[row] = n;
 }
 
-__global__ __launch_bounds__(kBnThreads) void bn_bwd_combine(const float *__restrict__ part, const float *__restrict__ cnt,
-                                                             const int32_t *__restrict__ count, int cap, int C,
-                                                             float *__restrict__ dgamma, float *__restrict__ dbeta,
-                                                             float *__restrict__ ntot) {
-    __shared__ float s1[kBnThreads], s2[kBnThreads], sn[kBnThreads];
-    const int c = blockIdx.x;
-    const int nact = min(*count, cap);
+// Four channels per workgroup, 256 threads along the rows of each, four rows in flight per thread.
+__global__ __launch_bounds__(1024) void bn_bwd_combine(const float *__restrict__ part, const float *__restrict__ cnt,
+                                                       const int32_t *__restrict__ count, int cap, int C, int max_rows, int pieces,
+                                                       float *__restrict__ dgamma, float *__restrict__ dbeta,
+                                                       float *__restrict__ ntot) {
+    __shared__ float s1[64], s2[64], sn[64];
+    const int ch = threadIdx.x & 3, row = threadIdx.x >> 2, c = blockIdx.x * 4 + ch;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int rows = (int)min((long long)min(*count, cap) * pieces, (long long)max_rows);
     float a = 0.f, q = 0.f, n = 0.f;
-    for (int b = threadIdx.x; b < nact; b += kBnThreads) {
-        a += part[((size_t)b * C + c) * 2];
-        q += part[((size_t)b * C + c) * 2 + 1];
-        n += cnt[b];
-    }
-    s1[threadIdx.x] = a; s2[threadIdx.x] = q; sn[threadIdx.x] = n;
-    __syncthreads();
-    for (int half = kBnThreads / 2; half > 0; half >>= 1) {
-        if ((int)threadIdx.x < half) {
-            s1[threadIdx.x] += s1[threadIdx.x + half];
-            s2[threadIdx.x] += s2[threadIdx.x + half];
-            sn[threadIdx.x] += sn[threadIdx.x + half];
+    for (int b0 = row; b0 < rows; b0 += 256 * 4) {
+        f32x2_a4 v[4];
+        float m[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int b = min(b0 + 256 * u, rows - 1);
+            v[u] = *(const f32x2_a4 *)(part + ((size_t)b * C + min(c, C - 1)) * 2);
+            m[u] = cnt[b];
         }
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (b0 + 256 * u < rows) {
+                a += v[u][0];
+                q += v[u][1];
+                n += m[u];
+            }
     }
-    if (threadIdx.x == 0) {
-        dbeta[c] = s1[0];
-        dgamma[c] = s2[0];
-        if (c == 0) *ntot = sn[0];
+    // a fixed tree: the 16 rows of a wave, then the 16 waves (a wave holds four channels: lane = 4 row + channel)
+    auto fold = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int off = 32; off >= 4; off >>= 1) {
+            a += __shfl_down(a, off);
+            q += __shfl_down(q, off);
+            n += __shfl_down(n, off);
+        }
+    };
+    fold();
+    if (lane < 4) { s1[wave * 4 + lane] = a; s2[wave * 4 + lane] = q; sn[wave * 4 + lane] = n; }
+    __syncthreads();
+    if (wave > 0) return;
+    a = s1[lane]; q = s2[lane]; n = sn[lane];
+    fold();
+    if (lane < 4 && c < C) {
+        dbeta[c] = a;
+        dgamma[c] = q;
+        if (c == 0) *ntot = n;
     }
 }
 
@@ -210,37 +248,49 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_dx(const uint4 *__restrict_
                                                         uint4 *dx /* may be dy */, const int32_t *__restrict__ indices,
                                                         const int32_t *__restrict__ count, const float *__restrict__ dgamma,
                                                         const float *__restrict__ dbeta, const float *__restrict__ ntot,
-                                                        BnParams p, BnAffine a) {
+                                                        int pieces, FastDiv div_pieces, BnParams p, BnAffine a) {
     constexpr int EPV = BnElem<DT>::EPV;
+    __shared__ __align__(16) float cf[6][kBnCoef];
     const int nact = min(*count, p.cap);
-    const uint32_t items = (uint32_t)nact * (uint32_t)p.slabs;
     const int pg = threadIdx.x >> 3, k = threadIdx.x & 7;
     const float n = *ntot, inv_n = n > 0.f ? 1.0f / n : 0.f;
-    for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
-        const uint32_t b = fdiv(item, p.div_slabs);
-        const BnPlace w = bn_place<EPV>(b, (int)(item - b * p.slabs), k, indices, p);
-        float mean[EPV], rstd[EPV], gam[EPV], bet[EPV], mg[EPV], mgx[EPV];
-        bn_coeffs<EPV>(a, w, p.C, mean, rstd, gam, bet);
+    for (int s0 = 0; s0 < p.slabs; s0 += bn_group_slabs(p)) {
+        const int ns = min(bn_group_slabs(p), p.slabs - s0);
+        const uint32_t items = (uint32_t)nact * (uint32_t)(ns * pieces);
+        BnBlock blk = bn_block(indices, fdiv(blockIdx.x, div_pieces) / (uint32_t)ns, p.cap);
+        BnCoefs<6> co = {cf, 0};
+        if (s0) __syncthreads();
+        co.load(s0 * p.cs, p.C, [&](int c, float *v) {
+            bn_affine_of(a, c, v);
+            v[4] = dbeta[c] * inv_n;
+            v[5] = dgamma[c] * inv_n;
+        });
+        for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
+            const uint32_t bs = fdiv(item, div_pieces);           // (block, slab of the group)
+            const int piece = (int)(item - bs * pieces);
+            const uint32_t b = ns == 1 ? bs : bs / (uint32_t)ns;
+            const int slab = s0 + (int)(bs - b * ns);
+            if (item != blockIdx.x) blk = bn_block(indices, b, p.cap);
+            const BnPlace w = bn_place<EPV>(blk, slab, k, p);
+            long long at[4];
+            uint4 vx[4], vg[4];
 #pragma unroll
-        for (int e = 0; e < EPV; ++e) {
-            const bool ok = w.chan_ok && w.c0 + e < p.C;
-            mg[e] = ok ? dbeta[w.c0 + e] * inv_n : 0.f;
-            mgx[e] = ok ? dgamma[w.c0 + e] * inv_n : 0.f;
-        }
-        for (int q0 = pg; q0 < p.hw; q0 += 32 * 2) {
-            long long at[2];
-            uint4 vx[2], vg[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                at[u] = bn_pixel(w, q0 + 32 * u, p);
-                vx[u] = vg[u] = make_uint4(0, 0, 0, 0);
+            for (int u = 0; u < 4; ++u) {
+                at[u] = bn_pixel(w, piece * kBnPiece + pg + 32 * u, p);
                 if (at[u] >= 0) {
                     vx[u] = x[at[u]];
                     vg[u] = dy[at[u]];
                 }
             }
+            float mean[EPV], rstd[EPV], gam[EPV], bet[EPV], mg[EPV], mgx[EPV];
+            co.get<EPV>(0, w.c0, mean);
+            co.get<EPV>(1, w.c0, rstd);
+            co.get<EPV>(2, w.c0, gam);
+            co.get<EPV>(3, w.c0, bet);
+            co.get<EPV>(4, w.c0, mg);
+            co.get<EPV>(5, w.c0, mgx);
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
+            for (int u = 0; u < 4; ++u)
                 if (at[u] >= 0) {
                     float f[EPV], g[EPV];
                     BnElem<DT>::unpack(vx[u], f);
@@ -257,9 +307,10 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_dx(const uint4 *__restrict_
     }
 }
 
-int bn_grid(int cap, const BnParams &p) {
-    const long long items = (long long)cap * p.slabs;
-    return (int)(items < 8192 ? items : 8192);
+// as many workgroups as the device holds at once (six to eight per CU), each with its coefficients loaded once
+int bn_grid(int cap, const BnParams &p, int pieces) {
+    const long long items = (long long)cap * p.slabs * pieces;
+    return (int)(items < 2048 ? items : 2048);
 }
 
 }  // namespace
@@ -288,8 +339,8 @@ extern "C" sbnet_status sbnet_sparse_bn_apply(const void *x, sbnet_dtype dtype, 
     if (cap == 0) return SBNET_OK;
     hipStream_t s = (hipStream_t)stream;
     const BnAffine a = {mean, var, gamma, beta, eps, relu ? 1 : 0};
-    const int grid = bn_grid(cap, p);
-    SBNET_BN_DISPATCH(bn_apply, (const uint4 *)x, (uint4 *)y, indices, count, p, a);
+    const int pieces = bn_pieces(p), grid = bn_grid(cap, p, pieces);
+    SBNET_BN_DISPATCH(bn_apply, (const uint4 *)x, (uint4 *)y, indices, count, pieces, make_fastdiv(pieces), p, a);
     return launch_status(who);
 }
 
@@ -320,9 +371,18 @@ extern "C" sbnet_status sbnet_sparse_bn_backward(const void *x, const void *dy, 
     float *part = (float *)workspace;
     float *cnt = part + (size_t)cap * C * 2;
     float *ntot = cnt + cap;
-    const int grid = cap > 0 ? bn_grid(cap, p) : 0;
-    if (cap > 0) SBNET_BN_DISPATCH(bn_bwd_partial, (const uint4 *)x, (const uint4 *)dy, indices, count, part, cnt, p, a);
-    hipLaunchKernelGGL(bn_bwd_combine, dim3(C), dim3(kBnThreads), 0, s, part, cnt, count, cap, C, dgamma, dbeta, ntot);
-    if (cap > 0) SBNET_BN_DISPATCH(bn_bwd_dx, (const uint4 *)x, (const uint4 *)dy, (uint4 *)dx, indices, count, dgamma, dbeta, ntot, p, a);
+    const int rows = bn_rows(cap, p), all = bn_pieces(p);
+    if (cap > 0) {
+        const int grid = rows * p.slabs;
+        SBNET_BN_DISPATCH(bn_bwd_partial, (const uint4 *)x, (const uint4 *)dy, indices, count, part, cnt, all, make_fastdiv(all),
+                          p, a);
+    }
+    hipLaunchKernelGGL(bn_bwd_combine, dim3((C + 3) / 4), dim3(1024), 0, s, part, cnt, count, cap, C, rows, all, dgamma, dbeta,
+                       ntot);
+    if (cap > 0) {
+        const int pieces = bn_pieces(p), grid = bn_grid(cap, p, pieces);
+        SBNET_BN_DISPATCH(bn_bwd_dx, (const uint4 *)x, (const uint4 *)dy, (uint4 *)dx, indices, count, dgamma, dbeta, ntot, pieces,
+                          make_fastdiv(pieces), p, a);
+    }
     return launch_status(who);
 }

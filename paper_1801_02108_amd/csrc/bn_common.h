@@ -1,8 +1,8 @@
 // Shared by the batch-norm kernels over active blocks (bn_stats.hip, bn_apply.hip): the work decomposition
-// (one item = an active block x a slab of 128 bytes of channels per pixel; 8 lanes per pixel strip, 32 pixel groups
+// (an item = a piece of an active block x a slab of 128 bytes of channels per pixel; 8 lanes per pixel strip, 32 pixel groups
 // per workgroup) and the element packing of the three storage types.
 #pragma once
-#include "common.h"
+#include "conv_common.h"
 
 namespace sbnet {
 
@@ -55,16 +55,7 @@ __device__ __forceinline__ uint4 bn_pack(const float *f) {
     if (DT == SBNET_F32) return make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3]));
     uint32_t w[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (DT == SBNET_BF16) {
-            w[i] = float_to_bf16_bits(f[2 * i]) | (float_to_bf16_bits(f[2 * i + 1]) << 16);
-        } else {
-            union { _Float16 h[2]; uint32_t u; } x;
-            x.h[0] = (_Float16)f[2 * i];
-            x.h[1] = (_Float16)f[2 * i + 1];
-            w[i] = x.u;
-        }
-    }
+    for (int i = 0; i < 4; ++i) w[i] = pack2<DT>(f[2 * i], f[2 * i + 1]);
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
@@ -89,6 +80,92 @@ inline sbnet_status bn_fill_params(const char *who, sbnet_dtype dtype, int N, in
     p->div_slabs = make_fastdiv((uint32_t)p->slabs);
     p->div_w = make_fastdiv((uint32_t)g->bsize_w);
     return SBNET_OK;
+}
+
+// ---- work items --------------------------------------------------------------------------------------------------
+constexpr int kBnPiece = 128;                 // pixels per item: four per thread
+constexpr int kBnSumGroups = 1024;            // workgroups of the kernels that form partial sums, four per CU
+typedef float f32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));     // workspaces are 4-byte aligned
+
+inline int bn_pieces(const BnParams &p) { return (p.hw + kBnPiece - 1) / kBnPiece; }
+// rows of partial sums: no more than the caller's bound on the blocks, which sizes the workspace
+inline int bn_rows(int cap, const BnParams &p) {
+    const int rows = p.slabs > 8 ? kBnSumGroups / 8 : kBnSumGroups / p.slabs;
+    return cap < rows ? cap : rows;
+}
+
+// origin of block b's window and this thread's place in the slab
+struct BnPlace {
+    int y0, x0, npx, c0;
+    bool chan_ok;
+    long long base;
+};
+
+struct BnBlock {
+    int n, by, bx;
+};
+// past the list (the first item of a workgroup, requested beside the count): some block, not used
+__device__ __forceinline__ BnBlock bn_block(const int32_t *indices, uint32_t b, int cap) {
+    const int32_t *t = indices + 3 * (size_t)min(b, (uint32_t)cap - 1u);
+    return {t[0], t[1], t[2]};
+}
+
+template <int EPV>
+__device__ __forceinline__ BnPlace bn_place(const BnBlock &t, int slab, int k, const BnParams &p) {
+    const int n = t.n, by = t.by, bx = t.bx;
+    BnPlace w;
+    w.y0 = p.g.boffset_h + by * p.g.bstride_h;
+    w.x0 = p.g.boffset_w + bx * p.g.bstride_w;
+    const int ylo = max(w.y0, 0), yhi = min(w.y0 + p.g.bsize_h, p.H), xlo = max(w.x0, 0), xhi = min(w.x0 + p.g.bsize_w, p.W);
+    w.npx = max(yhi - ylo, 0) * max(xhi - xlo, 0);
+    w.c0 = slab * p.cs + k * EPV;
+    w.chan_ok = w.c0 < p.C;
+    w.base = (long long)n * p.H * p.W * p.pix_vecs + (long long)(slab * (p.cs / EPV) + k);
+    return w;
+}
+
+// vector index of pixel q of the block (row-major inside the window), or -1 outside the image / the block
+__device__ __forceinline__ long long bn_pixel(const BnPlace &w, int q, const BnParams &p) {
+    const int i = (int)fdiv((uint32_t)q, p.div_w), j = q - i * p.g.bsize_w;
+    const int yy = w.y0 + i, xx = w.x0 + j;
+    if (!w.chan_ok || q >= p.hw || yy < 0 || yy >= p.H || xx < 0 || xx >= p.W) return -1;
+    return w.base + ((long long)yy * p.W + xx) * p.pix_vecs;
+}
+
+
+// Sums over the 32 pixel groups of a workgroup: thread c < 8 EPV gets channel c's s1 and s2, every thread the pixel count
+// (counted by the lanes that hold a pixel's first vector of the slab).
+template <int EPV>
+__device__ __forceinline__ float bn_reduce(float (*red)[32][8 * EPV + 1], int *redn, const float *s1, const float *s2, int npx,
+                                           float *t1, float *t2) {
+    constexpr int NCH = 8 * EPV;
+    const int pg = threadIdx.x >> 3, k = threadIdx.x & 7;
+#pragma unroll
+    for (int e = 0; e < EPV; ++e) {
+        red[0][pg][k * EPV + e] = s1[e];
+        red[1][pg][k * EPV + e] = s2[e];
+    }
+    if (k == 0) redn[pg] = npx;
+    __syncthreads();
+    // in place: thread (quarter, channel) sums eight groups into the first of them, then a thread per channel the four
+    const int ch = threadIdx.x % NCH, quarter = threadIdx.x / NCH;
+    float a = 0.f, b = 0.f;
+    if (quarter < 4) {
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {
+            a += red[0][quarter * 8 + g][ch];
+            b += red[1][quarter * 8 + g][ch];
+        }
+        red[0][quarter * 8][ch] = a;
+        red[1][quarter * 8][ch] = b;
+    }
+    int n = 0;
+#pragma unroll
+    for (int g = 0; g < 32; ++g) n += redn[g];
+    __syncthreads();
+    *t1 = (red[0][0][ch] + red[0][8][ch]) + (red[0][16][ch] + red[0][24][ch]);
+    *t2 = (red[1][0][ch] + red[1][8][ch]) + (red[1][16][ch] + red[1][24][ch]);
+    return (float)n;
 }
 
 }  // namespace sbnet

@@ -4,136 +4,132 @@
 // inside the image.
 //
 // Two kernels, no atomics, fixed summation order:
-//   bn_partial   one workgroup per (active block, slab of 128 bytes of channels per pixel).  Eight lanes read one
-//                pixel's 128-byte strip; a thread accumulates, in fp32, the sum and the sum of squares of its
-//                channels over every 32nd pixel, taken relative to the block's first pixel (which keeps the squares
-//                small when the mean is large against the spread); LDS reduces the 32 pixel groups; the block's
+//   bn_partial   one workgroup per (row, slab of 128 bytes of channels per pixel); a row is every rows-th piece of 128
+//                pixels.  Eight lanes read one pixel's 128-byte strip; a thread accumulates, in fp32, the sum and the sum
+//                of squares of its channels, taken relative to a pixel of the row's first block (which keeps the
+//                squares small when the mean is large against the spread); LDS reduces the 32 pixel groups; the row's
 //                (count, mean, sum of squared deviations) per channel goes to the workspace.
-//   bn_combine   one workgroup per channel merges the blocks' triples with the pairwise update of Chan, Golub and
+//   bn_combine   one workgroup per four channels merges the rows' triples with the pairwise update of Chan, Golub and
 //                LeVeque (mean += delta * n_b / n; M2 += M2_b + delta^2 * n_a * n_b / n): every thread a strided
-//                subset in list order, then a fixed tree over the threads.
+//                subset in order, then a fixed tree over the threads.
+// Bound by HBM (the active blocks read once) and, at these sizes, by the launches and the round trips of a workgroup.
+// bf16, before (a row per block, one workgroup per channel) -> now, partial + combine: 800 x 704 x 64, 880 blocks of 16 x 16
+// (28.8 MB): 8.1 + 5.2 -> 9.0 + 4.6 us; 844 x 494 x 64, 3746 blocks of 8 x 8 (30.7 MB): 10.8 + 13.0 -> 9.6 + 4.9 us.
 #include "bn_common.h"
 
 namespace sbnet {
 
-// workspace layout: float part[cap][C][2] (mean, M2), then float cnt[cap]
+// workspace layout: float part[rows][C][2] (mean, M2), at cnt float cnt[rows]; rows = gridDim.x / slabs <= cap
 template <int DT>
 __global__ __launch_bounds__(kBnThreads) void bn_partial(const uint4 *__restrict__ x, const int32_t *__restrict__ indices,
                                                          const int32_t *__restrict__ count, float *__restrict__ part,
-                                                         float *__restrict__ cnt, BnParams p) {
-    constexpr int EPV = BnElem<DT>::EPV;
-    __shared__ float red[2][32][8 * EPV + 1];
-    __shared__ float ref_s[8 * EPV];
-    const int nact = min(*count, p.cap);
-    const uint32_t items = (uint32_t)nact * (uint32_t)p.slabs;
+                                                         float *__restrict__ cnt, int pieces, FastDiv div_pieces, BnParams p) {
+    constexpr int EPV = BnElem<DT>::EPV, NCH = 8 * EPV;
+    __shared__ float red[2][32][NCH + 1];
+    __shared__ float ref_s[NCH];
+    __shared__ int redn[32];
     const int pg = threadIdx.x >> 3, k = threadIdx.x & 7;         // pixel group, vector of the slab
-    for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
-        const uint32_t b = fdiv(item, p.div_slabs);
-        const int slab = (int)(item - b * p.slabs);
-        const int n = indices[3 * b], by = indices[3 * b + 1], bx = indices[3 * b + 2];
-        const int y0 = p.g.boffset_h + by * p.g.bstride_h, x0 = p.g.boffset_w + bx * p.g.bstride_w;
-        // the part of the block inside the image
-        const int ylo = max(y0, 0), yhi = min(y0 + p.g.bsize_h, p.H), xlo = max(x0, 0), xhi = min(x0 + p.g.bsize_w, p.W);
-        const int npx = max(yhi - ylo, 0) * max(xhi - xlo, 0);
-        const int c0 = slab * p.cs + k * EPV;                     // this thread's first channel
-        const bool chan_ok = c0 < p.C;
-        const long long base = (long long)n * p.H * p.W * p.pix_vecs + (long long)(slab * (p.cs / EPV) + k);
-        // reference value per channel: the block's first inside pixel
-        if (threadIdx.x < 8) {
-            float f[EPV];
+    const uint32_t row = fdiv(blockIdx.x, p.div_slabs), rows = fdiv(gridDim.x, p.div_slabs);
+    const int slab = (int)(blockIdx.x - row * p.slabs);
+    BnBlock blk = bn_block(indices, fdiv(row, div_pieces), p.cap);
+    const uint32_t items = (uint32_t)min(*count, p.cap) * (uint32_t)pieces;
+    if (row >= items) return;
+    float ref[EPV], s1[EPV], s2[EPV];
 #pragma unroll
-            for (int e = 0; e < EPV; ++e) f[e] = 0.f;
-            if (npx > 0 && chan_ok) BnElem<DT>::unpack(x[base + ((long long)ylo * p.W + xlo) * p.pix_vecs], f);
-#pragma unroll
-            for (int e = 0; e < EPV; ++e) ref_s[k * EPV + e] = f[e];
-        }
-        __syncthreads();
-        float ref[EPV], s1[EPV], s2[EPV];
-#pragma unroll
-        for (int e = 0; e < EPV; ++e) {
-            ref[e] = ref_s[k * EPV + e];
-            s1[e] = s2[e] = 0.f;
-        }
-        for (int q0 = pg; q0 < p.hw; q0 += 32 * 4) {              // four independent loads in flight
-            uint4 v[4];
-            bool in[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int q = q0 + 32 * u;
-                const int i = (int)fdiv((uint32_t)q, p.div_w), j = q - i * p.g.bsize_w;
-                const int yy = y0 + i, xx = x0 + j;
-                in[u] = chan_ok && q < p.hw && yy >= 0 && yy < p.H && xx >= 0 && xx < p.W;
-                v[u] = make_uint4(0, 0, 0, 0);
-                if (in[u]) v[u] = x[base + ((long long)yy * p.W + xx) * p.pix_vecs];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (in[u]) {
-                    float f[EPV];
-                    BnElem<DT>::unpack(v[u], f);
-#pragma unroll
-                    for (int e = 0; e < EPV; ++e) {
-                        const float d = f[e] - ref[e];
-                        s1[e] += d;
-                        s2[e] = fmaf(d, d, s2[e]);
-                    }
-                }
-        }
-#pragma unroll
-        for (int e = 0; e < EPV; ++e) {
-            red[0][pg][k * EPV + e] = s1[e];
-            red[1][pg][k * EPV + e] = s2[e];
-        }
-        __syncthreads();
-        if (threadIdx.x < 8 * EPV) {                              // one thread per channel of the slab
-            const int c = slab * p.cs + threadIdx.x;
-            float a = 0.f, q2 = 0.f;
-            for (int gq = 0; gq < 32; ++gq) {
-                a += red[0][gq][threadIdx.x];
-                q2 += red[1][gq][threadIdx.x];
-            }
-            if (c < p.C) {
-                const float nf = (float)npx;
-                const float md = npx > 0 ? a / nf : 0.f;          // mean of the deviations
-                part[((size_t)b * p.C + c) * 2] = ref_s[threadIdx.x] + md;
-                part[((size_t)b * p.C + c) * 2 + 1] = npx > 0 ? fmaxf(q2 - a * md, 0.f) : 0.f;
-            }
-            if (slab == 0 && threadIdx.x == 0) cnt[b] = (float)npx;
-        }
-        __syncthreads();                                          // LDS free for the next item
+    for (int e = 0; e < EPV; ++e) ref[e] = s1[e] = s2[e] = 0.f;
+    {   // reference value per channel: the image's pixel next to the first block's origin
+        const BnPlace w = bn_place<EPV>(blk, slab, k, p);
+        if (w.chan_ok)
+            BnElem<DT>::unpack(x[w.base + ((long long)min(max(w.y0, 0), p.H - 1) * p.W + min(max(w.x0, 0), p.W - 1)) * p.pix_vecs], ref);
     }
+    int npx = 0;
+    for (uint32_t item = row; item < items; item += rows) {
+        const uint32_t b = fdiv(item, div_pieces);
+        const BnPlace w = bn_place<EPV>(blk, slab, k, p);
+        blk = bn_block(indices, fdiv(item + rows, div_pieces), p.cap);        // the next item's
+        const int q0 = (int)(item - b * pieces) * kBnPiece + pg;
+        long long at[4];
+        uint4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {                             // four independent loads in flight
+            at[u] = bn_pixel(w, q0 + 32 * u, p);
+            if (at[u] >= 0) {
+                v[u] = x[at[u]];
+                ++npx;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (at[u] >= 0) {
+                float f[EPV];
+                BnElem<DT>::unpack(v[u], f);
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    const float d = f[e] - ref[e];
+                    s1[e] += d;
+                    s2[e] = fmaf(d, d, s2[e]);
+                }
+            }
+    }
+    if (pg == 0) {
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) ref_s[k * EPV + e] = ref[e];
+    }
+    float a, q2;
+    const float n = bn_reduce<EPV>(red, redn, s1, s2, npx, &a, &q2);
+    const int c = slab * p.cs + threadIdx.x;
+    if (threadIdx.x < NCH && c < p.C) {
+        const float md = n > 0.f ? a / n : 0.f;                   // mean of the deviations
+        part[((size_t)row * p.C + c) * 2] = ref_s[threadIdx.x] + md;
+        part[((size_t)row * p.C + c) * 2 + 1] = n > 0.f ? fmaxf(q2 - a * md, 0.f) : 0.f;
+    }
+    if (slab == 0 && threadIdx.x == 0) cnt[row] = n;
 }
 
 // merge of two (count, mean, M2) triples; an empty side leaves the other unchanged
 __device__ __forceinline__ void bn_merge(float &n, float &m, float &m2, float nb, float mb, float m2b) {
     if (nb <= 0.f) return;
-    const float tot = n + nb, delta = mb - m;
-    m += delta * (nb / tot);
-    m2 += m2b + delta * delta * (n * nb / tot);
+    const float tot = n + nb, delta = mb - m, share = nb / tot;
+    m += delta * share;
+    m2 += m2b + delta * delta * (n * share);
     n = tot;
 }
 
-// one workgroup per channel: thread t merges blocks t, t + 256, ... in that order, then the 256 partial triples are
-// merged pairwise in a fixed tree
-__global__ __launch_bounds__(kBnThreads) void bn_combine(const float *__restrict__ part, const float *__restrict__ cnt,
-                                                         const int32_t *__restrict__ count, int cap, int C,
-                                                         float *__restrict__ mean, float *__restrict__ var) {
-    __shared__ float sn[kBnThreads], sm[kBnThreads], sq[kBnThreads];
-    const int c = blockIdx.x;
-    const int nact = min(*count, cap);
+// Four channels per workgroup: thread (t, channel) merges rows t, t + 256, ... in that order, four in flight, then the 256
+// partial triples are merged pairwise in a fixed tree.
+__global__ __launch_bounds__(1024) void bn_combine(const float *__restrict__ part, const float *__restrict__ cnt,
+                                                   const int32_t *__restrict__ count, int cap, int C, int max_rows, int pieces,
+                                                   float *__restrict__ mean, float *__restrict__ var) {
+    __shared__ float sn[64], sm[64], sq[64];
+    const int ch = threadIdx.x & 3, row = threadIdx.x >> 2, c = blockIdx.x * 4 + ch;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int rows = (int)min((long long)min(*count, cap) * pieces, (long long)max_rows);
     float n = 0.f, m = 0.f, m2 = 0.f;
-    for (int b = threadIdx.x; b < nact; b += kBnThreads)
-        bn_merge(n, m, m2, cnt[b], part[((size_t)b * C + c) * 2], part[((size_t)b * C + c) * 2 + 1]);
-    sn[threadIdx.x] = n; sm[threadIdx.x] = m; sq[threadIdx.x] = m2;
-    __syncthreads();
-    for (int half = kBnThreads / 2; half > 0; half >>= 1) {
-        if ((int)threadIdx.x < half) {
-            bn_merge(n, m, m2, sn[threadIdx.x + half], sm[threadIdx.x + half], sq[threadIdx.x + half]);
-            sn[threadIdx.x] = n; sm[threadIdx.x] = m; sq[threadIdx.x] = m2;
+    for (int b0 = row; b0 < rows; b0 += 256 * 4) {
+        f32x2_a4 v[4];
+        float k[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int b = min(b0 + 256 * u, rows - 1);
+            v[u] = *(const f32x2_a4 *)(part + ((size_t)b * C + min(c, C - 1)) * 2);
+            k[u] = cnt[b];
         }
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (b0 + 256 * u < rows) bn_merge(n, m, m2, k[u], v[u][0], v[u][1]);
     }
-    if (threadIdx.x == 0) {
+    // a fixed tree: the 16 rows of a wave, then the 16 waves (a wave holds four channels: lane = 4 row + channel)
+    auto fold = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int off = 32; off >= 4; off >>= 1) bn_merge(n, m, m2, __shfl_down(n, off), __shfl_down(m, off), __shfl_down(m2, off));
+    };
+    fold();
+    if (lane < 4) { sn[wave * 4 + lane] = n; sm[wave * 4 + lane] = m; sq[wave * 4 + lane] = m2; }
+    __syncthreads();
+    if (wave > 0) return;
+    n = sn[lane]; m = sm[lane]; m2 = sq[lane];
+    fold();
+    if (lane < 4 && c < C) {
         mean[c] = m;
         var[c] = n > 0.f ? m2 / n : 0.f;
     }
@@ -163,16 +159,17 @@ extern "C" sbnet_status sbnet_sparse_bn_stats(const void *x, sbnet_dtype dtype, 
     hipStream_t s = (hipStream_t)stream;
     float *part = (float *)workspace;
     float *cnt = part ? part + (size_t)cap * C * 2 : nullptr;
+    const int rows = bn_rows(cap, p), pieces = bn_pieces(p);
     if (cap > 0) {
-        const long long items = (long long)cap * p.slabs;
-        const int grid = (int)(items < 8192 ? items : 8192);
-        if (dtype == SBNET_F32)
-            hipLaunchKernelGGL(bn_partial<SBNET_F32>, dim3(grid), dim3(kBnThreads), 0, s, (const uint4 *)x, indices, count, part, cnt, p);
-        else if (dtype == SBNET_BF16)
-            hipLaunchKernelGGL(bn_partial<SBNET_BF16>, dim3(grid), dim3(kBnThreads), 0, s, (const uint4 *)x, indices, count, part, cnt, p);
-        else
-            hipLaunchKernelGGL(bn_partial<SBNET_F16>, dim3(grid), dim3(kBnThreads), 0, s, (const uint4 *)x, indices, count, part, cnt, p);
+        const int grid = rows * p.slabs;
+#define SBNET_BN_PARTIAL(DT)                                                                                              \
+    hipLaunchKernelGGL(bn_partial<DT>, dim3(grid), dim3(kBnThreads), 0, s, (const uint4 *)x, indices, count, part, cnt, pieces, \
+                       make_fastdiv(pieces), p)
+        if (dtype == SBNET_F32) SBNET_BN_PARTIAL(SBNET_F32);
+        else if (dtype == SBNET_BF16) SBNET_BN_PARTIAL(SBNET_BF16);
+        else SBNET_BN_PARTIAL(SBNET_F16);
+#undef SBNET_BN_PARTIAL
     }
-    hipLaunchKernelGGL(bn_combine, dim3(C), dim3(kBnThreads), 0, s, part, cnt, count, cap, C, mean, var);
+    hipLaunchKernelGGL(bn_combine, dim3((C + 3) / 4), dim3(1024), 0, s, part, cnt, count, cap, C, rows, pieces, mean, var);
     return launch_status(who);
 }

@@ -442,6 +442,16 @@ def test_sparse_bn_apply_and_backward(H, W, C, bo, N, dtype, relu):
         assert torch.equal(dx, dx2) and torch.equal(dgam, dgam2) and torch.equal(dbet, dbet2)
 
 
+@pytest.mark.parametrize("H,W,C,bo,N,dtype", [
+    (40, 44, 1032, 8, 1, "bf16"),          # more channels than the coefficients in LDS hold at once, a partial last slab
+    (270, 265, 8, 8, 1, "f16"),            # 1156 blocks: more items than rows of partial sums
+    (66, 50, 136, 20, 1, "f32"),           # 400 pixels a block: four pieces, the last one of 16
+])
+def test_normalisation_over_pieces_and_channel_groups(H, W, C, bo, N, dtype):
+    test_sparse_bn_stats(H, W, C, bo, N, dtype)
+    test_sparse_bn_apply_and_backward(H, W, C, bo, N, dtype, True)
+
+
 # --------------------------------------------------------------------------- fp32 convolution
 F32_CONV_CASES = [
     # H, W, Cin, Cout, k, s, bo, N, dtype: items are 64 output pixels x up to 64 channels, chunks whole groups of 8 channels
