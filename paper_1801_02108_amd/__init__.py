@@ -1,10 +1,12 @@
 """Thin Python binding of libsbnet_hip.so (see include/sbnet.h for the contract of every call).
 
 Argument marshalling only: torch tensors supply device memory and the current stream; every
-step of the path runs in the library's HIP kernels.  There is no CPU or PyTorch fallback: if
-the shared library is missing, importing a symbol from it raises.
+step of the path runs in the library's HIP kernels.  The marshalling itself is native
+(csrc/torch_calls.cpp); ctypes serves the host-only calls and the packing of weights.  There is
+no CPU or PyTorch fallback: if a shared library is missing, the first call into it raises.
 """
 import ctypes
+import importlib
 import os
 
 import torch
@@ -134,6 +136,24 @@ def lib():
     return _lib
 
 
+class _Calls:
+    """Stands for the native module until its first use, so that the package imports before anything is built."""
+
+    def __getattr__(self, name):
+        global _calls
+        lib()
+        try:
+            native = importlib.import_module("._torch_calls", __name__)
+        except ImportError as e:
+            raise ImportError("%s: run `python -m paper_1801_02108_amd.build` first" % e) from e
+        native.set_error(SbnetError)
+        _calls = native
+        return getattr(native, name)
+
+
+_calls = _Calls()
+
+
 def get_tuning():
     """The compute-tile choices in force, as a dict."""
     t = Tuning()
@@ -206,31 +226,13 @@ def workspace_bytes(N, g):
 
 def reduce_mask(mask, g, pool=POOL_AVG, threshold=0.0, indices=None, count=None, workspace=None):
     """mask [N,H,W] u8/f32 -> (indices int32 [cap,3], count int32 [1]) on the device."""
-    _dev(mask, "mask")
-    N, H, W = mask.shape
-    cap = N * g.bcount_h * g.bcount_w if indices is None else indices.shape[0]
-    if indices is None:
-        indices = torch.empty((cap, 3), dtype=torch.int32, device=mask.device)
-    if count is None:
-        count = torch.empty((1,), dtype=torch.int32, device=mask.device)
-    need = workspace_bytes(N, g)
-    if workspace is None:
-        workspace = torch.empty((need,), dtype=torch.uint8, device=mask.device)
-    _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32), _dev(workspace, "workspace")
-    _check(lib().sbnet_reduce_mask(_ptr(mask), _dt(mask), N, H, W, g, pool, float(threshold), _ptr(indices),
-                                   _ptr(count), cap, _ptr(workspace), workspace.numel() * workspace.element_size(),
-                                   _stream()))
-    return indices, count
+    return _calls.reduce_mask(mask, g, pool, threshold, indices, count, workspace)
 
 
 def reduce_mask_static(mask, g, indices, count, pool=POOL_AVG, threshold=0.0):
     """reduce_mask without a workspace argument (the library's built-in scratch): the caller passes every
     buffer, nothing is allocated on the way.  Returns (indices, count) as passed."""
-    _dev(mask, "mask"), _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    N, H, W = mask.shape
-    _check(lib().sbnet_reduce_mask_static(_ptr(mask), _dt(mask), N, H, W, g, pool, float(threshold), _ptr(indices),
-                                          _ptr(count), indices.shape[0], _stream()))
-    return indices, count
+    return _calls.reduce_mask_static(mask, g, indices, count, pool, threshold)
 
 
 def read_count(count, cap):
@@ -241,189 +243,65 @@ def read_count(count, cap):
 
 def sparse_gather(x, indices, count, g, tiles=None):
     """x [N,H,W,C] -> tiles [cap, bsize_h, bsize_w, C]; rows beyond the active count are untouched."""
-    _dev(x, "x"), _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    N, H, W, C = x.shape
-    cap = indices.shape[0]
-    if tiles is None:
-        tiles = torch.empty((cap, g.bsize_h, g.bsize_w, C), dtype=x.dtype, device=x.device)
-    _dev(tiles, "tiles", x.dtype)
-    assert tiles.shape == (cap, g.bsize_h, g.bsize_w, C)
-    _check(lib().sbnet_sparse_gather(_ptr(x), _dt(x), N, H, W, C, _ptr(indices), _ptr(count), cap, g, _ptr(tiles),
-                                     _stream()))
-    return tiles
+    return _calls.sparse_gather(x, indices, count, g, tiles)
 
 
 def sparse_scatter(tiles, indices, count, g, y, add=False):
     """tiles [cap, bsize_h, bsize_w, C] -> written or added into y [N,H,W,C] in place; returns y."""
-    _dev(tiles, "tiles"), _dev(y, "y", tiles.dtype)
-    _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    N, H, W, C = y.shape
-    cap = indices.shape[0]
-    assert tiles.shape == (cap, g.bsize_h, g.bsize_w, C), (tuple(tiles.shape), (cap, g.bsize_h, g.bsize_w, C))
-    _check(lib().sbnet_sparse_scatter(_ptr(tiles), _dt(tiles), _ptr(indices), _ptr(count), cap, g, _ptr(y), N, H, W,
-                                      C, int(bool(add)), _stream()))
-    return y
+    return _calls.sparse_scatter(tiles, indices, count, g, y, add)
 
 
 def sparse_gather_chw(x, indices, count, g, tiles=None):
     """Gather with the transpose fused in: x [N,H,W,C] -> channel-major tiles [cap,C,h,w]."""
-    _dev(x, "x"), _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    N, H, W, C = x.shape
-    cap = indices.shape[0]
-    if tiles is None:
-        tiles = torch.empty((cap, C, g.bsize_h, g.bsize_w), dtype=x.dtype, device=x.device)
-    _dev(tiles, "tiles", x.dtype)
-    assert tiles.shape == (cap, C, g.bsize_h, g.bsize_w)
-    _check(lib().sbnet_sparse_gather_chw(_ptr(x), _dt(x), N, H, W, C, _ptr(indices), _ptr(count), cap, g, _ptr(tiles),
-                                         _stream()))
-    return tiles
+    return _calls.sparse_gather_chw(x, indices, count, g, tiles)
 
 
 def sparse_scatter_chw(tiles, indices, count, g, y, add=False):
     """Scatter (or scatter-add) of channel-major tiles [cap,C,h,w] into y [N,H,W,C] in place; returns y."""
-    _dev(tiles, "tiles"), _dev(y, "y", tiles.dtype)
-    _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    N, H, W, C = y.shape
-    cap = indices.shape[0]
-    assert tiles.shape == (cap, C, g.bsize_h, g.bsize_w)
-    _check(lib().sbnet_sparse_scatter_chw(_ptr(tiles), _dt(tiles), _ptr(indices), _ptr(count), cap, g, _ptr(y), N, H, W,
-                                          C, int(bool(add)), _stream()))
-    return y
+    return _calls.sparse_scatter_chw(tiles, indices, count, g, y, add)
 
 
 def sparse_gather_backward(dtiles, indices, count, g, dx, workspace=None):
     """Gradient of sparse_gather: adds the tile gradients [cap,h,w,C] (overlapping halos included) into dx [N,H,W,C]."""
-    _dev(dtiles, "dtiles"), _dev(dx, "dx", dtiles.dtype)
-    _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    N, H, W, C = dx.shape
-    cap = indices.shape[0]
-    assert dtiles.shape == (cap, g.bsize_h, g.bsize_w, C)
-    need = lib().sbnet_gather_backward_workspace_bytes(N, g)
-    if workspace is None:
-        workspace = torch.empty((max(need, 4),), dtype=torch.uint8, device=dx.device)
-    _dev(workspace, "workspace", torch.uint8)
-    _check(lib().sbnet_sparse_gather_backward(_ptr(dtiles), _dt(dtiles), _ptr(indices), _ptr(count), cap, g, _ptr(dx),
-                                              N, H, W, C, _ptr(workspace), workspace.numel(), _stream()))
-    return dx
+    return _calls.sparse_gather_backward(dtiles, indices, count, g, dx, workspace)
 
 
 def sparse_bn_stats(x, indices, count, g, workspace=None):
     """Per-channel mean and biased variance of x [N,H,W,C] over the pixels of the active blocks; returns (mean, var)."""
-    _dev(x, "x"), _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    N, H, W, C = x.shape
-    cap = indices.shape[0]
-    need = lib().sbnet_bn_stats_workspace_bytes(cap, C)
-    if workspace is None:
-        workspace = torch.empty((max(need, 4),), dtype=torch.uint8, device=x.device)
-    _dev(workspace, "workspace", torch.uint8)
-    mean = torch.empty((C,), dtype=torch.float32, device=x.device)
-    var = torch.empty((C,), dtype=torch.float32, device=x.device)
-    _check(lib().sbnet_sparse_bn_stats(_ptr(x), _dt(x), N, H, W, C, _ptr(indices), _ptr(count), cap, g, _ptr(mean),
-                                       _ptr(var), _ptr(workspace), workspace.numel(), _stream()))
-    return mean, var
-
-
-def _vec(t, name, C):
-    if t is not None:
-        _dev(t, name, torch.float32)
-        assert t.shape == (C,)
-    return _ptr(t)
+    return _calls.sparse_bn_stats(x, indices, count, g, workspace)
 
 
 def sparse_bn_apply(x, indices, count, g, mean, var, gamma=None, beta=None, eps=1e-5, relu=False, y=None):
     """y = act(gamma (x - mean) / sqrt(var + eps) + beta) on the pixels of the active blocks, y untouched elsewhere
     (y defaults to x: in place); returns y."""
-    _dev(x, "x"), _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    N, H, W, C = x.shape
-    if y is None:
-        y = x
-    _dev(y, "y", x.dtype)
-    assert y.shape == x.shape
-    _check(lib().sbnet_sparse_bn_apply(_ptr(x), _dt(x), N, H, W, C, _ptr(indices), _ptr(count), indices.shape[0], g,
-                                       _vec(mean, "mean", C), _vec(var, "var", C), _vec(gamma, "gamma", C),
-                                       _vec(beta, "beta", C), float(eps), int(bool(relu)), _ptr(y), _stream()))
-    return y
+    return _calls.sparse_bn_apply(x, indices, count, g, mean, var, gamma, beta, eps, relu, y)
 
 
 def sparse_bn_backward(x, dy, indices, count, g, mean, var, gamma=None, beta=None, eps=1e-5, relu=False, dx=None,
                        workspace=None):
     """Gradients through sparse_bn_apply in training mode (mean, var = sparse_bn_stats of x over the same blocks);
     returns (dx, dgamma, dbeta); dx defaults to a new zero tensor and is written on the active blocks only."""
-    _dev(x, "x"), _dev(dy, "dy", x.dtype), _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    N, H, W, C = x.shape
-    cap = indices.shape[0]
-    if dx is None:
-        dx = torch.zeros_like(x)
-    _dev(dx, "dx", x.dtype)
-    assert dy.shape == x.shape and dx.shape == x.shape
-    need = lib().sbnet_bn_backward_workspace_bytes(cap, C)
-    if workspace is None:
-        workspace = torch.empty((max(need, 4),), dtype=torch.uint8, device=x.device)
-    _dev(workspace, "workspace", torch.uint8)
-    dgamma = torch.empty((C,), dtype=torch.float32, device=x.device)
-    dbeta = torch.empty((C,), dtype=torch.float32, device=x.device)
-    _check(lib().sbnet_sparse_bn_backward(_ptr(x), _ptr(dy), _dt(x), N, H, W, C, _ptr(indices), _ptr(count), cap, g,
-                                          _vec(mean, "mean", C), _vec(var, "var", C), _vec(gamma, "gamma", C),
-                                          _vec(beta, "beta", C), float(eps), int(bool(relu)), _ptr(dx), _ptr(dgamma),
-                                          _ptr(dbeta), _ptr(workspace), workspace.numel(), _stream()))
-    return dx, dgamma, dbeta
+    return _calls.sparse_bn_backward(x, dy, indices, count, g, mean, var, gamma, beta, eps, relu, dx, workspace)
 
 
 def relu_backward_on_tiles(y_tiles, dy_tiles, count, out=None):
     """dy where the forward activation y is positive, else 0, on the active tiles of two stacks of one shape."""
-    _dev(y_tiles, "y_tiles"), _dev(dy_tiles, "dy_tiles", y_tiles.dtype), _dev(count, "count", torch.int32)
-    assert y_tiles.shape == dy_tiles.shape
-    if out is None:
-        out = torch.empty_like(dy_tiles)
-    _dev(out, "out", y_tiles.dtype)
-    cap = y_tiles.shape[0]
-    _check(lib().sbnet_relu_backward_on_tiles(_ptr(y_tiles), _ptr(dy_tiles), _dt(y_tiles), _ptr(count), cap,
-                                              y_tiles[0].numel() if cap else 1, _ptr(out), _stream()))
-    return out
+    return _calls.relu_backward_on_tiles(y_tiles, dy_tiles, count, out)
 
 
 def bias_backward_on_tiles(dy_tiles, count, workspace=None):
     """Sum of dy [cap,h,w,C] over the active tiles and their pixels: float32 [C]."""
-    _dev(dy_tiles, "dy_tiles"), _dev(count, "count", torch.int32)
-    cap, h, w, C = dy_tiles.shape
-    need = lib().sbnet_bias_backward_workspace_bytes(cap, C)
-    if workspace is None:
-        workspace = torch.empty((max(need, 4),), dtype=torch.uint8, device=dy_tiles.device)
-    _dev(workspace, "workspace", torch.uint8)
-    db = torch.empty((C,), dtype=torch.float32, device=dy_tiles.device)
-    _check(lib().sbnet_bias_backward_on_tiles(_ptr(dy_tiles), _dt(dy_tiles), _ptr(count), cap, h * w, C, _ptr(db),
-                                              _ptr(workspace), workspace.numel(), _stream()))
-    return db
+    return _calls.bias_backward_on_tiles(dy_tiles, count, workspace)
 
 
 def relu_bias_backward_on_tiles(y_tiles, dy_tiles, count, out=None, workspace=None):
     """(dout, db): dy [cap,h,w,C] masked by y > 0 on the active tiles, and its per-channel sum (float32 [C]), in one pass."""
-    _dev(y_tiles, "y_tiles"), _dev(dy_tiles, "dy_tiles", y_tiles.dtype), _dev(count, "count", torch.int32)
-    assert y_tiles.shape == dy_tiles.shape
-    cap, h, w, C = dy_tiles.shape
-    if out is None:
-        out = torch.empty_like(dy_tiles)
-    _dev(out, "out", dy_tiles.dtype)
-    assert out.shape == dy_tiles.shape
-    need = lib().sbnet_bias_backward_workspace_bytes(cap, C)
-    if workspace is None:
-        workspace = torch.empty((max(need, 4),), dtype=torch.uint8, device=dy_tiles.device)
-    _dev(workspace, "workspace", torch.uint8)
-    db = torch.empty((C,), dtype=torch.float32, device=dy_tiles.device)
-    _check(lib().sbnet_relu_bias_backward_on_tiles(_ptr(y_tiles), _ptr(dy_tiles), _dt(dy_tiles), _ptr(count), cap, h * w, C,
-                                                   _ptr(out), _ptr(db), _ptr(workspace), workspace.numel(), _stream()))
-    return out, db
+    return _calls.relu_bias_backward_on_tiles(y_tiles, dy_tiles, count, out, workspace)
 
 
 def quantize_f8(x, scale=1.0, out=None):
     """x (f32 / bf16 / f16 device tensor) -> uint8 tensor of FP8 E4M3 (e4m3fn) codes of clamp(x * scale, +-448)."""
-    _dev(x, "x")
-    if out is None:
-        out = torch.empty(x.shape, dtype=torch.uint8, device=x.device)
-    _dev(out, "out", torch.uint8)
-    assert out.shape == x.shape
-    _check(lib().sbnet_quantize_f8(_ptr(x), _dt(x), x.numel(), float(scale), _ptr(out), _stream()))
-    return out
+    return _calls.quantize_f8(x, scale, out)
 
 
 def pack_weights_f8(w_f8):
@@ -439,61 +317,19 @@ def pack_weights_f8(w_f8):
 
 def conv_on_tiles_f8(tiles_f8, count, w_packed, bias=None, stride=1, relu=False, out_scale=1.0, out=None):
     """Valid convolution of FP8 tiles [cap,th,tw,Cin] (uint8 codes) with FP8 weights -> bf16 [cap,th',tw',Cout]."""
-    _dev(tiles_f8, "tiles_f8", torch.uint8), _dev(count, "count", torch.int32)
-    kh, kw, Cin, Cout = w_packed.shape
-    cap, th, tw, C = tiles_f8.shape
-    assert C == Cin and w_packed.dtype == torch.uint8
-    oh, ow = (th - kh) // stride + 1, (tw - kw) // stride + 1
-    if out is None:
-        out = torch.empty((cap, oh, ow, Cout), dtype=torch.bfloat16, device=tiles_f8.device)
-    _dev(out, "out", torch.bfloat16)
-    if bias is not None:
-        _dev(bias, "bias", torch.float32)
-    _check(lib().sbnet_conv_on_tiles_f8(_ptr(tiles_f8), _ptr(count), cap, th, tw, Cin, _ptr(w_packed.buf), _ptr(bias), kh,
-                                        kw, stride, stride, Cout, int(bool(relu)), float(out_scale), _ptr(out), _stream()))
-    return out
+    return _calls.conv_on_tiles_f8(tiles_f8, count, w_packed, bias, stride, relu, out_scale, out)
 
 
 def bottleneck_forward_keep_on_tiles(tiles, indices, count, g_in, H, W, weights):
     """Residual branch on tiles with its activations kept for the backward pass: returns (t1, t2, t3).
     weights = (w1, b1, w2, b2, w3, b3) as sparse_bottleneck takes them."""
-    _dev(tiles, "tiles"), _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    w1, b1, w2, b2, w3, b3 = weights
-    cap, th, tw, C = tiles.shape
-    Cm = w1.shape[3]
-    assert (th, tw) == (g_in.bsize_h, g_in.bsize_w) and cap == indices.shape[0]
-    new = lambda h, w, c: torch.empty((cap, h, w, c), dtype=tiles.dtype, device=tiles.device)
-    t1, t2, t3 = new(th, tw, Cm), new(th - 2, tw - 2, Cm), new(th - 2, tw - 2, C)
-    _check(lib().sbnet_bottleneck_forward_keep_on_tiles(_ptr(tiles), _dt(tiles), H, W, C, Cm, _ptr(indices), _ptr(count), cap,
-                                                        g_in, _ptr(w1.buf), _ptr(b1), _ptr(w2.buf), _ptr(b2), _ptr(w3.buf),
-                                                        _ptr(b3), _ptr(t1), _ptr(t2), _ptr(t3), _stream()))
-    return t1, t2, t3
+    return _calls.bottleneck_forward_keep_on_tiles(tiles, indices, count, g_in, H, W, weights)
 
 
 def bottleneck_backward_on_tiles(tiles, t1, t2, dt3, count, weights_t, workspace=None):
     """Backward of the residual branch on tiles from kept activations: returns (dtiles, dw1, db1, dw2, db2, dw3, db3).
     weights_t = (w1_t, w2_t, w3_t) from pack_weights_transposed of the three forward weight arrays."""
-    for name, t in (("tiles", tiles), ("t1", t1), ("t2", t2), ("dt3", dt3)):
-        _dev(t, name, tiles.dtype)
-    _dev(count, "count", torch.int32)
-    cap, th, tw, C = tiles.shape
-    Cm = t1.shape[3]
-    assert t1.shape == (cap, th, tw, Cm) and t2.shape == (cap, th - 2, tw - 2, Cm) and dt3.shape == (cap, th - 2, tw - 2, C)
-    w1_t, w2_t, w3_t = weights_t
-    assert w1_t.shape == (1, 1, C, Cm) and w2_t.shape == (3, 3, Cm, Cm) and w3_t.shape == (1, 1, Cm, C)
-    need = lib().sbnet_bottleneck_backward_workspace_bytes(_dt(tiles), cap, th, tw, C, Cm)
-    if workspace is None:
-        workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=tiles.device)
-    _dev(workspace, "workspace", torch.uint8)
-    dev = tiles.device
-    dtiles = torch.empty_like(tiles)
-    f32 = lambda *shape: torch.empty(shape, dtype=torch.float32, device=dev)
-    dw1, db1, dw2, db2, dw3, db3 = f32(1, 1, C, Cm), f32(Cm), f32(3, 3, Cm, Cm), f32(Cm), f32(1, 1, Cm, C), f32(C)
-    _check(lib().sbnet_bottleneck_backward_on_tiles(_ptr(tiles), _ptr(t1), _ptr(t2), _ptr(dt3), _dt(tiles), _ptr(count), cap,
-                                                    th, tw, C, Cm, _ptr(w1_t.buf), _ptr(w2_t.buf), _ptr(w3_t.buf),
-                                                    _ptr(dtiles), _ptr(dw1), _ptr(db1), _ptr(dw2), _ptr(db2), _ptr(dw3),
-                                                    _ptr(db3), _ptr(workspace), workspace.numel(), _stream()))
-    return dtiles, dw1, db1, dw2, db2, dw3, db3
+    return _calls.bottleneck_backward_on_tiles(tiles, t1, t2, dt3, count, weights_t, workspace)
 
 
 class PackedWeights:
@@ -516,19 +352,7 @@ def pack_weights(w_hwio):
 
 def conv_on_tiles(tiles, count, w_packed, bias=None, stride=1, relu=False, out=None):
     """Valid convolution on a tile stack [cap,th,tw,Cin] -> [cap,th',tw',Cout]."""
-    _dev(tiles, "tiles"), _dev(count, "count", torch.int32)
-    kh, kw, Cin, Cout = w_packed.shape
-    cap, th, tw, C = tiles.shape
-    assert C == Cin and w_packed.dtype == tiles.dtype
-    oh, ow = (th - kh) // stride + 1, (tw - kw) // stride + 1
-    if out is None:
-        out = torch.empty((cap, oh, ow, Cout), dtype=tiles.dtype, device=tiles.device)
-    _dev(out, "out", tiles.dtype)
-    if bias is not None:
-        _dev(bias, "bias", torch.float32)
-    _check(lib().sbnet_conv_on_tiles(_ptr(tiles), _dt(tiles), _ptr(count), cap, th, tw, Cin, _ptr(w_packed.buf),
-                                     _ptr(bias), kh, kw, stride, stride, Cout, int(bool(relu)), _ptr(out), _stream()))
-    return out
+    return _calls.conv_on_tiles(tiles, count, w_packed, bias, stride, relu, out)
 
 
 def pack_weights_transposed(w_hwio):
@@ -551,22 +375,7 @@ def conv_backward_data_workspace_bytes(dtype, cap, th, tw, kh, kw, stride, Cout)
 def conv_on_tiles_backward_data(dout_tiles, count, w_packed_t, th, tw, stride=1, out=None, workspace=None):
     """dL/d(tiles_in) [cap,th,tw,Cin] of conv_on_tiles (no bias, no activation) from dL/d(tiles_out)
     [cap,oh,ow,Cout]; w_packed_t from pack_weights_transposed of the forward weights."""
-    _dev(dout_tiles, "dout_tiles"), _dev(count, "count", torch.int32)
-    kh, kw, Cin, Cout = w_packed_t.shape
-    cap, oh, ow, C = dout_tiles.shape
-    assert C == Cout and w_packed_t.dtype == dout_tiles.dtype
-    assert oh == (th - kh) // stride + 1 and ow == (tw - kw) // stride + 1
-    if out is None:
-        out = torch.empty((cap, th, tw, Cin), dtype=dout_tiles.dtype, device=dout_tiles.device)
-    _dev(out, "out", dout_tiles.dtype)
-    need = conv_backward_data_workspace_bytes(dout_tiles.dtype, cap, th, tw, kh, kw, stride, Cout)
-    if workspace is None:
-        workspace = torch.empty((max(need, 16),), dtype=torch.uint8, device=dout_tiles.device)
-    _dev(workspace, "workspace", torch.uint8)
-    _check(lib().sbnet_conv_on_tiles_backward_data(_ptr(dout_tiles), _dt(dout_tiles), _ptr(count), cap, th, tw, Cin,
-                                                   _ptr(w_packed_t.buf), kh, kw, stride, stride, Cout, _ptr(out),
-                                                   _ptr(workspace), workspace.numel(), _stream()))
-    return out
+    return _calls.conv_on_tiles_backward_data(dout_tiles, count, w_packed_t, th, tw, stride, out, workspace)
 
 
 def conv_backward_weights_workspace_bytes(dtype, cap, th, tw, Cin, k, stride, Cout):
@@ -576,181 +385,50 @@ def conv_backward_weights_workspace_bytes(dtype, cap, th, tw, Cin, k, stride, Co
 def conv_on_tiles_backward_weights(tiles, dout_tiles, count, k, stride=1, out=None, workspace=None):
     """dL/dw [k,k,Cin,Cout] (float32) of conv_on_tiles from its input tiles [cap,th,tw,Cin] and dL/d(tiles_out)
     [cap,oh,ow,Cout], summed over the active tiles."""
-    _dev(tiles, "tiles"), _dev(dout_tiles, "dout_tiles", tiles.dtype), _dev(count, "count", torch.int32)
-    cap, th, tw, Cin = tiles.shape
-    cap2, oh, ow, Cout = dout_tiles.shape
-    assert cap2 == cap and oh == (th - k) // stride + 1 and ow == (tw - k) // stride + 1
-    if out is None:
-        out = torch.empty((k, k, Cin, Cout), dtype=torch.float32, device=tiles.device)
-    _dev(out, "out", torch.float32)
-    assert out.shape == (k, k, Cin, Cout)
-    need = conv_backward_weights_workspace_bytes(tiles.dtype, cap, th, tw, Cin, k, stride, Cout)
-    if workspace is None:
-        workspace = torch.empty((max(need, 16),), dtype=torch.uint8, device=tiles.device)
-    _dev(workspace, "workspace", torch.uint8)
-    _check(lib().sbnet_conv_on_tiles_backward_weights(_ptr(tiles), _ptr(dout_tiles), _dt(tiles), _ptr(count), cap, th, tw,
-                                                      Cin, k, k, stride, stride, Cout, _ptr(out), _ptr(workspace),
-                                                      workspace.numel(), _stream()))
-    return out
+    return _calls.conv_on_tiles_backward_weights(tiles, dout_tiles, count, k, stride, out, workspace)
 
 
 def sparse_conv(x, indices, count, g_in, g_out, w_packed, bias, y, stride=1, relu=False, add=False):
     """Fused gather -> valid conv -> scatter(-add) into y [N,H_out,W_out,Cout] in place; returns y."""
-    _dev(x, "x"), _dev(y, "y", x.dtype)
-    _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    kh, kw, Cin, Cout = w_packed.shape
-    N, H, W, C = x.shape
-    assert C == Cin and w_packed.dtype == x.dtype
-    Ny, Ho, Wo, Cy = y.shape
-    assert Ny == N and Cy == Cout
-    if bias is not None:
-        _dev(bias, "bias", torch.float32)
-    _check(lib().sbnet_sparse_conv(_ptr(x), _dt(x), N, H, W, Cin, _ptr(indices), _ptr(count), indices.shape[0],
-                                   g_in, g_out, _ptr(w_packed.buf), _ptr(bias), kh, kw, stride, stride, Cout,
-                                   int(bool(relu)), _ptr(y), Ho, Wo, int(bool(add)), _stream()))
-    return y
+    return _calls.sparse_conv(x, indices, count, g_in, g_out, w_packed, bias, y, stride, relu, add)
 
 
 def block_flags(mask, g, pool=POOL_AVG, threshold=0.0, flags=None):
     """mask [N,H,W] u8/f32 -> one flag byte per block (lexicographic), padded to a multiple of 16 bytes."""
-    _dev(mask, "mask")
-    N, H, W = mask.shape
-    need = lib().sbnet_block_flags_bytes(N, g)
-    if flags is None:
-        flags = torch.empty((need,), dtype=torch.uint8, device=mask.device)
-    _dev(flags, "flags", torch.uint8)
-    _check(lib().sbnet_block_flags(_ptr(mask), _dt(mask), N, H, W, g, pool, float(threshold), _ptr(flags), flags.numel(),
-                                   _stream()))
-    return flags
+    return _calls.block_flags(mask, g, pool, threshold, flags)
 
 
 def sparse_conv_from_flags(flags, x, g_in, g_out, w_packed, bias, y, indices, count, stride=1, relu=False, add=False):
     """Fused sparse conv fed by block flags; fills y in place and writes the index list and count.  Returns y."""
-    _dev(flags, "flags", torch.uint8), _dev(x, "x"), _dev(y, "y", x.dtype)
-    _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    kh, kw, Cin, Cout = w_packed.shape
-    N, H, W, C = x.shape
-    assert C == Cin and w_packed.dtype == x.dtype
-    Ny, Ho, Wo, Cy = y.shape
-    assert Ny == N and Cy == Cout and flags.numel() >= lib().sbnet_block_flags_bytes(N, g_in)
-    if bias is not None:
-        _dev(bias, "bias", torch.float32)
-    _check(lib().sbnet_sparse_conv_from_flags(_ptr(flags), _ptr(x), _dt(x), N, H, W, Cin, _ptr(indices), _ptr(count),
-                                              indices.shape[0], g_in, g_out, _ptr(w_packed.buf), _ptr(bias), kh, kw, stride,
-                                              stride, Cout, int(bool(relu)), _ptr(y), Ho, Wo, int(bool(add)), _stream()))
-    return y
+    return _calls.sparse_conv_from_flags(flags, x, g_in, g_out, w_packed, bias, y, indices, count, stride, relu, add)
 
 
 def sparse_conv_from_mask(mask, g_mask, x, g_in, g_out, w_packed, bias, y, indices, count, workspace, pool=POOL_AVG,
                           threshold=0.0, stride=1, relu=False, add=False):
     """reduce_mask + fused sparse conv in one call (two launches where the convolution kernel takes block flags);
     fills y in place and leaves the index list and the count in indices / count.  Returns y."""
-    _dev(mask, "mask"), _dev(x, "x"), _dev(y, "y", x.dtype), _dev(workspace, "workspace")
-    _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    kh, kw, Cin, Cout = w_packed.shape
-    N, H, W, C = x.shape
-    Nm, mH, mW = mask.shape
-    assert C == Cin and w_packed.dtype == x.dtype and Nm == N
-    Ny, Ho, Wo, Cy = y.shape
-    assert Ny == N and Cy == Cout
-    if bias is not None:
-        _dev(bias, "bias", torch.float32)
-    _check(lib().sbnet_sparse_conv_from_mask(_ptr(mask), _dt(mask), mH, mW, g_mask, pool, float(threshold), _ptr(x), _dt(x),
-                                             N, H, W, Cin, _ptr(indices), _ptr(count), indices.shape[0], g_in, g_out,
-                                             _ptr(w_packed.buf), _ptr(bias), kh, kw, stride, stride, Cout, int(bool(relu)),
-                                             _ptr(y), Ho, Wo, int(bool(add)), _ptr(workspace),
-                                             workspace.numel() * workspace.element_size(), _stream()))
-    return y
-
-
-def _unit_args(weights):
-    """(w1p, b1, w2p, b2, w3p, b3) -> checked pointers plus (C, Cm)."""
-    w1, b1, w2, b2, w3, b3 = weights
-    _, _, C, Cm = w1.shape
-    assert w2.shape == (3, 3, Cm, Cm) and w3.shape == (1, 1, Cm, C), (w1.shape, w2.shape, w3.shape)
-    for b, n in ((b1, Cm), (b2, Cm), (b3, C)):
-        _dev(b, "bias", torch.float32)
-        assert b.numel() == n
-    return (_ptr(w1.buf), _ptr(b1), _ptr(w2.buf), _ptr(b2), _ptr(w3.buf), _ptr(b3)), C, Cm
-
-
-def _pre_args(pre, C):
-    scale, shift = pre
-    _dev(scale, "pre_scale", torch.float32), _dev(shift, "pre_shift", torch.float32)
-    assert scale.numel() == C and shift.numel() == C
-    return _ptr(scale), _ptr(shift)
+    return _calls.sparse_conv_from_mask(mask, g_mask, x, g_in, g_out, w_packed, bias, y, indices, count, workspace,
+                                        pool, threshold, stride, relu, add)
 
 
 def bottleneck_on_tiles(tiles, indices, count, g_in, g_out, H, W, weights, out=None, pre=None):
     """Residual branch (1x1+ReLU, 3x3+ReLU, 1x1) on gathered tiles [cap,h,w,C] -> t3 [cap,bo,bo,C];
     pre = (scale, shift): pre-activation ReLU(scale * x + shift) in front of the first convolution."""
-    _dev(tiles, "tiles"), _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    ptrs, C, Cm = _unit_args(weights)
-    cap = indices.shape[0]
-    assert tiles.shape == (cap, g_in.bsize_h, g_in.bsize_w, C)
-    if out is None:
-        out = torch.empty((cap, g_out.bsize_h, g_out.bsize_w, C), dtype=tiles.dtype, device=tiles.device)
-    _dev(out, "out", tiles.dtype)
-    if pre is not None:
-        _check(lib().sbnet_bottleneck_on_tiles_preact(_ptr(tiles), _dt(tiles), H, W, C, Cm, _ptr(indices), _ptr(count),
-                                                      cap, g_in, g_out, *_pre_args(pre, C), *ptrs, _ptr(out), _stream()))
-        return out
-    _check(lib().sbnet_bottleneck_on_tiles(_ptr(tiles), _dt(tiles), H, W, C, Cm, _ptr(indices), _ptr(count), cap,
-                                           g_in, g_out, *ptrs, _ptr(out), _stream()))
-    return out
+    return _calls.bottleneck_on_tiles(tiles, indices, count, g_in, g_out, H, W, weights, out, pre)
 
 
 def sparse_bottleneck(x, indices, count, g_in, g_out, weights, y, pre=None):
     """Fused sparse residual unit: y[active] = x[active] + branch(x); y is a second buffer. Returns y.
     pre = (scale, shift): pre-activation form."""
-    _dev(x, "x"), _dev(y, "y", x.dtype), _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    ptrs, C, Cm = _unit_args(weights)
-    N, H, W, Cx = x.shape
-    assert Cx == C and y.shape == x.shape
-    if pre is not None:
-        _check(lib().sbnet_sparse_bottleneck_preact(_ptr(x), _dt(x), N, H, W, C, Cm, _ptr(indices), _ptr(count),
-                                                    indices.shape[0], g_in, g_out, *_pre_args(pre, C), *ptrs, _ptr(y),
-                                                    _stream()))
-        return y
-    _check(lib().sbnet_sparse_bottleneck(_ptr(x), _dt(x), N, H, W, C, Cm, _ptr(indices), _ptr(count),
-                                         indices.shape[0], g_in, g_out, *ptrs, _ptr(y), _stream()))
-    return y
+    return _calls.sparse_bottleneck(x, indices, count, g_in, g_out, weights, y, pre)
 
 
 def zero_outside(tiles, indices, count, g, H, W):
     """Zero, in place, the positions of tiles [cap,h,w,C] that lie outside the H x W image."""
-    _dev(tiles, "tiles"), _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    cap, h, w, C = tiles.shape
-    assert (h, w) == (g.bsize_h, g.bsize_w) and cap == indices.shape[0]
-    _check(lib().sbnet_zero_outside(_ptr(tiles), _dt(tiles), H, W, C, _ptr(indices), _ptr(count), cap, g, _stream()))
-    return tiles
+    return _calls.zero_outside(tiles, indices, count, g, H, W)
 
 
 def sparse_unit(x, indices, count, g_in, g_out, weights, y, stride=1, shortcut=None, workspace=None):
     """Residual unit of any width: weights = (w1p, b1, w2p, b2, w3p, b3) packed, shortcut = (wsp, bs) packed 1x1 with the
     unit's stride or None for the identity.  Writes the active blocks of y [N,H_out,W_out,Cout] in place; returns y."""
-    _dev(x, "x"), _dev(y, "y", x.dtype), _dev(indices, "indices", torch.int32), _dev(count, "count", torch.int32)
-    w1, b1, w2, b2, w3, b3 = weights
-    _, _, Cin, Cm = w1.shape
-    Cout = w3.shape[3]
-    assert w2.shape == (3, 3, Cm, Cm) and w3.shape[:3] == (1, 1, Cm)
-    for b, n in ((b1, Cm), (b2, Cm), (b3, Cout)):
-        _dev(b, "bias", torch.float32)
-        assert b.numel() == n
-    N, H, W, C = x.shape
-    Ny, Ho, Wo, Cy = y.shape
-    assert C == Cin and Cy == Cout and Ny == N
-    wsp, bs = (None, None) if shortcut is None else shortcut
-    if wsp is not None:
-        assert wsp.shape == (1, 1, Cin, Cout) and bs.numel() == Cout
-        _dev(bs, "shortcut bias", torch.float32)
-    cap = indices.shape[0]
-    need = lib().sbnet_sparse_unit_workspace_bytes(_dt(x), cap, g_in, g_out, Cin, Cm, Cout)
-    if workspace is None:
-        workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=x.device)
-    _dev(workspace, "workspace")
-    _check(lib().sbnet_sparse_unit(_ptr(x), _dt(x), N, H, W, Cin, Cm, Cout, stride, _ptr(indices), _ptr(count), cap, g_in, g_out,
-                                   _ptr(w1.buf), _ptr(b1), _ptr(w2.buf), _ptr(b2), _ptr(w3.buf), _ptr(b3),
-                                   _ptr(wsp.buf) if wsp is not None else None, _ptr(bs), _ptr(y), Ho, Wo, _ptr(workspace),
-                                   workspace.numel() * workspace.element_size(), _stream()))
-    return y
+    return _calls.sparse_unit(x, indices, count, g_in, g_out, weights, y, stride, shortcut, workspace)
