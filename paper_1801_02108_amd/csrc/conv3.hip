@@ -567,6 +567,27 @@ void conv3_pair_kernel(ConvParams p, Plan3 qb, Plan3 qs) {
     else conv3_body<DT, FUSED, ADD, CCS, 4, CBWP, PBWS, NVIS, 3, true>(p, qs);
 }
 
+// Stride 1, 65 ... 96 output channels (or any count that groups of 96 fill better than groups of 64): groups of 96 on
+// 256-pixel items beside the pair of shapes with groups of 64.  One wide item does the work of two 64-channel ones: the
+// rows are staged once and a quarter of the matrix steps, the empty half of the second group, falls away; 16-channel
+// chunks (two buffers of 32 do not fit beside 96 channels of weights) also skip the padding of 48 or 80 channels.  A
+// wide item takes about 9/8 of a 64-channel one (12.4 against 10.8 us in a single round of 96 -> 96 on 16x16 blocks), so
+// the count picks by rounds of work on 256 CUs: below one round of the narrow items they stay.  Measured, narrow
+// against wide: 593 blocks of 12x12, 48 -> 80: 28.1 and 22.5 us; 740 of 14x14, 128 -> 96: 51.5 and 43.5; 550 of 16x16,
+// 48 -> 96: 26.4 and 22.1, 96 -> 96: 35.5 and 34.6.  Not taken: up to 32 input channels, one narrow chunk (24 -> 96: 17.3 and
+// 18.0), and groups of 128, which were mixed (550 of 16x16, 48 -> 128: 26.6 and 27.4).
+template <int DT, bool FUSED, bool ADD, int NVIS>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void conv3_wide96_kernel(ConvParams p, Plan3 qw, Plan3 qb, Plan3 qs) {
+    const uint32_t nact = (uint32_t)max(min(*p.count, p.cap), 0);
+    const uint32_t rw = (nact * (uint32_t)(qw.mpasses * qw.ngroups) + 255u) >> 8, rb = (nact * (uint32_t)(qb.mpasses * qb.ngroups) + 255u) >> 8,
+                   rs = (nact * (uint32_t)(qs.mpasses * qs.ngroups) + 255u) >> 8;
+    const unsigned long long small8 = (unsigned long long)rs * (uint32_t)p.small_cost8, big8 = (unsigned long long)rb * 8u;
+    if ((unsigned long long)rw * 9u <= (big8 <= small8 ? big8 : small8)) conv3_body<DT, FUSED, ADD, 16, 4, 3, 2, 5, 3, true>(p, qw);
+    else if (big8 <= small8) conv3_body<DT, FUSED, ADD, 32, 4, 2, 2, 6, 3, true>(p, qb);
+    else conv3_body<DT, FUSED, ADD, 32, 4, 2, 1, NVIS, 3, true>(p, qs);
+}
+
 // 128-pixel items with groups of 96 / 128 output channels or of 64 in one launch, for strided tiles whose 256-pixel shape
 // has no room for the wider weight chunks (the 33x33 input tile of a 16x16 block).  Measured (192 -> 256 channels, stride
 // 2): with up to ~25 active blocks the 64-channel items are faster (19 against 22.5 us: more, shorter work items on an
@@ -647,7 +668,7 @@ static Shape3 plan3(const ConvParams &p, int pp, int nb = 2, bool only16 = false
         if (total > kLds3) continue;
         sh.cc = cc;
         q.nvec_in = (uint32_t)nvec;
-        q.nchunks = CinP / cc;
+        q.nchunks = (p.Cin + cc - 1) / cc;             // (no 16-channel chunk that would hold nothing but padding)
         q.div_nch = make_fastdiv((uint32_t)q.nchunks);
         q.w_off = (uint32_t)in_b;
         q.buf_bytes = (uint32_t)buf;
@@ -811,6 +832,34 @@ static void launch3_wide(bool fused, const ConvParams &p, const Shape3 &big, con
 #undef SBNET_L3W
 }
 
+// stride 1: groups of 96 beside the two shapes with groups of 64
+template <int DT>
+static void launch3_wide96(bool fused, const ConvParams &p, const Shape3 &wide, const Shape3 &big, const Shape3 &small, hipStream_t s) {
+    const long long items = (long long)p.cap * small.q.mpasses * small.q.ngroups;     // the most of the three
+    long long g = (items + 7) / 8 * 8;
+    if (g > 256) g = 256;
+    size_t lds = wide.lds_bytes > big.lds_bytes ? wide.lds_bytes : big.lds_bytes;
+    if (small.lds_bytes > lds) lds = small.lds_bytes;
+    ConvParams pt = p;
+    pt.small_cost8 = tuning().conv3_small_item_cost_eighths;
+#define SBNET_L3N(FU, AD, NVIS)                                                                                          \
+    do {                                                                                                                 \
+        auto kern = conv3_wide96_kernel<DT, FU, AD, NVIS>;                                                               \
+        (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);             \
+        hipLaunchKernelGGL(kern, dim3((int)g), dim3(512), lds, s, pt, wide.q, big.q, small.q);                           \
+    } while (0)
+#define SBNET_L3M(FU, AD)                                   \
+    do {                                                    \
+        if (small.nvi == 3) SBNET_L3N(FU, AD, 3);           \
+        else SBNET_L3N(FU, AD, 6);                          \
+    } while (0)
+    if (fused && p.add) SBNET_L3M(true, true);
+    else if (fused) SBNET_L3M(true, false);
+    else SBNET_L3M(false, false);
+#undef SBNET_L3M
+#undef SBNET_L3N
+}
+
 bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p0, hipStream_t s, sbnet_status *st, const char *who) {
     if (dt != SBNET_BF16 && dt != SBNET_F16) return false;
     if (p0.kh != p0.kw || (p0.kh != 3 && p0.kh != 1)) return false;
@@ -838,9 +887,9 @@ bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p0, hipStream_t s, 
     } else {
         // Strided tiles of up to 256 pixels whose rows fit in 16-channel chunks of five vectors per thread: groups of 128
         // output channels where the channel count is a multiple of that, of 96 where that spares a half-empty group of
-        // 64 (96, 288 ...).  Measured on the stage shapes: stride 1 gains nothing from them (96 -> 96) or loses (192 -> 192:
-        // its rows fit 32-channel chunks with 64-channel groups, twice the matrix steps per barrier), 96 -> 192 at
-        // stride 2 is the same with either.
+        // 64 (96, 288 ...).  Measured on the stage shapes: stride 1 loses with groups of 96 where those of 64 are full (192
+        // -> 192: its rows fit 32-channel chunks with 64-channel groups, twice the matrix steps per barrier; where they are
+        // not, see conv3_wide96_kernel), 96 -> 192 at stride 2 is the same with either.
         const int nbw = p.Cout % 128 == 0 ? 4 : (p.Cout % 96 == 0 && p.Cout % 64 != 0 ? 3 : 2);
         if (nbw > 2 && M <= 256 && p.sh > 1) {
             Shape3 wb, ws = plan3(p, 128, nbw);
@@ -873,6 +922,16 @@ bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p0, hipStream_t s, 
     if ((long long)p.cap * most_passes * ((p.Cout + 63) / 64) >= (1LL << 31)) return false;
     // with at most 256 items of the smaller tile whatever the count, the rule in the kernel never picks the larger one
     if (big.ok && small.ok && (long long)p.cap * small.q.mpasses * small.q.ngroups <= 256) big.ok = false;
+    if (big.ok && small.ok && p.Cin > 32 && p.kh == 3 && p.sh == 1 && p.sw == 1 && M <= 256 && big.cc == 32 && big.nvi == 6 && small.cc == 32 &&
+        (p.Cout + 95) / 96 * 3 < (p.Cout + 63) / 64 * 2) {
+        const Shape3 wide = plan3(p, 256, 3);                              // see conv3_wide96_kernel
+        if (wide.ok) {
+            if (dt == SBNET_BF16) launch3_wide96<SBNET_BF16>(fused, p, wide, big, small, s);
+            else launch3_wide96<SBNET_F16>(fused, p, wide, big, small, s);
+            *st = launch_status(who);
+            return true;
+        }
+    }
     if (big.ok && small.ok) launch3_pair(dt, fused, p, big, small, s);     // the device-side count picks the shape
     else if (big.ok) launch3(dt, fused, p, big, s);
     else launch3(dt, fused, p, small, s);

@@ -881,6 +881,44 @@ def test_sparse_conv_strided_wide_channel_groups(H, W, Cin, Cout, dtype, add):
         assert_close(to_host(y), ref, CONV_TOL[dtype], "unfused, %d blocks" % len(idx))
 
 
+@pytest.mark.parametrize("bo,side,Cin,Cout,dtype,add", [
+    (12, 140, 48, 80, "f16", False),     # ragged map; three chunks of 16 channels, 16 of 96 output channels empty
+    (16, 192, 96, 96, "bf16", True),     # six chunks, a full group of 96
+    (14, 168, 40, 72, "bf16", False),    # last chunk half filled, 24 output channels empty
+    (16, 190, 40, 288, "bf16", True),    # ragged map, three groups of 96
+])
+def test_sparse_conv_groups_of_96_at_stride_1(bo, side, Cin, Cout, dtype, add):
+    """One launch holds 256-pixel items with groups of 96 channels, and items of 256 and 128 pixels with groups of 64.
+    On a grid of 144 blocks the count picks the wide items with all of them active, the others with 100 and with 20."""
+    step("sparse_conv stride 1, groups of 96 %s" % ((bo, side, Cin, Cout, dtype, add),))
+    r = gen.rng_for(5, side * 100 + Cin + Cout)
+    g_in, g_out, Ho, Wo = sb.geometry(side, side, 3, 1, bo)
+    assert g_out.bcount_h * g_out.bcount_w == 144
+    x = gen.activations(r, (1, side, side, Cin), dtype)
+    w = gen.conv_weights(r, 3, 3, Cin, Cout, dtype)
+    b = gen.bias_vector(r, Cout, 0.5)
+    y0 = gen.activations(r, (1, Ho, Wo, Cout), dtype)
+    wp, d_b, d_x = sb.pack_weights(to_dev(w, dtype)), torch.from_numpy(b).cuda(), to_dev(x, dtype)
+    for n in (144, 100, 20):
+        blocks = np.zeros(144, np.uint8)
+        blocks[r.permutation(144)[:n]] = 1
+        mask = np.kron(blocks.reshape(1, 12, 12), np.ones((1, bo, bo), np.uint8))[:, :side, :side].copy()
+        d_idx, d_cnt = sb.reduce_mask(torch.from_numpy(mask).cuda(), g_out)      # window = output block
+        idx = orc.reduce_mask(mask, ogeom(g_out))
+        assert len(idx) == n
+        ref = orc.sparse_conv_dense(x, idx, ogeom(g_out), w, b, y0, stride=1, relu=True, add=add)
+        bm = orc.block_mask(idx, ogeom(g_out), 1, Ho, Wo)
+        y = to_dev(y0, dtype)
+        sb.sparse_conv(d_x, d_idx, d_cnt, g_in, g_out, wp, d_b, y, relu=True, add=add)
+        got = to_host(y)
+        assert_close(got, ref, CONV_TOL[dtype], "fused, %d blocks" % n)
+        assert np.array_equal(got[~bm], y0[~bm])
+        out = sb.conv_on_tiles(sb.sparse_gather(d_x, d_idx, d_cnt, g_in), d_cnt, wp, d_b, relu=True)
+        y = to_dev(y0, dtype)
+        sb.sparse_scatter(out, d_idx, d_cnt, g_out, y, add=add)
+        assert_close(to_host(y), ref, CONV_TOL[dtype], "unfused, %d blocks" % n)
+
+
 @pytest.mark.parametrize("dens", [1.0, 0.35])
 @pytest.mark.parametrize("Cin", [32, 40])
 def test_sparse_conv_more_tiles_than_workgroups(dens, Cin):
