@@ -4,8 +4,8 @@
 //   tile_relu_backward   dout = dy where the forward activation y is positive, else 0, on the tiles
 //                        b < min(*count, cap); tiles beyond the count are not touched.
 //   tile_bias_partial +  db[c] = sum over those tiles and their pixels of dy[b][pixel][c]: workgroup w of G (at most 256)
-//   tile_bias_sum        sums tiles w, w + G, ... per channel in fp32 (threads strided over pixels, one LDS reduction
-//                        at the end), then one workgroup per 64 channels adds the G sums in a fixed order: no
+//   tile_bias_sum        sums the w-th of G equal runs of their pixels per channel in fp32 (threads strided over pixels,
+//                        one LDS reduction at the end), then one workgroup per 64 channels adds the G sums in a fixed order: no
 //                        atomics, the same bits every run for a given cap.
 //   both in one pass     tile_bias_partial<.., MASK> masks dy by y, writes it and sums what it wrote: the gradient
 //                        that enters a convolution through its ReLU is read once for both.
@@ -51,25 +51,32 @@ __global__ __launch_bounds__(256) void tile_relu_backward(const uint32_t *__rest
         dout[vec_end + threadIdx.x] = relu_mask_word<DT>(y[vec_end + threadIdx.x], dy[vec_end + threadIdx.x]);
 }
 
-// part[w][c] = sum over the pixels of the tiles w, w + G, ... of workgroup w (G = gridDim.x).  VW = 4: a thread owns
-// 16 bytes (4 words) of a pixel's channels and every (256 / vectors per pixel)-th pixel; VW = 1:
-// one word, for channel counts that do not fill 16-byte vectors.  cw = 4-byte words per pixel (one f32 channel or two
-// 16-bit ones), cw / VW <= 256.  Every thread adds its pixels tile after tile in ascending order; the pixel groups
-// are then added in ascending order through LDS.
+// part[g][c] = sum over the pixels of workgroup g's run of dy[pixel][c]: the active tiles are one run of n * pixels pixels,
+// cut into G = gridDim.x equal runs.  VW = 4: a thread owns 16 bytes (4 words) of a pixel's channels and every
+// (kBiasThreads / vectors per pixel)-th pixel; VW = 1: one word, for channel counts that do not fill 16-byte vectors.
+// cw = 4-byte words per pixel (one f32 channel or two 16-bit ones), cw / VW <= 256.  Every thread adds its pixels in
+// ascending order; the pixel groups are then added through LDS in a fixed order, by slices.
 // MASK: the words of dy are first masked by the forward activation y (relu_mask_word), written to dout at the same
 // place (dout may be dy: every word is read and written by one thread) and summed as written.
+// Bound by memory.  With one workgroup of 256 threads per tile (four waves on a CU, two rounds of tiles where there are
+// more than 256) too few loads were in flight; sixteen waves on equal runs: the pass of ReLU
+// mask, bias sum and their total with 440 tiles of 16x16x64 went down by 3 to 5 us in a training step of 136.6 (133.7 and 131.9).
+constexpr int kBiasThreads = 1024;
+
 template <int DT, int VW, bool MASK>
-__global__ __launch_bounds__(256) void tile_bias_partial(const uint32_t *dy, const int32_t *__restrict__ count,
-                                                         int cap, int pixels, int C, int cw, float *__restrict__ part,
-                                                         const uint32_t *__restrict__ y, uint32_t *dout) {
+__global__ __launch_bounds__(kBiasThreads) void tile_bias_partial(const uint32_t *dy, const int32_t *__restrict__ count,
+                                                                  int cap, int pixels, int C, int cw, float *__restrict__ part,
+                                                                  const uint32_t *__restrict__ y, uint32_t *dout) {
     constexpr int EPW = DT == SBNET_F32 ? 1 : 2;
     constexpr int NE = VW * EPW;                                  // channels per thread
-    __shared__ float red[256][NE + 1];
+    __shared__ float red[kBiasThreads][NE + 1];
+    __shared__ float slice_sum[kBiasThreads];
     int n = *count;
     if (n > cap) n = cap;
-    if ((int)blockIdx.x >= n) return;                             // the sum reads no result of this workgroup
+    const size_t total = (size_t)(n > 0 ? n : 0) * pixels, run = (total + gridDim.x - 1) / gridDim.x;
+    const size_t lo = min(run * blockIdx.x, total), hi = min(lo + run, total);
     const int cvn = cw / VW;                                      // threads per pixel
-    const int groups = 256 / cvn;                                 // pixel groups that fit the workgroup
+    const int groups = kBiasThreads / cvn;                        // pixel groups that fit the workgroup
     const int w = threadIdx.x % cvn, pg = threadIdx.x / cvn;
     float acc[NE];
 #pragma unroll
@@ -100,27 +107,20 @@ __global__ __launch_bounds__(256) void tile_bias_partial(const uint32_t *dy, con
         else q[0] = v[0];
     };
     if (pg < groups) {
-        // the thread's pixels, tile after tile and in ascending order inside a tile, taken eight at a time whatever
-        // the tile they fall in: eight (with a mask sixteen) loads are in flight all the way
-        constexpr int U = 8;
-        const int ppt = (pixels + groups - 1) / groups;           // pixel slots of this thread per tile
-        const int total = ((n - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x) * ppt;
-        int b = blockIdx.x, px = pg;                               // slot j: tile b, pixel px
-        const size_t first = (size_t)blockIdx.x * pixels * cw + (size_t)w * VW;      // pixel 0 of the workgroup's first tile
-        for (int j0 = 0; j0 < total; j0 += U) {
+        constexpr int U = 4;                                      // four (with a mask eight) loads in flight per thread
+        const size_t first = lo * cw + (size_t)w * VW;
+        for (size_t px = lo + pg; px < hi; px += (size_t)groups * U) {
             uint32_t v[U][VW], a[U][VW];
             size_t off[U];
             bool ok[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                // a slot that holds no pixel reads pixel 0 of the first tile (always there) and is not used: no branch
+                // a slot that holds no pixel reads the run's first one (always there) and is not used: no branch
                 // between the loads
-                ok[u] = j0 + u < total && px < pixels;
-                off[u] = ok[u] ? ((size_t)b * pixels + px) * cw + (size_t)w * VW : first;
+                ok[u] = px + (size_t)u * groups < hi;
+                off[u] = ok[u] ? (px + (size_t)u * groups) * cw + (size_t)w * VW : first;
                 load(v[u], dy + off[u]);
                 if (MASK) load(a[u], y + off[u]);
-                px += groups;
-                if (px >= ppt * groups + pg) { px = pg; b += gridDim.x; }
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -134,31 +134,36 @@ __global__ __launch_bounds__(256) void tile_bias_partial(const uint32_t *dy, con
 #pragma unroll
     for (int e = 0; e < NE; ++e) red[threadIdx.x][e] = acc[e];
     __syncthreads();
-    if (threadIdx.x < (unsigned)cvn) {                            // groups in ascending order
-        float a[NE];
-#pragma unroll
-        for (int e = 0; e < NE; ++e) a[e] = 0.f;
-        for (int k = 0; k < groups; ++k)
-#pragma unroll
-            for (int e = 0; e < NE; ++e) a[e] += red[k * cvn + threadIdx.x][e];
-#pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            const int c = threadIdx.x * NE + e;
-            if (c < C) part[(size_t)blockIdx.x * C + c] = a[e];
+    // channel c is element c % NE of thread column c / NE; slice k of S adds the groups k, k + S, ..., then the slices are added
+    const int channels = cvn * NE;
+    if (channels >= kBiasThreads) {
+        for (int c = threadIdx.x; c < channels; c += kBiasThreads) {
+            float a = 0.f;
+            for (int k = 0; k < groups; ++k) a += red[k * cvn + c / NE][c % NE];
+            if (c < C) part[(size_t)blockIdx.x * C + c] = a;
         }
+        return;
+    }
+    const int S = min(kBiasThreads / channels, groups), c = threadIdx.x % channels, k0 = threadIdx.x / channels;
+    if (k0 < S) {
+        float a = 0.f;
+        for (int k = k0; k < groups; k += S) a += red[k * cvn + c / NE][c % NE];
+        slice_sum[k0 * channels + c] = a;
+    }
+    __syncthreads();
+    if (k0 == 0 && c < C) {
+        float a = slice_sum[c];
+        for (int k = 1; k < S; ++k) a += slice_sum[k * channels + c];
+        part[(size_t)blockIdx.x * C + c] = a;
     }
 }
 
-// db[c] = sum over the workgroups' results part[w][c], w < min(n, G): 64 channels per workgroup of 16 waves; wave k takes
+// db[c] = sum over the workgroups' results part[w][c], w < n: 64 channels per workgroup of 16 waves; wave k takes
 // the results k, k + 16, ... in ascending order, eight loads in flight, then the 16 sums are added in ascending order
-__global__ __launch_bounds__(1024) void tile_bias_sum(const float *__restrict__ part, const int32_t *__restrict__ count, int cap,
-                                                      int G, int C, float *__restrict__ db) {
+__global__ __launch_bounds__(1024) void tile_bias_sum(const float *__restrict__ part, int n, int C, float *__restrict__ db) {
     __shared__ float slice[16][64];
     const int lane = threadIdx.x & 63, k = threadIdx.x >> 6;
     const int c = blockIdx.x * 64 + lane;
-    int n = *count;
-    if (n > cap) n = cap;
-    if (n > G) n = G;
     float acc = 0.f;
     if (c < C) {
         for (int b = k; b < n; b += 128) {
@@ -240,9 +245,9 @@ sbnet_status bias_backward(const char *who, const void *y_tiles, const void *dy_
     hipStream_t s = (hipStream_t)stream;
     float *part = (float *)workspace;
     if (cap > 0) {
-        const int grid = cap < 256 ? cap : 256;
+        const int grid = cap < 256 ? cap : 256;                   // the workspace holds a result per tile, and 256 fill the device
 #define SBNET_BP2(DT, VW, MASK)                                                                                       \
-    hipLaunchKernelGGL((tile_bias_partial<DT, VW, MASK>), dim3(grid), dim3(256), 0, s, (const uint32_t *)dy_tiles, count, \
+    hipLaunchKernelGGL((tile_bias_partial<DT, VW, MASK>), dim3(grid), dim3(kBiasThreads), 0, s, (const uint32_t *)dy_tiles, count, \
                        cap, pixels, C, cw, part, (const uint32_t *)y_tiles, (uint32_t *)dout_tiles)
 #define SBNET_BP(DT)                                                   \
     do {                                                              \
@@ -259,7 +264,7 @@ sbnet_status bias_backward(const char *who, const void *y_tiles, const void *dy_
         sbnet_status st = launch_status(who);
         if (st != SBNET_OK) return st;
     }
-    hipLaunchKernelGGL(tile_bias_sum, dim3((C + 63) / 64), dim3(1024), 0, s, part, count, cap, cap < 256 ? cap : 256, C, db);
+    hipLaunchKernelGGL(tile_bias_sum, dim3((C + 63) / 64), dim3(1024), 0, s, part, cap < 256 ? cap : 256, C, db);
     return launch_status(who);
 }
 

@@ -221,6 +221,17 @@ def test_relu_and_bias_backward_on_tiles(B, h, w, C, dtype):
     assert (db0 == 0).all() and torch.equal(out2, out)             # no active tile: nothing written, zero sums
 
 
+@pytest.mark.parametrize("B,h,w,C,dtype", [
+    (300, 3, 5, 16, "bf16"),       # more tiles than workgroups: runs that end inside a tile
+    (260, 1, 1, 8, "f16"),         # one thread column, most runs of two pixels and the last ones empty
+    (2, 40, 40, 2048, "bf16"),     # the most channels a pixel may have: no slices in the last sum
+    (2, 9, 9, 1024, "f32"),
+    (3, 7, 7, 48, "f16"),          # six thread columns: threads of the last group stay idle
+])
+def test_relu_and_bias_backward_on_runs_of_pixels(B, h, w, C, dtype):
+    test_relu_and_bias_backward_on_tiles(B, h, w, C, dtype)
+
+
 @pytest.mark.parametrize("C,Cm,dens", [(64, 64, 0.02), (256, 64, 0.004), (96, 24, 0.01)])
 def test_residual_unit_backward_composed_from_single_calls(C, Cm, dens):
     """The residual branch of a unit (Sec. 3.3) forward with its activations kept, then every gradient from library
