@@ -52,6 +52,28 @@ sbnet_status unit_down_try(const char *who, const void *x, sbnet_dtype dt, int N
                            const void *w3, const float *b3, const void *ws, const float *bs, void *y, int Ho, int Wo,
                            void *stream);
 
+// tile_backward.hip: sbnet_bias_backward_on_tiles of up to three stacks, in one pair of launches where the workspace holds
+// their partial sums and their channels fill 16-byte vectors, else one after the other; the same bits either way.
+struct BiasStack {
+    const void *dy;
+    int pixels, C;
+    float *db;
+};
+sbnet_status bias_backward_stacks(const BiasStack *stacks, int n, sbnet_dtype dtype, const int32_t *count, int cap, void *workspace,
+                                  size_t workspace_bytes, void *stream);
+
+// conv.hip: sbnet_conv_on_tiles_backward_data with the result zeroed where y, the forward activation in the place of din,
+// is not positive.  SBNET_EUNSUPPORTED, with nothing launched, for shapes whose kernel does not do that.
+sbnet_status backward_data_masked(const char *who, const void *dout_tiles, sbnet_dtype dtype, const int32_t *count, int cap, int th,
+                                  int tw, int Cin, const void *w_packed_t, int kh, int kw, int Cout, const void *y, void *din_tiles,
+                                  void *workspace, size_t workspace_bytes, void *stream);
+
+// conv.hip: a pointwise convolution with ReLU whose result is zero at pixels outside the H x W image (sbnet_conv_on_tiles, then
+// sbnet_zero_outside).  SBNET_EUNSUPPORTED, with nothing launched, for shapes whose kernel does not do that.
+sbnet_status pointwise_inside(const char *who, const void *tiles_in, sbnet_dtype dtype, const int32_t *indices, const int32_t *count,
+                              int cap, const sbnet_geom *g_in, int H, int W, int Cin, const void *w_packed, const float *bias, int Cout,
+                              void *tiles_out, void *stream);
+
 // do the byte ranges [a, a + a_bytes) and [b, b + b_bytes) share a byte?
 inline bool ranges_overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes) {
     const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;

@@ -379,6 +379,16 @@ static sbnet_status check_conv_shape(const char *who, sbnet_dtype dt, int cap, i
 static const int kLdsBudget = 64 * 1024;      // preferred: two workgroups per CU
 static const int kLdsMax = 160 * 1024;        // gfx950 LDS per workgroup
 
+// index triple (b, 0, 0) for tile b: every tile as a sample of its own with a single block
+__global__ void tile_indices(int32_t *__restrict__ idx, int cap) {
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b < cap) {
+        idx[3 * b] = b;
+        idx[3 * b + 1] = 0;
+        idx[3 * b + 2] = 0;
+    }
+}
+
 template <bool FUSED>
 static sbnet_status run_conv(const char *who, sbnet_dtype dt, ConvParams &p, hipStream_t s) {
     if (p.cap == 0) return SBNET_OK;
@@ -392,6 +402,15 @@ static sbnet_status run_conv(const char *who, sbnet_dtype dt, ConvParams &p, hip
 
     if (use_mfma(dt, p.Cin, p.Cout)) p.w32_offset = packed_elems(dt, p.kh, p.kw, p.Cin, p.Cout) / 2 / 8;
     sbnet_status st16 = SBNET_OK;
+    if (p.mask || p.inside) return conv3_try(dt, FUSED, p, s, &st16, who) ? st16 : SBNET_EUNSUPPORTED;
+    if (FUSED && p.own_sample) {
+        // conv3.hip works without the list; the other kernels get one
+        if (!conv16_accepts(dt, FUSED, p) && conv3_try(dt, FUSED, p, s, &st16, who)) return st16;
+        p.own_sample = 0;
+        hipLaunchKernelGGL(tile_indices, dim3((p.cap + 255) / 256), dim3(256), 0, s, const_cast<int32_t *>(p.indices), p.cap);
+        st16 = launch_status(who);
+        if (st16 != SBNET_OK) return st16;
+    }
     if (conv16_try(dt, FUSED, p, s, &st16, who)) return st16;
     if (conv3_try(dt, FUSED, p, s, &st16, who)) return st16;
 
@@ -543,16 +562,6 @@ __global__ void spread_tiles(const V *__restrict__ dout, V *__restrict__ framed,
     }
 }
 
-// index triple (b, 0, 0) for tile b: every tile as a sample of its own with a single block
-__global__ void tile_indices(int32_t *__restrict__ idx, int cap) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < cap) {
-        idx[3 * b] = b;
-        idx[3 * b + 1] = 0;
-        idx[3 * b + 2] = 0;
-    }
-}
-
 }  // namespace sbnet
 
 static size_t framed_elems(int cap, int th, int tw, int kh, int kw, int Cout) {
@@ -568,12 +577,9 @@ extern "C" size_t sbnet_conv_backward_data_workspace_bytes(sbnet_dtype dtype, in
     return (bytes + 255) / 256 * 256;
 }
 
-extern "C" sbnet_status sbnet_conv_on_tiles_backward_data(const void *dout_tiles, sbnet_dtype dtype,
-                                                          const int32_t *count, int cap, int th, int tw, int Cin,
-                                                          const void *w_packed_t, int kh, int kw, int sh, int sw,
-                                                          int Cout, void *din_tiles, void *workspace,
-                                                          size_t workspace_bytes, void *stream) {
-    const char *who = "sbnet_conv_on_tiles_backward_data";
+static sbnet_status backward_data(const char *who, const void *dout_tiles, sbnet_dtype dtype, const int32_t *count, int cap, int th,
+                                  int tw, int Cin, const void *w_packed_t, int kh, int kw, int sh, int sw, int Cout, const void *mask,
+                                  void *din_tiles, void *workspace, size_t workspace_bytes, void *stream) {
     if (!dout_tiles || !count || !w_packed_t || !din_tiles || !workspace)
         return fail(SBNET_EINVAL, "%s: null pointer", who);
     sbnet_status st = check_conv_shape(who, dtype, cap, th, tw, Cin, kh, kw, sh, sw, Cout);
@@ -597,19 +603,17 @@ extern "C" sbnet_status sbnet_conv_on_tiles_backward_data(const void *dout_tiles
         p.count = count; p.cap = cap;
         p.th = th; p.tw = tw; p.Cin = Cout; p.Cout = Cin;
         p.kh = 1; p.kw = 1; p.sh = 1; p.sw = 1; p.relu = 0;
+        p.mask = mask;
         return run_conv<false>(who, dtype, p, s);
     }
     if (sh == 1 && sw == 1) {
         // No stride, nothing to spread: the frame of zeros is what the fused kernels read around an image anyway.
         // Every tile of dout is taken as a sample of its own (oh x ow), gathered with a window that starts kh-1 / kw-1
         // outside it, and the result "scattered" into a th x tw image that is the tile of din.
-        int32_t *idx = (int32_t *)workspace;
-        hipLaunchKernelGGL(tile_indices, dim3((cap + 255) / 256), dim3(256), 0, s, idx, cap);
-        st = launch_status(who);
-        if (st != SBNET_OK) return st;
         ConvParams p = {};
         p.in = dout_tiles; p.out = din_tiles; p.w = w_packed_t; p.bias = nullptr;
-        p.indices = idx; p.count = count; p.cap = cap;
+        p.indices = (const int32_t *)workspace; p.own_sample = 1; p.mask = mask;      // the list: written where a kernel reads it
+        p.count = count; p.cap = cap;
         p.th = ph; p.tw = pw; p.Cin = Cout; p.Cout = Cin;
         p.kh = kh; p.kw = kw; p.sh = 1; p.sw = 1; p.relu = 0; p.add = 0;
         p.g_in.bsize_h = ph; p.g_in.bsize_w = pw; p.g_in.bstride_h = ph; p.g_in.bstride_w = pw;
@@ -619,6 +623,7 @@ extern "C" sbnet_status sbnet_conv_on_tiles_backward_data(const void *dout_tiles
         p.H = oh; p.W = ow; p.Ho = th; p.Wo = tw;
         return run_conv<true>(who, dtype, p, s);
     }
+    if (mask) return SBNET_EUNSUPPORTED;
     const int vb = row_bytes % 16 == 0 ? 16 : row_bytes % 8 == 0 ? 8 : row_bytes % 4 == 0 ? 4 : 2;
     const int cv = (int)(row_bytes / vb);
     const long long per_tile = (long long)ph * pw * cv;
@@ -641,6 +646,39 @@ extern "C" sbnet_status sbnet_conv_on_tiles_backward_data(const void *dout_tiles
     p.th = ph; p.tw = pw; p.Cin = Cout; p.Cout = Cin;
     p.kh = kh; p.kw = kw; p.sh = 1; p.sw = 1; p.relu = 0;
     return run_conv<false>(who, dtype, p, s);
+}
+
+extern "C" sbnet_status sbnet_conv_on_tiles_backward_data(const void *dout_tiles, sbnet_dtype dtype,
+                                                          const int32_t *count, int cap, int th, int tw, int Cin,
+                                                          const void *w_packed_t, int kh, int kw, int sh, int sw,
+                                                          int Cout, void *din_tiles, void *workspace,
+                                                          size_t workspace_bytes, void *stream) {
+    const char *who = "sbnet_conv_on_tiles_backward_data";
+    return backward_data(who, dout_tiles, dtype, count, cap, th, tw, Cin, w_packed_t, kh, kw, sh, sw, Cout, nullptr, din_tiles, workspace,
+                         workspace_bytes, stream);
+}
+
+sbnet_status sbnet::backward_data_masked(const char *who, const void *dout_tiles, sbnet_dtype dtype, const int32_t *count, int cap,
+                                         int th, int tw, int Cin, const void *w_packed_t, int kh, int kw, int Cout, const void *y,
+                                         void *din_tiles, void *workspace, size_t workspace_bytes, void *stream) {
+    if ((uintptr_t)y & 15) return SBNET_EUNSUPPORTED;
+    return backward_data(who, dout_tiles, dtype, count, cap, th, tw, Cin, w_packed_t, kh, kw, 1, 1, Cout, y, din_tiles, workspace,
+                         workspace_bytes, stream);
+}
+
+sbnet_status sbnet::pointwise_inside(const char *who, const void *tiles_in, sbnet_dtype dtype, const int32_t *indices,
+                                     const int32_t *count, int cap, const sbnet_geom *g_in, int H, int W, int Cin, const void *w_packed,
+                                     const float *bias, int Cout, void *tiles_out, void *stream) {
+    if (((uintptr_t)tiles_in | (uintptr_t)tiles_out | (uintptr_t)w_packed) & 15) return SBNET_EUNSUPPORTED;
+    if (cap <= 0 || H <= 0 || W <= 0 || check_conv_shape(who, dtype, cap, g_in->bsize_h, g_in->bsize_w, Cin, 1, 1, 1, 1, Cout) != SBNET_OK)
+        return SBNET_EUNSUPPORTED;
+    ConvParams p = {};
+    p.in = tiles_in; p.out = tiles_out; p.w = w_packed; p.bias = bias;
+    p.indices = indices; p.count = count; p.cap = cap;
+    p.th = g_in->bsize_h; p.tw = g_in->bsize_w; p.Cin = Cin; p.Cout = Cout;
+    p.kh = 1; p.kw = 1; p.sh = 1; p.sw = 1; p.relu = 1; p.inside = 1;
+    p.g_in = *g_in; p.H = H; p.W = W;
+    return run_conv<false>(who, dtype, p, (hipStream_t)stream);
 }
 
 extern "C" sbnet_status sbnet_sparse_conv(const void *x, sbnet_dtype dtype, int N, int H, int W, int Cin,

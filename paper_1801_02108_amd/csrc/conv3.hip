@@ -88,9 +88,15 @@ struct Chunk3 {
 // one wave per SIMD the matrix core stood idle through both: per chunk the kernel took about the SUM of its matrix,
 // LDS and load time.  With the roles in different waves of the same SIMD they overlap.  Both roles walk the same
 // chunk sequence and meet at the same barrier per chunk.
-template <int DT, bool FUSED, bool ADD, int CC, int WP, int CBW, int PBW, int NVI, int KH = 3, bool SPEC = false>
+// EPI: kEpiMask zeroes results where p.mask is not positive, kEpiInside at pixels outside the image (both in the gradient and
+// the training forward of the residual unit, where a pass of their own read and wrote the whole stack again).
+constexpr int kEpiNone = 0, kEpiMask = 1, kEpiInside = 2;
+
+template <int DT, bool FUSED, bool ADD, int CC, int WP, int CBW, int PBW, int NVI, int KH = 3, bool SPEC = false, int EPI = kEpiNone>
 __device__ __forceinline__ void conv3_body(const ConvParams &p, const Plan3 &q) {
     static_assert(FUSED || !ADD, "adding into the output is part of the fused form");
+    static_assert(EPI == kEpiNone || !ADD, "the sum is not masked");
+    constexpr bool LIST = FUSED || EPI == kEpiInside;        // the index list is read
     // Register sets for chunks in flight.  Two (requests two chunks further ahead) were measured for the small
     // workgroup tiles and gained nothing: the compiler's wait before a vector's LDS write allows only one set's
     // worth of younger loads, and those tiles are bound by the issue of their staging instructions anyway.
@@ -146,7 +152,7 @@ __device__ __forceinline__ void conv3_body(const ConvParams &p, const Plan3 &q) 
         c.pass = (int)fdiv(rest, q.div_ng);
         c.ng = (int)rest - c.pass * q.ngroups;
         c.n = c.by = c.bx = 0;
-        if (FUSED) {
+        if (LIST) {
             const int32_t *t = p.indices + 3 * (size_t)c.b + lane_zero;
             c.n = t[0];
             c.by = t[1];
@@ -156,10 +162,14 @@ __device__ __forceinline__ void conv3_body(const ConvParams &p, const Plan3 &q) 
     };
     auto resolve = [&](const Item3 &c) __attribute__((always_inline)) {
         Item3 r = c;
-        if (FUSED) {
+        if (LIST) {
             r.n = __builtin_amdgcn_readfirstlane(c.n);
             r.by = __builtin_amdgcn_readfirstlane(c.by);
             r.bx = __builtin_amdgcn_readfirstlane(c.bx);
+        }
+        if (FUSED && p.own_sample) {                 // (whatever the list holds)
+            r.n = (int)c.b;
+            r.by = r.bx = 0;
         }
         return r;
     };
@@ -455,6 +465,32 @@ __device__ __forceinline__ void conv3_body(const ConvParams &p, const Plan3 &q) 
                     return origin + (uint32_t)((i * out_w + j) * p.Cout) * 2u;
                 };
                 const int chg = cur.it.ng * GW + cw * CBW * 32;                    // first channel of the wave
+                // what the results are masked by, at the places of the stores: all requested at once
+                uint4 act[EPI == kEpiMask ? PBW : 1][CBW][2];
+                if (EPI == kEpiMask) {
+                    const long long at = (const char *)obase - (const char *)p.out;
+                    const __amdgpu_buffer_rsrc_t mrs = __builtin_amdgcn_make_buffer_rsrc(
+                        (void *)((const char *)p.mask + at), 0, (int)obytes, (int)kBufWord3);
+#pragma unroll
+                    for (int pb = 0; pb < PBW; ++pb)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            bool ok;
+                            const uint32_t off = pixel_offset(p_lo + (uint32_t)((pw * PBW + pb) * 32 + j * 16) + (lane >> 2), ok);
+#pragma unroll
+                            for (int cb = 0; cb < CBW; ++cb) {
+                                const int ch = chg + cb * 32 + (lane & 3) * 8;
+                                act[EPI == kEpiMask ? pb : 0][cb][j] = buf_load16(mrs, (ok && ch < p.Cout) ? off + (uint32_t)ch * 2u : kOutOfRange);
+                            }
+                        }
+                }
+                auto outside = [&](uint32_t px) __attribute__((always_inline)) {
+                    const uint32_t pc = min(px, (uint32_t)M - 1u);
+                    const uint32_t i = fdiv(pc, p.div_ow), j = pc - i * p.ow;
+                    const int yy = p.g_in.boffset_h + cur.it.by * p.g_in.bstride_h + (int)i;
+                    const int xx = p.g_in.boffset_w + cur.it.bx * p.g_in.bstride_w + (int)j;
+                    return (uint32_t)yy >= (uint32_t)p.H || (uint32_t)xx >= (uint32_t)p.W;
+                };
 #pragma unroll
                 for (int pb = 0; pb < PBW; ++pb) {
                     const uint32_t pblock = p_lo + (uint32_t)((pw * PBW + pb) * 32);
@@ -501,7 +537,13 @@ __device__ __forceinline__ void conv3_body(const ConvParams &p, const Plan3 &q) 
                         const int ch = chg + cb * 32 + (lane & 3) * 8;
 #pragma unroll
                         for (int j = 0; j < 2; ++j) {
-                            const uint4 v = *(const uint4 *)(ost + (j * 16 + (lane >> 2)) * kOst3Ps + (lane & 3) * 16);
+                            uint4 v = *(const uint4 *)(ost + (j * 16 + (lane >> 2)) * kOst3Ps + (lane & 3) * 16);
+                            if (EPI == kEpiMask) {
+                                const uint4 a = act[EPI == kEpiMask ? pb : 0][cb][j];
+                                v.x &= positive_halves<DT>(a.x); v.y &= positive_halves<DT>(a.y);
+                                v.z &= positive_halves<DT>(a.z); v.w &= positive_halves<DT>(a.w);
+                            }
+                            if (EPI == kEpiInside && outside(pblock + j * 16 + (lane >> 2))) v = make_uint4(0, 0, 0, 0);
                             buf_store16(ors, (ok2[j] && ch < p.Cout) ? off2[j] + (uint32_t)ch * 2u : kOutOfRange, v);
                         }
                         __builtin_amdgcn_wave_barrier();
@@ -527,18 +569,18 @@ __device__ __forceinline__ void conv3_body(const ConvParams &p, const Plan3 &q) 
     }
 }
 
-template <int DT, bool FUSED, bool ADD, int CC, int WP, int CBW, int PBW, int NVI>
+template <int DT, bool FUSED, bool ADD, int CC, int WP, int CBW, int PBW, int NVI, int EPI = kEpiNone>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void conv3_kernel(ConvParams p, Plan3 q) {
-    conv3_body<DT, FUSED, ADD, CC, WP, CBW, PBW, NVI, 3, true>(p, q);
+    conv3_body<DT, FUSED, ADD, CC, WP, CBW, PBW, NVI, 3, true, EPI>(p, q);
 }
 
 // Pointwise convolutions wait on memory, not on the matrix cores: their kernel is built for two workgroups per CU
 // (at most 256 registers, and the host picks a tile shape whose LDS plan fits twice).
-template <int DT, bool FUSED, bool ADD, int CC, int WP, int CBW, int PBW, int NVI>
+template <int DT, bool FUSED, bool ADD, int CC, int WP, int CBW, int PBW, int NVI, int EPI = kEpiNone>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void conv3_pointwise_kernel(ConvParams p, Plan3 q) {
-    conv3_body<DT, FUSED, ADD, CC, WP, CBW, PBW, NVI, 1, false>(p, q);
+    conv3_body<DT, FUSED, ADD, CC, WP, CBW, PBW, NVI, 1, false, EPI>(p, q);
 }
 
 // The 256-pixel and the 128-pixel tile shape in one launch: the device-side count picks one (rounds of work on 256
@@ -552,7 +594,8 @@ void conv3_pointwise_kernel(ConvParams p, Plan3 q) {
 // staged once for 96 / 128 channels instead of once per 64, a 96-channel layer does not pay for a half-empty second
 // group, and a wave reads 5 / 6 fragments per 6 / 8 MFMAs instead of 4 per 4.  Their weight chunks are larger, so
 // these run on 16-channel chunks.
-template <int DT, bool FUSED, bool ADD, int CCB, int NVIB, int CCS, int NVIS, int PBWB = 2, int PBWS = 1, int CBWP = 2>
+template <int DT, bool FUSED, bool ADD, int CCB, int NVIB, int CCS, int NVIS, int PBWB = 2, int PBWS = 1, int CBWP = 2,
+          int EPI = kEpiNone>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void conv3_pair_kernel(ConvParams p, Plan3 qb, Plan3 qs) {
     const int nact = max(min(*p.count, p.cap), 0);
@@ -561,10 +604,10 @@ void conv3_pair_kernel(ConvParams p, Plan3 qb, Plan3 qs) {
     // the ratio is given for the 128- against the 256-pixel item (5/8 as measured); a 256-pixel item against a
     // 384-pixel one is taken as 6/8 (on the 18x18 outputs of a data gradient one round of either took 12.2 and 14.9 us)
     const uint32_t cost8 = PBWB == 3 ? ((uint32_t)p.small_cost8 * 6u + 2u) / 5u : (uint32_t)p.small_cost8;
-    if ((unsigned long long)rb * 8u <= (unsigned long long)rs * cost8) conv3_body<DT, FUSED, ADD, CCB, 4, CBWP, PBWB, NVIB, 3, true>(p, qb);
+    if ((unsigned long long)rb * 8u <= (unsigned long long)rs * cost8) conv3_body<DT, FUSED, ADD, CCB, 4, CBWP, PBWB, NVIB, 3, true, EPI>(p, qb);
     // (128 pixels x 128 channels: a wave takes 64 x 64, four fragment reads per four MFMAs, rather than 32 x 128, five)
     else if (CBWP == 4 && PBWS == 1) conv3_body<DT, FUSED, ADD, CCS, 2, 2, 2, NVIS, 3, true>(p, qs);
-    else conv3_body<DT, FUSED, ADD, CCS, 4, CBWP, PBWS, NVIS, 3, true>(p, qs);
+    else conv3_body<DT, FUSED, ADD, CCS, 4, CBWP, PBWS, NVIS, 3, true, EPI>(p, qs);
 }
 
 // Stride 1, 65 ... 96 output channels (or any count that groups of 96 fill better than groups of 64): groups of 96 on
@@ -682,11 +725,12 @@ static Shape3 plan3(const ConvParams &p, int pp, int nb = 2, bool only16 = false
     return sh;
 }
 
-template <int DT, bool FUSED, bool ADD, int WP, int CBW, int PBW>
+// (with EPI: pointwise, or for kEpiMask the fused 3x3 form on 32-channel chunks)
+template <int DT, bool FUSED, bool ADD, int WP, int CBW, int PBW, int EPI>
 static void launch3_cc(const ConvParams &p, const Shape3 &sh, int grid, hipStream_t s) {
 #define SBNET_L3(CC, NVI)                                                                                      \
     do {                                                                                                       \
-        auto kern = conv3_kernel<DT, FUSED, ADD, CC, WP, CBW, PBW, NVI>;                                       \
+        auto kern = conv3_kernel<DT, FUSED, ADD, CC, WP, CBW, PBW, NVI, EPI>;                                      \
         if (sh.lds_bytes > 48 * 1024)                                                                          \
             (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,          \
                                       (int)sh.lds_bytes);                                                      \
@@ -695,29 +739,45 @@ static void launch3_cc(const ConvParams &p, const Shape3 &sh, int grid, hipStrea
     if (p.kh == 1) {                                  // pointwise
 #define SBNET_L1(CC, NVI)                                                                                      \
     do {                                                                                                       \
-        auto kern = conv3_pointwise_kernel<DT, FUSED, ADD, CC, WP, CBW, PBW, NVI>;                             \
+        auto kern = conv3_pointwise_kernel<DT, FUSED, ADD, CC, WP, CBW, PBW, NVI, EPI>;                             \
         if (sh.lds_bytes > 48 * 1024)                                                                          \
             (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,          \
                                       (int)sh.lds_bytes);                                                      \
         hipLaunchKernelGGL(kern, dim3(grid), dim3(256), sh.lds_bytes, s, p, sh.q);                             \
     } while (0)
-        if (sh.cc == 64 && sh.nvi == 5) SBNET_L1(64, 5);
-        else if (sh.cc == 64) SBNET_L1(64, 9);
-        else if (sh.nvi == 3) SBNET_L1(32, 3);
-        else SBNET_L1(32, 6);
+        if constexpr (EPI == kEpiNone || !FUSED) {
+            if (sh.cc == 64 && sh.nvi == 5) SBNET_L1(64, 5);
+            else if (sh.cc == 64) SBNET_L1(64, 9);
+            else if (sh.nvi == 3) SBNET_L1(32, 3);
+            else SBNET_L1(32, 6);
+        }
 #undef SBNET_L1
-    } else if (sh.cc == 32 && sh.nvi == 3) SBNET_L3(32, 3);
-    else if (sh.cc == 32) SBNET_L3(32, 6);
-    else if (sh.nvi == 5) SBNET_L3(16, 5);
-    else SBNET_L3(16, 9);
+    } else if constexpr (EPI == kEpiNone || FUSED) {
+        if (sh.cc == 32 && sh.nvi == 3) SBNET_L3(32, 3);
+        else if (sh.cc == 32) SBNET_L3(32, 6);
+        else if constexpr (EPI == kEpiNone) {
+            if (sh.nvi == 5) SBNET_L3(16, 5);
+            else SBNET_L3(16, 9);
+        }
+    }
 #undef SBNET_L3
 }
 
-template <int DT, bool FUSED, bool ADD>
+template <int DT, bool FUSED, bool ADD, int EPI = kEpiNone>
 static void launch3_shape(const ConvParams &p, const Shape3 &sh, int grid, hipStream_t s) {
-    if (sh.pp == 256) launch3_cc<DT, FUSED, ADD, 4, 2, 2>(p, sh, grid, s);
-    else if (sh.pp == 128) launch3_cc<DT, FUSED, ADD, 4, 2, 1>(p, sh, grid, s);
-    else launch3_cc<DT, FUSED, ADD, 2, 1, 1>(p, sh, grid, s);
+    if (sh.pp == 256) launch3_cc<DT, FUSED, ADD, 4, 2, 2, EPI>(p, sh, grid, s);
+    else if (sh.pp == 128) launch3_cc<DT, FUSED, ADD, 4, 2, 1, EPI>(p, sh, grid, s);
+    else launch3_cc<DT, FUSED, ADD, 2, 1, 1, EPI>(p, sh, grid, s);
+}
+
+template <int DT>
+static void launch3_dt(bool fused, const ConvParams &p, const Shape3 &sh, int grid, hipStream_t s) {
+    if (p.mask && fused) launch3_shape<DT, true, false, kEpiMask>(p, sh, grid, s);
+    else if (p.mask) launch3_shape<DT, false, false, kEpiMask>(p, sh, grid, s);
+    else if (p.inside) launch3_shape<DT, false, false, kEpiInside>(p, sh, grid, s);
+    else if (fused && p.add) launch3_shape<DT, true, true>(p, sh, grid, s);
+    else if (fused) launch3_shape<DT, true, false>(p, sh, grid, s);
+    else launch3_shape<DT, false, false>(p, sh, grid, s);
 }
 
 static void launch3(sbnet_dtype dt, bool fused, const ConvParams &p, const Shape3 &sh, hipStream_t s) {
@@ -726,22 +786,15 @@ static void launch3(sbnet_dtype dt, bool fused, const ConvParams &p, const Shape
     const long long most = p.kh == 1 && 2 * sh.lds_bytes <= (size_t)kLds3 ? 512 : 256;   // persistent workgroups: one per CU, two for pointwise
     if (g > most) g = most;
     const int grid = (int)g;
-    if (dt == SBNET_BF16) {
-        if (fused && p.add) launch3_shape<SBNET_BF16, true, true>(p, sh, grid, s);
-        else if (fused) launch3_shape<SBNET_BF16, true, false>(p, sh, grid, s);
-        else launch3_shape<SBNET_BF16, false, false>(p, sh, grid, s);
-    } else {
-        if (fused && p.add) launch3_shape<SBNET_F16, true, true>(p, sh, grid, s);
-        else if (fused) launch3_shape<SBNET_F16, true, false>(p, sh, grid, s);
-        else launch3_shape<SBNET_F16, false, false>(p, sh, grid, s);
-    }
+    if (dt == SBNET_BF16) launch3_dt<SBNET_BF16>(fused, p, sh, grid, s);
+    else launch3_dt<SBNET_F16>(fused, p, sh, grid, s);
 }
 
-template <int DT, bool FUSED, bool ADD, int CCB, int NVIB, int PBWB = 2, int PBWS = 1>
+template <int DT, bool FUSED, bool ADD, int CCB, int NVIB, int PBWB = 2, int PBWS = 1, int EPI = kEpiNone>
 static void launch3_pair_small(const ConvParams &p, const Shape3 &big, const Shape3 &small, int grid, size_t lds, hipStream_t s) {
 #define SBNET_L3P(CCS, NVIS)                                                                                   \
     do {                                                                                                       \
-        auto kern = conv3_pair_kernel<DT, FUSED, ADD, CCB, NVIB, CCS, NVIS, PBWB, PBWS>;                       \
+        auto kern = conv3_pair_kernel<DT, FUSED, ADD, CCB, NVIB, CCS, NVIS, PBWB, PBWS, 2, EPI>;               \
         if (lds > 48 * 1024)                                                                                   \
             (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
         ConvParams pt = p;                                                                                     \
@@ -750,8 +803,10 @@ static void launch3_pair_small(const ConvParams &p, const Shape3 &big, const Sha
     } while (0)
     if (small.cc == 32 && small.nvi == 3) SBNET_L3P(32, 3);
     else if (small.cc == 32) SBNET_L3P(32, 6);
-    else if (small.nvi == 5) SBNET_L3P(16, 5);
-    else SBNET_L3P(16, 9);
+    else if constexpr (EPI == kEpiNone) {
+        if (small.nvi == 5) SBNET_L3P(16, 5);
+        else SBNET_L3P(16, 9);
+    }
 #undef SBNET_L3P
 }
 
@@ -770,6 +825,13 @@ static void launch3_pair_big(const ConvParams &p, const Shape3 &big, const Shape
     else launch3_pair_small<DT, FUSED, ADD, 16, 9>(p, big, small, grid, lds, s);
 }
 
+template <int DT>
+static void launch3_pair_mask(const ConvParams &p, const Shape3 &big, const Shape3 &small, int grid, size_t lds, hipStream_t s) {
+    if (big.pp == 384) launch3_pair_small<DT, true, false, 32, 7, 3, 2, kEpiMask>(p, big, small, grid, lds, s);
+    else if (big.nvi == 3) launch3_pair_small<DT, true, false, 32, 3, 2, 1, kEpiMask>(p, big, small, grid, lds, s);
+    else launch3_pair_small<DT, true, false, 32, 6, 2, 1, kEpiMask>(p, big, small, grid, lds, s);
+}
+
 // both tile shapes in one launch
 static void launch3_pair(sbnet_dtype dt, bool fused, const ConvParams &p, const Shape3 &big, const Shape3 &small, hipStream_t s) {
     const long long items = (long long)p.cap * small.q.mpasses * small.q.ngroups;     // the smaller tile has more items
@@ -777,6 +839,11 @@ static void launch3_pair(sbnet_dtype dt, bool fused, const ConvParams &p, const 
     if (g > 256) g = 256;                             // one persistent workgroup per CU
     const int grid = (int)g;
     const size_t lds = big.lds_bytes > small.lds_bytes ? big.lds_bytes : small.lds_bytes;
+    if (p.mask) {
+        if (dt == SBNET_BF16) launch3_pair_mask<SBNET_BF16>(p, big, small, grid, lds, s);
+        else launch3_pair_mask<SBNET_F16>(p, big, small, grid, lds, s);
+        return;
+    }
     if (dt == SBNET_BF16) {
         if (fused && p.add) launch3_pair_big<SBNET_BF16, true, true>(p, big, small, grid, lds, s);
         else if (fused) launch3_pair_big<SBNET_BF16, true, false>(p, big, small, grid, lds, s);
@@ -891,7 +958,7 @@ bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p0, hipStream_t s, 
         // -> 192: its rows fit 32-channel chunks with 64-channel groups, twice the matrix steps per barrier; where they are
         // not, see conv3_wide96_kernel), 96 -> 192 at stride 2 is the same with either.
         const int nbw = p.Cout % 128 == 0 ? 4 : (p.Cout % 96 == 0 && p.Cout % 64 != 0 ? 3 : 2);
-        if (nbw > 2 && M <= 256 && p.sh > 1) {
+        if (nbw > 2 && M <= 256 && p.sh > 1 && !p.mask) {
             Shape3 wb, ws = plan3(p, 128, nbw);
             wb.ok = false;
             if (M > 128) wb = plan3(p, 256, nbw);
@@ -922,7 +989,9 @@ bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p0, hipStream_t s, 
     if ((long long)p.cap * most_passes * ((p.Cout + 63) / 64) >= (1LL << 31)) return false;
     // with at most 256 items of the smaller tile whatever the count, the rule in the kernel never picks the larger one
     if (big.ok && small.ok && (long long)p.cap * small.q.mpasses * small.q.ngroups <= 256) big.ok = false;
-    if (big.ok && small.ok && p.Cin > 32 && p.kh == 3 && p.sh == 1 && p.sw == 1 && M <= 256 && big.cc == 32 && big.nvi == 6 && small.cc == 32 &&
+    if (p.mask && p.kh == 3 && (!fused || p.add || (big.ok && big.cc != 32) || (small.ok && small.cc != 32))) return false;
+    if (p.inside && (fused || p.kh != 1)) return false;
+    if (big.ok && small.ok && !p.mask && p.Cin > 32 && p.kh == 3 && p.sh == 1 && p.sw == 1 && M <= 256 && big.cc == 32 && big.nvi == 6 && small.cc == 32 &&
         (p.Cout + 95) / 96 * 3 < (p.Cout + 63) / 64 * 2) {
         const Shape3 wide = plan3(p, 256, 3);                              // see conv3_wide96_kernel
         if (wide.ok) {

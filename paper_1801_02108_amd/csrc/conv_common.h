@@ -48,6 +48,10 @@ struct ConvParams {
     int32_t *indices_out;    // [cap][3]
     int32_t *count_out;      // [1]
     FastDiv div_bps, div_bw, div_grid;       // blocks per sample, blocks per block row, workgroups along x
+    int own_sample;          // fused form: block b is the one block of sample b; indices is not read for its values
+    // conv3.hip, what happens to a result before it is stored:
+    const void *mask;        // laid out as out: results are zeroed where this is not positive (or null)
+    int inside;              // unfused form, with indices, g_in, H, W: zeroed at pixels outside the image
     int small_cost8;         // conv3.hip, two tile shapes in one launch: cost of the smaller item in eighths of the larger
     int wide_min_items;      // conv3.hip, 64-channel or wider output groups in one launch: wide from this many work items
     // MFMA path work decomposition
@@ -121,6 +125,12 @@ __device__ __forceinline__ f32x16 mfma32x32x16(uint4 a, uint4 b, f32x16 c) {
     } else {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
     }
+}
+
+// the halves of w whose value is positive: 0xffff, the others 0
+template <int DT>
+__device__ __forceinline__ uint32_t positive_halves(uint32_t w) {
+    return (unpack_lo<DT>(w) > 0.f ? 0xffffu : 0u) | (unpack_hi<DT>(w) > 0.f ? 0xffff0000u : 0u);
 }
 
 typedef short i16x2 __attribute__((ext_vector_type(2)));

@@ -64,9 +64,9 @@ __global__ __launch_bounds__(256) void tile_relu_backward(const uint32_t *__rest
 constexpr int kBiasThreads = 1024;
 
 template <int DT, int VW, bool MASK>
-__global__ __launch_bounds__(kBiasThreads) void tile_bias_partial(const uint32_t *dy, const int32_t *__restrict__ count,
-                                                                  int cap, int pixels, int C, int cw, float *__restrict__ part,
-                                                                  const uint32_t *__restrict__ y, uint32_t *dout) {
+__device__ __forceinline__ void bias_partial(const uint32_t *dy, const int32_t *__restrict__ count,
+                                             int cap, int pixels, int C, int cw, float *__restrict__ part,
+                                             const uint32_t *__restrict__ y, uint32_t *dout) {
     constexpr int EPW = DT == SBNET_F32 ? 1 : 2;
     constexpr int NE = VW * EPW;                                  // channels per thread
     __shared__ float red[kBiasThreads][NE + 1];
@@ -158,9 +158,30 @@ __global__ __launch_bounds__(kBiasThreads) void tile_bias_partial(const uint32_t
     }
 }
 
+template <int DT, int VW, bool MASK>
+__global__ __launch_bounds__(kBiasThreads) void tile_bias_partial(const uint32_t *dy, const int32_t *__restrict__ count, int cap,
+                                                                  int pixels, int C, int cw, float *__restrict__ part,
+                                                                  const uint32_t *__restrict__ y, uint32_t *dout) {
+    bias_partial<DT, VW, MASK>(dy, count, cap, pixels, C, cw, part, y, dout);
+}
+
+// several stacks in one launch, blockIdx.y picks: their sums are each too short to fill the time of a launch
+constexpr int kBiasStacks = 3;
+struct BiasJobs {
+    const uint32_t *dy[kBiasStacks];
+    float *part[kBiasStacks], *db[kBiasStacks];
+    int pixels[kBiasStacks], C[kBiasStacks];
+};
+
+template <int DT>
+__global__ __launch_bounds__(kBiasThreads) void tile_bias_partials(BiasJobs q, const int32_t *__restrict__ count, int cap) {
+    const int k = blockIdx.y, C = q.C[k];
+    bias_partial<DT, 4, false>(q.dy[k], count, cap, q.pixels[k], C, C * (DT == SBNET_F32 ? 4 : 2) / 4, q.part[k], nullptr, nullptr);
+}
+
 // db[c] = sum over the workgroups' results part[w][c], w < n: 64 channels per workgroup of 16 waves; wave k takes
 // the results k, k + 16, ... in ascending order, eight loads in flight, then the 16 sums are added in ascending order
-__global__ __launch_bounds__(1024) void tile_bias_sum(const float *__restrict__ part, int n, int C, float *__restrict__ db) {
+__device__ __forceinline__ void bias_sum(const float *__restrict__ part, int n, int C, float *__restrict__ db) {
     __shared__ float slice[16][64];
     const int lane = threadIdx.x & 63, k = threadIdx.x >> 6;
     const int c = blockIdx.x * 64 + lane;
@@ -187,6 +208,12 @@ __global__ __launch_bounds__(1024) void tile_bias_sum(const float *__restrict__ 
         db[c] = t;
     }
 }
+
+__global__ __launch_bounds__(1024) void tile_bias_sum(const float *__restrict__ part, int n, int C, float *__restrict__ db) {
+    bias_sum(part, n, C, db);
+}
+
+__global__ __launch_bounds__(1024) void tile_bias_sums(BiasJobs q, int n) { bias_sum(q.part[blockIdx.y], n, q.C[blockIdx.y], q.db[blockIdx.y]); }
 
 }  // namespace
 }  // namespace sbnet
@@ -283,4 +310,38 @@ extern "C" sbnet_status sbnet_relu_bias_backward_on_tiles(const void *y_tiles, c
     if (!y_tiles) return fail(SBNET_EINVAL, "sbnet_relu_bias_backward_on_tiles: null pointer");
     return bias_backward("sbnet_relu_bias_backward_on_tiles", y_tiles, dy_tiles, dtype, count, cap, pixels, C, dout_tiles, db,
                          workspace, workspace_bytes, stream);
+}
+
+sbnet_status sbnet::bias_backward_stacks(const BiasStack *stacks, int n, sbnet_dtype dtype, const int32_t *count, int cap, void *workspace,
+                                         size_t workspace_bytes, void *stream) {
+    BiasJobs q = {};
+    size_t used = 0;
+    int most = 0;
+    bool together = n > 1 && n <= kBiasStacks && cap > 0 && is_float_dtype(dtype) && workspace && ((uintptr_t)workspace & 3) == 0;
+    for (int k = 0; k < n && together; ++k) {
+        const BiasStack &t = stacks[k];
+        together = t.dy && t.db && t.pixels > 0 && t.C > 0 && ((uintptr_t)t.dy & 15) == 0 && (long long)t.C * elem_bytes(dtype) % 16 == 0 &&
+                   (long long)t.C * elem_bytes(dtype) / 16 <= 256;
+        q.dy[k] = (const uint32_t *)t.dy; q.db[k] = t.db; q.pixels[k] = t.pixels; q.C[k] = t.C;
+        q.part[k] = (float *)((char *)workspace + used);
+        used += sbnet_bias_backward_workspace_bytes(cap, t.C);
+        if (t.C > most) most = t.C;
+    }
+    if (!together || used > workspace_bytes) {
+        for (int k = 0; k < n; ++k) {
+            const sbnet_status st = sbnet_bias_backward_on_tiles(stacks[k].dy, dtype, count, cap, stacks[k].pixels, stacks[k].C, stacks[k].db,
+                                                                 workspace, workspace_bytes, stream);
+            if (st != SBNET_OK) return st;
+        }
+        return SBNET_OK;
+    }
+    hipStream_t s = (hipStream_t)stream;
+    const int grid = cap < 256 ? cap : 256;
+    if (dtype == SBNET_F32) hipLaunchKernelGGL(tile_bias_partials<SBNET_F32>, dim3(grid, n), dim3(kBiasThreads), 0, s, q, count, cap);
+    else if (dtype == SBNET_BF16) hipLaunchKernelGGL(tile_bias_partials<SBNET_BF16>, dim3(grid, n), dim3(kBiasThreads), 0, s, q, count, cap);
+    else hipLaunchKernelGGL(tile_bias_partials<SBNET_F16>, dim3(grid, n), dim3(kBiasThreads), 0, s, q, count, cap);
+    const sbnet_status st = launch_status("sbnet_bias_backward_on_tiles");
+    if (st != SBNET_OK) return st;
+    hipLaunchKernelGGL(tile_bias_sums, dim3((most + 63) / 64, n), dim3(1024), 0, s, q, grid);
+    return launch_status("sbnet_bias_backward_on_tiles");
 }

@@ -299,6 +299,53 @@ def test_residual_unit_backward_composed_from_single_calls(C, Cm, dens):
         assert torch.equal(got[:n] if got.dim() == 4 and got.shape[0] == n + 1 else got, want[:n] if want.dim() == 4 and want.shape[0] == n + 1 else want)
 
 
+@pytest.mark.parametrize("n,cap,bo,C,Cm,dtype", [
+    (5, 7, 8, 64, 16, "bf16"),         # 10x10 input tiles: one pass of 128 pixels
+    (2, 2, 4, 96, 24, "bf16"),         # ... of 64
+    (300, 301, 16, 64, 32, "f16"),     # 18x18 tiles, the 384-pixel items
+    (40, 301, 16, 64, 32, "bf16"),     # ... and the 256-pixel ones beside them
+    (90, 100, 24, 48, 40, "bf16"),     # 26x26: 256 pixels beside 128, channels that end inside a group
+    (3, 4, 8, 24, 8, "f32"),           # no matrix kernel: passes of their own
+    (3, 4, 8, 12, 6, "bf16"),
+    (0, 3, 8, 64, 16, "bf16"),
+])
+def test_residual_unit_in_one_call_equals_single_calls(n, cap, bo, C, Cm, dtype):
+    """Masks and zeroing in the epilogues of the convolutions, bias sums in one launch: the bits of the single calls."""
+    step("residual unit, one call %s" % ((n, cap, bo, C, Cm, dtype),))
+    r = gen.rng_for(29, n * 100 + bo + C + Cm)
+    side, per = 20 * bo - 3, 20                     # blocks at the right and bottom edge reach outside the image
+    g_in, g_out, _, _ = sb.geometry(side, side, 3, 1, bo)
+    th = bo + 2
+    cells = np.sort(r.permutation(per * per)[:cap])[::-1].copy()      # the last cells first: the edge is among the active
+    idx = torch.from_numpy(np.stack([np.zeros(cap), cells // per, cells % per], 1).astype(np.int32)).cuda()
+    cnt = torch.tensor([n], dtype=torch.int32).cuda()
+    dev = lambda a: to_dev(gen.round_to(a.astype(np.float32), dtype), dtype)   # noqa: E731
+    w1, w2, w3 = (gen.conv_weights(r, k, k, a, b, dtype) for k, a, b in ((1, C, Cm), (3, Cm, Cm), (1, Cm, C)))
+    b1, b2, b3 = (torch.from_numpy(gen.bias_vector(r, c, 0.5)).cuda() for c in (Cm, Cm, C))
+    p1, p2, p3 = (sb.pack_weights(to_dev(w, dtype)) for w in (w1, w2, w3))
+    tiles = dev(gen.activations(r, (cap, th, th, C), dtype))
+    t1 = sb.conv_on_tiles(tiles, cnt, p1, b1, relu=True)
+    sb.zero_outside(t1, idx, cnt, g_in, side, side)
+    t2 = sb.conv_on_tiles(t1, cnt, p2, b2, relu=True)
+    t3 = sb.conv_on_tiles(t2, cnt, p3, b3)
+    keep = sb.bottleneck_forward_keep_on_tiles(tiles, idx, cnt, g_in, side, side, (p1, b1, p2, b2, p3, b3))
+    for got, want in zip(keep, (t1, t2, t3)):
+        assert torch.equal(got[:n], want[:n])
+    q1, q2, q3 = (sb.pack_weights_transposed(to_dev(w, dtype)) for w in (w1, w2, w3))
+    d3 = dev(gen.activations(r, (cap, bo, bo, C), dtype))
+    dt2 = sb.conv_on_tiles_backward_data(d3, cnt, q3, bo, bo)
+    dt2, db2 = sb.relu_bias_backward_on_tiles(t2, dt2, cnt)
+    dt1 = sb.conv_on_tiles_backward_data(dt2, cnt, q2, th, th)
+    dt1, db1 = sb.relu_bias_backward_on_tiles(t1, dt1, cnt)
+    want = (sb.conv_on_tiles_backward_data(dt1, cnt, q1, th, th), sb.conv_on_tiles_backward_weights(tiles, dt1, cnt, 1), db1,
+            sb.conv_on_tiles_backward_weights(t1, dt2, cnt, 3), db2, sb.conv_on_tiles_backward_weights(t2, d3, cnt, 1),
+            sb.bias_backward_on_tiles(d3, cnt))
+    one = sb.bottleneck_backward_on_tiles(tiles, t1, t2, d3, cnt, (q1, q2, q3))
+    assert torch.equal(one[0][:n], want[0][:n])
+    for k in range(1, 7):
+        assert torch.equal(one[k], want[k]), k
+
+
 def test_weight_gradient_of_a_stack_beyond_two_gib():
     """13 500 tiles of 18 x 18 x 256 (the residual unit's first convolution at the batched configurations' scale) are
     2.24 GB: byte offsets into the stack do not fit 31 bits, and the kernel addresses every tile through a descriptor
