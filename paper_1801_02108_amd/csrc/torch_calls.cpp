@@ -71,11 +71,12 @@ float *bias_of(PyObject *o, const char *name = "bias") {
     return none(o) ? nullptr : (float *)ptr(dev(o, name, at::kFloat));
 }
 
-int i32(PyObject *o) {
+int64_t i64(PyObject *o) {
     const long v = PyLong_AsLong(o);
     if (v == -1 && PyErr_Occurred()) throw python_error();
-    return (int)v;
+    return v;
 }
+int i32(PyObject *o) { return (int)i64(o); }
 float f32(PyObject *o) {
     const double v = PyFloat_AsDouble(o);
     if (v == -1.0 && PyErr_Occurred()) throw python_error();
@@ -85,6 +86,14 @@ int flag(PyObject *o) {
     const int v = PyObject_IsTrue(o);
     if (v < 0) throw python_error();
     return v;
+}
+
+// output extent of a valid convolution, floor((t - k) / stride) + 1; zero or less for a tile smaller than the kernel, which the
+// library refuses
+int64_t extent(int64_t t, int64_t k, int64_t stride) {
+    if (stride == 0) raise(PyExc_ZeroDivisionError, "stride must not be zero");
+    const int64_t d = t - k, q = d / stride;
+    return q - (d % stride != 0 && (d < 0) != (stride < 0)) + 1;
 }
 
 struct Geo : sbnet_geom {
@@ -346,11 +355,12 @@ PyObject *conv_f8(Args a) {                         // tiles_f8, count, w_packed
     const Packed w(a[2]);
     const Dims4 s(t, "tiles_f8");
     require(s.d == w.cin && w.dtype == at::kByte, "channels or type of the packed weights");
-    const int st = i32(a[4]);
+    const int64_t st = i64(a[4]);
+    const int64_t sz[4] = {s.a, extent(s.b, w.kh, st), extent(s.c, w.kw, st), w.cout};
     Tensor own;
-    const Tensor &out = output(a[7], "out", {s.a, (s.b - w.kh) / st + 1, (s.c - w.kw) / st + 1, w.cout}, t, at::kBFloat16, own);
+    const Tensor &out = output(a[7], "out", sz, t, at::kBFloat16, own);
     call(sbnet_conv_on_tiles_f8, (const uint8_t *)ptr(t), (const int32_t *)ptr(cnt), s.a, s.b, s.c, s.d, (const void *)w.buf, bias_of(a[3]),
-         w.kh, w.kw, st, st, w.cout, flag(a[5]), f32(a[6]), ptr(out), stream());
+         w.kh, w.kw, (int)st, (int)st, w.cout, flag(a[5]), f32(a[6]), ptr(out), stream());
     return give(a[7], own);
 }
 
@@ -359,11 +369,12 @@ PyObject *conv_on_tiles(Args a) {                   // tiles, count, w_packed, b
     const Packed w(a[2]);
     const Dims4 s(t, "tiles");
     require(s.d == w.cin && w.dtype == t.scalar_type(), "channels or type of the packed weights");
-    const int st = i32(a[4]);
+    const int64_t st = i64(a[4]);
+    const int64_t sz[4] = {s.a, extent(s.b, w.kh, st), extent(s.c, w.kw, st), w.cout};
     Tensor own;
-    const Tensor &out = output(a[6], "out", {s.a, (s.b - w.kh) / st + 1, (s.c - w.kw) / st + 1, w.cout}, t, t.scalar_type(), own);
+    const Tensor &out = output(a[6], "out", sz, t, t.scalar_type(), own);
     call(sbnet_conv_on_tiles, ptr(t), dt_of(t), (const int32_t *)ptr(cnt), s.a, s.b, s.c, s.d, (const void *)w.buf, bias_of(a[3]), w.kh, w.kw,
-         st, st, w.cout, flag(a[5]), ptr(out), stream());
+         (int)st, (int)st, w.cout, flag(a[5]), ptr(out), stream());
     return give(a[6], own);
 }
 
@@ -371,9 +382,10 @@ PyObject *backward_data(Args a) {                   // dout_tiles, count, w_pack
     const Tensor &d = dev(a[0], "dout_tiles"), &cnt = dev(a[1], "count", at::kInt);
     const Packed w(a[2]);
     const Dims4 s(d, "dout_tiles");
-    const int th = i32(a[3]), tw = i32(a[4]), st = i32(a[5]);
+    const int64_t h = i64(a[3]), wd = i64(a[4]), stride = i64(a[5]);
     require(s.d == w.cout && w.dtype == d.scalar_type(), "channels or type of the packed weights");
-    require(s.b == (th - w.kh) / st + 1 && s.c == (tw - w.kw) / st + 1, "shape of dout_tiles");
+    require(s.b == extent(h, w.kh, stride) && s.c == extent(wd, w.kw, stride), "shape of dout_tiles");
+    const int th = (int)h, tw = (int)wd, st = (int)stride;
     Tensor oo, own;
     const Tensor &out = output(a[6], "out", {s.a, th, tw, w.cin}, d, d.scalar_type(), oo);
     size_t wb;
@@ -386,8 +398,9 @@ PyObject *backward_data(Args a) {                   // dout_tiles, count, w_pack
 PyObject *backward_weights(Args a) {                // tiles, dout_tiles, count, k, stride, out, workspace
     const Tensor &t = dev(a[0], "tiles"), &d = dev(a[1], "dout_tiles", t.scalar_type()), &cnt = dev(a[2], "count", at::kInt);
     const Dims4 s(t, "tiles"), o(d, "dout_tiles");
-    const int k = i32(a[3]), st = i32(a[4]);
-    require(o.a == s.a && o.b == (s.b - k) / st + 1 && o.c == (s.c - k) / st + 1, "shape of dout_tiles");
+    const int64_t side = i64(a[3]), stride = i64(a[4]);
+    require(o.a == s.a && o.b == extent(s.b, side, stride) && o.c == extent(s.c, side, stride), "shape of dout_tiles");
+    const int k = (int)side, st = (int)stride;
     Tensor oo, own;
     const Tensor &out = output(a[5], "out", {k, k, s.d, o.d}, t, at::kFloat, oo);
     require(Dims4(out, "out").is(k, k, s.d, o.d), "shape of out");
