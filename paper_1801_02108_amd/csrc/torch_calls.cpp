@@ -8,6 +8,8 @@
 // the benchmark stage of six units and a reduction (13 launches) 103 us a pass -> 71, which is its device time.
 #include <Python.h>
 
+#include <optional>
+
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
@@ -116,6 +118,31 @@ struct Dims4 {
     bool is(int64_t p, int64_t q, int64_t r, int64_t s) const { return a == p && b == q && c == r && d == s; }
 };
 
+// The n objects of an argument that holds several (weights with their biases and the like), kept until the call is over: an
+// iterator's objects may have no other owner, and another thread may change a list while the interpreter lock is released.
+struct Several {
+    PyObject *item[6] = {};
+    Several(PyObject *o, int n, const char *what) {
+        PyObject *it = PyObject_GetIter(o), *x = nullptr;
+        if (!it) throw python_error();
+        int k = 0;
+        while ((x = PyIter_Next(it)) && k < n) item[k++] = x;
+        const bool ok = !x && k == n && !PyErr_Occurred();
+        Py_XDECREF(x);
+        Py_DECREF(it);
+        if (ok) return;
+        drop();
+        if (PyErr_Occurred()) throw python_error();
+        raise(PyExc_ValueError, "%s", what);
+    }
+    ~Several() { drop(); }
+    Several(const Several &) = delete;
+    void drop() {
+        for (PyObject *&x : item) Py_CLEAR(x);
+    }
+    PyObject *operator[](int i) const { return item[i]; }
+};
+
 struct Packed {                                     // a PackedWeights object
     void *buf;
     int kh, kw, cin, cout;
@@ -130,7 +157,7 @@ struct Packed {                                     // a PackedWeights object
             cin = (int)PyLong_AsLong(PyTuple_GET_ITEM(s, 2)); cout = (int)PyLong_AsLong(PyTuple_GET_ITEM(s, 3));
             dtype = reinterpret_cast<THPDtype *>(d)->scalar_type;
         }
-        Py_XDECREF(b); Py_XDECREF(s); Py_XDECREF(d);                // the caller's tuple keeps the object, and the buffer with it
+        Py_XDECREF(b); Py_XDECREF(s); Py_XDECREF(d);                // the caller, or Several, keeps the object, and the buffer with it
         if (PyErr_Occurred()) throw python_error();
         if (!ok) raise(PyExc_TypeError, "packed weights (PackedWeights) are expected");
     }
@@ -469,15 +496,11 @@ PyObject *conv_from_mask(Args a) {
 
 // (w1, b1, w2, b2, w3, b3) of a residual unit; biases of the widths given
 struct Unit {
+    Several it;
     void *w[3];
     float *b[3];
     int cin, cm, cout;
-    Unit(PyObject *o, bool need_bias) {
-        PyObject *seq = PySequence_Fast(o, "weights must be (w1, b1, w2, b2, w3, b3)");
-        if (!seq) throw python_error();
-        struct Drop { PyObject *o; ~Drop() { Py_DECREF(o); } } drop{seq};
-        if (PySequence_Fast_GET_SIZE(seq) != 6) raise(PyExc_ValueError, "weights must be (w1, b1, w2, b2, w3, b3)");
-        PyObject **it = PySequence_Fast_ITEMS(seq);
+    Unit(PyObject *o, bool need_bias) : it(o, 6, "weights must be (w1, b1, w2, b2, w3, b3)") {
         const Packed w1(it[0]), w2(it[2]), w3(it[4]);
         cin = w1.cin; cm = w1.cout; cout = w3.cout;
         require(w2.is(3, 3, cm, cm) && w3.kh == 1 && w3.kw == 1 && w3.cin == cm, "shapes of the unit's weights");
@@ -493,15 +516,13 @@ struct Unit {
 };
 
 struct Pre {                                        // (scale, shift) or None
+    std::optional<Several> it;
     const float *scale = nullptr, *shift = nullptr;
     Pre(PyObject *o, int C) {
         if (none(o)) return;
-        PyObject *seq = PySequence_Fast(o, "pre must be (scale, shift)");
-        if (!seq) throw python_error();
-        struct Drop { PyObject *o; ~Drop() { Py_DECREF(o); } } drop{seq};
-        if (PySequence_Fast_GET_SIZE(seq) != 2) raise(PyExc_ValueError, "pre must be (scale, shift)");
-        const Tensor &a = dev(PySequence_Fast_GET_ITEM(seq, 0), "pre_scale", at::kFloat);
-        const Tensor &b = dev(PySequence_Fast_GET_ITEM(seq, 1), "pre_shift", at::kFloat);
+        it.emplace(o, 2, "pre must be (scale, shift)");
+        const Tensor &a = dev((*it)[0], "pre_scale", at::kFloat);
+        const Tensor &b = dev((*it)[1], "pre_shift", at::kFloat);
         require(a.numel() == C && b.numel() == C, "pre_scale or pre_shift");
         scale = (const float *)ptr(a);
         shift = (const float *)ptr(b);
@@ -554,14 +575,12 @@ PyObject *sparse_unit(Args a) {                     // x, indices, count, g_in, 
     require(s.d == u.cin && o.d == u.cout && o.a == s.a, "shapes of the unit's weights, x or y");
     void *ws = nullptr;
     float *bs = nullptr;
+    std::optional<Several> sc;
     if (!none(a[8])) {
-        PyObject *seq = PySequence_Fast(a[8], "shortcut must be (weights, bias)");
-        if (!seq) throw python_error();
-        struct Drop { PyObject *o; ~Drop() { Py_DECREF(o); } } drop{seq};
-        if (PySequence_Fast_GET_SIZE(seq) != 2) raise(PyExc_ValueError, "shortcut must be (weights, bias)");
-        if (!none(PySequence_Fast_GET_ITEM(seq, 0))) {
-            const Packed p(PySequence_Fast_GET_ITEM(seq, 0));
-            const Tensor &b = dev(PySequence_Fast_GET_ITEM(seq, 1), "shortcut bias", at::kFloat);
+        sc.emplace(a[8], 2, "shortcut must be (weights, bias)");
+        if (!none((*sc)[0])) {
+            const Packed p((*sc)[0]);
+            const Tensor &b = dev((*sc)[1], "shortcut bias", at::kFloat);
             require(p.is(1, 1, u.cin, u.cout) && b.numel() == u.cout, "shapes of the shortcut");
             ws = p.buf;
             bs = (float *)ptr(b);
@@ -607,11 +626,8 @@ PyObject *unit_backward(Args a) {                   // tiles, t1, t2, dt3, count
     const int Cm = (int)Dims4(t1, "t1").d;
     require(Dims4(t1, "t1").is(s.a, s.b, s.c, Cm) && Dims4(t2, "t2").is(s.a, s.b - 2, s.c - 2, Cm) &&
                 Dims4(d, "dt3").is(s.a, s.b - 2, s.c - 2, s.d), "shape of t1, t2 or dt3");
-    PyObject *seq = PySequence_Fast(a[5], "weights_t must be (w1_t, w2_t, w3_t)");
-    if (!seq) throw python_error();
-    struct Drop { PyObject *o; ~Drop() { Py_DECREF(o); } } drop{seq};
-    if (PySequence_Fast_GET_SIZE(seq) != 3) raise(PyExc_ValueError, "weights_t must be (w1_t, w2_t, w3_t)");
-    const Packed w1(PySequence_Fast_GET_ITEM(seq, 0)), w2(PySequence_Fast_GET_ITEM(seq, 1)), w3(PySequence_Fast_GET_ITEM(seq, 2));
+    const Several it(a[5], 3, "weights_t must be (w1_t, w2_t, w3_t)");
+    const Packed w1(it[0]), w2(it[1]), w3(it[2]);
     require(w1.is(1, 1, s.d, Cm) && w2.is(3, 3, Cm, Cm) && w3.is(1, 1, Cm, s.d), "shapes of the transposed weights");
     Tensor own, dx = at::empty_like(t);
     size_t wb;

@@ -1,8 +1,11 @@
 """The binding's argument checks (csrc/torch_calls.cpp): what a call refuses it refuses before it asks the device for
 anything, so fake device tensors on the CPU reach them."""
+import weakref
+
 import pytest
 import torch
 from torch._subclasses.fake_tensor import FakeTensorMode
+from torch.utils._python_dispatch import TorchDispatchMode
 
 import paper_1801_02108_amd as sb
 
@@ -38,3 +41,45 @@ def test_extents_of_tiles_smaller_than_the_kernel_round_down(which):
     """floor((2 - 3) / 2) + 1 = 0: gradients of one pixel do not belong to such tiles."""
     with pytest.raises(AssertionError):
         convolutions(2, 1, 2)[which]()
+
+
+class _Reached(Exception):
+    pass
+
+
+class _AtFirstAllocation(TorchDispatchMode):
+    """Calls `look` and ends the call under test where it allocates its first result."""
+
+    def __init__(self, look):
+        super().__init__()
+        self.look = look
+
+    def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+        if func is not torch.ops.aten.empty.memory_format:
+            return func(*args, **(kwargs or {}))
+        self.look()
+        raise _Reached
+
+
+def test_weights_that_only_an_iterator_holds_live_until_the_call_is_over():
+    g, _, _, _ = sb.geometry(16, 16, 3, 1, 4)
+    tiles, idx, cnt = fake(2, 6, 6, 16), fake(2, 3, dtype=torch.int32), fake(1, dtype=torch.int32)
+    made = [packed(*shape) for shape in ((1, 1, 16, 8), (3, 3, 8, 8), (1, 1, 8, 16))]
+    refs, alive = [weakref.ref(w) for w in made], []
+
+    def weights():
+        while made:
+            yield made.pop(0)
+            yield None                                # this call takes a missing bias
+
+    with pytest.raises(_Reached), _AtFirstAllocation(lambda: alive.extend(r() is not None for r in refs)):
+        sb.bottleneck_forward_keep_on_tiles(tiles, idx, cnt, g, 16, 16, weights())
+    assert alive == [True] * 3
+
+
+@pytest.mark.parametrize("n", (5, 7))
+def test_a_wrong_number_of_weights_is_an_error(n):
+    g, _, _, _ = sb.geometry(16, 16, 3, 1, 4)
+    tiles, idx, cnt = fake(2, 6, 6, 16), fake(2, 3, dtype=torch.int32), fake(1, dtype=torch.int32)
+    with pytest.raises(ValueError):
+        sb.bottleneck_forward_keep_on_tiles(tiles, idx, cnt, g, 16, 16, [None] * n)
