@@ -146,7 +146,7 @@ class _Calls:
             native = importlib.import_module("._torch_calls", __name__)
         except ImportError as e:
             raise ImportError("%s: run `python -m paper_1801_02108_amd.build` first" % e) from e
-        native.set_error(SbnetError)
+        native.set_types(SbnetError, Geom)
         _calls = native
         return getattr(native, name)
 

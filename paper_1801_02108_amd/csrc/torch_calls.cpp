@@ -21,7 +21,9 @@
 namespace {
 
 PyObject *g_error = nullptr;                       // SbnetError(code, text)
+PyObject *g_geom = nullptr;                        // Geom
 PyObject *s_buf, *s_shape, *s_dtype;               // attribute names of PackedWeights
+PyObject *s_contents, *s_obj;                      // ... of ctypes.pointer(geom) and ctypes.byref(geom)
 
 [[noreturn]] void raise(PyObject *type, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
 [[noreturn]] void raise(PyObject *type, const char *fmt, ...) {
@@ -98,14 +100,41 @@ int64_t extent(int64_t t, int64_t k, int64_t stride) {
     return q - (d % stride != 0 && (d < 0) != (stride < 0)) + 1;
 }
 
-struct Geo : sbnet_geom {
+[[noreturn]] void raise_status(int status, const char *text) {
+    PyObject *e = PyObject_CallFunction(g_error, "is", status, text);
+    if (e) PyErr_SetObject(g_error, e);
+    Py_XDECREF(e);
+    throw python_error();
+}
+
+struct Geo : sbnet_geom {                           // a Geom, or a ctypes pointer to one
     explicit Geo(PyObject *o) {
+        if (none(o)) raise_status(SBNET_EINVAL, "no geometry");
+        if (read(o)) return;
+        for (PyObject *name : {s_contents, s_obj}) {
+            PyObject *g = PyObject_GetAttr(o, name);
+            if (!g) {
+                if (!PyErr_ExceptionMatches(PyExc_AttributeError)) throw python_error();
+                PyErr_Clear();
+                continue;
+            }
+            const bool ok = read(g);
+            Py_DECREF(g);
+            if (ok) return;
+        }
+        raise(PyExc_TypeError, "a geometry (Geom) is expected");
+    }
+
+private:
+    bool read(PyObject *o) {
+        const int is = PyObject_IsInstance(o, g_geom);
+        if (is < 0) throw python_error();
+        if (!is) return false;
         Py_buffer v;
         if (PyObject_GetBuffer(o, &v, PyBUF_SIMPLE) < 0) throw python_error();
-        const bool ok = v.len == (Py_ssize_t)sizeof(sbnet_geom);
-        if (ok) memcpy(static_cast<sbnet_geom *>(this), v.buf, sizeof(sbnet_geom));
+        memcpy(static_cast<sbnet_geom *>(this), v.buf, sizeof(sbnet_geom));
         PyBuffer_Release(&v);
-        if (!ok) raise(PyExc_TypeError, "a geometry (Geom) is expected");
+        return true;
     }
 };
 
@@ -205,11 +234,7 @@ template <typename F, typename... A> void call(F f, A... a) {
     PyThreadState *s = PyEval_SaveThread();
     const sbnet_status st = f(a...);
     PyEval_RestoreThread(s);
-    if (st == SBNET_OK) return;
-    PyObject *e = PyObject_CallFunction(g_error, "is", (int)st, sbnet_last_error());
-    if (e) PyErr_SetObject(g_error, e);
-    Py_XDECREF(e);
-    throw python_error();
+    if (st != SBNET_OK) raise_status((int)st, sbnet_last_error());
 }
 
 struct List {                                       // index list and count
@@ -642,9 +667,9 @@ PyObject *unit_backward(Args a) {                   // tiles, t1, t2, dt3, count
                  THPVariable_Wrap(dw3), THPVariable_Wrap(db3));
 }
 
-PyObject *set_error(Args a) {
-    Py_XDECREF(g_error);
-    g_error = same(a[0]);
+PyObject *set_types(Args a) {                       // SbnetError, Geom
+    Py_XSETREF(g_error, same(a[0]));
+    Py_XSETREF(g_geom, same(a[1]));
     Py_RETURN_NONE;
 }
 
@@ -667,7 +692,7 @@ PyObject *entry(PyObject *, PyObject *const *args, Py_ssize_t n) {
 
 #define CALL(name, fn, n) {name, (PyCFunction)(void (*)(void))entry<fn, n>, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
-    CALL("set_error", set_error, 1),
+    CALL("set_types", set_types, 2),
     CALL("reduce_mask", reduce_mask, 7),
     CALL("reduce_mask_static", reduce_mask_static, 6),
     CALL("sparse_gather", gather<false>, 5),
@@ -708,5 +733,7 @@ extern "C" __attribute__((visibility("default"))) PyObject *PyInit__torch_calls(
     s_buf = PyUnicode_InternFromString("buf");
     s_shape = PyUnicode_InternFromString("shape");
     s_dtype = PyUnicode_InternFromString("dtype");
+    s_contents = PyUnicode_InternFromString("contents");
+    s_obj = PyUnicode_InternFromString("_obj");
     return PyModule_Create(&module);
 }

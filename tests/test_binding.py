@@ -1,5 +1,6 @@
 """The binding's argument checks (csrc/torch_calls.cpp): what a call refuses it refuses before it asks the device for
 anything, so fake device tensors on the CPU reach them."""
+import ctypes
 import weakref
 
 import pytest
@@ -83,3 +84,21 @@ def test_a_wrong_number_of_weights_is_an_error(n):
     tiles, idx, cnt = fake(2, 6, 6, 16), fake(2, 3, dtype=torch.int32), fake(1, dtype=torch.int32)
     with pytest.raises(ValueError):
         sb.bottleneck_forward_keep_on_tiles(tiles, idx, cnt, g, 16, 16, [None] * n)
+
+
+def test_a_geometry_is_a_geom_and_nothing_of_its_size():
+    g, _, _, _ = sb.geometry(16, 16, 3, 1, 4)
+    mask, idx, cnt = fake(1, 16, 16), fake(16, 3, dtype=torch.int32), fake(1, dtype=torch.int32)
+
+    def reduce(geom):
+        sb.reduce_mask(mask, geom, 1, 0.0, None, cnt, None)
+
+    for wrong in (bytes(g), bytearray(g), (ctypes.c_int * 8)(*g.astuple()), g.astuple(), 7):
+        with pytest.raises(TypeError, match="Geom"):
+            reduce(wrong)
+    with pytest.raises(sb.SbnetError) as e:
+        reduce(None)
+    assert e.value.code == sb.EINVAL
+    for right in (g, type("Derived", (sb.Geom,), {})(*g.astuple()), ctypes.pointer(g), ctypes.byref(g)):
+        with pytest.raises(_Reached), _AtFirstAllocation(lambda: None):
+            reduce(right)
