@@ -195,7 +195,22 @@ struct Packed {                                     // a PackedWeights object
 
 void *stream() { return (void *)c10::hip::getCurrentHIPStream().stream(); }
 
-Tensor empty(at::IntArrayRef size, const Tensor &like, at::ScalarType dt) { return at::empty(size, like.options().dtype(dt)); }
+// The interpreter lock is given back where a call may wait for the device: in the library (room in the device's queue), and in
+// an allocation (the allocator may free its cache or wait for events), which would otherwise stop every thread, and for
+// good if what the device waits for is a host callback that needs the lock.
+struct Unlocked {
+    PyThreadState *s = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(s); }
+};
+
+Tensor empty(at::IntArrayRef size, const Tensor &like, at::ScalarType dt) {
+    const Unlocked u;
+    return at::empty(size, like.options().dtype(dt));
+}
+Tensor zeros_like(const Tensor &like) {
+    const Unlocked u;
+    return at::zeros_like(like);
+}
 // a workspace of at least `need` bytes (never empty): the caller's, or a new one kept in `own`
 void *space(PyObject *o, const Tensor &like, size_t need, size_t least, Tensor &own, size_t *bytes, bool any_type = false) {
     if (none(o)) {
@@ -229,11 +244,13 @@ template <typename... O> PyObject *tuple(O... o) {
     return t;
 }
 
-// a call of the C ABI with the interpreter lock released (it may wait for room in the device's queue)
+// a call of the C ABI
 template <typename F, typename... A> void call(F f, A... a) {
-    PyThreadState *s = PyEval_SaveThread();
-    const sbnet_status st = f(a...);
-    PyEval_RestoreThread(s);
+    sbnet_status st;
+    {
+        const Unlocked u;
+        st = f(a...);
+    }
     if (st != SBNET_OK) raise_status((int)st, sbnet_last_error());
 }
 
@@ -346,7 +363,7 @@ PyObject *bn_backward(Args a) {                     // x, dy, indices, count, g,
     const Geo g(a[4]);
     const Dims4 s(x, "x");
     Tensor fresh;
-    if (none(a[11])) fresh = at::zeros_like(x);
+    if (none(a[11])) fresh = zeros_like(x);
     const Tensor &dx = none(a[11]) ? fresh : dev(a[11], "dx", x.scalar_type());
     require(dy.sizes() == x.sizes() && dx.sizes() == x.sizes(), "shape of dy or dx");
     Tensor own, dgamma = empty({s.d}, x, at::kFloat), dbeta = empty({s.d}, x, at::kFloat);
@@ -654,7 +671,7 @@ PyObject *unit_backward(Args a) {                   // tiles, t1, t2, dt3, count
     const Several it(a[5], 3, "weights_t must be (w1_t, w2_t, w3_t)");
     const Packed w1(it[0]), w2(it[1]), w3(it[2]);
     require(w1.is(1, 1, s.d, Cm) && w2.is(3, 3, Cm, Cm) && w3.is(1, 1, Cm, s.d), "shapes of the transposed weights");
-    Tensor own, dx = at::empty_like(t);
+    Tensor own, dx = empty(t.sizes(), t, t.scalar_type());
     size_t wb;
     void *ws = space(a[6], t, sbnet_bottleneck_backward_workspace_bytes(dt_of(t), s.a, s.b, s.c, s.d, Cm), 256, own, &wb);
     Tensor dw1 = empty({1, 1, s.d, Cm}, t, at::kFloat), db1 = empty({Cm}, t, at::kFloat), dw2 = empty({3, 3, Cm, Cm}, t, at::kFloat),
