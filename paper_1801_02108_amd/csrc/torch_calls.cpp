@@ -207,7 +207,7 @@ Tensor empty(at::IntArrayRef size, const Tensor &like, at::ScalarType dt) {
     const Unlocked u;
     return at::empty(size, like.options().dtype(dt));
 }
-Tensor zeros_like(const Tensor &like) {
+Tensor zeros_of(const Tensor &like) {
     const Unlocked u;
     return at::zeros_like(like);
 }
@@ -363,7 +363,7 @@ PyObject *bn_backward(Args a) {                     // x, dy, indices, count, g,
     const Geo g(a[4]);
     const Dims4 s(x, "x");
     Tensor fresh;
-    if (none(a[11])) fresh = zeros_like(x);
+    if (none(a[11])) fresh = zeros_of(x);
     const Tensor &dx = none(a[11]) ? fresh : dev(a[11], "dx", x.scalar_type());
     require(dy.sizes() == x.sizes() && dx.sizes() == x.sizes(), "shape of dy or dx");
     Tensor own, dgamma = empty({s.d}, x, at::kFloat), dbeta = empty({s.d}, x, at::kFloat);
