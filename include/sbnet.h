@@ -214,9 +214,9 @@ sbnet_status sbnet_sparse_gather_backward(const void *dtiles, sbnet_dtype dtype,
  * over the pixels of the blocks b < min(*count, cap) that lie inside the image (every pixel once:
  * g must describe non-overlapping blocks, else SBNET_EINVAL).  With no such pixel both are 0.
  * x: [N][H][W][C] in `dtype` (F32, BF16 or F16; C * element size a multiple of 16 bytes);
- * mean, var: device float32 [C].  Sums are formed in fp32 in a fixed order (per block, relative to
- * the block's first pixel; blocks merged in a fixed tree): no atomics, the result does not depend on
- * scheduling.  workspace: device, sbnet_bn_stats_workspace_bytes(cap, C) bytes, 4-byte aligned,
+ * mean, var: device float32 [C].  Sums are formed in fp32 in a fixed order (partial sums over pieces of
+ * the blocks, each relative to an active pixel, merged in a fixed tree): no atomics, the
+ * same bits every run for a given cap.  workspace: device, sbnet_bn_stats_workspace_bytes(cap, C) bytes, 4-byte aligned,
  * overwritten.
  */
 size_t sbnet_bn_stats_workspace_bytes(int cap, int C);

@@ -6,9 +6,10 @@
 // Two kernels, no atomics, fixed summation order:
 //   bn_partial   one workgroup per (row, slab of 128 bytes of channels per pixel); a row is every rows-th piece of 128
 //                pixels.  Eight lanes read one pixel's 128-byte strip; a thread accumulates, in fp32, the sum and the sum
-//                of squares of its channels, taken relative to a pixel of the row's first block (which keeps the
-//                squares small when the mean is large against the spread); LDS reduces the 32 pixel groups; the row's
-//                (count, mean, sum of squared deviations) per channel goes to the workspace.
+//                of squares of its channels, taken relative to the first active pixel that it holds (which keeps the
+//                squares small when the mean is large against the spread; pixels outside the active blocks are never
+//                looked at).  The 32 pixel groups' (count, mean, sum of squared deviations) are merged through LDS and
+//                go to the workspace.
 //   bn_combine   one workgroup per four channels merges the rows' triples with the pairwise update of Chan, Golub and
 //                LeVeque (mean += delta * n_b / n; M2 += M2_b + delta^2 * n_a * n_b / n): every thread a strided
 //                subset in order, then a fixed tree over the threads.
@@ -19,15 +20,43 @@
 
 namespace sbnet {
 
+// The triples (n[g], mean[g * stride], m2[g * stride]), g < G, as one: the mean relative to the first non-empty one's, then the
+// squares about it.  G is small and the loops unrolled: no division but one.
+template <int G>
+__device__ __forceinline__ void bn_merge_of(const int *n, const float *mean, const float *m2, int stride, int *nt, float *mt, float *m2t) {
+    int c[G], total = 0;
+    float m[G], s[G], ref = 0.f, a = 0.f, q = 0.f;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {                                 // (all reads in flight; an empty triple is three zeros)
+        c[g] = n[g];
+        m[g] = mean[g * stride];
+        s[g] = m2[g * stride];
+    }
+#pragma unroll
+    for (int g = G - 1; g >= 0; --g) {
+        total += c[g];
+        ref = c[g] > 0 ? m[g] : ref;
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const float d = m[g] - ref, nd = (float)c[g] * d;
+        a += nd;
+        q += fmaf(nd, d, s[g]);
+    }
+    const float md = total > 0 ? a / (float)total : 0.f;
+    *nt = total;
+    *mt = ref + md;
+    *m2t = fmaxf(q - a * md, 0.f);
+}
+
 // workspace layout: float part[rows][C][2] (mean, M2), at cnt float cnt[rows]; rows = gridDim.x / slabs <= cap
 template <int DT>
 __global__ __launch_bounds__(kBnThreads) void bn_partial(const uint4 *__restrict__ x, const int32_t *__restrict__ indices,
                                                          const int32_t *__restrict__ count, float *__restrict__ part,
                                                          float *__restrict__ cnt, int pieces, FastDiv div_pieces, BnParams p) {
-    constexpr int EPV = BnElem<DT>::EPV, NCH = 8 * EPV;
-    __shared__ float red[2][32][NCH + 1];
-    __shared__ float ref_s[NCH];
-    __shared__ int redn[32];
+    constexpr int EPV = BnElem<DT>::EPV, NCH = 8 * EPV, LD = NCH + 1;
+    __shared__ float means[32][LD], squares[32][LD];
+    __shared__ int ns[32], nw[4];
     const int pg = threadIdx.x >> 3, k = threadIdx.x & 7;         // pixel group, vector of the slab
     const uint32_t row = fdiv(blockIdx.x, p.div_slabs), rows = fdiv(gridDim.x, p.div_slabs);
     const int slab = (int)(blockIdx.x - row * p.slabs);
@@ -37,11 +66,6 @@ __global__ __launch_bounds__(kBnThreads) void bn_partial(const uint4 *__restrict
     float ref[EPV], s1[EPV], s2[EPV];
 #pragma unroll
     for (int e = 0; e < EPV; ++e) ref[e] = s1[e] = s2[e] = 0.f;
-    {   // reference value per channel: the image's pixel next to the first block's origin
-        const BnPlace w = bn_place<EPV>(blk, slab, k, p);
-        if (w.chan_ok)
-            BnElem<DT>::unpack(x[w.base + ((long long)min(max(w.y0, 0), p.H - 1) * p.W + min(max(w.x0, 0), p.W - 1)) * p.pix_vecs], ref);
-    }
     int npx = 0;
     for (uint32_t item = row; item < items; item += rows) {
         const uint32_t b = fdiv(item, div_pieces);
@@ -53,14 +77,19 @@ __global__ __launch_bounds__(kBnThreads) void bn_partial(const uint4 *__restrict
 #pragma unroll
         for (int u = 0; u < 4; ++u) {                             // four independent loads in flight
             at[u] = bn_pixel(w, q0 + 32 * u, p);
-            if (at[u] >= 0) {
-                v[u] = x[at[u]];
-                ++npx;
-            }
+            if (at[u] >= 0) v[u] = x[at[u]];
+        }
+        if (npx == 0) {                                           // the thread's first pixel is its reference
+            uint4 first = make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int u = 3; u >= 0; --u)
+                if (at[u] >= 0) first = v[u];
+            BnElem<DT>::unpack(first, ref);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             if (at[u] >= 0) {
+                ++npx;
                 float f[EPV];
                 BnElem<DT>::unpack(v[u], f);
 #pragma unroll
@@ -71,19 +100,32 @@ __global__ __launch_bounds__(kBnThreads) void bn_partial(const uint4 *__restrict
                 }
             }
     }
-    if (pg == 0) {
+    // the 32 pixel groups by eights, then the four results (in place of their first groups')
+    const float share = npx > 0 ? 1.f / (float)npx : 0.f;
 #pragma unroll
-        for (int e = 0; e < EPV; ++e) ref_s[k * EPV + e] = ref[e];
+    for (int e = 0; e < EPV; ++e) {
+        const float md = s1[e] * share;
+        means[pg][k * EPV + e] = ref[e] + md;
+        squares[pg][k * EPV + e] = s2[e] - s1[e] * md;
     }
-    float a, q2;
-    const float n = bn_reduce<EPV>(red, redn, s1, s2, npx, &a, &q2);
+    if (k == 0) ns[pg] = npx;
+    __syncthreads();
+    const int ch = threadIdx.x % NCH, quarter = threadIdx.x / NCH;
+    int n = 0;
+    float m = 0.f, m2 = 0.f;
+    if (quarter < 4) {
+        bn_merge_of<8>(&ns[quarter * 8], &means[quarter * 8][ch], &squares[quarter * 8][ch], LD, &n, &m, &m2);
+        means[quarter * 8][ch] = m;
+        squares[quarter * 8][ch] = m2;
+        if (ch == 0) nw[quarter] = n;
+    }
+    __syncthreads();
     const int c = slab * p.cs + threadIdx.x;
-    if (threadIdx.x < NCH && c < p.C) {
-        const float md = n > 0.f ? a / n : 0.f;                   // mean of the deviations
-        part[((size_t)row * p.C + c) * 2] = ref_s[threadIdx.x] + md;
-        part[((size_t)row * p.C + c) * 2 + 1] = n > 0.f ? fmaxf(q2 - a * md, 0.f) : 0.f;
-    }
-    if (slab == 0 && threadIdx.x == 0) cnt[row] = n;
+    if (threadIdx.x >= NCH || c >= p.C) return;
+    bn_merge_of<4>(nw, &means[0][ch], &squares[0][ch], 8 * LD, &n, &m, &m2);
+    part[((size_t)row * p.C + c) * 2] = m;
+    part[((size_t)row * p.C + c) * 2 + 1] = m2;
+    if (slab == 0 && threadIdx.x == 0) cnt[row] = (float)n;
 }
 
 // merge of two (count, mean, M2) triples; an empty side leaves the other unchanged

@@ -452,6 +452,43 @@ def test_normalisation_over_pieces_and_channel_groups(H, W, C, bo, N, dtype):
     test_sparse_bn_apply_and_backward(H, W, C, bo, N, dtype, True)
 
 
+def test_bn_stats_of_a_list_that_starts_outside_the_image():
+    """The first block of the list has no pixel inside the image, and the pixels nearest to it belong to no active block:
+    whatever they hold, the statistics are those of the other blocks."""
+    step("bn_stats, first block outside")
+    r = gen.rng_for(30)
+    for dtype, bad in (("f32", np.nan), ("bf16", np.nan), ("f16", np.inf), ("f32", 1e30)):
+        _, g, _, _ = sb.geometry(32, 32, 3, 1, 16)
+        g.bcount_h = 3
+        x = gen.round_to((gen.activations(r, (1, 32, 32, 16), "f32") + 20).astype(np.float32), dtype)
+        x[0, 16:, :16] = bad
+        idx = np.array([(0, 2, 0), (0, 0, 0), (0, 0, 1), (0, 1, 1)], np.int32)
+        d_idx, d_cnt = dev_indices(idx, 4)
+        mean, var = sb.sparse_bn_stats(to_dev(x, dtype), d_idx, d_cnt, g)
+        rm, rv = orc.bn_stats(x, idx[1:], ogeom(g))
+        assert np.allclose(mean.cpu().numpy(), rm, rtol=1e-5) and np.allclose(var.cpu().numpy(), rv, rtol=2e-4)
+
+
+def test_bn_stats_with_outliers_where_a_row_of_partial_sums_begins():
+    """20 736 blocks of 8x8 in 1024 rows; the first pixel of every row's first block is 1000 standard deviations off.  It is
+    the reference of one pixel group in 32: a 32nd of the squares are 10^6 where the variance is 770, forty times the
+    whole, and their sum of up to 42 terms is rounded at random: 40 * 2^-24 * sqrt(42) = 1.6e-5 of a row, less in the
+    average of 1024 rows (as sampled: 1e-5 holds)."""
+    step("bn_stats, outliers")
+    r = gen.rng_for(31)
+    H = W = 1152
+    _, g, _, _ = sb.geometry(H, W, 3, 1, 8)
+    x = r.standard_normal((1, H, W, 4)).astype(np.float32)
+    idx = np.stack(np.meshgrid([0], np.arange(144), np.arange(144), indexing="ij"), -1).reshape(-1, 3).astype(np.int32)
+    for _, by, bx in idx[:1024]:
+        x[0, 8 * by, 8 * bx] = 1000.0
+    d_idx, d_cnt = dev_indices(idx, len(idx))
+    mean, var = sb.sparse_bn_stats(torch.from_numpy(x).cuda(), d_idx, d_cnt, g)
+    rv = x.astype(np.float64).var(axis=(0, 1, 2))
+    err = np.abs(var.cpu().numpy() - rv).max() / rv.min()
+    assert err < 1e-5, err
+
+
 # --------------------------------------------------------------------------- fp32 convolution
 F32_CONV_CASES = [
     # H, W, Cin, Cout, k, s, bo, N, dtype: items are 64 output pixels x up to 64 channels, chunks whole groups of 8 channels
