@@ -80,23 +80,26 @@ __global__ __launch_bounds__(kBnThreads) void bn_apply(const uint4 *x, uint4 *y,
     const int pg = threadIdx.x >> 3, k = threadIdx.x & 7;
     for (int s0 = 0; s0 < p.slabs; s0 += bn_group_slabs(p)) {
         const int ns = min(bn_group_slabs(p), p.slabs - s0);
-        const uint32_t items = (uint32_t)nact * (uint32_t)(ns * pieces);
-        BnBlock blk = bn_block(indices, fdiv(blockIdx.x, div_pieces) / (uint32_t)ns, p.cap);
+        const uint32_t units = (uint32_t)nact * (uint32_t)ns;     // (block, slab of the group)
+        BnWalk it(blockIdx.x, gridDim.x, (uint32_t)pieces, div_pieces);
+        uint32_t b = it.unit / (uint32_t)ns;
+        int slab = (int)(it.unit - b * ns);
+        BnBlock blk = bn_block(indices, b, p.cap);
         BnCoefs<4> co = {cf, 0};
         if (s0) __syncthreads();
         co.load(s0 * p.cs, p.C, [&](int c, float *v) { bn_affine_of(a, c, v); });
-        for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
-            const uint32_t bs = fdiv(item, div_pieces);           // (block, slab of the group)
-            const int piece = (int)(item - bs * pieces);
-            const uint32_t b = ns == 1 ? bs : bs / (uint32_t)ns;
-            const int slab = s0 + (int)(bs - b * ns);
-            if (item != blockIdx.x) blk = bn_block(indices, b, p.cap);
-            const BnPlace w = bn_place<EPV>(blk, slab, k, p);
+        while (it.unit < units) {
+            const BnPlace w = bn_place<EPV>(blk, s0 + slab, k, p);
+            const int q0 = (int)it.piece * kBnPiece + pg;
+            it.advance();
+            b = ns == 1 ? it.unit : it.unit / (uint32_t)ns;       // the next item's
+            slab = (int)(it.unit - b * ns);
+            blk = bn_block(indices, b, p.cap);
             long long at[4];
             uint4 v[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                at[u] = bn_pixel(w, piece * kBnPiece + pg + 32 * u, p);
+                at[u] = bn_pixel(w, q0 + 32 * u, p);
                 if (at[u] >= 0) v[u] = x[at[u]];
             }
             float mean[EPV], rstd[EPV], gam[EPV], bet[EPV];
@@ -141,9 +144,10 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_partial(const uint4 *__rest
 #pragma unroll
         for (int i = 0; i < 4; ++i) cf[i][threadIdx.x] = v[i];
     }
-    BnBlock blk = bn_block(indices, fdiv(row, div_pieces), p.cap);
-    const uint32_t items = (uint32_t)min(*count, p.cap) * (uint32_t)pieces;
-    if (row >= items) return;
+    BnWalk it(row, rows, (uint32_t)pieces, div_pieces);
+    BnBlock blk = bn_block(indices, it.unit, p.cap);
+    const uint32_t nact = (uint32_t)min(*count, p.cap);
+    if (it.unit >= nact) return;
     __syncthreads();
     float mean[EPV], rstd[EPV], gam[EPV], bet[EPV], s1[EPV], s2[EPV];
 #pragma unroll
@@ -153,11 +157,11 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_partial(const uint4 *__rest
         s1[e] = s2[e] = 0.f;
     }
     int npx = 0;
-    for (uint32_t item = row; item < items; item += rows) {
-        const uint32_t b = fdiv(item, div_pieces);
+    while (it.unit < nact) {
         const BnPlace w = bn_place<EPV>(blk, slab, k, p);
-        blk = bn_block(indices, fdiv(item + rows, div_pieces), p.cap);        // the next item's
-        const int q0 = (int)(item - b * pieces) * kBnPiece + pg;
+        const int q0 = (int)it.piece * kBnPiece + pg;
+        it.advance();
+        blk = bn_block(indices, it.unit, p.cap);                  // the next item's
         long long at[4];
         uint4 vx[4], vg[4];
 #pragma unroll
@@ -256,8 +260,11 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_dx(const uint4 *__restrict_
     const float n = *ntot, inv_n = n > 0.f ? 1.0f / n : 0.f;
     for (int s0 = 0; s0 < p.slabs; s0 += bn_group_slabs(p)) {
         const int ns = min(bn_group_slabs(p), p.slabs - s0);
-        const uint32_t items = (uint32_t)nact * (uint32_t)(ns * pieces);
-        BnBlock blk = bn_block(indices, fdiv(blockIdx.x, div_pieces) / (uint32_t)ns, p.cap);
+        const uint32_t units = (uint32_t)nact * (uint32_t)ns;     // (block, slab of the group)
+        BnWalk it(blockIdx.x, gridDim.x, (uint32_t)pieces, div_pieces);
+        uint32_t b = it.unit / (uint32_t)ns;
+        int slab = (int)(it.unit - b * ns);
+        BnBlock blk = bn_block(indices, b, p.cap);
         BnCoefs<6> co = {cf, 0};
         if (s0) __syncthreads();
         co.load(s0 * p.cs, p.C, [&](int c, float *v) {
@@ -265,18 +272,18 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_dx(const uint4 *__restrict_
             v[4] = dbeta[c] * inv_n;
             v[5] = dgamma[c] * inv_n;
         });
-        for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
-            const uint32_t bs = fdiv(item, div_pieces);           // (block, slab of the group)
-            const int piece = (int)(item - bs * pieces);
-            const uint32_t b = ns == 1 ? bs : bs / (uint32_t)ns;
-            const int slab = s0 + (int)(bs - b * ns);
-            if (item != blockIdx.x) blk = bn_block(indices, b, p.cap);
-            const BnPlace w = bn_place<EPV>(blk, slab, k, p);
+        while (it.unit < units) {
+            const BnPlace w = bn_place<EPV>(blk, s0 + slab, k, p);
+            const int q0 = (int)it.piece * kBnPiece + pg;
+            it.advance();
+            b = ns == 1 ? it.unit : it.unit / (uint32_t)ns;       // the next item's
+            slab = (int)(it.unit - b * ns);
+            blk = bn_block(indices, b, p.cap);
             long long at[4];
             uint4 vx[4], vg[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                at[u] = bn_pixel(w, piece * kBnPiece + pg + 32 * u, p);
+                at[u] = bn_pixel(w, q0 + 32 * u, p);
                 if (at[u] >= 0) {
                     vx[u] = x[at[u]];
                     vg[u] = dy[at[u]];

@@ -96,13 +96,33 @@ inline int bn_rows(int cap, const BnParams &p) {
 
 // origin of block b's window and this thread's place in the slab
 struct BnPlace {
-    int y0, x0, npx, c0;
+    int y0, x0, c0;
     bool chan_ok;
     long long base;
 };
 
 struct BnBlock {
     int n, by, bx;
+};
+
+// Item number `first` + i * `step` of a list of (unit, piece) items, `pieces` of them to a unit, carried along: the number itself
+// need not fit 32 bits (a unit's window may lie outside the image for the most part, so the memory does not bound it).
+struct BnWalk {
+    uint32_t unit, piece, du, dp, pieces;
+    __device__ __forceinline__ BnWalk(uint32_t first, uint32_t step, uint32_t pieces_, const FastDiv &div_pieces) : pieces(pieces_) {
+        unit = fdiv(first, div_pieces);
+        piece = first - unit * pieces;
+        du = fdiv(step, div_pieces);
+        dp = step - du * pieces;
+    }
+    __device__ __forceinline__ void advance() {
+        unit += du;
+        piece += dp;
+        if (piece >= pieces) {
+            piece -= pieces;
+            ++unit;
+        }
+    }
 };
 // past the list (the first item of a workgroup, requested beside the count): some block, not used
 __device__ __forceinline__ BnBlock bn_block(const int32_t *indices, uint32_t b, int cap) {
@@ -116,8 +136,6 @@ __device__ __forceinline__ BnPlace bn_place(const BnBlock &t, int slab, int k, c
     BnPlace w;
     w.y0 = p.g.boffset_h + by * p.g.bstride_h;
     w.x0 = p.g.boffset_w + bx * p.g.bstride_w;
-    const int ylo = max(w.y0, 0), yhi = min(w.y0 + p.g.bsize_h, p.H), xlo = max(w.x0, 0), xhi = min(w.x0 + p.g.bsize_w, p.W);
-    w.npx = max(yhi - ylo, 0) * max(xhi - xlo, 0);
     w.c0 = slab * p.cs + k * EPV;
     w.chan_ok = w.c0 < p.C;
     w.base = (long long)n * p.H * p.W * p.pix_vecs + (long long)(slab * (p.cs / EPV) + k);

@@ -60,18 +60,19 @@ __global__ __launch_bounds__(kBnThreads) void bn_partial(const uint4 *__restrict
     const int pg = threadIdx.x >> 3, k = threadIdx.x & 7;         // pixel group, vector of the slab
     const uint32_t row = fdiv(blockIdx.x, p.div_slabs), rows = fdiv(gridDim.x, p.div_slabs);
     const int slab = (int)(blockIdx.x - row * p.slabs);
-    BnBlock blk = bn_block(indices, fdiv(row, div_pieces), p.cap);
-    const uint32_t items = (uint32_t)min(*count, p.cap) * (uint32_t)pieces;
-    if (row >= items) return;
+    BnWalk it(row, rows, (uint32_t)pieces, div_pieces);
+    BnBlock blk = bn_block(indices, it.unit, p.cap);
+    const uint32_t nact = (uint32_t)min(*count, p.cap);
+    if (it.unit >= nact) return;
     float ref[EPV], s1[EPV], s2[EPV];
 #pragma unroll
     for (int e = 0; e < EPV; ++e) ref[e] = s1[e] = s2[e] = 0.f;
     int npx = 0;
-    for (uint32_t item = row; item < items; item += rows) {
-        const uint32_t b = fdiv(item, div_pieces);
+    while (it.unit < nact) {
         const BnPlace w = bn_place<EPV>(blk, slab, k, p);
-        blk = bn_block(indices, fdiv(item + rows, div_pieces), p.cap);        // the next item's
-        const int q0 = (int)(item - b * pieces) * kBnPiece + pg;
+        const int q0 = (int)it.piece * kBnPiece + pg;
+        it.advance();
+        blk = bn_block(indices, it.unit, p.cap);                  // the next item's
         long long at[4];
         uint4 v[4];
 #pragma unroll

@@ -469,6 +469,26 @@ def test_bn_stats_of_a_list_that_starts_outside_the_image():
         assert np.allclose(mean.cpu().numpy(), rm, rtol=1e-5) and np.allclose(var.cpu().numpy(), rv, rtol=2e-4)
 
 
+def test_normalisation_of_blocks_far_larger_than_the_image():
+    """32 780 samples of 16x16 under one block of 4096x4095 each: more than 2^32 pieces of 128 pixels, nearly all of them
+    outside the image."""
+    step("bn, blocks beyond the image")
+    N, C = 32780, 8
+    g = sb.Geom(4096, 4095, 4096, 4095, 0, 0, 1, 1)
+    x = torch.randn((N, 16, 16, C), device="cuda", generator=torch.Generator("cuda").manual_seed(1)).to(torch.bfloat16)
+    x[1000:] += 3.0
+    idx = torch.zeros((N, 3), dtype=torch.int32)
+    idx[:, 0] = torch.arange(N)
+    idx, cnt = idx.cuda(), torch.tensor([N], dtype=torch.int32).cuda()
+    mean, var = sb.sparse_bn_stats(x, idx, cnt, g)
+    x64 = x.double()
+    rm, rv = x64.mean((0, 1, 2)), x64.var((0, 1, 2), unbiased=False)
+    assert torch.allclose(mean.double(), rm, rtol=1e-5) and torch.allclose(var.double(), rv, rtol=2e-4)
+    y = sb.sparse_bn_apply(x, idx, cnt, g, mean, var, y=torch.zeros_like(x))
+    ref = (x64 - rm) / (rv + 1e-5).sqrt()
+    assert ((y.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4).all()
+
+
 def test_bn_stats_with_outliers_where_a_row_of_partial_sums_begins():
     """20 736 blocks of 8x8 in 1024 rows; the first pixel of every row's first block is 1000 standard deviations off.  It is
     the reference of one pixel group in 32: a 32nd of the squares are 10^6 where the variance is 770, forty times the
