@@ -151,10 +151,11 @@ __global__ __launch_bounds__(256) void conv_f32_kernel(F32Params p) {
                     const int ch = chunk * p.cc8 * 8 + c * E;
                     const int gx = gx0 + col;
                     dst[u] = pix < npix ? pix * p.S + c * E : -1;
-                    // rows above and below the sample fall outside its descriptor and read as zeros, so does what is put there
+                    // outside the sample: an offset outside its descriptor, which reads as zeros (of rows far enough below
+                    // the product would wrap back into it)
                     const int at = V4 ? min(ch, p.Cin - 4) : ch;
-                    uint32_t off = (uint32_t)((((gy0 + row) * p.W + gx) * p.Cin + at) * (int)sizeof(T));
-                    if (gx < 0 || gx >= p.W || ch >= p.Cin || gy0 + row < 0) off = kOutOfRange;
+                    uint32_t off = (((uint32_t)(gy0 + row) * p.W + gx) * p.Cin + at) * (uint32_t)sizeof(T);
+                    if ((uint32_t)gx >= (uint32_t)p.W || ch >= p.Cin || (uint32_t)(gy0 + row) >= (uint32_t)p.H) off = kOutOfRange;
                     if (V4) {
                         const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)off, 0, 0);
                         xv[u] = __builtin_bit_cast(float4, t);

@@ -556,6 +556,20 @@ def test_fp32_convolution_unfused_and_fused(H, W, Cin, Cout, k, s, bo, N, dtype)
         assert_close(to_host(out), ref, tol, "unfused")
 
 
+def test_fp32_convolution_of_windows_far_below_the_image():
+    """Input windows 2^20 rows below an image whose rows are 4 KiB: the rows' byte offsets are multiples of 2^32, and all
+    they hold is zeros; the output blocks are inside."""
+    step("fp32 conv, windows far below")
+    r = gen.rng_for(32)
+    g_in, g_out = sb.Geom(10, 10, 8, 8, 1 << 20, -1, 1, 8), sb.Geom(8, 8, 8, 8, 0, 0, 1, 8)
+    x, w, b = gen.activations(r, (1, 16, 64, 16), "f32"), gen.conv_weights(r, 3, 3, 16, 16, "f32"), gen.bias_vector(r, 16)
+    d_idx, d_cnt = dev_indices(np.array([(0, 0, k) for k in range(8)], np.int32))
+    y = torch.full((1, 16, 64, 16), 7.0).cuda()
+    sb.sparse_conv(to_dev(x, "f32"), d_idx, d_cnt, g_in, g_out, sb.pack_weights(to_dev(w, "f32")), torch.from_numpy(b).cuda(), y)
+    got = to_host(y)
+    assert (got[0, :8] == b).all() and (got[0, 8:] == 7.0).all()
+
+
 # --------------------------------------------------------------------------- convolution on tiles
 CONV_CASES = [
     # B, th, tw, Cin, Cout, k, s, dtype, relu, bias
