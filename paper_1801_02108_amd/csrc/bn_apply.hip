@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kBnThreads) void bn_apply(const uint4 *x, uint4 *y,
                                                        int pieces, FastDiv div_pieces, BnParams p, BnAffine a) {
     constexpr int EPV = BnElem<DT>::EPV;
     __shared__ __align__(16) float cf[4][kBnCoef];
-    const int nact = min(*count, p.cap);
+    const int nact = max(min(*count, p.cap), 0);
     const int pg = threadIdx.x >> 3, k = threadIdx.x & 7;
     for (int s0 = 0; s0 < p.slabs; s0 += bn_group_slabs(p)) {
         const int ns = min(bn_group_slabs(p), p.slabs - s0);
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_partial(const uint4 *__rest
     }
     BnWalk it(row, rows, (uint32_t)pieces, div_pieces);
     BnBlock blk = bn_block(indices, it.unit, p.cap);
-    const uint32_t nact = (uint32_t)min(*count, p.cap);
+    const uint32_t nact = (uint32_t)max(min(*count, p.cap), 0);
     if (it.unit >= nact) return;
     __syncthreads();
     float mean[EPV], rstd[EPV], gam[EPV], bet[EPV], s1[EPV], s2[EPV];
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_dx(const uint4 *__restrict_
                                                         int pieces, FastDiv div_pieces, BnParams p, BnAffine a) {
     constexpr int EPV = BnElem<DT>::EPV;
     __shared__ __align__(16) float cf[6][kBnCoef];
-    const int nact = min(*count, p.cap);
+    const int nact = max(min(*count, p.cap), 0);
     const int pg = threadIdx.x >> 3, k = threadIdx.x & 7;
     const float n = *ntot, inv_n = n > 0.f ? 1.0f / n : 0.f;
     for (int s0 = 0; s0 < p.slabs; s0 += bn_group_slabs(p)) {

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kBnThreads) void bn_partial(const uint4 *__restrict
     const int slab = (int)(blockIdx.x - row * p.slabs);
     BnWalk it(row, rows, (uint32_t)pieces, div_pieces);
     BnBlock blk = bn_block(indices, it.unit, p.cap);
-    const uint32_t nact = (uint32_t)min(*count, p.cap);
+    const uint32_t nact = (uint32_t)max(min(*count, p.cap), 0);
     if (it.unit >= nact) return;
     float ref[EPV], s1[EPV], s2[EPV];
 #pragma unroll

@@ -107,7 +107,7 @@ __global__ __launch_bounds__(256) void conv_f32_kernel(F32Params p) {
         }
     };
     locate(fdiv(blockIdx.x, p.div_pn));
-    const uint32_t items = (uint32_t)min(*p.count, p.cap) * per_tile;
+    const uint32_t items = (uint32_t)max(min(*p.count, p.cap), 0) * per_tile;
     const uint32_t sample_bytes = (uint32_t)p.H * p.W * p.Cin * (uint32_t)sizeof(T);
     for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
         const uint32_t b = fdiv(item, p.div_pn);

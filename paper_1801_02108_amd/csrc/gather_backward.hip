@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kGbThreads, 5) void gb_either(V *__restrict__ dx, c
                                                         const int32_t *__restrict__ map, const int32_t *__restrict__ indices,
                                                         const int32_t *__restrict__ count, int cells_from, int segs, uint32_t piece,
                                                         FastDiv div_segs, FastDiv div_tr, GbParams p) {
-    const int nact = min(*count, p.cap);
+    const int nact = max(min(*count, p.cap), 0);
     if (nact >= cells_from) gb_cells<V, DT, 1, 2>(dx, dtiles, map, p);
     else gb_tiles<V, DT, U>(dx, dtiles, map, indices, (uint32_t)nact, segs, piece, div_segs, div_tr, p);
 }

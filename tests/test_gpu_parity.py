@@ -556,6 +556,26 @@ def test_fp32_convolution_unfused_and_fused(H, W, Cin, Cout, k, s, bo, N, dtype)
         assert_close(to_host(out), ref, tol, "unfused")
 
 
+def test_a_negative_count_is_an_empty_list():
+    step("negative count")
+    r = gen.rng_for(33)
+    g_in, g_out, _, _ = sb.geometry(40, 56, 3, 1, 8)
+    idx, cnt = dev_indices(np.array([(0, 1, 1), (0, 2, 3)], np.int32))[0], torch.tensor([-3], dtype=torch.int32).cuda()
+    x = to_dev(gen.activations(r, (1, 40, 56, 16), "f32"), "f32")
+    y = x.clone()
+    sb.sparse_conv(x, idx, cnt, g_in, g_out, sb.pack_weights(to_dev(gen.conv_weights(r, 3, 3, 16, 16, "f32"), "f32")), None, y)
+    assert torch.equal(x, y)
+    for C in (16, 272):                              # by cells, by tiles
+        dx = torch.ones((1, 40, 56, C)).cuda()
+        sb.sparse_gather_backward(torch.ones((2, 10, 10, C)).cuda(), idx, cnt, g_in, dx)
+        assert (dx == 1).all()
+    mean, var = sb.sparse_bn_stats(x, idx, cnt, g_out)
+    assert (mean == 0).all() and (var == 0).all()
+    sb.sparse_bn_apply(x, idx, cnt, g_out, mean, var, y=y)
+    dx, dgamma, dbeta = sb.sparse_bn_backward(x, x, idx, cnt, g_out, mean, var)
+    assert torch.equal(x, y) and (dx == 0).all() and (dgamma == 0).all() and (dbeta == 0).all()
+
+
 def test_fp32_convolution_of_windows_far_below_the_image():
     """Input windows 2^20 rows below an image whose rows are 4 KiB: the rows' byte offsets are multiples of 2^32, and all
     they hold is zeros; the output blocks are inside."""
