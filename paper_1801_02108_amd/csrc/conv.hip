@@ -9,6 +9,8 @@
 // take), which are asked first:
 //   conv_direct  any shape, any of f32/bf16/f16: one thread per output element, fp32 FMA chain.
 //                Left for tiles so wide that the rows of 64 output pixels do not fit LDS (from about 1100 pixels).
+//                Bound by its loads, two per product: 64 x 1290 x 24 -> 40, one tile: 9.63 ms with the weights' places
+//                worked out per product -> 5.69 (8.61 with one weight array per input channel).
 //   conv_mfma    bf16/f16 with Cin % 8 == 0 and Cout % 8 == 0, kernel sizes other than 3x3 (and 3x3 tiles too
 //                large for the other kernels' LDS plans): implicit GEMM on the matrix cores.
 //                Per workgroup: up to 256 output pixels x 64 output channels, fp32 accumulators in
@@ -28,7 +30,16 @@ namespace sbnet {
 // ------------------------------------------------------------------------------------------
 // direct kernel
 // ------------------------------------------------------------------------------------------
-template <int DT, bool FUSED>
+// K channels of one tap, in ascending order: the weights of an output channel lie in pairs, 32 elements from one to the next
+template <int DT, int K>
+__device__ __forceinline__ float direct_dot(const typename Elem<DT>::T *x, const typename Elem<DT>::T *w, float acc) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) acc = fmaf(Elem<DT>::load(x + k), Elem<DT>::load(w + (k >> 1) * 32 + (k & 1)), acc);
+    return acc;
+}
+
+// R: Cin % 8
+template <int DT, bool FUSED, int R>
 __global__ __launch_bounds__(256) void conv_direct(ConvParams p) {
     typedef typename Elem<DT>::T T;
     const T *in = (const T *)p.in;
@@ -37,6 +48,8 @@ __global__ __launch_bounds__(256) void conv_direct(ConvParams p) {
     const int nact = min(*p.count, p.cap);
     const uint32_t per_tile = (uint32_t)p.oh * p.ow * p.Cout;
     const FastDiv div_cout = p.div_cv;  // reused: divides by Cout in this kernel
+    const int taps = p.kh * p.kw;
+    const uint32_t block = (uint32_t)fma_weight_index(0, 0, 16, taps, (p.Cin + 7) >> 3);
     for (int b = blockIdx.y; b < nact; b += gridDim.y) {
         int n = 0, y0 = 0, x0 = 0, oy0 = 0, ox0 = 0;
         if (FUSED) {
@@ -51,6 +64,7 @@ __global__ __launch_bounds__(256) void conv_direct(ConvParams p) {
             const uint32_t pix = fdiv(e, div_cout);
             const int o = (int)(e - pix * p.Cout);
             const int i = (int)fdiv(pix, p.div_ow), j = (int)pix - i * p.ow;
+            const T *wo = w + (size_t)(o >> 4) * block + (o & 15) * 2;      // fma_weight_index
             float acc = p.bias ? p.bias[o] : 0.f;
             for (int r = 0; r < p.kh; ++r)
                 for (int t = 0; t < p.kw; ++t) {
@@ -63,9 +77,10 @@ __global__ __launch_bounds__(256) void conv_direct(ConvParams p) {
                     } else {
                         src = in + (((size_t)b * p.th + yy) * p.tw + xx) * p.Cin;
                     }
-                    for (int c = 0; c < p.Cin; ++c)
-                        acc = fmaf(Elem<DT>::load(src + c),
-                                   Elem<DT>::load(w + fma_weight_index(r * p.kw + t, c, o, p.kh * p.kw, (p.Cin + 7) >> 3)), acc);
+                    const T *wp = wo + (size_t)(r * p.kw + t) * 128;
+                    int c = 0;
+                    for (; c + 8 <= p.Cin; c += 8, wp += (size_t)taps * 128) acc = direct_dot<DT, 8>(src + c, wp, acc);
+                    acc = direct_dot<DT, R>(src + c, wp, acc);
                 }
             if (p.relu) acc = fmaxf(acc, 0.f);
             if (FUSED) {
@@ -389,6 +404,23 @@ __global__ void tile_indices(int32_t *__restrict__ idx, int cap) {
     }
 }
 
+template <int DT, bool FUSED>
+static void launch_direct(const ConvParams &p, dim3 grid, hipStream_t s) {
+#define SBNET_DIRECT(R) \
+    case R: hipLaunchKernelGGL((conv_direct<DT, FUSED, R>), grid, dim3(256), 0, s, p); break
+    switch (p.Cin % 8) {
+        SBNET_DIRECT(0);
+        SBNET_DIRECT(1);
+        SBNET_DIRECT(2);
+        SBNET_DIRECT(3);
+        SBNET_DIRECT(4);
+        SBNET_DIRECT(5);
+        SBNET_DIRECT(6);
+        SBNET_DIRECT(7);
+    }
+#undef SBNET_DIRECT
+}
+
 template <bool FUSED>
 static sbnet_status run_conv(const char *who, sbnet_dtype dt, ConvParams &p, hipStream_t s) {
     if (p.cap == 0) return SBNET_OK;
@@ -419,11 +451,9 @@ static sbnet_status run_conv(const char *who, sbnet_dtype dt, ConvParams &p, hip
         p.div_cv = make_fastdiv(p.Cout);
         const long long per_tile = M * p.Cout;
         dim3 grid((unsigned)((per_tile + 255) / 256 > 64 ? 64 : (per_tile + 255) / 256), (unsigned)(p.cap > 4096 ? 4096 : p.cap));
-#define SBNET_DIRECT(DT) hipLaunchKernelGGL((conv_direct<DT, FUSED>), grid, dim3(256), 0, s, p)
-        if (dt == SBNET_F32) SBNET_DIRECT(SBNET_F32);
-        else if (dt == SBNET_BF16) SBNET_DIRECT(SBNET_BF16);
-        else SBNET_DIRECT(SBNET_F16);
-#undef SBNET_DIRECT
+        if (dt == SBNET_F32) launch_direct<SBNET_F32, FUSED>(p, grid, s);
+        else if (dt == SBNET_BF16) launch_direct<SBNET_BF16, FUSED>(p, grid, s);
+        else launch_direct<SBNET_F16, FUSED>(p, grid, s);
         return launch_status(who);
     }
 
