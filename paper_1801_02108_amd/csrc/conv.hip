@@ -8,9 +8,10 @@
 // take) and conv_f32_try (conv_f32.hip: fp32 arithmetic, for float32 and for channel counts the 16-bit kernels do not
 // take), which are asked first:
 //   conv_direct  any shape, any of f32/bf16/f16: one thread per output element, fp32 FMA chain.
-//                Left for tiles so wide that the rows of 64 output pixels do not fit LDS (from about 1100 pixels).
-//                Bound by its loads, two per product: 64 x 1290 x 24 -> 40, one tile: 9.63 ms with the weights' places
-//                worked out per product -> 5.69 (8.61 with one weight array per input channel).
+//                For few products per pixel (direct_is_faster) and for tiles so wide that the rows of 64 output pixels do
+//                not fit LDS (from about 1100 pixels).  Bound by its loads, two per product: 64 x 1290 x 24 -> 40, one
+//                tile: 9.63 ms with the weights' places worked out per product -> 5.69 (8.61 with one weight array per
+//                input channel).
 //   conv_mfma    bf16/f16 with Cin % 8 == 0 and Cout % 8 == 0, kernel sizes other than 3x3 (and 3x3 tiles too
 //                large for the other kernels' LDS plans): implicit GEMM on the matrix cores.
 //                Per workgroup: up to 256 output pixels x 64 output channels, fp32 accumulators in
@@ -404,6 +405,19 @@ __global__ void tile_indices(int32_t *__restrict__ idx, int cap) {
     }
 }
 
+// Few products for an output element and few output channels for an input one: conv_f32's pixels in LDS and 16 x 16 tiles of
+// matrix work are mostly padding.  L products per element, the lines lie at (L + 2) Cout = 160 and, where even all blocks of the
+// list are not one round of threads, at L = 36.  400 x 352, half of the blocks of 16 x 16, f32, one thread per element
+// against conv_f32: 3x3 1 -> 1: 4.6 us / 8.9, 1 -> 8: 8.5 / 9.1, 4 -> 4: 7.0 / 9.1, 2 -> 8: 9.1 / 9.1, 1 -> 16: 13.7 / 9.4,
+// 3 -> 8: 10.3 / 9.4, 8 -> 4: 10.4 / 9.0; 1x1 4 -> 4: 3.7 / 8.0, 8 -> 16: 7.4 / 8.7, 32 -> 2: 5.3 / 9.3, 1 -> 32: 12.4 / 10.1;
+// 5x5 1 -> 4: 10.1 / 10.5, 1 -> 8: 15.6 / 10.7.  64 x 64, blocks of 8 x 8: 3x3 1 -> 32: 4.45 / 4.74, 4 -> 32: 4.62 / 4.76,
+// 8 -> 8: 4.71 / 4.58, 16 -> 1: 5.95 / 5.03.
+static bool direct_is_faster(const ConvParams &p, long long M) {
+    const long long L = (long long)p.kh * p.kw * p.Cin;
+    if (L <= 36 && p.cap * M * p.Cout <= (1LL << 17)) return true;
+    return L <= 100 && p.Cout <= 16 && (L + 2) * p.Cout <= 160;
+}
+
 template <int DT, bool FUSED>
 static void launch_direct(const ConvParams &p, dim3 grid, hipStream_t s) {
 #define SBNET_DIRECT(R) \
@@ -447,7 +461,7 @@ static sbnet_status run_conv(const char *who, sbnet_dtype dt, ConvParams &p, hip
     if (conv3_try(dt, FUSED, p, s, &st16, who)) return st16;
 
     if (!use_mfma(dt, p.Cin, p.Cout)) {
-        if (conv_f32_try(dt, FUSED, p, s, &st16, who)) return st16;
+        if (!direct_is_faster(p, M) && conv_f32_try(dt, FUSED, p, s, &st16, who)) return st16;
         p.div_cv = make_fastdiv(p.Cout);
         const long long per_tile = M * p.Cout;
         dim3 grid((unsigned)((per_tile + 255) / 256 > 64 ? 64 : (per_tile + 255) / 256), (unsigned)(p.cap > 4096 ? 4096 : p.cap));

@@ -516,7 +516,7 @@ F32_CONV_CASES = [
     (33, 41, 3, 17, 3, 1, 16, 2, "f32"),     # scalar staging, a second block of output channels with one channel
     (30, 30, 24, 24, 3, 1, 15, 1, "f32"),    # 225 pixels: a last pass of 33, rows that straddle passes
     (40, 36, 46, 38, 3, 1, 12, 1, "f32"),    # six groups of 8 channels, the last one partial
-    (36, 36, 64, 80, 3, 1, 16, 1, "f32"),    # several chunks and two output groups of three blocks, the last one empty
+    (36, 36, 64, 80, 3, 1, 16, 1, "f32"),    # five output groups of one block of 16 channels
     (20, 20, 132, 64, 3, 1, 10, 1, "f32"),   # many chunks
     (26, 26, 12, 20, 5, 2, 4, 1, "f32"),     # 25 taps, stride 2
     (16, 150, 8, 16, 1, 1, 100, 1, "f32"),   # 1x1, output rows longer than a pass
@@ -526,11 +526,10 @@ F32_CONV_CASES = [
 ]
 
 
-@pytest.mark.parametrize("H,W,Cin,Cout,k,s,bo,N,dtype", F32_CONV_CASES)
-def test_fp32_convolution_unfused_and_fused(H, W, Cin, Cout, k, s, bo, N, dtype):
+def check_fp32_convolution(H, W, Cin, Cout, k, s, bo, N, dtype, room=2):
     """fp32 products and sums of up to 25 * 132 terms: rounding of the sum below 2^-24 * sqrt(3300) * 3 = 1e-5 of the
     result's RMS with random signs; 16-bit results one rounding more (the tolerances of CONV_TOL)."""
-    step("fp32 conv %s" % ((H, W, Cin, Cout, k, s, bo, N, dtype),))
+    step("fp32 conv %s" % ((H, W, Cin, Cout, k, s, bo, N, dtype, room),))
     r = gen.rng_for(12, H * 1000 + W + Cin)
     g_in, g_out, Ho, Wo = sb.geometry(H, W, k, s, bo)
     x = gen.activations(r, (N, H, W, Cin), dtype)
@@ -542,7 +541,7 @@ def test_fp32_convolution_unfused_and_fused(H, W, Cin, Cout, k, s, bo, N, dtype)
     for dens in (0.0, 1.0) if bo > 1000 else (0.0, 0.02, 1.0):
         mask = (r.random((N, Ho, Wo)) < dens).astype(np.float32)
         idx = orc.reduce_mask(mask, ogeom(g_out))
-        d_idx, d_cnt = dev_indices(idx, len(idx) + 2)
+        d_idx, d_cnt = dev_indices(idx, len(idx) + room)
         for add, relu in ((False, True), (True, False)):
             y = to_dev(y0, dtype)
             sb.sparse_conv(to_dev(x, dtype), d_idx, d_cnt, g_in, g_out, wp, torch.from_numpy(b).cuda(), y, stride=s, relu=relu, add=add)
@@ -554,6 +553,29 @@ def test_fp32_convolution_unfused_and_fused(H, W, Cin, Cout, k, s, bo, N, dtype)
         out = sb.conv_on_tiles(tiles, d_cnt, wp, torch.from_numpy(b).cuda(), stride=s, relu=False)[:len(idx)]
         ref = orc.conv_valid(to_host(tiles)[:len(idx)], w, b, stride=s)
         assert_close(to_host(out), ref, tol, "unfused")
+
+
+@pytest.mark.parametrize("H,W,Cin,Cout,k,s,bo,N,dtype", F32_CONV_CASES)
+def test_fp32_convolution_unfused_and_fused(H, W, Cin, Cout, k, s, bo, N, dtype):
+    check_fp32_convolution(H, W, Cin, Cout, k, s, bo, N, dtype)
+
+
+@pytest.mark.parametrize("H,W,Cin,Cout,k,s,bo,N,dtype", [c for c in F32_CONV_CASES if c[6] < 1000] + [
+    (32, 24, 2, 36, 3, 1, 8, 1, "f16"),      # all channels of a pixel one by one, the padding zeroed once
+    (30, 30, 24, 128, 3, 1, 10, 1, "f32"),   # two output groups of four blocks
+    (36, 36, 100, 80, 3, 1, 16, 1, "f32"),   # four chunks and two output groups of three blocks, the last one empty
+])
+def test_fp32_convolution_with_a_list_of_many(H, W, Cin, Cout, k, s, bo, N, dtype):
+    """A bound of 1500 and more on the blocks: more work items than the device holds, so that an item takes several blocks of 16
+    output channels (with a short list it takes one) and no shape runs as one round of one thread per element."""
+    check_fp32_convolution(H, W, Cin, Cout, k, s, bo, N, dtype, room=1500)
+
+
+@pytest.mark.parametrize("Cin", range(1, 11))
+def test_fp32_convolution_of_few_products(Cin):
+    """One thread per output element: every remainder of the channels by eight, and eight of them and more."""
+    check_fp32_convolution(20, 25, Cin, 1, 3, 1, 8, 1, "f32", room=5000)
+    check_fp32_convolution(20, 25, Cin, 10, 1, 1, 8, 1, "f32" if Cin % 2 else "bf16", room=5000)
 
 
 def test_a_negative_count_is_an_empty_list():
