@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void tile_relu_backward(const uint32_t *__rest
 
 // part[g][c] = sum over the pixels of workgroup g's run of dy[pixel][c]: the active tiles are one run of n * pixels pixels,
 // cut into G = gridDim.x equal runs.  VW = 4: a thread owns 16 bytes (4 words) of a pixel's channels and every
-// (kBiasThreads / vectors per pixel)-th pixel; VW = 1: one word, for channel counts that do not fill 16-byte vectors.
+// (T / vectors per pixel)-th pixel; VW = 1: one word, for channel counts that do not fill 16-byte vectors.
 // cw = 4-byte words per pixel (one f32 channel or two 16-bit ones), cw / VW <= 256.  Every thread adds its pixels in
 // ascending order; the pixel groups are then added through LDS in a fixed order, by slices.
 // MASK: the words of dy are first masked by the forward activation y (relu_mask_word), written to dout at the same
@@ -61,22 +61,27 @@ __global__ __launch_bounds__(256) void tile_relu_backward(const uint32_t *__rest
 // Bound by memory.  With one workgroup of 256 threads per tile (four waves on a CU, two rounds of tiles where there are
 // more than 256) too few loads were in flight; sixteen waves on equal runs: the pass of ReLU
 // mask, bias sum and their total with 440 tiles of 16x16x64 went down by 3 to 5 us in a training step of 136.6 (133.7 and 131.9).
-constexpr int kBiasThreads = 1024;
+// T threads; where a run is a few pixels per thread (bias_few) four waves end sooner than sixteen.
+constexpr int kBiasThreads = 1024, kBiasFew = 256;
+struct BiasLds {
+    float red[kBiasThreads * 9];                  // [T][channels per thread + 1]
+    float slice_sum[kBiasThreads];
+};
 
-template <int DT, int VW, bool MASK>
-__device__ __forceinline__ void bias_partial(const uint32_t *dy, const int32_t *__restrict__ count,
+template <int DT, int VW, bool MASK, int T>
+__device__ __forceinline__ void bias_partial(BiasLds &lds, const uint32_t *dy, const int32_t *__restrict__ count,
                                              int cap, int pixels, int C, int cw, float *__restrict__ part,
                                              const uint32_t *__restrict__ y, uint32_t *dout) {
     constexpr int EPW = DT == SBNET_F32 ? 1 : 2;
     constexpr int NE = VW * EPW;                                  // channels per thread
-    __shared__ float red[kBiasThreads][NE + 1];
-    __shared__ float slice_sum[kBiasThreads];
+    float (*red)[NE + 1] = (float (*)[NE + 1])lds.red;
+    float *slice_sum = lds.slice_sum;
     int n = *count;
     if (n > cap) n = cap;
     const size_t total = (size_t)(n > 0 ? n : 0) * pixels, run = (total + gridDim.x - 1) / gridDim.x;
     const size_t lo = min(run * blockIdx.x, total), hi = min(lo + run, total);
     const int cvn = cw / VW;                                      // threads per pixel
-    const int groups = kBiasThreads / cvn;                        // pixel groups that fit the workgroup
+    const int groups = T / cvn;                                   // pixel groups that fit the workgroup
     const int w = threadIdx.x % cvn, pg = threadIdx.x / cvn;
     float acc[NE];
 #pragma unroll
@@ -136,15 +141,16 @@ __device__ __forceinline__ void bias_partial(const uint32_t *dy, const int32_t *
     __syncthreads();
     // channel c is element c % NE of thread column c / NE; slice k of S adds the groups k, k + S, ..., then the slices are added
     const int channels = cvn * NE;
-    if (channels >= kBiasThreads) {
-        for (int c = threadIdx.x; c < channels; c += kBiasThreads) {
+    if (channels >= T) {
+        for (int c = threadIdx.x; c < channels; c += T) {
             float a = 0.f;
             for (int k = 0; k < groups; ++k) a += red[k * cvn + c / NE][c % NE];
             if (c < C) part[(size_t)blockIdx.x * C + c] = a;
         }
         return;
     }
-    const int S = min(kBiasThreads / channels, groups), c = threadIdx.x % channels, k0 = threadIdx.x / channels;
+    // (both chains short: with few channels there are up to 1024 groups)
+    const int S = min(min(T / channels, groups), 32), c = threadIdx.x % channels, k0 = threadIdx.x / channels;
     if (k0 < S) {
         float a = 0.f;
         for (int k = k0; k < groups; k += S) a += red[k * cvn + c / NE][c % NE];
@@ -158,11 +164,12 @@ __device__ __forceinline__ void bias_partial(const uint32_t *dy, const int32_t *
     }
 }
 
-template <int DT, int VW, bool MASK>
-__global__ __launch_bounds__(kBiasThreads) void tile_bias_partial(const uint32_t *dy, const int32_t *__restrict__ count, int cap,
-                                                                  int pixels, int C, int cw, float *__restrict__ part,
-                                                                  const uint32_t *__restrict__ y, uint32_t *dout) {
-    bias_partial<DT, VW, MASK>(dy, count, cap, pixels, C, cw, part, y, dout);
+template <int DT, int VW, bool MASK, int T>
+__global__ __launch_bounds__(T) void tile_bias_partial(const uint32_t *dy, const int32_t *__restrict__ count, int cap,
+                                                       int pixels, int C, int cw, float *__restrict__ part,
+                                                       const uint32_t *__restrict__ y, uint32_t *dout) {
+    __shared__ BiasLds lds;
+    bias_partial<DT, VW, MASK, T>(lds, dy, count, cap, pixels, C, cw, part, y, dout);
 }
 
 // several stacks in one launch, blockIdx.y picks: their sums are each too short to fill the time of a launch
@@ -171,12 +178,16 @@ struct BiasJobs {
     const uint32_t *dy[kBiasStacks];
     float *part[kBiasStacks], *db[kBiasStacks];
     int pixels[kBiasStacks], C[kBiasStacks];
+    bool few[kBiasStacks];                        // bias_few: the same threads, and so the same bits, as in a launch of its own
 };
 
 template <int DT>
 __global__ __launch_bounds__(kBiasThreads) void tile_bias_partials(BiasJobs q, const int32_t *__restrict__ count, int cap) {
-    const int k = blockIdx.y, C = q.C[k];
-    bias_partial<DT, 4, false>(q.dy[k], count, cap, q.pixels[k], C, C * (DT == SBNET_F32 ? 4 : 2) / 4, q.part[k], nullptr, nullptr);
+    __shared__ BiasLds lds;
+    const int k = blockIdx.y, C = q.C[k], cw = C * (DT == SBNET_F32 ? 4 : 2) / 4;
+    if (!q.few[k]) bias_partial<DT, 4, false, kBiasThreads>(lds, q.dy[k], count, cap, q.pixels[k], C, cw, q.part[k], nullptr, nullptr);
+    else if (threadIdx.x < kBiasFew)              // (whole waves leave)
+        bias_partial<DT, 4, false, kBiasFew>(lds, q.dy[k], count, cap, q.pixels[k], C, cw, q.part[k], nullptr, nullptr);
 }
 
 // db[c] = sum over the workgroups' results part[w][c], w < n: 64 channels per workgroup of 16 waves; wave k takes
@@ -253,6 +264,17 @@ extern "C" size_t sbnet_bias_backward_workspace_bytes(int cap, int C) {
 
 namespace {
 
+// workgroups: the workspace holds a result per tile, and 256 fill the device
+int bias_grid(int cap) { return cap < 256 ? cap : 256; }
+
+// Up to eight pixels per thread of four waves, every tile of the list active.  Sums of C channels on sixteen waves against four:
+// 8 tiles of 4x4x512: 5.7 and 5.2 us, 100 of 8x8x256: 6.3 and 5.7, 64 of 16x16x64: 6.3 and 6.0, 440 of 16x16x64 (twice the line)
+// 7.0 and 7.3, with the mask 10.6 and 12.1.
+bool bias_few(int cap, int pixels, int vectors) {
+    const long long run = ((long long)cap * pixels + bias_grid(cap) - 1) / bias_grid(cap);
+    return run * vectors <= 2048;
+}
+
 // db = per-channel sum over the active tiles of dy (y == nullptr) or of dy masked by y > 0, which is also written to dout
 sbnet_status bias_backward(const char *who, const void *y_tiles, const void *dy_tiles, sbnet_dtype dtype, const int32_t *count,
                            int cap, int pixels, int C, void *dout_tiles, float *db, void *workspace, size_t workspace_bytes,
@@ -272,11 +294,17 @@ sbnet_status bias_backward(const char *who, const void *y_tiles, const void *dy_
     hipStream_t s = (hipStream_t)stream;
     float *part = (float *)workspace;
     if (cap > 0) {
-        const int grid = cap < 256 ? cap : 256;                   // the workspace holds a result per tile, and 256 fill the device
-#define SBNET_BP2(DT, VW, MASK)                                                                                       \
-    hipLaunchKernelGGL((tile_bias_partial<DT, VW, MASK>), dim3(grid), dim3(kBiasThreads), 0, s, (const uint32_t *)dy_tiles, count, \
+        const int grid = bias_grid(cap);
+        const bool few = bias_few(cap, pixels, vec ? cw / 4 : cw);
+#define SBNET_BP3(DT, VW, MASK, T)                                                                                    \
+    hipLaunchKernelGGL((tile_bias_partial<DT, VW, MASK, T>), dim3(grid), dim3(T), 0, s, (const uint32_t *)dy_tiles, count, \
                        cap, pixels, C, cw, part, (const uint32_t *)y_tiles, (uint32_t *)dout_tiles)
-#define SBNET_BP(DT)                                                   \
+#define SBNET_BP2(DT, VW, MASK)                                       \
+    do {                                                              \
+        if (few) SBNET_BP3(DT, VW, MASK, kBiasFew);                   \
+        else SBNET_BP3(DT, VW, MASK, kBiasThreads);                   \
+    } while (0)
+#define SBNET_BP(DT)                                                  \
     do {                                                              \
         if (vec && mask) SBNET_BP2(DT, 4, true);                      \
         else if (vec) SBNET_BP2(DT, 4, false);                        \
@@ -288,10 +316,11 @@ sbnet_status bias_backward(const char *who, const void *y_tiles, const void *dy_
         else SBNET_BP(SBNET_F16);
 #undef SBNET_BP
 #undef SBNET_BP2
+#undef SBNET_BP3
         sbnet_status st = launch_status(who);
         if (st != SBNET_OK) return st;
     }
-    hipLaunchKernelGGL(tile_bias_sum, dim3((C + 63) / 64), dim3(1024), 0, s, part, cap < 256 ? cap : 256, C, db);
+    hipLaunchKernelGGL(tile_bias_sum, dim3((C + 63) / 64), dim3(1024), 0, s, part, bias_grid(cap), C, db);
     return launch_status(who);
 }
 
@@ -324,6 +353,7 @@ sbnet_status sbnet::bias_backward_stacks(const BiasStack *stacks, int n, sbnet_d
                    (long long)t.C * elem_bytes(dtype) / 16 <= 256;
         q.dy[k] = (const uint32_t *)t.dy; q.db[k] = t.db; q.pixels[k] = t.pixels; q.C[k] = t.C;
         q.part[k] = (float *)((char *)workspace + used);
+        q.few[k] = bias_few(cap, t.pixels, (int)((long long)t.C * elem_bytes(dtype) / 16));
         used += sbnet_bias_backward_workspace_bytes(cap, t.C);
         if (t.C > most) most = t.C;
     }
@@ -336,7 +366,7 @@ sbnet_status sbnet::bias_backward_stacks(const BiasStack *stacks, int n, sbnet_d
         return SBNET_OK;
     }
     hipStream_t s = (hipStream_t)stream;
-    const int grid = cap < 256 ? cap : 256;
+    const int grid = bias_grid(cap);
     if (dtype == SBNET_F32) hipLaunchKernelGGL(tile_bias_partials<SBNET_F32>, dim3(grid, n), dim3(kBiasThreads), 0, s, q, count, cap);
     else if (dtype == SBNET_BF16) hipLaunchKernelGGL(tile_bias_partials<SBNET_BF16>, dim3(grid, n), dim3(kBiasThreads), 0, s, q, count, cap);
     else hipLaunchKernelGGL(tile_bias_partials<SBNET_F16>, dim3(grid, n), dim3(kBiasThreads), 0, s, q, count, cap);

@@ -227,6 +227,10 @@ def test_relu_and_bias_backward_on_tiles(B, h, w, C, dtype):
     (2, 40, 40, 2048, "bf16"),     # the most channels a pixel may have: no slices in the last sum
     (2, 9, 9, 1024, "f32"),
     (3, 7, 7, 48, "f16"),          # six thread columns: threads of the last group stay idle
+    (8, 16, 16, 64, "bf16"),       # the longest run on four waves
+    (8, 17, 16, 64, "bf16"),       # ... and the next one, on sixteen
+    (40, 30, 30, 6, "bf16"),       # words instead of vectors, 341 pixel groups
+    (20, 64, 64, 2, "f16"),        # 1024 pixel groups for two channels
 ])
 def test_relu_and_bias_backward_on_runs_of_pixels(B, h, w, C, dtype):
     test_relu_and_bias_backward_on_tiles(B, h, w, C, dtype)
