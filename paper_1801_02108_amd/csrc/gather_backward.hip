@@ -13,7 +13,7 @@
 //   gb_cells       tiles that reach further, and dense lists of small cells: work items are cells of the block grid
 //                  (bstride_h x bstride_w pixels), each looking up the at most (R+1)^2 tiles that can cover it,
 //                  R = ceil((bsize - bstride) / bstride).
-// gb_either holds both and lets the device-side count pick.
+// gb_either holds both and lets the device-side count pick; gb_near and gb_far go by cells only.
 #include "tile_add.h"
 
 namespace sbnet {
@@ -281,13 +281,11 @@ __device__ __forceinline__ void gb_tiles(V *__restrict__ dx, const V *__restrict
     }
 }
 
-// Tiles of small cells (at most 2048 vectors: 64 channels on 16 x 16 blocks) whose list holds at least half of the blocks run
-// cell by cell, where no pixel of a halo is visited twice; all others tile by tile.  bf16, 16 x 16 blocks (old = cells only):
-//   800 x 704 x 64     5 % of the blocks 15.2 -> 9.1 us, 10 % 17.4 -> 10.3, 30 % 25.1 -> 20.5; 50 % cells 29.5, tiles 30.2;
-//                      100 % cells 43.2, tiles 44.2 (8 x 8 blocks: 10 % 20.7 -> 11.9; 50 % 32.3 / 34.1; 100 % 48.2 / 55.0)
-//   400 x 352 x 256    10 % 31.4 -> 9.8, 30 % 39.8 -> 19.3, 100 % 47.4 -> 41.6 (32 x 32 blocks: 10 % 99.8 -> 9.5)
+// Both ways in one launch: cell by cell from `cells_from` active blocks, tile by tile below (gb_cells_from).  Seven workgroups
+// per CU: three vectors per thread in flight on five were slower both ways (800 x 704 x 64, blocks of 16 x 16, 35 % of them
+// by tiles: 22.3 against 20.0 us; 8 x 8 all of them by cells: 49.4 against 47.0).
 template <typename V, int DT, int U>
-__global__ __launch_bounds__(kGbThreads, 5) void gb_either(V *__restrict__ dx, const V *__restrict__ dtiles,
+__global__ __launch_bounds__(kGbThreads, 7) void gb_either(V *__restrict__ dx, const V *__restrict__ dtiles,
                                                         const int32_t *__restrict__ map, const int32_t *__restrict__ indices,
                                                         const int32_t *__restrict__ count, int cells_from, int segs, uint32_t piece,
                                                         FastDiv div_segs, FastDiv div_tr, GbParams p) {
@@ -297,33 +295,56 @@ __global__ __launch_bounds__(kGbThreads, 5) void gb_either(V *__restrict__ dx, c
 }
 
 template <typename V, int DT>
+__global__ __launch_bounds__(kGbThreads) void gb_near(V *__restrict__ dx, const V *__restrict__ dtiles,
+                                                      const int32_t *__restrict__ map, GbParams p) {
+    gb_cells<V, DT, 1, 2>(dx, dtiles, map, p);
+}
+
+template <typename V, int DT>
 __global__ __launch_bounds__(kGbThreads) void gb_far(V *__restrict__ dx, const V *__restrict__ dtiles,
                                                      const int32_t *__restrict__ map, GbParams p) {
     gb_cells<V, DT, kGbMaxR, 2>(dx, dtiles, map, p);
 }
 
+// From how many active blocks on a launch runs cell by cell, for tiles that reach over one following block at most.  By tiles a
+// launch has work for every workgroup whatever the list, but pixels of a halo are visited by each of their tiles; by cells
+// no pixel is visited twice.  bf16, by cells against by tiles:
+//   halos of at least half a cell (8 x 8 blocks): where the active tiles do not fit the caches, 75 MB of them:
+//     800 x 704 x 64   65 % (73 MB) 35.3 and 35.4 us, 100 % 46.6 and 48.3;  800 x 704 x 128   20 % 32.5 and 26.1, 35 % (79 MB) 39.9
+//     and 42.6, 100 % 89.7 and 126;  200 x 176 x 256   100 % 18.6 and 16.4
+//   narrower halos: nearly full lists, where there are cells enough for the device and they are not large:
+//     16 x 16 blocks, 800 x 704 x 64   80 % 38.2 and 36.6, 100 % 43.1 and 44.1;  x 96   80 % 54.9 and 53.7, 100 % 62.5 and 64.8;
+//     x 256   100 % 215 and 204;  400 x 352 x 64   100 % 17.7 and 14.9;  24 x 24, 800 x 704 x 48   80 % 29.0 and 27.6, 100 % 32.6 and 33.7
+static int gb_cells_from(const GbParams &p, long long ncells, int vec_bytes) {
+    const long long nblocks = (long long)p.N * p.g.bcount_h * p.g.bcount_w;
+    if (2ull * p.tile_vecs >= 3ull * p.cell_vecs) return (int)(75000000 / ((long long)p.tile_vecs * vec_bytes)) + 1;
+    return ncells >= 1024 && p.cell_vecs <= 4096 ? (int)((nblocks * 7 + 7) / 8) : 0x7fffffff;
+}
+
 template <typename V, int DT>
 static void launch_gb(void *dx, const void *dtiles, const int32_t *map, const int32_t *indices, const int32_t *count,
                       const GbParams &p, hipStream_t s) {
-    constexpr int U = 3;                                         // vectors per thread in flight
-    const long long ncells = (long long)p.N * p.cells_h * p.cells_w, nblocks = (long long)p.N * p.g.bcount_h * p.g.bcount_w;
+    constexpr int U = 2;                                         // vectors per thread in flight
+    const long long ncells = (long long)p.N * p.cells_h * p.cells_w;
     // pieces of a tile: one step of a workgroup each, a tile that is little more than one step whole
     const int segs = p.tile_vecs <= 4 * kGbThreads ? 1 : (int)((p.tile_vecs + kGbThreads * U - 1) / (kGbThreads * U));
     const uint32_t piece = (p.tile_vecs + segs - 1) / segs;
     const long long items = (long long)p.cap * segs;
-    if (p.R_h <= 1 && p.R_w <= 1 && items < (1LL << 31)) {
-        // a cell that is one step of a workgroup, all of them resident at once, needs no list: one memory round trip less
-        // (83 x 192 x 32 x 2, 8 x 8 blocks, 37 active: 6.0 us against 7.0)
-        const bool tiny = p.cell_vecs <= 2 * kGbThreads && ncells <= 1024;
-        const int cells_from = tiny ? 0 : p.cell_vecs <= 2048 ? (int)((nblocks * 5 + 7) / 8) : 0x7fffffff;
-        const int gt = tiny ? 1 : (int)(items < 4096 ? items : 4096);
-        const int gc = p.cap >= cells_from ? (int)(ncells < 16384 ? ncells : 16384) : 1;
-        hipLaunchKernelGGL((gb_either<V, DT, U>), dim3(gt > gc ? gt : gc), dim3(kGbThreads), 0, s, (V *)dx, (const V *)dtiles, map,
-                           indices, count, cells_from, segs, piece, make_fastdiv(segs), make_fastdiv(p.tile_row_vecs), p);
+    const int grid = (int)(ncells < 16384 ? ncells : 16384);
+    if (p.R_h > 1 || p.R_w > 1) {
+        hipLaunchKernelGGL((gb_far<V, DT>), dim3(grid), dim3(kGbThreads), 0, s, (V *)dx, (const V *)dtiles, map, p);
         return;
     }
-    const int grid = (int)(ncells < 16384 ? ncells : 16384);
-    hipLaunchKernelGGL((gb_far<V, DT>), dim3(grid), dim3(kGbThreads), 0, s, (V *)dx, (const V *)dtiles, map, p);
+    // cells that are one step of a workgroup each, all of them resident at once, need no list: one memory round trip less
+    // (200 x 176 x 64, 8 x 8 blocks, a tenth of them: 6.6 us against 8.0 by tiles)
+    if ((p.cell_vecs <= 2 * kGbThreads && ncells <= 1024) || items >= (1LL << 31)) {
+        hipLaunchKernelGGL((gb_near<V, DT>), dim3(grid), dim3(kGbThreads), 0, s, (V *)dx, (const V *)dtiles, map, p);
+        return;
+    }
+    const int cells_from = gb_cells_from(p, ncells, (int)sizeof(V));
+    const int gt = (int)(items < 4096 ? items : 4096), gc = p.cap >= cells_from ? grid : 1;
+    hipLaunchKernelGGL((gb_either<V, DT, U>), dim3(gt > gc ? gt : gc), dim3(kGbThreads), 0, s, (V *)dx, (const V *)dtiles, map,
+                       indices, count, cells_from, segs, piece, make_fastdiv(segs), make_fastdiv(p.tile_row_vecs), p);
 }
 
 template <int DT>

@@ -334,14 +334,18 @@ def test_gather_backward(H, W, C, k, s, bo, N, dtype):
         assert torch.equal(dx, dx2)
 
 
-# One kernel runs tile by tile (below five eighths of the blocks, or cells of more than 2048 vectors) or cell by cell
+# One kernel runs tile by tile or cell by cell (from seven eighths of the blocks, or from 75 MB of active tiles where the halo is
+# as wide as half a cell), one cell by cell only
 @pytest.mark.parametrize("H,W,C,k,s,bo,N,dtype", [
-    (70, 90, 64, 3, 1, 16, 2, "bf16"),     # 2592 vectors a tile: four pieces, ragged blocks
+    (530, 550, 8, 3, 1, 16, 1, "bf16"),    # 1190 blocks and 256 vectors a cell: both ways
+    (66, 66, 64, 3, 1, 16, 49, "f16"),     # 49 samples of ragged blocks, 2048 vectors a cell, six pieces a tile: both ways
     (50, 66, 260, 3, 1, 8, 1, "f32"),      # 4160 vectors a cell: tile by tile at every share
     (66, 66, 26, 3, 1, 24, 1, "f16"),      # 4-byte words, 13 per pixel
     (61, 53, 128, 3, 2, 8, 1, "f16"),      # strided geometry: tile 17, stride 16
     (64, 48, 64, 5, 1, 16, 1, "bf16"),     # halo 2
-    (130, 130, 64, 3, 1, 8, 2, "bf16"),    # 800 vectors a tile: one piece of two steps
+    (250, 270, 64, 3, 1, 8, 2, "bf16"),    # 800 vectors a tile: one piece of two steps
+    (130, 130, 64, 3, 1, 8, 2, "bf16"),    # ... and few enough cells for the kernel without a list
+    (384, 384, 256, 3, 1, 8, 1, "bf16"),   # 75 MB are 1465 of 2304 tiles
 ])
 def test_gather_backward_by_tiles_and_by_cells(H, W, C, k, s, bo, N, dtype):
     step("gather_backward by tiles / cells %s" % ((H, W, C, k, s, bo, N, dtype),))
