@@ -436,7 +436,7 @@ static void launch_direct(const ConvParams &p, dim3 grid, hipStream_t s) {
 }
 
 template <bool FUSED>
-static sbnet_status run_conv(const char *who, sbnet_dtype dt, ConvParams &p, hipStream_t s) {
+static sbnet_status run_conv(const char *who, sbnet_dtype dt, ConvParams &p, hipStream_t s, ConvForm form = ConvForm::plain) {
     if (p.cap == 0) return SBNET_OK;
     p.oh = (p.th - p.kh) / p.sh + 1;
     p.ow = (p.tw - p.kw) / p.sw + 1;
@@ -448,11 +448,11 @@ static sbnet_status run_conv(const char *who, sbnet_dtype dt, ConvParams &p, hip
 
     if (use_mfma(dt, p.Cin, p.Cout)) p.w32_offset = packed_elems(dt, p.kh, p.kw, p.Cin, p.Cout) / 2 / 8;
     sbnet_status st16 = SBNET_OK;
-    if (p.mask || p.inside) return conv3_try(dt, FUSED, p, s, &st16, who) ? st16 : SBNET_EUNSUPPORTED;
-    if (FUSED && p.own_sample) {
-        // conv3.hip works without the list; the other kernels get one
-        if (!conv16_accepts(dt, FUSED, p) && conv3_try(dt, FUSED, p, s, &st16, who)) return st16;
-        p.own_sample = 0;
+    if (form == ConvForm::mask || form == ConvForm::inside)
+        return conv3_try(dt, FUSED, p, s, &st16, who, form) ? st16 : SBNET_EUNSUPPORTED;
+    if (form == ConvForm::own) {
+        // conv3.hip works without the list; the other kernels, and its shapes on 16-channel chunks, get one
+        if (!conv16_accepts(dt, FUSED, p) && conv3_try(dt, FUSED, p, s, &st16, who, form)) return st16;
         hipLaunchKernelGGL(tile_indices, dim3((p.cap + 255) / 256), dim3(256), 0, s, const_cast<int32_t *>(p.indices), p.cap);
         st16 = launch_status(who);
         if (st16 != SBNET_OK) return st16;
@@ -647,8 +647,8 @@ static sbnet_status backward_data(const char *who, const void *dout_tiles, sbnet
         p.count = count; p.cap = cap;
         p.th = th; p.tw = tw; p.Cin = Cout; p.Cout = Cin;
         p.kh = 1; p.kw = 1; p.sh = 1; p.sw = 1; p.relu = 0;
-        p.mask = mask;
-        return run_conv<false>(who, dtype, p, s);
+        p.indices = (const int32_t *)mask;
+        return run_conv<false>(who, dtype, p, s, mask ? ConvForm::mask : ConvForm::plain);
     }
     if (sh == 1 && sw == 1) {
         // No stride, nothing to spread: the frame of zeros is what the fused kernels read around an image anyway.
@@ -656,7 +656,7 @@ static sbnet_status backward_data(const char *who, const void *dout_tiles, sbnet
         // outside it, and the result "scattered" into a th x tw image that is the tile of din.
         ConvParams p = {};
         p.in = dout_tiles; p.out = din_tiles; p.w = w_packed_t; p.bias = nullptr;
-        p.indices = (const int32_t *)workspace; p.own_sample = 1; p.mask = mask;      // the list: written where a kernel reads it
+        p.indices = (const int32_t *)(mask ? mask : workspace);            // the list: written where a kernel reads it
         p.count = count; p.cap = cap;
         p.th = ph; p.tw = pw; p.Cin = Cout; p.Cout = Cin;
         p.kh = kh; p.kw = kw; p.sh = 1; p.sw = 1; p.relu = 0; p.add = 0;
@@ -665,7 +665,7 @@ static sbnet_status backward_data(const char *who, const void *dout_tiles, sbnet
         p.g_out.bsize_h = th; p.g_out.bsize_w = tw; p.g_out.bstride_h = th; p.g_out.bstride_w = tw;
         p.g_out.boffset_h = p.g_out.boffset_w = 0; p.g_out.bcount_h = p.g_out.bcount_w = 1;
         p.H = oh; p.W = ow; p.Ho = th; p.Wo = tw;
-        return run_conv<true>(who, dtype, p, s);
+        return run_conv<true>(who, dtype, p, s, mask ? ConvForm::mask : ConvForm::own);
     }
     if (mask) return SBNET_EUNSUPPORTED;
     const int vb = row_bytes % 16 == 0 ? 16 : row_bytes % 8 == 0 ? 8 : row_bytes % 4 == 0 ? 4 : 2;
@@ -720,9 +720,9 @@ sbnet_status sbnet::pointwise_inside(const char *who, const void *tiles_in, sbne
     p.in = tiles_in; p.out = tiles_out; p.w = w_packed; p.bias = bias;
     p.indices = indices; p.count = count; p.cap = cap;
     p.th = g_in->bsize_h; p.tw = g_in->bsize_w; p.Cin = Cin; p.Cout = Cout;
-    p.kh = 1; p.kw = 1; p.sh = 1; p.sw = 1; p.relu = 1; p.inside = 1;
+    p.kh = 1; p.kw = 1; p.sh = 1; p.sw = 1; p.relu = 1;
     p.g_in = *g_in; p.H = H; p.W = W;
-    return run_conv<false>(who, dtype, p, (hipStream_t)stream);
+    return run_conv<false>(who, dtype, p, (hipStream_t)stream, ConvForm::inside);
 }
 
 extern "C" sbnet_status sbnet_sparse_conv(const void *x, sbnet_dtype dtype, int N, int H, int W, int Cin,

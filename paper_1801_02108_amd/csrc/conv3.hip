@@ -88,15 +88,16 @@ struct Chunk3 {
 // one wave per SIMD the matrix core stood idle through both: per chunk the kernel took about the SUM of its matrix,
 // LDS and load time.  With the roles in different waves of the same SIMD they overlap.  Both roles walk the same
 // chunk sequence and meet at the same barrier per chunk.
-// EPI: kEpiMask zeroes results where p.mask is not positive, kEpiInside at pixels outside the image (both in the gradient and
-// the training forward of the residual unit, where a pass of their own read and wrote the whole stack again).
-constexpr int kEpiNone = 0, kEpiMask = 1, kEpiInside = 2;
+// EPI: the ConvForm.  kEpiMask zeroes results where the mask is not positive, kEpiInside at pixels outside the image (both in the
+// gradient and the training forward of the residual unit, where a pass of their own read and wrote the whole stack again).
+constexpr int kEpiNone = 0, kEpiOwn = 1, kEpiMask = 2, kEpiInside = 3;
 
 template <int DT, bool FUSED, bool ADD, int CC, int WP, int CBW, int PBW, int NVI, int KH = 3, bool SPEC = false, int EPI = kEpiNone>
 __device__ __forceinline__ void conv3_body(const ConvParams &p, const Plan3 &q) {
     static_assert(FUSED || !ADD, "adding into the output is part of the fused form");
     static_assert(EPI == kEpiNone || !ADD, "the sum is not masked");
-    constexpr bool LIST = FUSED || EPI == kEpiInside;        // the index list is read
+    constexpr bool OWN = FUSED && (EPI == kEpiOwn || EPI == kEpiMask);
+    constexpr bool LIST = (FUSED && !OWN) || EPI == kEpiInside;      // the index list is read
     // Register sets for chunks in flight.  Two (requests two chunks further ahead) were measured for the small
     // workgroup tiles and gained nothing: the compiler's wait before a vector's LDS write allows only one set's
     // worth of younger loads, and those tiles are bound by the issue of their staging instructions anyway.
@@ -167,10 +168,7 @@ __device__ __forceinline__ void conv3_body(const ConvParams &p, const Plan3 &q) 
             r.by = __builtin_amdgcn_readfirstlane(c.by);
             r.bx = __builtin_amdgcn_readfirstlane(c.bx);
         }
-        if (FUSED && p.own_sample) {                 // (whatever the list holds)
-            r.n = (int)c.b;
-            r.by = r.bx = 0;
-        }
+        if (OWN) r.n = (int)c.b;
         return r;
     };
     const int in_w = FUSED ? p.W : p.tw;                          // pixels per row of the addressed array
@@ -470,7 +468,7 @@ __device__ __forceinline__ void conv3_body(const ConvParams &p, const Plan3 &q) 
                 if (EPI == kEpiMask) {
                     const long long at = (const char *)obase - (const char *)p.out;
                     const __amdgpu_buffer_rsrc_t mrs = __builtin_amdgcn_make_buffer_rsrc(
-                        (void *)((const char *)p.mask + at), 0, (int)obytes, (int)kBufWord3);
+                        (void *)((const char *)p.indices + at), 0, (int)obytes, (int)kBufWord3);
 #pragma unroll
                     for (int pb = 0; pb < PBW; ++pb)
 #pragma unroll
@@ -619,16 +617,16 @@ void conv3_pair_kernel(ConvParams p, Plan3 qb, Plan3 qs) {
 // against wide: 593 blocks of 12x12, 48 -> 80: 28.1 and 22.5 us; 740 of 14x14, 128 -> 96: 51.5 and 43.5; 550 of 16x16,
 // 48 -> 96: 26.4 and 22.1, 96 -> 96: 35.5 and 34.6.  Not taken: up to 32 input channels, one narrow chunk (24 -> 96: 17.3 and
 // 18.0), and groups of 128, which were mixed (550 of 16x16, 48 -> 128: 26.6 and 27.4).
-template <int DT, bool FUSED, bool ADD, int NVIS>
+template <int DT, bool FUSED, bool ADD, int NVIS, int EPI = kEpiNone>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void conv3_wide96_kernel(ConvParams p, Plan3 qw, Plan3 qb, Plan3 qs) {
     const uint32_t nact = (uint32_t)max(min(*p.count, p.cap), 0);
     const uint32_t rw = (nact * (uint32_t)(qw.mpasses * qw.ngroups) + 255u) >> 8, rb = (nact * (uint32_t)(qb.mpasses * qb.ngroups) + 255u) >> 8,
                    rs = (nact * (uint32_t)(qs.mpasses * qs.ngroups) + 255u) >> 8;
     const unsigned long long small8 = (unsigned long long)rs * (uint32_t)p.small_cost8, big8 = (unsigned long long)rb * 8u;
-    if ((unsigned long long)rw * 9u <= (big8 <= small8 ? big8 : small8)) conv3_body<DT, FUSED, ADD, 16, 4, 3, 2, 5, 3, true>(p, qw);
-    else if (big8 <= small8) conv3_body<DT, FUSED, ADD, 32, 4, 2, 2, 6, 3, true>(p, qb);
-    else conv3_body<DT, FUSED, ADD, 32, 4, 2, 1, NVIS, 3, true>(p, qs);
+    if ((unsigned long long)rw * 9u <= (big8 <= small8 ? big8 : small8)) conv3_body<DT, FUSED, ADD, 16, 4, 3, 2, 5, 3, true, EPI>(p, qw);
+    else if (big8 <= small8) conv3_body<DT, FUSED, ADD, 32, 4, 2, 2, 6, 3, true, EPI>(p, qb);
+    else conv3_body<DT, FUSED, ADD, 32, 4, 2, 1, NVIS, 3, true, EPI>(p, qs);
 }
 
 // 128-pixel items with groups of 96 / 128 output channels or of 64 in one launch, for strided tiles whose 256-pixel shape
@@ -725,7 +723,7 @@ static Shape3 plan3(const ConvParams &p, int pp, int nb = 2, bool only16 = false
     return sh;
 }
 
-// (with EPI: pointwise, or for kEpiMask the fused 3x3 form on 32-channel chunks)
+// (with EPI: pointwise, or for kEpiOwn and kEpiMask the fused 3x3 form on 32-channel chunks)
 template <int DT, bool FUSED, bool ADD, int WP, int CBW, int PBW, int EPI>
 static void launch3_cc(const ConvParams &p, const Shape3 &sh, int grid, hipStream_t s) {
 #define SBNET_L3(CC, NVI)                                                                                      \
@@ -771,23 +769,24 @@ static void launch3_shape(const ConvParams &p, const Shape3 &sh, int grid, hipSt
 }
 
 template <int DT>
-static void launch3_dt(bool fused, const ConvParams &p, const Shape3 &sh, int grid, hipStream_t s) {
-    if (p.mask && fused) launch3_shape<DT, true, false, kEpiMask>(p, sh, grid, s);
-    else if (p.mask) launch3_shape<DT, false, false, kEpiMask>(p, sh, grid, s);
-    else if (p.inside) launch3_shape<DT, false, false, kEpiInside>(p, sh, grid, s);
+static void launch3_dt(bool fused, ConvForm form, const ConvParams &p, const Shape3 &sh, int grid, hipStream_t s) {
+    if (form == ConvForm::own) launch3_shape<DT, true, false, kEpiOwn>(p, sh, grid, s);
+    else if (form == ConvForm::mask && fused) launch3_shape<DT, true, false, kEpiMask>(p, sh, grid, s);
+    else if (form == ConvForm::mask) launch3_shape<DT, false, false, kEpiMask>(p, sh, grid, s);
+    else if (form == ConvForm::inside) launch3_shape<DT, false, false, kEpiInside>(p, sh, grid, s);
     else if (fused && p.add) launch3_shape<DT, true, true>(p, sh, grid, s);
     else if (fused) launch3_shape<DT, true, false>(p, sh, grid, s);
     else launch3_shape<DT, false, false>(p, sh, grid, s);
 }
 
-static void launch3(sbnet_dtype dt, bool fused, const ConvParams &p, const Shape3 &sh, hipStream_t s) {
+static void launch3(sbnet_dtype dt, bool fused, ConvForm form, const ConvParams &p, const Shape3 &sh, hipStream_t s) {
     long long items = (long long)p.cap * sh.q.mpasses * sh.q.ngroups;
     long long g = (items + 7) / 8 * 8;
     const long long most = p.kh == 1 && 2 * sh.lds_bytes <= (size_t)kLds3 ? 512 : 256;   // persistent workgroups: one per CU, two for pointwise
     if (g > most) g = most;
     const int grid = (int)g;
-    if (dt == SBNET_BF16) launch3_dt<SBNET_BF16>(fused, p, sh, grid, s);
-    else launch3_dt<SBNET_F16>(fused, p, sh, grid, s);
+    if (dt == SBNET_BF16) launch3_dt<SBNET_BF16>(fused, form, p, sh, grid, s);
+    else launch3_dt<SBNET_F16>(fused, form, p, sh, grid, s);
 }
 
 template <int DT, bool FUSED, bool ADD, int CCB, int NVIB, int PBWB = 2, int PBWS = 1, int EPI = kEpiNone>
@@ -825,23 +824,27 @@ static void launch3_pair_big(const ConvParams &p, const Shape3 &big, const Shape
     else launch3_pair_small<DT, FUSED, ADD, 16, 9>(p, big, small, grid, lds, s);
 }
 
-template <int DT>
-static void launch3_pair_mask(const ConvParams &p, const Shape3 &big, const Shape3 &small, int grid, size_t lds, hipStream_t s) {
-    if (big.pp == 384) launch3_pair_small<DT, true, false, 32, 7, 3, 2, kEpiMask>(p, big, small, grid, lds, s);
-    else if (big.nvi == 3) launch3_pair_small<DT, true, false, 32, 3, 2, 1, kEpiMask>(p, big, small, grid, lds, s);
-    else launch3_pair_small<DT, true, false, 32, 6, 2, 1, kEpiMask>(p, big, small, grid, lds, s);
+// kEpiOwn, kEpiMask: 32-channel chunks
+template <int DT, int EPI>
+static void launch3_pair_epi(const ConvParams &p, const Shape3 &big, const Shape3 &small, int grid, size_t lds, hipStream_t s) {
+    if (big.pp == 384) launch3_pair_small<DT, true, false, 32, 7, 3, 2, EPI>(p, big, small, grid, lds, s);
+    else if (big.nvi == 3) launch3_pair_small<DT, true, false, 32, 3, 2, 1, EPI>(p, big, small, grid, lds, s);
+    else launch3_pair_small<DT, true, false, 32, 6, 2, 1, EPI>(p, big, small, grid, lds, s);
 }
 
 // both tile shapes in one launch
-static void launch3_pair(sbnet_dtype dt, bool fused, const ConvParams &p, const Shape3 &big, const Shape3 &small, hipStream_t s) {
+static void launch3_pair(sbnet_dtype dt, bool fused, ConvForm form, const ConvParams &p, const Shape3 &big, const Shape3 &small, hipStream_t s) {
     const long long items = (long long)p.cap * small.q.mpasses * small.q.ngroups;     // the smaller tile has more items
     long long g = (items + 7) / 8 * 8;
     if (g > 256) g = 256;                             // one persistent workgroup per CU
     const int grid = (int)g;
     const size_t lds = big.lds_bytes > small.lds_bytes ? big.lds_bytes : small.lds_bytes;
-    if (p.mask) {
-        if (dt == SBNET_BF16) launch3_pair_mask<SBNET_BF16>(p, big, small, grid, lds, s);
-        else launch3_pair_mask<SBNET_F16>(p, big, small, grid, lds, s);
+    if (form != ConvForm::plain) {
+        const bool mask = form == ConvForm::mask;
+        if (dt == SBNET_BF16 && mask) launch3_pair_epi<SBNET_BF16, kEpiMask>(p, big, small, grid, lds, s);
+        else if (dt == SBNET_BF16) launch3_pair_epi<SBNET_BF16, kEpiOwn>(p, big, small, grid, lds, s);
+        else if (mask) launch3_pair_epi<SBNET_F16, kEpiMask>(p, big, small, grid, lds, s);
+        else launch3_pair_epi<SBNET_F16, kEpiOwn>(p, big, small, grid, lds, s);
         return;
     }
     if (dt == SBNET_BF16) {
@@ -901,7 +904,7 @@ static void launch3_wide(bool fused, const ConvParams &p, const Shape3 &big, con
 
 // stride 1: groups of 96 beside the two shapes with groups of 64
 template <int DT>
-static void launch3_wide96(bool fused, const ConvParams &p, const Shape3 &wide, const Shape3 &big, const Shape3 &small, hipStream_t s) {
+static void launch3_wide96(bool fused, ConvForm form, const ConvParams &p, const Shape3 &wide, const Shape3 &big, const Shape3 &small, hipStream_t s) {
     const long long items = (long long)p.cap * small.q.mpasses * small.q.ngroups;     // the most of the three
     long long g = (items + 7) / 8 * 8;
     if (g > 256) g = 256;
@@ -909,25 +912,27 @@ static void launch3_wide96(bool fused, const ConvParams &p, const Shape3 &wide, 
     if (small.lds_bytes > lds) lds = small.lds_bytes;
     ConvParams pt = p;
     pt.small_cost8 = tuning().conv3_small_item_cost_eighths;
-#define SBNET_L3N(FU, AD, NVIS)                                                                                          \
+#define SBNET_L3N(FU, AD, NVIS, EPI)                                                                                     \
     do {                                                                                                                 \
-        auto kern = conv3_wide96_kernel<DT, FU, AD, NVIS>;                                                               \
+        auto kern = conv3_wide96_kernel<DT, FU, AD, NVIS, EPI>;                                                               \
         (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);             \
         hipLaunchKernelGGL(kern, dim3((int)g), dim3(512), lds, s, pt, wide.q, big.q, small.q);                           \
     } while (0)
-#define SBNET_L3M(FU, AD)                                   \
+#define SBNET_L3M(FU, AD, EPI)                              \
     do {                                                    \
-        if (small.nvi == 3) SBNET_L3N(FU, AD, 3);           \
-        else SBNET_L3N(FU, AD, 6);                          \
+        if (small.nvi == 3) SBNET_L3N(FU, AD, 3, EPI);      \
+        else SBNET_L3N(FU, AD, 6, EPI);                     \
     } while (0)
-    if (fused && p.add) SBNET_L3M(true, true);
-    else if (fused) SBNET_L3M(true, false);
-    else SBNET_L3M(false, false);
+    if (form == ConvForm::own) SBNET_L3M(true, false, kEpiOwn);
+    else if (fused && p.add) SBNET_L3M(true, true, kEpiNone);
+    else if (fused) SBNET_L3M(true, false, kEpiNone);
+    else SBNET_L3M(false, false, kEpiNone);
 #undef SBNET_L3M
 #undef SBNET_L3N
 }
 
-bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p0, hipStream_t s, sbnet_status *st, const char *who) {
+bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p0, hipStream_t s, sbnet_status *st, const char *who, ConvForm form) {
+    const bool mask = form == ConvForm::mask, own = form == ConvForm::own;
     if (dt != SBNET_BF16 && dt != SBNET_F16) return false;
     if (p0.kh != p0.kw || (p0.kh != 3 && p0.kh != 1)) return false;
     if (p0.Cin % 8 != 0 || p0.Cout % 8 != 0) return false;
@@ -958,7 +963,7 @@ bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p0, hipStream_t s, 
         // -> 192: its rows fit 32-channel chunks with 64-channel groups, twice the matrix steps per barrier; where they are
         // not, see conv3_wide96_kernel), 96 -> 192 at stride 2 is the same with either.
         const int nbw = p.Cout % 128 == 0 ? 4 : (p.Cout % 96 == 0 && p.Cout % 64 != 0 ? 3 : 2);
-        if (nbw > 2 && M <= 256 && p.sh > 1 && !p.mask) {
+        if (nbw > 2 && M <= 256 && p.sh > 1 && form == ConvForm::plain) {
             Shape3 wb, ws = plan3(p, 128, nbw);
             wb.ok = false;
             if (M > 128) wb = plan3(p, 256, nbw);
@@ -989,21 +994,21 @@ bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p0, hipStream_t s, 
     if ((long long)p.cap * most_passes * ((p.Cout + 63) / 64) >= (1LL << 31)) return false;
     // with at most 256 items of the smaller tile whatever the count, the rule in the kernel never picks the larger one
     if (big.ok && small.ok && (long long)p.cap * small.q.mpasses * small.q.ngroups <= 256) big.ok = false;
-    if (p.mask && p.kh == 3 && (!fused || p.add || (big.ok && big.cc != 32) || (small.ok && small.cc != 32))) return false;
-    if (p.inside && (fused || p.kh != 1)) return false;
-    if (big.ok && small.ok && !p.mask && p.Cin > 32 && p.kh == 3 && p.sh == 1 && p.sw == 1 && M <= 256 && big.cc == 32 && big.nvi == 6 && small.cc == 32 &&
+    if ((own || (mask && p.kh == 3)) && (!fused || p.add || p.kh != 3 || (big.ok && big.cc != 32) || (small.ok && small.cc != 32))) return false;
+    if (form == ConvForm::inside && (fused || p.kh != 1)) return false;
+    if (big.ok && small.ok && !mask && p.Cin > 32 && p.kh == 3 && p.sh == 1 && p.sw == 1 && M <= 256 && big.cc == 32 && big.nvi == 6 && small.cc == 32 &&
         (p.Cout + 95) / 96 * 3 < (p.Cout + 63) / 64 * 2) {
         const Shape3 wide = plan3(p, 256, 3);                              // see conv3_wide96_kernel
         if (wide.ok) {
-            if (dt == SBNET_BF16) launch3_wide96<SBNET_BF16>(fused, p, wide, big, small, s);
-            else launch3_wide96<SBNET_F16>(fused, p, wide, big, small, s);
+            if (dt == SBNET_BF16) launch3_wide96<SBNET_BF16>(fused, form, p, wide, big, small, s);
+            else launch3_wide96<SBNET_F16>(fused, form, p, wide, big, small, s);
             *st = launch_status(who);
             return true;
         }
     }
-    if (big.ok && small.ok) launch3_pair(dt, fused, p, big, small, s);     // the device-side count picks the shape
-    else if (big.ok) launch3(dt, fused, p, big, s);
-    else launch3(dt, fused, p, small, s);
+    if (big.ok && small.ok) launch3_pair(dt, fused, form, p, big, small, s);     // the device-side count picks the shape
+    else if (big.ok) launch3(dt, fused, form, p, big, s);
+    else launch3(dt, fused, form, p, small, s);
     *st = launch_status(who);
     return true;
 }

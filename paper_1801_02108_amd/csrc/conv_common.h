@@ -32,7 +32,7 @@ struct ConvParams {
     const void *w;           // packed weights
     size_t w32_offset;       // MFMA path: start (in 16-byte units) of the 32x32x16 operand copy inside w
     const float *bias;       // [Cout] or null
-    const int32_t *indices;  // fused form only
+    const int32_t *indices;  // fused form, and ConvForm::inside; ConvForm::mask: the mask in its place
     const int32_t *count;
     int cap;
     int th, tw, oh, ow;
@@ -48,10 +48,6 @@ struct ConvParams {
     int32_t *indices_out;    // [cap][3]
     int32_t *count_out;      // [1]
     FastDiv div_bps, div_bw, div_grid;       // blocks per sample, blocks per block row, workgroups along x
-    int own_sample;          // fused form: block b is the one block of sample b; indices is not read for its values
-    // conv3.hip, what happens to a result before it is stored:
-    const void *mask;        // laid out as out: results are zeroed where this is not positive (or null)
-    int inside;              // unfused form, with indices, g_in, H, W: zeroed at pixels outside the image
     int small_cost8;         // conv3.hip, two tile shapes in one launch: cost of the smaller item in eighths of the larger
     int wide_min_items;      // conv3.hip, 64-channel or wider output groups in one launch: wide from this many work items
     // MFMA path work decomposition
@@ -162,7 +158,16 @@ bool conv_f32_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t s
 __host__ __device__ __forceinline__ size_t fma_weight_index(int tap, int c, int o, int taps, int C8) {
     return (((size_t)(o >> 4) * C8 + (c >> 3)) * taps + tap) * 128 + (((c & 7) >> 1) * 16 + (o & 15)) * 2 + (c & 1);
 }
+// What the gradients of a tile convolution and the training forward of the residual unit ask of conv3.hip, each in kernels of its
+// own (a flag looked at per chunk cost the others up to 2 %).
+enum class ConvForm {
+    plain,
+    own,        // fused: block b is the one block of sample b; no list is read
+    mask,       // fused (then as `own`) or not: results are zeroed where p.indices, laid out as out, is not positive
+    inside      // not fused, with indices, g_in, H, W: results are zeroed at pixels outside the image
+};
 // conv3.hip: the same contract for the LDS-tiled 3x3 kernel (any stride, tile size and channel counts that are multiples of 8).
-bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t s, sbnet_status *st, const char *who);
+bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t s, sbnet_status *st, const char *who,
+               ConvForm form = ConvForm::plain);
 
 }  // namespace sbnet
