@@ -449,7 +449,7 @@ static sbnet_status run_conv(const char *who, sbnet_dtype dt, ConvParams &p, hip
     if (use_mfma(dt, p.Cin, p.Cout)) p.w32_offset = packed_elems(dt, p.kh, p.kw, p.Cin, p.Cout) / 2 / 8;
     sbnet_status st16 = SBNET_OK;
     if (form == ConvForm::mask || form == ConvForm::inside)
-        return conv3_try(dt, FUSED, p, s, &st16, who, form) ? st16 : SBNET_EUNSUPPORTED;
+        return !conv16_accepts(dt, FUSED, p) && conv3_try(dt, FUSED, p, s, &st16, who, form) ? st16 : SBNET_EUNSUPPORTED;
     if (form == ConvForm::own) {
         // conv3.hip works without the list; the other kernels, and its shapes on 16-channel chunks, get one
         if (!conv16_accepts(dt, FUSED, p) && conv3_try(dt, FUSED, p, s, &st16, who, form)) return st16;

@@ -996,10 +996,11 @@ bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p0, hipStream_t s, 
     if (big.ok && small.ok && (long long)p.cap * small.q.mpasses * small.q.ngroups <= 256) big.ok = false;
     if ((own || (mask && p.kh == 3)) && (!fused || p.add || p.kh != 3 || (big.ok && big.cc != 32) || (small.ok && small.cc != 32))) return false;
     if (form == ConvForm::inside && (fused || p.kh != 1)) return false;
-    if (big.ok && small.ok && !mask && p.Cin > 32 && p.kh == 3 && p.sh == 1 && p.sw == 1 && M <= 256 && big.cc == 32 && big.nvi == 6 && small.cc == 32 &&
+    if (big.ok && small.ok && p.Cin > 32 && p.kh == 3 && p.sh == 1 && p.sw == 1 && M <= 256 && big.cc == 32 && big.nvi == 6 && small.cc == 32 &&
         (p.Cout + 95) / 96 * 3 < (p.Cout + 63) / 64 * 2) {
         const Shape3 wide = plan3(p, 256, 3);                              // see conv3_wide96_kernel
         if (wide.ok) {
+            if (mask) return false;                                        // (16-channel chunks: another order of summation)
             if (dt == SBNET_BF16) launch3_wide96<SBNET_BF16>(fused, form, p, wide, big, small, s);
             else launch3_wide96<SBNET_F16>(fused, form, p, wide, big, small, s);
             *st = launch_status(who);

@@ -167,6 +167,7 @@ enum class ConvForm {
     inside      // not fused, with indices, g_in, H, W: results are zeroed at pixels outside the image
 };
 // conv3.hip: the same contract for the LDS-tiled 3x3 kernel (any stride, tile size and channel counts that are multiples of 8).
+// `mask` is refused where the plain form runs in another order of summation than the kernels with a mask have.
 bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t s, sbnet_status *st, const char *who,
                ConvForm form = ConvForm::plain);
 

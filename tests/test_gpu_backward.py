@@ -309,6 +309,9 @@ def test_residual_unit_backward_composed_from_single_calls(C, Cm, dens):
     (300, 301, 16, 64, 32, "f16"),     # 18x18 tiles, the 384-pixel items
     (40, 301, 16, 64, 32, "bf16"),     # ... and the 256-pixel ones beside them
     (90, 100, 24, 48, 40, "bf16"),     # 26x26: 256 pixels beside 128, channels that end inside a group
+    (60, 70, 14, 64, 32, "bf16"),      # 16x16 tiles: the 3x3 data gradient is conv16.hip's, with a pass for the mask
+    (20, 24, 30, 48, 64, "f16"),       # 32x32
+    (150, 160, 12, 96, 80, "bf16"),    # groups of 96 channels for the single call, likewise
     (3, 4, 8, 24, 8, "f32"),           # no matrix kernel: passes of their own
     (3, 4, 8, 12, 6, "bf16"),
     (0, 3, 8, 64, 16, "bf16"),
