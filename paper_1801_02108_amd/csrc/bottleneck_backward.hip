@@ -10,8 +10,7 @@
 // Every step is one of the library's tile calls; the workspace holds dt2, dt1 and the largest scratch any of them asks for.
 // The stacks are what bounds it, so the small steps ride on the large ones where the kernels can: the ReLU masks on the
 // stores of the data gradients, the zeroing outside the image on those of the first convolution (conv3.hip; elsewhere they
-// are passes of their own), and the three bias sums, each too short for its two launches, are one pair of launches at the
-// end.  Training step of a 256/64 unit, 165 blocks of 16x16: 258.8 -> 244.2 us.
+// are passes of their own), and the three bias sums, each too short for its two launches, are one pair of launches.  Training step of a 256/64 unit, 165 blocks of 16x16: 258.8 -> 244.2 us.
 // The matching forward pass that keeps t1 and t2 is the same three convolutions as single calls.
 #include "common.h"
 
@@ -72,7 +71,7 @@ extern "C" sbnet_status sbnet_bottleneck_backward_on_tiles(const void *tiles_in,
     void *dt2 = ws + l.dt2_off, *dt1 = ws + l.dt1_off, *scratch = ws + l.scratch_off;
     const size_t sb = l.scratch_bytes;
     sbnet_status st;
-    // data gradient, zero where y is not positive, on the list of stacks to be summed for the bias gradients (at the end, together)
+    // data gradient, zero where y is not positive, on the list of stacks to be summed for the bias gradients (later, together)
     BiasStack sums[3] = {{dt3, oh * ow, C, db3}};
     int nsums = 1;
     auto masked_data = [&](const void *g, int h, int w, int ci, const void *wt, int k, int co, const void *y, void *din, float *db) {
@@ -96,8 +95,9 @@ extern "C" sbnet_status sbnet_bottleneck_backward_on_tiles(const void *tiles_in,
     SBNET_STEP(masked_data(dt2, th, tw, Cm, w2_t, 3, Cm, t1, dt1, db1));
     // first convolution (1x1, C -> Cm)
     SBNET_STEP(sbnet_conv_on_tiles_backward_weights(tiles_in, dt1, dtype, count, cap, th, tw, C, 1, 1, 1, 1, Cm, dw1, scratch, sb, stream));
-    SBNET_STEP(sbnet_conv_on_tiles_backward_data(dt1, dtype, count, cap, th, tw, C, w1_t, 1, 1, 1, 1, Cm, dtiles_in, scratch, sb, stream));
+    // (the sums before the last step: dtiles_in may lie where dt3 does)
     SBNET_STEP(bias_backward_stacks(sums, nsums, dtype, count, cap, scratch, sb, stream));
+    SBNET_STEP(sbnet_conv_on_tiles_backward_data(dt1, dtype, count, cap, th, tw, C, w1_t, 1, 1, 1, 1, Cm, dtiles_in, scratch, sb, stream));
 #undef SBNET_STEP
     return SBNET_OK;
 }

@@ -353,6 +353,31 @@ def test_residual_unit_in_one_call_equals_single_calls(n, cap, bo, C, Cm, dtype)
         assert torch.equal(one[k], want[k]), k
 
 
+def test_residual_unit_backward_writes_over_its_incoming_gradient():
+    """dL/dx on the input tiles in the memory that dL/dt3 lay in: every step that reads the one runs before the step that
+    writes the other."""
+    step("residual unit backward, dx over dt3")
+    import ctypes
+    r = gen.rng_for(34)
+    cap, bo, C, Cm = 40, 8, 64, 32
+    th = bo + 2
+    dev = lambda *shape: to_dev(gen.activations(r, shape, "bf16"), "bf16")   # noqa: E731
+    x, t1, t2, dt3 = dev(cap, th, th, C), dev(cap, th, th, Cm), dev(cap, bo, bo, Cm), dev(cap, bo, bo, C)
+    q = [sb.pack_weights_transposed(to_dev(gen.conv_weights(r, k, k, a, b, "bf16"), "bf16")) for k, a, b in ((1, C, Cm), (3, Cm, Cm), (1, Cm, C))]
+    cnt = torch.tensor([cap], dtype=torch.int32).cuda()
+    want = sb.bottleneck_backward_on_tiles(x, t1, t2, dt3, cnt, q)
+    got = [torch.empty_like(w) for w in want]
+    got[0].view(-1)[:dt3.numel()] = dt3.view(-1)
+    need = sb.lib().sbnet_bottleneck_backward_workspace_bytes(sb.BF16, cap, th, th, C, Cm)
+    ws = torch.empty((need,), dtype=torch.uint8, device="cuda")
+    p = lambda t: ctypes.c_void_p(t.data_ptr())   # noqa: E731
+    assert sb.lib().sbnet_bottleneck_backward_on_tiles(
+        p(x), p(t1), p(t2), p(got[0]), sb.BF16, p(cnt), cap, th, th, C, Cm, *[p(w.buf) for w in q], *[p(g) for g in got], p(ws), need,
+        ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == sb.OK
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+
+
 def test_weight_gradient_of_a_stack_beyond_two_gib():
     """13 500 tiles of 18 x 18 x 256 (the residual unit's first convolution at the batched configurations' scale) are
     2.24 GB: byte offsets into the stack do not fit 31 bits, and the kernel addresses every tile through a descriptor
