@@ -493,24 +493,20 @@ def test_normalisation_of_blocks_far_larger_than_the_image():
     assert ((y.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4).all()
 
 
-def test_bn_stats_with_outliers_where_a_row_of_partial_sums_begins():
-    """20 736 blocks of 8x8 in 1024 rows; the first pixel of every row's first block is 1000 standard deviations off.  It is
-    the reference of one pixel group in 32: a 32nd of the squares are 10^6 where the variance is 770, forty times the
-    whole, and their sum of up to 42 terms is rounded at random: 40 * 2^-24 * sqrt(42) = 1.6e-5 of a row, less in the
-    average of 1024 rows (as sampled: 1e-5 holds)."""
-    step("bn_stats, outliers")
+def test_bn_stats_with_an_outlier_where_the_sums_begin():
+    """Two blocks of 96x96 in two rows of partial sums; the first pixel is 1000 standard deviations off.  It is the reference of
+    one pixel group of 32 in one row: a 64th of the squares are 10^6, the variance is 55.  Their 144 terms each are added
+    with an error of at most 2^-24 of the sum: 10^6 / 64 * 144 / 2 * 2^-24 / 55 = 1.2e-3 if all of it fell on one side (of the whole
+    data about that pixel, 64 times as much)."""
+    step("bn_stats, outlier")
     r = gen.rng_for(31)
-    H = W = 1152
-    _, g, _, _ = sb.geometry(H, W, 3, 1, 8)
-    x = r.standard_normal((1, H, W, 4)).astype(np.float32)
-    idx = np.stack(np.meshgrid([0], np.arange(144), np.arange(144), indexing="ij"), -1).reshape(-1, 3).astype(np.int32)
-    for _, by, bx in idx[:1024]:
-        x[0, 8 * by, 8 * bx] = 1000.0
-    d_idx, d_cnt = dev_indices(idx, len(idx))
-    mean, var = sb.sparse_bn_stats(torch.from_numpy(x).cuda(), d_idx, d_cnt, g)
-    rv = x.astype(np.float64).var(axis=(0, 1, 2))
-    err = np.abs(var.cpu().numpy() - rv).max() / rv.min()
-    assert err < 1e-5, err
+    _, g, _, _ = sb.geometry(96, 192, 3, 1, 96)
+    x = r.standard_normal((1, 96, 192, 32)).astype(np.float32)
+    x[0, 0, 0] = 1000.0
+    d_idx, d_cnt = dev_indices(np.array([(0, 0, 0), (0, 0, 1)], np.int32))
+    _, var = sb.sparse_bn_stats(torch.from_numpy(x).cuda(), d_idx, d_cnt, g)
+    err = (var.cpu().numpy() / x.astype(np.float64).var(axis=(0, 1, 2)) - 1.0)
+    assert np.abs(err).max() < 1.2e-3, err
 
 
 # --------------------------------------------------------------------------- fp32 convolution
