@@ -40,7 +40,6 @@ struct F32Params {
     int kh, kw, sh, sw, oh, ow, tw;
     int mpasses, ngroups, nchunks;
     int C8, cc8, S;                       // groups of 8 input channels: in all, in a chunk; floats between pixels in LDS
-    int fill;                             // 16-byte vectors of the pixels in LDS, if channels past Cin are zeroed there once, else 0
     int per_px, d_c, d_px, d_row, d_col;  // staging: vectors per pixel of a chunk; 256 vectors further on = d_px pixels
                                           // (d_row rows and d_col columns) and d_c vectors
     FastDiv div_pn, div_ng, div_ow, div_px, div_tw;
@@ -92,7 +91,11 @@ __global__ __launch_bounds__(256) void conv_f32_kernel(F32Params p) {
     bool fresh = true;
     // Channel by channel, and all channels one chunk: those past Cin are zeroed once and not staged (requesting them took the
     // address unit as long as the others: 800 x 704 x 1 -> 8, all blocks: 50.0 -> 43.7 us)
-    for (int v = threadIdx.x; v < p.fill; v += 256) *(float4 *)(xl + v * 4) = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (!V4 && p.per_px < p.cc8 * 8) {
+        const int full = (int)fdiv(kF32Pix, p.div_ow), out_rows = min(kF32Pix - full * p.ow ? full + 2 : full, p.oh);      // as on the host
+        const int floats = ((out_rows - 1) * p.sh + kh) * p.tw * p.S;
+        for (int v = threadIdx.x * 4; v < floats; v += 256 * 4) *(float4 *)(xl + v) = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
 
     // this thread's first staged element, and its step: element index / pixel / row / column carried along instead of divided
     const int px_first = (int)fdiv(threadIdx.x, p.div_px), c_first = (int)threadIdx.x - px_first * p.per_px;
@@ -342,10 +345,7 @@ bool conv_f32_try(sbnet_dtype dt, bool fused, const ConvParams &c, hipStream_t s
     if (lds > 160 * 1024) return false;
     p.S = stride(p.cc8);
     p.per_px = p.cc8 * 8 / (v4 ? 4 : 1);
-    if (!v4 && p.nchunks == 1 && p.Cin < p.per_px) {
-        p.per_px = p.Cin;
-        p.fill = (int)(rows * p.tw * p.S / 4);
-    }
+    if (!v4 && p.nchunks == 1) p.per_px = p.Cin;
     p.d_px = 256 / p.per_px; p.d_c = 256 % p.per_px;
     p.d_row = p.d_px / p.tw; p.d_col = p.d_px % p.tw;
     p.div_px = make_fastdiv(p.per_px);
