@@ -247,8 +247,8 @@ sbnet_status sbnet_sparse_bn_apply(const void *x, sbnet_dtype dtype, int N, int 
  *   dbeta[c] = sum g,  dgamma[c] = sum g * xhat   over the active pixels,
  *   dx = gamma / sqrt(var + eps) * (g - dbeta / n - xhat * dgamma / n)   on the active pixels;
  * other pixels of dx are left as they are; dx may be dy.  dgamma, dbeta: device float32 [C],
- * written also when gamma / beta are NULL.  Sums in fp32 in a fixed order (per block, then a fixed
- * tree over the blocks): no atomics.  workspace: device, 4-byte aligned,
+ * written also when gamma / beta are NULL.  Sums in fp32 in a fixed order (partial sums over pieces of
+ * the blocks, then a fixed tree): no atomics, the same bits every run for a given cap.  workspace: device, 4-byte aligned,
  * sbnet_bn_backward_workspace_bytes(cap, C) bytes, overwritten.
  */
 size_t sbnet_bn_backward_workspace_bytes(int cap, int C);
@@ -286,6 +286,9 @@ sbnet_status sbnet_conv_on_tiles(const void *tiles_in, sbnet_dtype dtype, const 
  * that the convolution result is not rounded to `dtype` before the add; the intermediate tile
  * stacks never exist.  x: [N][H][W][Cin]; y: [N][H_out][W_out][Cout].
  * g_in/g_out as produced by sbnet_geometry for this convolution.  y must not overlap x (not even in part).
+ * Pixels outside the image are zeros: with a weight that is infinite or NaN a result next to the border is
+ * NaN (as on a gathered tile) or, where one thread computes it (float32 and odd channel counts with few
+ * products per pixel, very wide tiles), without that product.
  */
 sbnet_status sbnet_sparse_conv(const void *x, sbnet_dtype dtype, int N, int H, int W, int Cin,
                                const int32_t *indices, const int32_t *count, int cap,
@@ -459,7 +462,9 @@ sbnet_status sbnet_conv_on_tiles_f8(const void *tiles_in_f8, const int32_t *coun
 
 /*
  * Backward pass of the residual branch of a bottleneck unit on tiles (Sec. 3.3; the forward branch is
- * sbnet_bottleneck_on_tiles), composed from the calls above; nothing but they runs.  The caller keeps
+ * sbnet_bottleneck_on_tiles), with the results, bit for bit, of the calls above: three weight, data and
+ * bias gradients and two ReLU masks (where a convolution's kernel can, its stores are masked in place of a
+ * pass, and the bias sums share their launches).  dtiles_in may lie where dt3 does.  The caller keeps
  * the forward activations t1 = ReLU(W1 x + b1) with the positions outside the image set to zero
  * ([cap][th][tw][Cm]) and t2 = ReLU(W2 * t1 + b2) ([cap][th-2][tw-2][Cm]) - a training forward pass
  * runs the three convolutions as single calls, the fused kernel does not keep them - and passes
@@ -472,8 +477,8 @@ sbnet_status sbnet_conv_on_tiles_f8(const void *tiles_in_f8, const int32_t *coun
  */
 /*
  * The forward pass that keeps what the call below needs: the residual branch of sbnet_bottleneck_on_tiles
- * as its three convolutions in single calls, writing t1 (with the positions outside the H x W image set
- * to zero, [cap][th][tw][Cm]), t2 ([cap][th-2][tw-2][Cm]) and t3 ([cap][th-2][tw-2][C]).  Weights from
+ * as its three convolutions, with the results, bit for bit, of single calls (sbnet_zero_outside after the
+ * first), writing t1 (with the positions outside the H x W image set to zero, [cap][th][tw][Cm]), t2 ([cap][th-2][tw-2][Cm]) and t3 ([cap][th-2][tw-2][C]).  Weights from
  * sbnet_pack_weights, biases float32 or NULL; any element type and channel counts the tile convolution
  * takes.  th, tw = g_in->bsize.  The results equal the fused kernel's up to its rounding of t1 and t2.
  */

@@ -434,7 +434,7 @@ def test_sparse_bn_apply_and_backward(H, W, C, bo, N, dtype, relu):
         assert np.array_equal(gotdx[~inside], d0[~inside])
         npx = int(inside.sum())
         if npx:
-            # sums of npx terms of unit scale in fp32, partial sums per block then a tree
+            # sums of npx terms of unit scale in fp32, partial sums over pieces of the blocks then a tree
             stol = 3e-5 * np.sqrt(npx) + 1e-4
             assert np.abs(dgam.cpu().numpy() - rdg).max() <= stol * max(1.0, np.abs(rdg).max() / np.sqrt(npx)), np.abs(dgam.cpu().numpy() - rdg).max()
             assert np.abs(dbet.cpu().numpy() - rdb).max() <= stol * max(1.0, np.abs(rdb).max() / np.sqrt(npx))
@@ -596,6 +596,24 @@ def test_a_negative_count_is_an_empty_list():
     sb.sparse_bn_apply(x, idx, cnt, g_out, mean, var, y=y)
     dx, dgamma, dbeta = sb.sparse_bn_backward(x, x, idx, cnt, g_out, mean, var)
     assert torch.equal(x, y) and (dx == 0).all() and (dgamma == 0).all() and (dbeta == 0).all()
+
+
+def test_fp32_convolution_with_an_infinite_weight_is_that_on_gathered_tiles():
+    """Pixels outside the image are zeros in the products, fused as on a tile that was gathered: next to the border the
+    result is NaN where an infinite weight meets one."""
+    step("fp32 conv, infinite weight")
+    r = gen.rng_for(35)
+    g_in, g_out, _, _ = sb.geometry(32, 32, 3, 1, 8)
+    x, w = gen.activations(r, (1, 32, 32, 16), "f32") + 9.0, gen.conv_weights(r, 3, 3, 16, 16, "f32")
+    w[0, 0, 3, 5] = np.inf
+    idx = np.stack(np.meshgrid([0], np.arange(4), np.arange(4), indexing="ij"), -1).reshape(-1, 3).astype(np.int32)
+    d_idx, d_cnt = dev_indices(idx)
+    wp, d_x = sb.pack_weights(to_dev(w, "f32")), to_dev(x, "f32")
+    y = sb.sparse_conv(d_x, d_idx, d_cnt, g_in, g_out, wp, None, torch.zeros((1, 32, 32, 16)).cuda())
+    out = sb.conv_on_tiles(sb.sparse_gather(d_x, d_idx, d_cnt, g_in), d_cnt, wp)
+    want = sb.sparse_scatter(out, d_idx, d_cnt, g_out, torch.zeros((1, 32, 32, 16)).cuda())
+    assert torch.allclose(y, want, rtol=1e-5, atol=1e-4, equal_nan=True)
+    assert y[0, 0, :, 5].isnan().all() and (y[0, 1:, 1:, 5] == np.inf).all() and y[..., 6].isfinite().all()
 
 
 def test_fp32_convolution_of_windows_far_below_the_image():
