@@ -15,7 +15,7 @@
 //                subset in order, then a fixed tree over the threads.
 // Bound by HBM (the active blocks read once) and, at these sizes, by the launches and the round trips of a workgroup.
 // bf16, before (a row per block, one workgroup per channel) -> now, partial + combine: 800 x 704 x 64, 880 blocks of 16 x 16
-// (28.8 MB): 8.1 + 5.2 -> 9.0 + 4.6 us; 844 x 494 x 64, 3746 blocks of 8 x 8 (30.7 MB): 10.8 + 13.0 -> 9.6 + 4.9 us.
+// (28.8 MB): 8.1 + 5.2 -> 8.5 + 4.5 us; 844 x 494 x 64, 3746 blocks of 8 x 8 (30.7 MB): 10.8 + 13.0 -> 9.6 + 4.9 us.
 #include "bn_common.h"
 
 namespace sbnet {
