@@ -411,10 +411,12 @@ __global__ void tile_indices(int32_t *__restrict__ idx, int cap) {
 // against conv_f32: 3x3 1 -> 1: 4.6 us / 8.9, 1 -> 8: 8.5 / 9.1, 4 -> 4: 7.0 / 9.1, 2 -> 8: 9.1 / 9.1, 1 -> 16: 13.7 / 9.4,
 // 3 -> 8: 10.3 / 9.4, 8 -> 4: 10.4 / 9.0; 1x1 4 -> 4: 3.7 / 8.0, 8 -> 16: 7.4 / 8.7, 32 -> 2: 5.3 / 9.3, 1 -> 32: 12.4 / 10.1;
 // 5x5 1 -> 4: 10.1 / 10.5, 1 -> 8: 15.6 / 10.7.  64 x 64, blocks of 8 x 8: 3x3 1 -> 32: 4.45 / 4.74, 4 -> 32: 4.62 / 4.76,
-// 8 -> 8: 4.71 / 4.58, 16 -> 1: 5.95 / 5.03.
+// 8 -> 8: 4.71 / 4.58, 16 -> 1: 5.95 / 5.03.  And tiles of few pixels, of whose 64 places an item of conv_f32 fills that many:
+// 200 x 200 x 16 -> 16, blocks of 2 x 2: 12.4 / 20.3; of 4 x 4: 14.9 / 7.0.
 static bool direct_is_faster(const ConvParams &p, long long M) {
     const long long L = (long long)p.kh * p.kw * p.Cin;
     if (L <= 36 && p.cap * M * p.Cout <= (1LL << 17)) return true;
+    if (M <= 8 && M * L * p.Cout <= 10000) return true;
     return L <= 100 && p.Cout <= 16 && (L + 2) * p.Cout <= 160;
 }
 

@@ -578,6 +578,12 @@ def test_fp32_convolution_of_few_products(Cin):
     check_fp32_convolution(20, 25, Cin, 10, 1, 1, 8, 1, "f32" if Cin % 2 else "bf16", room=5000)
 
 
+@pytest.mark.parametrize("H,W,Cin,Cout,dtype", [(40, 45, 16, 16, "f32"), (33, 30, 20, 12, "f32"), (24, 30, 17, 14, "f16")])
+def test_fp32_convolution_on_tiles_of_few_pixels(H, W, Cin, Cout, dtype):
+    """2x2 output pixels, below the limit on the products of a tile: one thread per output element."""
+    check_fp32_convolution(H, W, Cin, Cout, 3, 1, 2, 1, dtype)
+
+
 def test_a_negative_count_is_an_empty_list():
     step("negative count")
     r = gen.rng_for(33)
