@@ -67,8 +67,22 @@ __device__ __forceinline__ void bn_affine_of(const BnAffine &a, int c, float *v)
     v[3] = a.beta ? a.beta[c] : 0.f;
 }
 
-// the slabs of an item range are walked in groups whose channels fit the LDS copy: group gi holds slabs [gi * per, ...)
-__device__ __forceinline__ int bn_group_slabs(const BnParams &p) { return kBnCoef / p.cs; }
+// A workgroup walks the items of one group of slabs, whose channels fit the LDS copy; the groups share the grid evenly (a grid
+// of bn_grid).  One group after the other in every workgroup left most of them idle where pixels have thousands of
+// channels: 32 x 32 x 4096, 10 blocks of 8 x 8: 16.7 us, now 5.3.
+__host__ __device__ __forceinline__ int bn_group_slabs(const BnParams &p) { return kBnCoef / p.cs; }
+__host__ __device__ __forceinline__ int bn_groups(const BnParams &p) { return (p.slabs + bn_group_slabs(p) - 1) / bn_group_slabs(p); }
+struct BnGroup {
+    int s0, ns;                               // its slabs
+    uint32_t first, step;                     // items of this workgroup
+    __device__ __forceinline__ explicit BnGroup(const BnParams &p) {
+        const uint32_t groups = (uint32_t)bn_groups(p);
+        first = groups == 1 ? blockIdx.x : blockIdx.x / groups;
+        step = groups == 1 ? gridDim.x : gridDim.x / groups;
+        s0 = (int)(blockIdx.x - first * groups) * bn_group_slabs(p);
+        ns = min(bn_group_slabs(p), p.slabs - s0);
+    }
+};
 
 template <int DT>
 __global__ __launch_bounds__(kBnThreads) void bn_apply(const uint4 *x, uint4 *y,                       // y may be x
@@ -78,49 +92,47 @@ __global__ __launch_bounds__(kBnThreads) void bn_apply(const uint4 *x, uint4 *y,
     __shared__ __align__(16) float cf[4][kBnCoef];
     const int nact = max(min(*count, p.cap), 0);
     const int pg = threadIdx.x >> 3, k = threadIdx.x & 7;
-    for (int s0 = 0; s0 < p.slabs; s0 += bn_group_slabs(p)) {
-        const int ns = min(bn_group_slabs(p), p.slabs - s0);
-        const uint32_t units = (uint32_t)nact * (uint32_t)ns;     // (block, slab of the group)
-        BnWalk it(blockIdx.x, gridDim.x, (uint32_t)pieces, div_pieces);
-        uint32_t b = it.unit / (uint32_t)ns;
-        int slab = (int)(it.unit - b * ns);
-        BnBlock blk = bn_block(indices, b, p.cap);
-        BnCoefs<4> co = {cf, 0};
-        if (s0) __syncthreads();
-        co.load(s0 * p.cs, p.C, [&](int c, float *v) { bn_affine_of(a, c, v); });
-        while (it.unit < units) {
-            const BnPlace w = bn_place<EPV>(blk, s0 + slab, k, p);
-            const int q0 = (int)it.piece * kBnPiece + pg;
-            it.advance();
-            b = ns == 1 ? it.unit : it.unit / (uint32_t)ns;       // the next item's
-            slab = (int)(it.unit - b * ns);
-            blk = bn_block(indices, b, p.cap);
-            long long at[4];
-            uint4 v[4];
+    const BnGroup gr(p);
+    const int s0 = gr.s0, ns = gr.ns;
+    const uint32_t units = (uint32_t)nact * (uint32_t)ns;     // (block, slab of the group)
+    BnWalk it(gr.first, gr.step, (uint32_t)pieces, div_pieces);
+    uint32_t b = it.unit / (uint32_t)ns;
+    int slab = (int)(it.unit - b * ns);
+    BnBlock blk = bn_block(indices, b, p.cap);
+    BnCoefs<4> co = {cf, 0};
+    co.load(s0 * p.cs, p.C, [&](int c, float *v) { bn_affine_of(a, c, v); });
+    while (it.unit < units) {
+        const BnPlace w = bn_place<EPV>(blk, s0 + slab, k, p);
+        const int q0 = (int)it.piece * kBnPiece + pg;
+        it.advance();
+        b = ns == 1 ? it.unit : it.unit / (uint32_t)ns;       // the next item's
+        slab = (int)(it.unit - b * ns);
+        blk = bn_block(indices, b, p.cap);
+        long long at[4];
+        uint4 v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                at[u] = bn_pixel(w, q0 + 32 * u, p);
-                if (at[u] >= 0) v[u] = x[at[u]];
-            }
-            float mean[EPV], rstd[EPV], gam[EPV], bet[EPV];
-            co.get<EPV>(0, w.c0, mean);
-            co.get<EPV>(1, w.c0, rstd);
-            co.get<EPV>(2, w.c0, gam);
-            co.get<EPV>(3, w.c0, bet);
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (at[u] >= 0) {
-                    float f[EPV];
-                    BnElem<DT>::unpack(v[u], f);
-#pragma unroll
-                    for (int e = 0; e < EPV; ++e) {
-                        const float z = fmaf(gam[e], (f[e] - mean[e]) * rstd[e], bet[e]);
-                        f[e] = a.relu ? fmaxf(z, 0.f) : z;
-                    }
-                    // a vector that straddles the channel count cannot occur: a pixel's channels fill whole vectors
-                    y[at[u]] = bn_pack<DT>(f);
-                }
+        for (int u = 0; u < 4; ++u) {
+            at[u] = bn_pixel(w, q0 + 32 * u, p);
+            if (at[u] >= 0) v[u] = x[at[u]];
         }
+        float mean[EPV], rstd[EPV], gam[EPV], bet[EPV];
+        co.get<EPV>(0, w.c0, mean);
+        co.get<EPV>(1, w.c0, rstd);
+        co.get<EPV>(2, w.c0, gam);
+        co.get<EPV>(3, w.c0, bet);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (at[u] >= 0) {
+                float f[EPV];
+                BnElem<DT>::unpack(v[u], f);
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    const float z = fmaf(gam[e], (f[e] - mean[e]) * rstd[e], bet[e]);
+                    f[e] = a.relu ? fmaxf(z, 0.f) : z;
+                }
+                // a vector that straddles the channel count cannot occur: a pixel's channels fill whole vectors
+                y[at[u]] = bn_pack<DT>(f);
+            }
     }
 }
 
@@ -258,66 +270,69 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_dx(const uint4 *__restrict_
     const int nact = max(min(*count, p.cap), 0);
     const int pg = threadIdx.x >> 3, k = threadIdx.x & 7;
     const float n = *ntot, inv_n = n > 0.f ? 1.0f / n : 0.f;
-    for (int s0 = 0; s0 < p.slabs; s0 += bn_group_slabs(p)) {
-        const int ns = min(bn_group_slabs(p), p.slabs - s0);
-        const uint32_t units = (uint32_t)nact * (uint32_t)ns;     // (block, slab of the group)
-        BnWalk it(blockIdx.x, gridDim.x, (uint32_t)pieces, div_pieces);
-        uint32_t b = it.unit / (uint32_t)ns;
-        int slab = (int)(it.unit - b * ns);
-        BnBlock blk = bn_block(indices, b, p.cap);
-        BnCoefs<6> co = {cf, 0};
-        if (s0) __syncthreads();
-        co.load(s0 * p.cs, p.C, [&](int c, float *v) {
-            bn_affine_of(a, c, v);
-            v[4] = dbeta[c] * inv_n;
-            v[5] = dgamma[c] * inv_n;
-        });
-        while (it.unit < units) {
-            const BnPlace w = bn_place<EPV>(blk, s0 + slab, k, p);
-            const int q0 = (int)it.piece * kBnPiece + pg;
-            it.advance();
-            b = ns == 1 ? it.unit : it.unit / (uint32_t)ns;       // the next item's
-            slab = (int)(it.unit - b * ns);
-            blk = bn_block(indices, b, p.cap);
-            long long at[4];
-            uint4 vx[4], vg[4];
+    const BnGroup gr(p);
+    const int s0 = gr.s0, ns = gr.ns;
+    const uint32_t units = (uint32_t)nact * (uint32_t)ns;     // (block, slab of the group)
+    BnWalk it(gr.first, gr.step, (uint32_t)pieces, div_pieces);
+    uint32_t b = it.unit / (uint32_t)ns;
+    int slab = (int)(it.unit - b * ns);
+    BnBlock blk = bn_block(indices, b, p.cap);
+    BnCoefs<6> co = {cf, 0};
+    co.load(s0 * p.cs, p.C, [&](int c, float *v) {
+        bn_affine_of(a, c, v);
+        v[4] = dbeta[c] * inv_n;
+        v[5] = dgamma[c] * inv_n;
+    });
+    while (it.unit < units) {
+        const BnPlace w = bn_place<EPV>(blk, s0 + slab, k, p);
+        const int q0 = (int)it.piece * kBnPiece + pg;
+        it.advance();
+        b = ns == 1 ? it.unit : it.unit / (uint32_t)ns;       // the next item's
+        slab = (int)(it.unit - b * ns);
+        blk = bn_block(indices, b, p.cap);
+        long long at[4];
+        uint4 vx[4], vg[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                at[u] = bn_pixel(w, q0 + 32 * u, p);
-                if (at[u] >= 0) {
-                    vx[u] = x[at[u]];
-                    vg[u] = dy[at[u]];
-                }
+        for (int u = 0; u < 4; ++u) {
+            at[u] = bn_pixel(w, q0 + 32 * u, p);
+            if (at[u] >= 0) {
+                vx[u] = x[at[u]];
+                vg[u] = dy[at[u]];
             }
-            float mean[EPV], rstd[EPV], gam[EPV], bet[EPV], mg[EPV], mgx[EPV];
-            co.get<EPV>(0, w.c0, mean);
-            co.get<EPV>(1, w.c0, rstd);
-            co.get<EPV>(2, w.c0, gam);
-            co.get<EPV>(3, w.c0, bet);
-            co.get<EPV>(4, w.c0, mg);
-            co.get<EPV>(5, w.c0, mgx);
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (at[u] >= 0) {
-                    float f[EPV], g[EPV];
-                    BnElem<DT>::unpack(vx[u], f);
-                    BnElem<DT>::unpack(vg[u], g);
-#pragma unroll
-                    for (int e = 0; e < EPV; ++e) {
-                        const float xh = (f[e] - mean[e]) * rstd[e];
-                        const float ge = (a.relu && !(fmaf(gam[e], xh, bet[e]) > 0.f)) ? 0.f : g[e];
-                        f[e] = gam[e] * rstd[e] * (ge - mg[e] - xh * mgx[e]);
-                    }
-                    dx[at[u]] = bn_pack<DT>(f);
-                }
         }
+        float mean[EPV], rstd[EPV], gam[EPV], bet[EPV], mg[EPV], mgx[EPV];
+        co.get<EPV>(0, w.c0, mean);
+        co.get<EPV>(1, w.c0, rstd);
+        co.get<EPV>(2, w.c0, gam);
+        co.get<EPV>(3, w.c0, bet);
+        co.get<EPV>(4, w.c0, mg);
+        co.get<EPV>(5, w.c0, mgx);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (at[u] >= 0) {
+                float f[EPV], g[EPV];
+                BnElem<DT>::unpack(vx[u], f);
+                BnElem<DT>::unpack(vg[u], g);
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    const float xh = (f[e] - mean[e]) * rstd[e];
+                    const float ge = (a.relu && !(fmaf(gam[e], xh, bet[e]) > 0.f)) ? 0.f : g[e];
+                    f[e] = gam[e] * rstd[e] * (ge - mg[e] - xh * mgx[e]);
+                }
+                dx[at[u]] = bn_pack<DT>(f);
+            }
     }
 }
 
-// as many workgroups as the device holds at once (six to eight per CU), each with its coefficients loaded once
-int bn_grid(int cap, const BnParams &p, int pieces) {
-    const long long items = (long long)cap * p.slabs * pieces;
-    return (int)(items < 2048 ? items : 2048);
+// A multiple of the groups, and no more than the device's 256 CUs hold in whole rounds, each workgroup with its coefficients
+// loaded once: seven per CU for bn_apply (its registers allow five to nine), twice four for bn_bwd_dx.  With eight, the last
+// 256 of bn_apply ran alone at the end: 800 x 704 x 256 in bf16, all blocks of 16 x 16: 2048 workgroups 137 us, 1792 112.
+constexpr int kBnApplyGrid = 1792, kBnDxGrid = 2048;
+int bn_grid(int cap, const BnParams &p, int pieces, int resident) {
+    const int groups = bn_groups(p);
+    const long long per = (long long)cap * (p.slabs < bn_group_slabs(p) ? p.slabs : bn_group_slabs(p)) * pieces;
+    const long long most = groups < resident ? resident / groups : 1;
+    return (int)(per < most ? per : most) * groups;
 }
 
 }  // namespace
@@ -346,7 +361,7 @@ extern "C" sbnet_status sbnet_sparse_bn_apply(const void *x, sbnet_dtype dtype, 
     if (cap == 0) return SBNET_OK;
     hipStream_t s = (hipStream_t)stream;
     const BnAffine a = {mean, var, gamma, beta, eps, relu ? 1 : 0};
-    const int pieces = bn_pieces(p), grid = bn_grid(cap, p, pieces);
+    const int pieces = bn_pieces(p), grid = bn_grid(cap, p, pieces, kBnApplyGrid);
     SBNET_BN_DISPATCH(bn_apply, (const uint4 *)x, (uint4 *)y, indices, count, pieces, make_fastdiv(pieces), p, a);
     return launch_status(who);
 }
@@ -387,7 +402,7 @@ extern "C" sbnet_status sbnet_sparse_bn_backward(const void *x, const void *dy, 
     hipLaunchKernelGGL(bn_bwd_combine, dim3((C + 3) / 4), dim3(1024), 0, s, part, cnt, count, cap, C, rows, all, dgamma, dbeta,
                        ntot);
     if (cap > 0) {
-        const int pieces = bn_pieces(p), grid = bn_grid(cap, p, pieces);
+        const int pieces = bn_pieces(p), grid = bn_grid(cap, p, pieces, kBnDxGrid);
         SBNET_BN_DISPATCH(bn_bwd_dx, (const uint4 *)x, (const uint4 *)dy, (uint4 *)dx, indices, count, dgamma, dbeta, ntot, pieces,
                           make_fastdiv(pieces), p, a);
     }

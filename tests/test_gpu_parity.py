@@ -448,6 +448,7 @@ def test_sparse_bn_apply_and_backward(H, W, C, bo, N, dtype, relu):
 
 @pytest.mark.parametrize("H,W,C,bo,N,dtype", [
     (40, 44, 1032, 8, 1, "bf16"),          # more channels than the coefficients in LDS hold at once, a partial last slab
+    (64, 60, 2056, 8, 1, "bf16"),          # five groups of channels, the last one of 8; more items in a group than its workgroups
     (270, 265, 8, 8, 1, "f16"),            # 1156 blocks: more items than rows of partial sums
     (66, 50, 136, 20, 1, "f32"),           # 400 pixels a block: four pieces, the last one of 16
 ])
