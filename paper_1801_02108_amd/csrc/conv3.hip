@@ -611,12 +611,15 @@ void conv3_pair_kernel(ConvParams p, Plan3 qb, Plan3 qs) {
 // Stride 1, 65 ... 96 output channels (or any count that groups of 96 fill better than groups of 64): groups of 96 on
 // 256-pixel items beside the pair of shapes with groups of 64.  One wide item does the work of two 64-channel ones: the
 // rows are staged once and a quarter of the matrix steps, the empty half of the second group, falls away; 16-channel
-// chunks (two buffers of 32 do not fit beside 96 channels of weights) also skip the padding of 48 or 80 channels.  A
-// wide item takes about 9/8 of a 64-channel one (12.4 against 10.8 us in a single round of 96 -> 96 on 16x16 blocks), so
-// the count picks by rounds of work on 256 CUs: below one round of the narrow items they stay.  Measured, narrow
-// against wide: 593 blocks of 12x12, 48 -> 80: 28.1 and 22.5 us; 740 of 14x14, 128 -> 96: 51.5 and 43.5; 550 of 16x16,
-// 48 -> 96: 26.4 and 22.1, 96 -> 96: 35.5 and 34.6.  Not taken: up to 32 input channels, one narrow chunk (24 -> 96: 17.3 and
-// 18.0), and groups of 128, which were mixed (550 of 16x16, 48 -> 128: 26.6 and 27.4).
+// chunks (two buffers of 32 do not fit beside 96 channels of weights) also skip the padding of 48 or 80 channels.  The
+// count picks by rounds of work on 256 CUs: a wide round costs as much as its matrix steps, 9/8 to 12/8 of a narrow one by the
+// chunks' padding, and 2/8 for the chunks' barriers, 2/8 more where the last group is not full (wide_cost8).  Measured
+// slopes per round, narrow and wide: 16x16 blocks, 40 -> 96: 4.0 and 5.5 us, 48 -> 80: 4.3 and 6.6, 96 -> 96: 6.2 and 9.4, 128 -> 72:
+// 8.1 and 12.8; 12x12, 48 -> 80: 3.7 and 5.8, 128 -> 96: 7.2 and 12.6.  400 x 352, narrow alone, wide at 9/8, this rule: 60 % of
+// 16x16, 128 -> 72: 27.5, 32.8, 27.7; 96 -> 96: 21.9, 24.5, 22.2; all of 12x12, 48 -> 80: 35.0, 26.5, 26.7.  Three shapes in
+// a launch cost up to 0.6 us over two where few blocks are active (8 % of 16x16, 96 -> 96: 8.0 and 8.5), so a list too short
+// for a second round of narrow items, where the wide ones are never picked, takes conv3_pair_kernel.  Not taken: up to 32 input channels, one
+// narrow chunk (24 -> 96: 17.3 and 18.0), and groups of 128, which were mixed (550 of 16x16, 48 -> 128: 26.6 and 27.4).
 template <int DT, bool FUSED, bool ADD, int NVIS, int EPI = kEpiNone>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void conv3_wide96_kernel(ConvParams p, Plan3 qw, Plan3 qb, Plan3 qs) {
@@ -624,7 +627,7 @@ void conv3_wide96_kernel(ConvParams p, Plan3 qw, Plan3 qb, Plan3 qs) {
     const uint32_t rw = (nact * (uint32_t)(qw.mpasses * qw.ngroups) + 255u) >> 8, rb = (nact * (uint32_t)(qb.mpasses * qb.ngroups) + 255u) >> 8,
                    rs = (nact * (uint32_t)(qs.mpasses * qs.ngroups) + 255u) >> 8;
     const unsigned long long small8 = (unsigned long long)rs * (uint32_t)p.small_cost8, big8 = (unsigned long long)rb * 8u;
-    if ((unsigned long long)rw * 9u <= (big8 <= small8 ? big8 : small8)) conv3_body<DT, FUSED, ADD, 16, 4, 3, 2, 5, 3, true, EPI>(p, qw);
+    if ((unsigned long long)rw * (uint32_t)p.wide_cost8 <= (big8 <= small8 ? big8 : small8)) conv3_body<DT, FUSED, ADD, 16, 4, 3, 2, 5, 3, true, EPI>(p, qw);
     else if (big8 <= small8) conv3_body<DT, FUSED, ADD, 32, 4, 2, 2, 6, 3, true, EPI>(p, qb);
     else conv3_body<DT, FUSED, ADD, 32, 4, 2, 1, NVIS, 3, true, EPI>(p, qs);
 }
@@ -912,6 +915,7 @@ static void launch3_wide96(bool fused, ConvForm form, const ConvParams &p, const
     if (small.lds_bytes > lds) lds = small.lds_bytes;
     ConvParams pt = p;
     pt.small_cost8 = tuning().conv3_small_item_cost_eighths;
+    pt.wide_cost8 = 12 * ((p.Cin + 15) / 16 * 16) / ((p.Cin + 31) / 32 * 32) + 2 + (p.Cout % 96 ? 2 : 0);
 #define SBNET_L3N(FU, AD, NVIS, EPI)                                                                                     \
     do {                                                                                                                 \
         auto kern = conv3_wide96_kernel<DT, FU, AD, NVIS, EPI>;                                                               \
@@ -997,7 +1001,7 @@ bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p0, hipStream_t s, 
     if ((own || (mask && p.kh == 3)) && (!fused || p.add || p.kh != 3 || (big.ok && big.cc != 32) || (small.ok && small.cc != 32))) return false;
     if (form == ConvForm::inside && (fused || p.kh != 1)) return false;
     if (big.ok && small.ok && p.Cin > 32 && p.kh == 3 && p.sh == 1 && p.sw == 1 && M <= 256 && big.cc == 32 && big.nvi == 6 && small.cc == 32 &&
-        (p.Cout + 95) / 96 * 3 < (p.Cout + 63) / 64 * 2) {
+        (p.Cout + 95) / 96 * 3 < (p.Cout + 63) / 64 * 2 && (long long)p.cap * big.q.mpasses * big.q.ngroups > 256) {
         const Shape3 wide = plan3(p, 256, 3);                              // see conv3_wide96_kernel
         if (wide.ok) {
             if (mask) return false;                                        // (16-channel chunks: another order of summation)

@@ -49,7 +49,10 @@ struct ConvParams {
     int32_t *count_out;      // [1]
     FastDiv div_bps, div_bw, div_grid;       // blocks per sample, blocks per block row, workgroups along x
     int small_cost8;         // conv3.hip, two tile shapes in one launch: cost of the smaller item in eighths of the larger
-    int wide_min_items;      // conv3.hip, 64-channel or wider output groups in one launch: wide from this many work items
+    union {                  // conv3.hip, 64-channel or wider output groups in one launch:
+        int wide_min_items;  // wide from this many work items,
+        int wide_cost8;      // or cost of a round of the wide items in eighths of one of 256 pixels x 64 channels
+    };
     // MFMA path work decomposition
     int CinP;                // Cin rounded up to 32
     int CC;                  // channels per LDS chunk (multiple of 32)
