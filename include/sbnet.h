@@ -67,6 +67,7 @@ typedef struct {
 typedef struct {
     /* residual unit: cost of an 8 x 8 sub-tile in eighths of a 16 x 16 one; the size whose cost-weighted rounds of
        work over 256 workgroups are fewer is run (8 x 8: four times the items, a shorter latency chain each).
+       Lists whose bound costs at most one eighth more in 8 x 8 sub-tiles than one round of 16 x 16 ones run 8 x 8.
        Default 3; 0 = always 8 x 8; 1000 = always 16 x 16 where the block allows it. */
     int unit_small_item_cost_eighths;
     /* LDS-tiled 3x3 convolution: cost of a 128-pixel work item in eighths of a 256-pixel one; the shape whose

@@ -910,18 +910,26 @@ static sbnet_status bneck_entry(const char *who, bool fused, const void *in, voi
     // Sub-tile side: 16 x 16 where the block allows it, or 8 x 8: four times the work items at 1.56x the halo overhead
     // and a shorter latency chain each, which wins where the larger items leave most CUs idle or the last round of
     // them nearly empty.  The device decides from its count (see BneckParams); both variants are launched and one of
-    // them returns at once (a few microseconds).
+    // them returns at once.
     const bool can16 = !wide && g_out->bsize_h % 16 == 0 && g_out->bsize_w % 16 == 0;
+    // The returning launch costs 1.5 to 1.9 us.  Where the list's bound allows three rounds of 8 x 8 items at most, 16 x 16
+    // ones can win an eighth (one round against three: 8 eighths to 9) on lists near their bound and lose the launch on all
+    // others, so only the 8 x 8 variant is launched.  192 blocks of 16 x 16, us with two launches -> with one: 64/16 at
+    // 19 active blocks 8.4 -> 6.7, 128/32 at 115 12.2 -> 10.5, 256/64 at 58 11.6 -> 9.7, at 131 19.1 -> 18.2, at 173 18.9
+    // -> 19.2, at 192 19.3 -> 19.1; a stage of six units (143 blocks, 36 active) 70.6 -> 62.7.  With a pre-activation an
+    // 8 x 8 item costs more than three eighths (256/64 at 192: 24.5 -> 25.8): there the line is two rounds, up to which
+    // 16 x 16 items never win.
     const int cost8 = tuning().unit_small_item_cost_eighths;
+    const long long rounds8 = ((long long)cap * (p.oh / 8) * (p.ow / 8) + 255) / 256;
+    const bool only8 = !can16 || rounds8 * cost8 <= (pre_scale ? 7 : 9);
     hipStream_t s = (hipStream_t)stream;
     for (int ts = 16; ts >= 8; ts -= 8) {
-        if (ts == 16 && !can16) continue;
-        p.per16 = can16 ? (p.oh / 16) * (p.ow / 16) : 0;
+        p.per16 = !only8 ? (p.oh / 16) * (p.ow / 16) : 0;
         p.per8 = (p.oh / 8) * (p.ow / 8);
         p.cost8 = cost8;
         p.want16 = ts == 16;
-        if (can16 && ts == 16 && cost8 <= 0) continue;          // can never be chosen
-        if (can16 && ts == 8 && cost8 >= 1000) continue;        // neither can this one
+        if (ts == 16 && only8) continue;                        // (cost8 = 0: can never be chosen)
+        if (!only8 && ts == 8 && cost8 >= 1000) continue;       // neither can this one
         p.sub_h = p.oh / ts; p.sub_w = p.ow / ts;
         p.div_sub = make_fastdiv((uint32_t)p.sub_h * p.sub_w);
         p.div_subw = make_fastdiv((uint32_t)p.sub_w);

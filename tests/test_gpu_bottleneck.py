@@ -136,6 +136,43 @@ def _unit_case(N, H, W, C, Cm, bo, dtype):
             assert_close(got, orc.sparse_bottleneck_dense(x, idx, ogeom(g_out), *ws), CONV_TOL[dtype], "dense unit")
 
 
+@pytest.mark.parametrize("cap", [128, 129, 192, 193])
+@pytest.mark.parametrize("C,Cm,dtype,preact,on_tiles", [(96, 24, "bf16", False, False), (256, 64, "f16", True, False),
+                                                        (192, 48, "bf16", False, True)])
+def test_unit_variants_around_the_lists_bound(C, Cm, dtype, preact, on_tiles, cap):
+    """Which sub-tile sizes are launched follows the bound of the list, which of them runs its count: one result."""
+    step("unit, list bound %s" % ((C, Cm, dtype, preact, on_tiles, cap),))
+    r = gen.rng_for(3, C + cap)
+    N, H, W = 1, 16 * 14, 16 * 14                              # 196 blocks
+    g_in, g_out, _, _ = sb.geometry(H, W, 3, 1, 16)
+    dx = to_dev(gen.activations(r, (N, H, W, C), dtype), dtype)
+    dws = dev_weights(gen.bottleneck_weights(r, C, Cm, dtype), dtype)
+    pre = (torch.full((C,), 0.9).cuda(), torch.full((C,), 0.1).cuda()) if preact else None
+    blocks = np.stack([np.zeros(196), np.repeat(np.arange(14), 14), np.tile(np.arange(14), 14)], 1).astype(np.int32)
+    idx = torch.from_numpy(blocks[r.permutation(196)[:cap]]).cuda()
+    try:
+        for n in (1, 64, 65, cap):
+            cnt = torch.tensor([n], dtype=torch.int32).cuda()
+            got = {}
+            for cost in (None, 0, 1000):                       # the default, 8 x 8 forced, 16 x 16 forced
+                if cost is not None:
+                    sb.set_tuning(unit_small_item_cost_eighths=cost)
+                if on_tiles:
+                    out = torch.zeros((cap, 16, 16, C), dtype=TORCH_DT[dtype], device="cuda")
+                    got[cost] = sb.bottleneck_on_tiles(sb.sparse_gather(dx, idx, cnt, g_in), idx, cnt, g_in, g_out, H, W, dws,
+                                                       out=out, pre=pre)[:n]
+                else:
+                    got[cost] = dx.clone()
+                    sb.sparse_bottleneck(dx, idx, cnt, g_in, g_out, dws, got[cost], pre=pre)
+                sb.set_tuning()
+            assert torch.equal(got[None], got[0]) and torch.equal(got[None], got[1000]), n
+            assert not on_tiles or bool((got[None] != 0).any())
+            assert on_tiles or int((got[None] != dx).any(-1).sum()) > n * 200       # the listed blocks and no others
+            assert on_tiles or int((got[None] != dx).any(-1).sum()) <= n * 256
+    finally:
+        sb.set_tuning()
+
+
 @pytest.mark.parametrize("N,H,W,C,bo,dtype", [(2, 48, 48, 256, 16, "bf16"), (1, 40, 56, 128, 16, "f16"), (2, 40, 24, 256, 8, "bf16"),
                                               (1, 37, 29, 64, 8, "f16")])
 def test_preactivation_unit(N, H, W, C, bo, dtype):
