@@ -420,6 +420,18 @@ static bool direct_is_faster(const ConvParams &p, long long M) {
     return L <= 100 && p.Cout <= 16 && (L + 2) * p.Cout <= 160;
 }
 
+// Shapes of conv16.hip that conv_wave.hip serves better.  Up to 32 output channels half of conv16's matrix work is padding:
+// 800 x 704, blocks of 16, 64 -> 32, conv16 and conv_wave: 3 % active 6.5 and 5.0 us, 10 % (220 blocks, nearly a full round of
+// conv16) 6.7 and 7.1, 30 % 14.7 and 12.1, all 35.9 and 30.6.  More than 64: conv16 launches a persistent workgroup per CU and
+// group of 64, and the second group's wait for the first's whatever the count; 400 x 352, 64 -> 128: 5 % active 10.9 and 5.7 us,
+// 20 % 12.0 and 9.1, all 28.0 and 25.8; beyond 640 tiles of 16 x 16 it is even (800 x 704: 30 % 29.8 and 31.0, all 80 and 85),
+// and so it is where all of conv16's workgroups fit the device (64 -> 128, 110 tiles: 6.6 and 8.3).  33 to 64 channels: conv16's
+// item, a tile per workgroup, wins from about half a round on (64 -> 64, 220 blocks 7.4 and 9.3, 660 16.1 and 16.7, 2200 41 and 48).
+static bool wave_before_16(const ConvParams &p) {
+    const long long tiles = (long long)p.cap * (p.oh / 16) * (p.ow / 16);
+    return p.Cout <= 32 || (p.Cout > 64 && tiles <= 640 && tiles * ((p.Cout + 63) / 64) > 256);
+}
+
 template <int DT, bool FUSED>
 static void launch_direct(const ConvParams &p, dim3 grid, hipStream_t s) {
 #define SBNET_DIRECT(R) \
@@ -450,15 +462,17 @@ static sbnet_status run_conv(const char *who, sbnet_dtype dt, ConvParams &p, hip
 
     if (use_mfma(dt, p.Cin, p.Cout)) p.w32_offset = packed_elems(dt, p.kh, p.kw, p.Cin, p.Cout) / 2 / 8;
     sbnet_status st16 = SBNET_OK;
-    if (form == ConvForm::mask || form == ConvForm::inside)
-        return !conv16_accepts(dt, FUSED, p) && conv3_try(dt, FUSED, p, s, &st16, who, form) ? st16 : SBNET_EUNSUPPORTED;
-    if (form == ConvForm::own) {
-        // conv3.hip works without the list; the other kernels, and its shapes on 16-channel chunks, get one
-        if (!conv16_accepts(dt, FUSED, p) && conv3_try(dt, FUSED, p, s, &st16, who, form)) return st16;
+    const bool takes16 = conv16_accepts(dt, FUSED, p), wave = !takes16 || wave_before_16(p);
+    if (form != ConvForm::plain) {
+        if (wave && conv_wave_try(dt, FUSED, p, s, &st16, who, form)) return st16;
+        if (!takes16 && conv3_try(dt, FUSED, p, s, &st16, who, form)) return st16;
+        if (form != ConvForm::own) return SBNET_EUNSUPPORTED;
+        // the kernels above work without the list; conv16.hip, and conv3.hip's shapes on 16-channel chunks, get one
         hipLaunchKernelGGL(tile_indices, dim3((p.cap + 255) / 256), dim3(256), 0, s, const_cast<int32_t *>(p.indices), p.cap);
         st16 = launch_status(who);
         if (st16 != SBNET_OK) return st16;
     }
+    if (wave && conv_wave_try(dt, FUSED, p, s, &st16, who)) return st16;
     if (conv16_try(dt, FUSED, p, s, &st16, who)) return st16;
     if (conv3_try(dt, FUSED, p, s, &st16, who)) return st16;
 
@@ -793,7 +807,7 @@ extern "C" sbnet_status sbnet_sparse_conv_from_flags(const uint8_t *flags, const
         p.flags = flags;
         p.total_blocks = N * g_in->bcount_h * g_in->bcount_w;
         p.indices_out = indices; p.count_out = count;
-        fold = conv16_accepts(dtype, true, p);
+        fold = conv16_accepts(dtype, true, p) && !(Cout > 64 && wave_before_16(p));      // (up to 64 the launch saved is worth more)
     }
     if (!fold) {
         sbnet_status st = flags_to_indices(who, flags, N, g_in, indices, count, cap, s);
