@@ -5,7 +5,20 @@
 // workgroups, each of which keeps a partial dw in registers for all its tiles and writes it once; a second kernel adds
 // the partial results in a fixed order (no atomics: the result does not depend on scheduling).
 //
-// wgrad_mfma (3x3 or 1x1, stride 1 or 2, BF16/F16, channel counts multiples of 8): a workgroup owns 64 input by 64
+// wgrad_tile (3x3, stride 1, BF16/F16, channel counts multiples of 8) and wgrad_run (1x1, stride 1; the tiles are one run of
+// pixels): a workgroup owns 32 x 32 channels by nine taps, or 64 x 64.  Its four matrix waves split the PIXELS of a stage
+// among them and add up through LDS at the end, so that a split's partial result costs a quarter of the workgroups it took
+// when the waves split the channels: as many workgroups as CUs write 64 partial results of 64 -> 64 weights (9.4 MB) instead of
+// up to 256.  Four more waves only move: tiles go from memory to LDS as they lie (buffer_load ... lds, two or three stages ahead,
+// never through registers), and the matrix operands, which need eight consecutive pixels of one channel, are read with
+// the transposing LDS read (ds_read_b64_tr_b16).  Segments of eight pixels pair up freely, so that rows are padded to 8 pixels
+// instead of 16, and pixels beside the tile, rows past its end and channels past the last arrive as zeros by the buffer
+// descriptor.  Bound by the copies: the address unit takes 47 clocks for one of 64-byte pieces (37 a stage of a 16 x 16 tile).
+// Both launches, us, before (wgrad_mfma) and after: 3x3, 64 -> 64, tiles of 16 x 16: 165 tiles 22.9 -> 17.5, 440 24.7 -> 20.4; of
+// 8 x 8: 440 26.0 -> 16.3; 32 -> 32, 12 x 12, 2200 tiles 50.8 -> 20.5; 96 -> 96, 16 x 16, 440 40.2 -> 33.2.  1x1: 256 -> 64 on 165 tiles of
+// 18 x 18 15.0 -> 11.4, on 550 26.3 -> 22.6; 96 -> 24 on 550 23.7 -> 13.0.
+//
+// wgrad_mfma (3x3 on long lists, 3x3 and 1x1 with a stride of 2; BF16/F16, channel counts multiples of 8): a workgroup owns 64 input by 64
 // output channels, one 32x32 block per wave with one fp32 accumulator per tap (nine, or one).  Tiles pass through LDS a few output
 // rows at a time (a "stage"), stored channel-major so that a lane's matrix operand (8 consecutive pixels of one
 // channel) is one aligned 16-byte read:
@@ -289,6 +302,291 @@ __global__ __launch_bounds__(256) void wgrad_mfma(WgradParams p) {
     }
 }
 
+// ---- 3x3, stride 1: 32 x 32 channels per workgroup
+constexpr int kStageT = 48 * 1024;           // LDS bytes of a stage; three of them are also what the four waves' sums take
+constexpr int kCopiesT = 12;                 // most 1 KB copies of a stage per moving wave
+
+struct TilePlan {
+    int R, tps;              // output rows of a stage; tiles of a stage (1 where a tile takes several stages)
+    int slices;              // stages of a tile
+    int spr, xp, gp;         // 8-pixel segments per output row; LDS pixels per row of x and of dout
+    int x_copies, copies;    // 1 KB copies of a stage: of x, of both
+    int steps;               // pairs of segments of a stage
+    FastDiv div_xt, div_xp, div_gt, div_gp, div_spr, div_seg, div_slices;     // pixels per tile's rows and per row; segments per row and per tile
+};
+
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// four pixels of one channel: lane l of a 16-lane group names pixel l / 4 and channels 4 (l % 4) .. + 3 and gets channel l
+__device__ __forceinline__ uint2 read_tr(const lds_byte *p) {
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p));
+}
+__device__ __forceinline__ void wait_copies(int n) {     // until at most n of this wave's copies are on their way
+    switch (n) {
+#define SBNET_WAIT(N) case N: __builtin_amdgcn_s_waitcnt(0x0F70 | N); break
+        SBNET_WAIT(1); SBNET_WAIT(2); SBNET_WAIT(3); SBNET_WAIT(4); SBNET_WAIT(5); SBNET_WAIT(6);
+        SBNET_WAIT(7); SBNET_WAIT(8); SBNET_WAIT(9); SBNET_WAIT(10); SBNET_WAIT(11); SBNET_WAIT(12);
+#undef SBNET_WAIT
+        default: __builtin_amdgcn_s_waitcnt(0x0F70);
+    }
+}
+
+template <int DT>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void wgrad_tile(WgradParams p, TilePlan q) {
+    extern __shared__ __align__(16) char lds[];
+    lds_byte *const ldsb = (lds_byte *)lds;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int sigma = blockIdx.x % p.nsplit, cbob = blockIdx.x / p.nsplit;
+    const int cb = cbob / p.nob, ob = cbob - cb * p.nob;
+    int n = *p.count;
+    if (n > p.cap) n = p.cap;
+    const int ns = splits_used(n, p.nsplit, p.split_factor);
+    if (n <= 0 || sigma >= ns) return;
+    // stages sigma, sigma + ns, ... of all: stage u is slice u % slices of tile u / slices, or tiles u tps .. + tps - 1
+    const int total = q.tps > 1 ? (n + q.tps - 1) / q.tps : n * q.slices;
+    const int nst = sigma < total ? (total - sigma + ns - 1) / ns : 0;
+
+    if (wave >= 4) {
+        // ---- moving: copy j of a stage is 16 pixels of 32 channels, 64 bytes each, linear in LDS; wave w moves copies w, w + 4, ...
+        const int first = wave - 4;
+        uint32_t rel[kCopiesT];                      // byte offset in the stage's first tile at its first row
+#pragma unroll
+        for (int i = 0; i < kCopiesT; ++i) {
+            const int j = first + 4 * i;
+            const bool isx = j < q.x_copies;
+            const uint32_t px = (uint32_t)((isx ? j : j - q.x_copies) * 16 + (lane >> 2));
+            const int ch = (isx ? cb : ob) * 32 + (lane & 3) * 8;
+            const FastDiv dt = isx ? q.div_xt : q.div_gt, dp = isx ? q.div_xp : q.div_gp;
+            const uint32_t t = fdiv(px, dt), in = px - t * dt.d, row = fdiv(in, dp), col = in - row * dp.d;
+            const uint32_t w = isx ? p.tw : p.ow, h = isx ? p.th : p.oh, C = isx ? p.Cin : p.Cout;
+            // (rows below a tile that is cut in slices are outside its descriptor)
+            const bool ok = (int)t < q.tps && col < w && row < h && ch < (int)C;
+            rel[i] = ok ? t * (isx ? p.x_tile_bytes : p.g_tile_bytes) + ((row * w + col) * C + ch) * 2u : kOutOfRange;
+        }
+        const int mine = (q.copies - first + 3) / 4;
+        auto move = [&](int k) __attribute__((always_inline)) {         // the workgroup's stage k
+            const uint32_t u = (uint32_t)(sigma + k * ns);
+            const uint32_t b = q.tps > 1 ? u * q.tps : fdiv(u, q.div_slices);
+            const uint32_t h = q.tps > 1 ? 0u : u - b * q.slices;
+            const uint32_t tiles = q.tps > 1 ? min((uint32_t)n - b, (uint32_t)q.tps) : 1u;
+            const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)((const char *)p.x + (size_t)b * p.x_tile_bytes), 0, (int)(tiles * p.x_tile_bytes), kBufWord3);
+            const __amdgpu_buffer_rsrc_t gr = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)((const char *)p.g + (size_t)b * p.g_tile_bytes), 0, (int)(tiles * p.g_tile_bytes), kBufWord3);
+            const uint32_t xs = h * (uint32_t)(q.R * p.tw * p.Cin * 2), gs = h * (uint32_t)(q.R * p.ow * p.Cout * 2);
+            lds_byte *to = ldsb + (k % 3) * kStageT;
+#pragma unroll
+            for (int i = 0; i < kCopiesT; ++i) {
+                const int j = first + 4 * i;
+                if (j < q.x_copies)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void *)(to + j * 1024), 16, (int)(rel[i] + xs), 0, 0, 0);
+                else if (j < q.copies)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(gr, (lds_void *)(to + j * 1024), 16, (int)(rel[i] + gs), 0, 0, 0);
+            }
+        };
+        if (nst > 0) move(0);
+        if (nst > 1) move(1);
+        wait_copies(nst > 1 ? mine : 0);
+        __builtin_amdgcn_s_barrier();
+        for (int k = 0; k < nst; ++k) {
+            if (k + 2 < nst) move(k + 2);
+            __builtin_amdgcn_sched_barrier(0);
+            wait_copies(k + 2 < nst ? mine : 0);     // stage k + 1 has landed
+            __builtin_amdgcn_s_barrier();
+        }
+        __syncthreads();                             // (the sums below)
+    } else {
+        f32x16 acc[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[k][e] = 0.f;
+        // ---- matrix steps: step s takes segments 2 s (lanes 0..31) and 2 s + 1 of the stage, wave w steps w, w + 4, ...
+        const uint32_t lane_at = (uint32_t)(((lane & 15) >> 2) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8);
+        struct Ops { uint2 g[2], x[3][3]; };
+        auto load = [&](Ops &o, const lds_byte *st, int s) __attribute__((always_inline)) {
+            const uint32_t seg = (uint32_t)(2 * s + (lane >> 5));
+            const uint32_t t = fdiv(seg, q.div_seg), in = seg - t * q.div_seg.d, row = fdiv(in, q.div_spr), c = in - row * q.div_spr.d;
+            const lds_byte *gp = st + q.x_copies * 1024 + (t * q.div_gt.d + row * q.gp + c * 8) * 64 + lane_at;
+            const lds_byte *xp = st + (t * q.div_xt.d + row * q.xp + c * 8) * 64 + lane_at;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) o.g[k] = read_tr(gp + k * 256);
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) o.x[r][k] = read_tr(xp + r * q.xp * 64 + k * 256);
+        };
+        auto step = [&](const Ops &o) __attribute__((always_inline)) {
+            const uint4 b = make_uint4(o.g[0].x, o.g[0].y, o.g[1].x, o.g[1].y);
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                const uint4 v0 = make_uint4(o.x[r][0].x, o.x[r][0].y, o.x[r][1].x, o.x[r][1].y);
+                const uint4 v1 = make_uint4(o.x[r][2].x, o.x[r][2].y, 0u, 0u);
+                acc[3 * r] = mfma32x32x16<DT>(v0, b, acc[3 * r]);
+                acc[3 * r + 2] = mfma32x32x16<DT>(window2(v0, v1), b, acc[3 * r + 2]);
+                acc[3 * r + 1] = mfma32x32x16<DT>(window1(v0, v1), b, acc[3 * r + 1]);
+            }
+        };
+        __syncthreads();                             // stage 0
+        for (int k = 0; k < nst; ++k) {
+            const lds_byte *st = ldsb + (k % 3) * kStageT;
+            Ops o0, o1;
+            if (wave < q.steps) load(o0, st, wave);
+            for (int s = wave; s < q.steps; s += 8) {
+                if (s + 4 < q.steps) load(o1, st, s + 4);
+                __builtin_amdgcn_sched_barrier(0);
+                step(o0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (s + 4 < q.steps) {
+                    if (s + 8 < q.steps) load(o0, st, s + 8);
+                    __builtin_amdgcn_sched_barrier(0);
+                    step(o1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __syncthreads();
+        }
+        // ---- the four waves' sums (each over its own pixels) through LDS, [wave][tap][input channel][output channel]
+        float *mine = (float *)lds + wave * (9 * 1024);
+#pragma unroll
+        for (int k = 0; k < 9; ++k)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) mine[k * 1024 + (8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)) * 32 + (lane & 31)] = acc[k][e];
+        __syncthreads();
+    }
+    // added in the order of the waves and written as the split's partial result
+    float *out = p.part + (size_t)sigma * split_stride(9, p.CinP, p.CoutP);
+    for (int i = threadIdx.x; i < 9 * 256; i += 512) {
+        const float4 *a = (const float4 *)lds + i;
+        const float4 v0 = a[0], v1 = a[9 * 256], v2 = a[2 * 9 * 256], v3 = a[3 * 9 * 256];
+        const float4 v = make_float4(((v0.x + v1.x) + v2.x) + v3.x, ((v0.y + v1.y) + v2.y) + v3.y, ((v0.z + v1.z) + v2.z) + v3.z,
+                                     ((v0.w + v1.w) + v2.w) + v3.w);
+        const int tap = i >> 8, row = (i >> 3) & 31, col = (i & 7) * 4;
+        *(float4 *)(out + ((size_t)tap * p.CinP + cb * 32 + row) * p.CoutP + ob * 32 + col) = v;
+    }
+}
+
+// ---- 1x1, stride 1: 64 x 64 channels per workgroup; the tiles are one run of pixels, whatever their shape
+constexpr int kRunPx = 128;                  // pixels of a stage: 16 KB of x and 16 KB of dout
+constexpr int kRunStage = 2 * kRunPx * 128;
+constexpr int kRunDepth = 4;                 // LDS buffers
+
+template <int DT>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void wgrad_run(WgradParams p) {
+    extern __shared__ __align__(16) char lds[];
+    lds_byte *const ldsb = (lds_byte *)lds;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int sigma = blockIdx.x % p.nsplit, cbob = blockIdx.x / p.nsplit;
+    const int cb = cbob / p.nob, ob = cbob - cb * p.nob;
+    int n = *p.count;
+    if (n > p.cap) n = p.cap;
+    const int ns = splits_used(n, p.nsplit, p.split_factor);
+    if (n <= 0 || sigma >= ns) return;
+    const long long px = (long long)n * p.th * p.tw;
+    const int total = (int)((px + kRunPx - 1) / kRunPx);
+    const int nst = sigma < total ? (total - sigma + ns - 1) / ns : 0;          // stages sigma, sigma + ns, ...
+
+    if (wave >= 4) {
+        // ---- moving: a copy is 8 pixels of 64 channels, 128 bytes each; piece k of pixel q lies at place k ^ 4 (q / 2 % 2), which
+        //      spreads the four pixels of a transposing read over all banks.  Wave w moves every fourth copy.
+        constexpr int N = kRunPx / 8 / 4;            // copies of either operand per wave and stage
+        const int q = (wave - 4) * 8 + (lane >> 3);
+        const int ch = ((lane & 7) ^ (((q >> 1) & 1) << 2)) * 8;
+        const uint32_t xrel = cb * 64 + ch < p.Cin ? (uint32_t)(q * p.Cin + cb * 64 + ch) * 2u : kOutOfRange;
+        const uint32_t grel = ob * 64 + ch < p.Cout ? (uint32_t)(q * p.Cout + ob * 64 + ch) * 2u : kOutOfRange;
+        auto move = [&](int k) __attribute__((always_inline)) {
+            const long long at = (long long)(sigma + (long long)k * ns) * kRunPx;
+            const uint32_t here = (uint32_t)min((long long)kRunPx, px - at);     // pixels beyond the run are outside the descriptors
+            const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)((const char *)p.x + at * p.Cin * 2), 0, (int)(here * p.Cin * 2u), kBufWord3);
+            const __amdgpu_buffer_rsrc_t gr = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)((const char *)p.g + at * p.Cout * 2), 0, (int)(here * p.Cout * 2u), kBufWord3);
+            lds_byte *to = ldsb + (k % kRunDepth) * kRunStage + (wave - 4) * 1024;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void *)(to + i * 4096), 16, (int)(xrel + (uint32_t)i * 64u * p.Cin), 0, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(gr, (lds_void *)(to + kRunPx * 128 + i * 4096), 16,
+                                                         (int)(grel + (uint32_t)i * 64u * p.Cout), 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        // (stages past the last one are not requested: then everything is waited for)
+        auto wait = [&](int k) __attribute__((always_inline)) {                  // until stage k has landed, k + 1 and k + 2 behind it
+            if (k + 2 < nst) __builtin_amdgcn_s_waitcnt(0x0F70 | ((4 * N) & 15) | (((4 * N) >> 4) << 14));
+            else if (k + 1 < nst) __builtin_amdgcn_s_waitcnt(0x0F70 | ((2 * N) & 15) | (((2 * N) >> 4) << 14));
+            else __builtin_amdgcn_s_waitcnt(0x0F70);
+        };
+        for (int k = 0; k < 3 && k < nst; ++k) move(k);
+        wait(0);
+        __builtin_amdgcn_s_barrier();
+        for (int k = 0; k < nst; ++k) {
+            if (k + 3 < nst) move(k + 3);
+            wait(k + 1);
+            __builtin_amdgcn_s_barrier();
+        }
+        __syncthreads();                             // (the sums below)
+    } else {
+        f32x16 acc[2][2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
+        const int l16 = lane & 15;
+        uint32_t at[2];                              // this lane's part of a read of channels 32 h .. + 31
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int piece = (h * 4 + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) ^ ((l16 >> 3) << 2);
+            at[h] = (uint32_t)(((lane >> 5) * 8 + (l16 >> 2)) * 128 + piece * 16 + (lane & 1) * 8);
+        }
+        __syncthreads();                             // stage 0
+        for (int k = 0; k < nst; ++k) {
+            const lds_byte *st = ldsb + (k % kRunDepth) * kRunStage + wave * 2 * 2048;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {            // 16 pixels each
+                uint4 x[2], g[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const lds_byte *a = st + s * 2048 + at[h], *b = a + kRunPx * 128;
+                    const uint2 a0 = read_tr(a), a1 = read_tr(a + 512), b0 = read_tr(b), b1 = read_tr(b + 512);
+                    x[h] = make_uint4(a0.x, a0.y, a1.x, a1.y);
+                    g[h] = make_uint4(b0.x, b0.y, b1.x, b1.y);
+                }
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) acc[a][b] = mfma32x32x16<DT>(x[a], g[b], acc[a][b]);
+            }
+            __syncthreads();
+        }
+        // ---- the four waves' sums (each over its own pixels) through LDS, [wave][input channel][output channel]
+        float *mine = (float *)lds + wave * 4096;
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    mine[(a * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)) * 64 + b * 32 + (lane & 31)] = acc[a][b][e];
+        __syncthreads();
+    }
+    float *out = p.part + (size_t)sigma * split_stride(1, p.CinP, p.CoutP);
+    for (int i = threadIdx.x; i < 1024; i += 512) {
+        const float4 *a = (const float4 *)lds + i;
+        const float4 v0 = a[0], v1 = a[1024], v2 = a[2048], v3 = a[3072];
+        const float4 v = make_float4(((v0.x + v1.x) + v2.x) + v3.x, ((v0.y + v1.y) + v2.y) + v3.y, ((v0.z + v1.z) + v2.z) + v3.z,
+                                     ((v0.w + v1.w) + v2.w) + v3.w);
+        *(float4 *)(out + (size_t)(cb * 64 + (i >> 4)) * p.CoutP + ob * 64 + (i & 15) * 4) = v;
+    }
+}
+
 template <int DT>
 __device__ __forceinline__ float load_elem(const void *p, size_t i) {
     if (DT == SBNET_F32) return ((const float *)p)[i];
@@ -366,8 +664,49 @@ struct WgradPlan {
     bool mfma;
     int kh, s, nseg, nsplit, ncb, nob, CinP, CoutP;
     bool flat;               // 1x1 at stride 1: the tile as one run of pixels
+    bool tile;               // wgrad_tile, with t
+    TilePlan t;
     size_t part_bytes;
 };
+
+// 3x3 stride 1: false where a stage does not hold a row of outputs
+bool plan_tile(int th, int tw, int oh, int ow, TilePlan *t) {
+    const int spr = (ow + 7) / 8, gp = 8 * spr, xp = gp + 2;
+    auto x_bytes = [&](long long rows, int tps) { return (tps * (rows + 2) * xp * 64 + 1023) / 1024 * 1024; };
+    auto g_bytes = [&](long long rows, int tps) { return (tps * rows * gp * 64 + 1023) / 1024 * 1024; };
+    auto fits = [&](long long rows, int tps) {
+        // (a fragment's last read goes up to 128 bytes beyond the rows of x, into those of dout)
+        return x_bytes(rows, tps) + g_bytes(rows, tps) <= kStageT && (x_bytes(rows, tps) + g_bytes(rows, tps)) / 1024 <= 4 * kCopiesT;
+    };
+    int R = spr % 2 ? (oh + 1) / 2 * 2 : oh;               // an even number of segments
+    t->tps = 1;
+    if (fits(R, 1)) {
+        while (t->tps < 4 && fits(R, t->tps + 1)) ++t->tps;
+    } else {
+        const int unit = spr % 2 ? 2 : 1;
+        R = R / unit * unit;
+        while (R > 0 && !fits(R, 1)) R -= unit;
+        if (R <= 0) return false;
+        const int slices = (oh + R - 1) / R;               // slices of about the same height
+        R = ((oh + slices - 1) / slices + unit - 1) / unit * unit;
+    }
+    t->R = R;
+    t->slices = (oh + R - 1) / R;
+    t->spr = spr;
+    t->xp = xp;
+    t->gp = gp;
+    t->x_copies = (int)(x_bytes(R, t->tps) / 1024);
+    t->copies = t->x_copies + (int)(g_bytes(R, t->tps) / 1024);
+    t->steps = t->tps * R * spr / 2;
+    t->div_xt = make_fastdiv((uint32_t)((R + 2) * xp));
+    t->div_xp = make_fastdiv((uint32_t)xp);
+    t->div_gt = make_fastdiv((uint32_t)(R * gp));
+    t->div_gp = make_fastdiv((uint32_t)gp);
+    t->div_spr = make_fastdiv((uint32_t)spr);
+    t->div_seg = make_fastdiv((uint32_t)(R * spr));
+    t->div_slices = make_fastdiv((uint32_t)t->slices);
+    return true;
+}
 
 bool plan_wgrad(sbnet_dtype dt, int cap, int th, int tw, int Cin, int kh, int kw, int sh, int sw, int Cout, WgradPlan *q) {
     const int oh = (th - kh) / sh + 1, ow = (tw - kw) / sw + 1;
@@ -377,16 +716,40 @@ bool plan_wgrad(sbnet_dtype dt, int cap, int th, int tw, int Cin, int kh, int kw
               Cout % 8 == 0 && (q->flat || (ow <= 32 && tw <= 32 * sw + 2)) &&
               (long long)th * tw * Cin * 2 < (1LL << 30) && (long long)oh * ow * Cout * 2 < (1LL << 30);
     q->kh = kh;
-    if (q->mfma) {
+    q->tile = (dt == SBNET_BF16 || dt == SBNET_F16) && kh == 3 && kw == 3 && sh == 1 && sw == 1 && Cin % 8 == 0 && Cout % 8 == 0 &&
+              4LL * th * tw * Cin * 2 < (1LL << 30) && 4LL * oh * ow * Cout * 2 < (1LL << 30) &&
+              plan_tile(th, tw, oh, ow, &q->t);
+    if (q->tile && q->mfma) {
+        // Long lists of tiles that 64 x 64 blocks and 16-pixel rows fit: wgrad_mfma, which stages a pixel once for twice the
+        // channels (64 -> 64, tiles of 16 x 16: 14.1 ns a tile against 19.1), though it starts and ends slower (its partial
+        // results are two to four times as many bytes): us by it and by wgrad_tile, 440 tiles 24.7 and 20.4, 2200 49.6 and
+        // 54.1; 128 -> 128, 165 tiles 27.5 and 25.6, 440 42.6 and 46.1; 256 -> 256, 60 tiles 37.7 and 37.7, 440 125 and 155.  The
+        // line lies at 1000 tiles of 256 pixels by the number of 64 x 64 blocks.  Where more than a fifth of its work is
+        // padding wgrad_tile wins at any length (2200 tiles: 96 -> 96 147 and 116, 32 -> 32 46.7 and 24.0, 64 -> 64 of 8 x 8
+        // 35.2 and 22.7).
+        const long long p64 = (long long)((Cin + 63) / 64) * ((Cout + 63) / 64), p32 = (long long)((Cin + 31) / 32) * ((Cout + 31) / 32);
+        const long long px16 = ow <= 16 ? (oh + 7LL) / 8 * 8 * 16 : (oh + 3LL) / 4 * 4 * 32, px8 = (long long)q->t.slices * q->t.R * q->t.gp;
+        if (p32 * px8 * 10 >= p64 * 4 * px16 * 8 && (long long)cap * oh * ow * p64 > 1000 * 256) q->tile = false;
+    }
+    if (q->tile) {
+        q->s = q->nseg = 1;
+        q->ncb = (Cin + 31) / 32;
+        q->nob = (Cout + 31) / 32;
+        q->CinP = q->ncb * 32;
+        q->CoutP = q->nob * 32;
+        q->nsplit = 256 / (q->ncb * q->nob);               // one workgroup per CU
+        if (q->nsplit > 8) q->nsplit = q->nsplit / 8 * 8;  // splits of one channel block share an XCD's L2 with the others
+        if (q->nsplit < 1) q->nsplit = 1;
+    } else if (q->mfma) {
         q->s = sh;
         q->nseg = q->flat || (ow <= 16 && tw <= 16 * sw + 2) ? 1 : 2;
         q->ncb = (Cin + 63) / 64;
         q->nob = (Cout + 63) / 64;
         q->CinP = q->ncb * 64;
         q->CoutP = q->nob * 64;
-        // one workgroup per CU for 3x3 (its two stages take 100 KB of LDS); two for 1x1 (70 KB), whose stages hold
-        // little matrix work and wait on memory: the second workgroup's loads fill that wait
-        int ns = (kh == 1 ? 512 : 256) / (q->ncb * q->nob);
+        // one workgroup per CU for 3x3 (its two stages take 100 KB of LDS) and wgrad_run (its four 128 KB); two for strided 1x1
+        // (70 KB), whose stages hold little matrix work and wait on memory: the second workgroup's loads fill that wait
+        int ns = (kh == 1 && !q->flat ? 512 : 256) / (q->ncb * q->nob);
         ns = ns / 8 * 8;                                   // splits of one channel block share an XCD's L2 with the others
         if (ns < 8) ns = 8;
         q->nsplit = ns;
@@ -416,16 +779,29 @@ void launch_mfma(const WgradParams &p, hipStream_t s) {
 
 template <int DT>
 void launch_mfma_dt(const WgradPlan &q, const WgradParams &p, hipStream_t s) {
+    if (q.kh == 1 && q.flat) {
+        constexpr int bytes = kRunDepth * kRunStage;
+        static_assert(bytes >= 4 * 4096 * 4 && bytes <= 160 * 1024, "the stages; the four waves' sums");
+        (void)hipFuncSetAttribute((const void *)wgrad_run<DT>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        hipLaunchKernelGGL(wgrad_run<DT>, dim3(p.nsplit * p.ncb * p.nob), dim3(512), bytes, s, p);
+        return;
+    }
+    if (q.tile) {
+        constexpr int bytes = 3 * kStageT;
+        static_assert(bytes >= 4 * 9 * 1024 * 4 && bytes <= 160 * 1024, "three stages; the four waves' sums");
+        (void)hipFuncSetAttribute((const void *)wgrad_tile<DT>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        hipLaunchKernelGGL(wgrad_tile<DT>, dim3(p.nsplit * p.ncb * p.nob), dim3(512), bytes, s, p, q.t);
+        return;
+    }
     if (q.kh == 3) {
         if (q.s == 1 && q.nseg == 1) launch_mfma<DT, 3, 1, 1>(p, s);
         else if (q.s == 1) launch_mfma<DT, 3, 1, 2>(p, s);
         else if (q.nseg == 1) launch_mfma<DT, 3, 2, 1>(p, s);
         else launch_mfma<DT, 3, 2, 2>(p, s);
+    } else if (q.nseg == 1) {
+        launch_mfma<DT, 1, 2, 1>(p, s);
     } else {
-        if (q.s == 1 && q.nseg == 1) launch_mfma<DT, 1, 1, 1>(p, s);
-        else if (q.s == 1) launch_mfma<DT, 1, 1, 2>(p, s);
-        else if (q.nseg == 1) launch_mfma<DT, 1, 2, 1>(p, s);
-        else launch_mfma<DT, 1, 2, 2>(p, s);
+        launch_mfma<DT, 1, 2, 2>(p, s);
     }
 }
 
@@ -466,14 +842,8 @@ extern "C" sbnet_status sbnet_conv_on_tiles_backward_weights(const void *tiles_i
     p.split_factor = taps == 1 ? tune.wgrad_split_factor_1x1 : tune.wgrad_split_factor_3x3;
     p.x_tile_bytes = (uint32_t)((size_t)th * tw * Cin * 2);
     p.g_tile_bytes = (uint32_t)((size_t)p.oh * p.ow * Cout * 2);
-    if (q.mfma && q.flat) {
-        // 1x1 at stride 1 pairs pixel with pixel, whatever the tile's shape: the matrix kernel sees rows of 16 pixels
-        // (the tile sizes in bytes stay the true ones, so the pixels past the end of the last row read as zeros)
-        p.th = p.oh = (th * tw + 15) / 16;
-        p.tw = p.ow = 16;
-    }
     if (cap > 0) {
-        if (q.mfma) {
+        if (q.mfma || q.tile) {
             if (dtype == SBNET_BF16) launch_mfma_dt<SBNET_BF16>(q, p, s);
             else launch_mfma_dt<SBNET_F16>(q, p, s);
         } else {

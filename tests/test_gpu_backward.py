@@ -111,6 +111,38 @@ def test_conv_on_tiles_backward_weights(B, th, tw, Cin, Cout, k, s, dtype):
             assert torch.equal(dw, dw2)                  # fixed summation order: the same bits again
 
 
+@pytest.mark.parametrize("B,cap,oh,ow,Cin,Cout,k,dtype", [
+    (7, 7, 8, 8, 64, 64, 3, "bf16"),       # four tiles to a stage, the last stage holds three
+    (9, 12, 5, 7, 40, 24, 3, "f16"),       # one segment a row and an odd number of rows: a row of zeros
+    (5, 5, 1, 1, 8, 8, 3, "bf16"),
+    (3, 3, 3, 40, 32, 72, 3, "bf16"),      # five segments a row
+    (2, 2, 41, 37, 64, 32, 3, "f16"),      # tiles in slices, the last one short
+    (2, 2, 3, 170, 8, 40, 3, "bf16"),      # a row or two to a slice
+    (70, 70, 12, 12, 96, 96, 3, "bf16"),   # more tiles than splits of nine channel blocks
+    (30, 1100, 16, 16, 64, 64, 3, "bf16"), # a list bound that takes the kernel for long lists
+    (300, 300, 4, 4, 16, 16, 3, "f16"),    # fewer stages than splits
+    (5, 9, 9, 15, 72, 64, 1, "f16"),       # runs of pixels that end inside a stage
+    (64, 64, 16, 16, 64, 136, 1, "bf16"),
+    (3, 3, 2, 3, 256, 8, 1, "bf16"),       # less than a stage
+])
+def test_weight_gradient_stages(B, cap, oh, ow, Cin, Cout, k, dtype):
+    step("weight gradient, stages %s" % ((B, cap, oh, ow, Cin, Cout, k, dtype),))
+    r = gen.rng_for(6, oh * 1000 + ow * 10 + Cin + Cout)
+    x = gen.activations(r, (cap, oh + k - 1, ow + k - 1, Cin), dtype)
+    g = gen.activations(r, (cap, oh, ow, Cout), dtype)
+    xd, gd = to_dev(x, dtype), to_dev(g, dtype)
+    # what lies beyond the count is not read
+    xd[B:] = float("nan")
+    gd[B:] = float("nan")
+    for n in (B, B - 1, 1):
+        cnt = torch.tensor([n], dtype=torch.int32).cuda()
+        dw = sb.conv_on_tiles_backward_weights(xd, gd, cnt, k)
+        want = orc.conv_valid_backward_weights(x[:n], g[:n], k, k)
+        # products are exact in fp32, sums of n oh ow of them in any order
+        assert_close(to_host(dw), want, 1e-4, "weight gradient, %d tiles" % n)
+        assert torch.equal(dw, sb.conv_on_tiles_backward_weights(xd, gd, cnt, k))
+
+
 def test_sparse_conv_gradients_end_to_end():
     """dL/dx and dL/dw of the whole sparse convolution from library calls only: gather of dL/dy with the output
     geometry, data gradient on tiles, gather_backward into the image; gather of x, weight gradient on the two tile
