@@ -3,9 +3,9 @@
 // gather of the input tile and the scatter (or scatter-add, Sec. 3.4) of the output block
 // happen inside the same kernel, so the tile stacks never reach HBM.
 //
-// Two kernels here, three more behind conv16_try / conv3_try (conv16.hip: 3x3 stride 1 on tiles whose sides are
-// multiples of 16 with 32 or 64 input channels; conv3.hip: every other 3x3 case the 16-bit matrix instructions can
-// take) and conv_f32_try (conv_f32.hip: fp32 arithmetic, for float32 and for channel counts the 16-bit kernels do not
+// Two kernels here, four more behind conv_wave_try / conv16_try / conv3_try (conv_wave.hip: 3x3 of stride 1 or 2 where the
+// weights fit LDS; conv16.hip: 3x3 stride 1 on tiles whose sides are multiples of 16 with 32 or 64 input channels; conv3.hip:
+// every other 3x3 case the 16-bit matrix instructions can take) and conv_f32_try (conv_f32.hip: fp32 arithmetic, for float32 and for channel counts the 16-bit kernels do not
 // take), which are asked first:
 //   conv_direct  any shape, any of f32/bf16/f16: one thread per output element, fp32 FMA chain.
 //                For few products per pixel (direct_is_faster) and for tiles so wide that the rows of 64 output pixels do

@@ -173,7 +173,7 @@ enum class ConvForm {
 // `mask` is refused where the plain form runs in another order of summation than the kernels with a mask have.
 bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t s, sbnet_status *st, const char *who,
                ConvForm form = ConvForm::plain);
-// conv_wave.hip: the same contract for 3x3 stride-1 layers whose weights stay in LDS.
+// conv_wave.hip: the same contract for 3x3 layers of stride 1 or 2 whose weights stay in LDS.
 bool conv_wave_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t s, sbnet_status *st, const char *who,
                    ConvForm form = ConvForm::plain);
 

@@ -1,4 +1,4 @@
-// 3x3 stride-1 tile convolution, bf16 / f16, for layers whose weights stay in LDS: all input channels by a group of 32, 64
+// 3x3 tile convolution of stride 1 or 2, bf16 / f16, for layers whose weights stay in LDS: all input channels by a group of 32, 64
 // or 96 output channels, at most about 100 KB (Sec. 3.2 and 3.4 of arXiv 1801.02108: the regular convolution between
 // gather and scatter; fused with both, and as the data gradient of a tile convolution).
 //
@@ -19,6 +19,9 @@
 // Measured, conv3 -> this (400 x 352, bf16, us): 64 -> 64, blocks of 8, 5 % active 6.6 -> 5.5, 20 % 9.3 -> 6.7, all 26.4 -> 16.2;
 // blocks of 14 7.7 -> 5.7, 9.3 -> 8.7, 18.2 -> 17.2; 32 -> 32, blocks of 14, all 11.9 -> 8.2 (4.4 TB/s: memory); 48 -> 80, blocks
 // of 12, 30 % 16.7 -> 12.2, all 26.9 -> 23.4; 1600 x 1408, half of all blocks, 64 -> 64 blocks of 12 142 -> 113, of 14 112 -> 109.
+//   * Stride 2: items of 32 pixels (their rows are twice as many and twice as wide), chunks of 16 channels (so that 64 -> 96 keeps
+//     all its weights beside eight buffers), the even columns of a row before its odd ones.  conv3 -> this: 800 x 704 to
+//     400 x 352, blocks of 16, 64 -> 96, 5 % active 9.1 -> 7.4, 30 % 18.3 -> 12.5; 32 -> 32, all 17.6 -> 11.7.
 // What bounds it at many items: matrix steps 37 % of the time, LDS 34 %, the address unit (copies of 64-byte pieces, stores)
 // 40 %, vector instructions 39 %; with fewer than two items per wave the latency of an item and the copy of the weights.
 // The sum over (chunk of 32 channels, tap, 16 channels) runs in the order of conv3's 32-channel chunks: same bits.
@@ -52,17 +55,21 @@ typedef __attribute__((address_space(3))) unsigned char lds_byte;      // (a poi
 // The 16-byte piece k of staged pixel q is kept at place k ^ place_key(q) of the pixel's 64 bytes.  Sixteen neighbouring
 // pixels take four keys, eight neighbouring ones, read together with the next piece, two that differ in bit 1: either
 // way the lanes of a read cover all banks.
-__device__ __forceinline__ uint32_t place_key(uint32_t px) { return ((px >> 1) & 2u) | ((px >> 3) & 1u); }
+// At stride 2 a pixel has two pieces (16 channels a chunk), and the even columns of a row are staged before its odd ones: the
+// pixels of a read are neighbours again.
+template <int STR>
+__device__ __forceinline__ uint32_t place_key(uint32_t px) { return STR == 2 ? (px >> 3) & 1u : ((px >> 1) & 2u) | ((px >> 3) & 1u); }
 
 // The items start + wave, start + wave + 8, ... below end, 32 PBW pixels by CBW blocks of 32 channels each.
 // request_weights: copies the group's weights and its bias to LDS.
-template <int DT, bool FUSED, bool ADD, int NB, int EPI, int CBW, int PBW, typename Weights>
+template <int DT, bool FUSED, bool ADD, int NB, int EPI, int STR, int CBW, int PBW, typename Weights>
 __device__ __forceinline__ void wave_items(const ConvParams &p, const PlanW &q, unsigned char *lds, uint32_t start, uint32_t end,
                                            int ng, const Weights &request_weights) {
     constexpr bool OWN = FUSED && EPI != kWavePlain;
     constexpr int SM = PBW == 2 ? 0 : CBW == NB ? 1 : 2;      // which of the plan's item sizes
     constexpr int SPLIT = NB / CBW;                  // items that share their pixels
     constexpr int PP = PBW * 32;
+    constexpr int CC = STR == 2 ? 16 : 32, CV = CC / 8;       // channels per chunk; 16-byte pieces of a staged pixel
     constexpr int D = CBW * PBW >= 6 ? 1 : 2;        // steps the fragment reads run ahead of the matrix steps
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -70,7 +77,7 @@ __device__ __forceinline__ void wave_items(const ConvParams &p, const PlanW &q, 
     const int M = p.oh * p.ow;
     unsigned char *buf = lds + q.buf_off + wave * q.buf_bytes;
     lds_byte *buf_l = (lds_byte *)lds + (q.buf_off + wave * q.buf_bytes);
-    const int nchunks = (q.nks + 1) >> 1;
+    const int nchunks = STR == 2 ? q.nks : (q.nks + 1) >> 1;
 
     struct Item { uint32_t b; int pass, cb0, n, by, bx; };
     int lane_zero = 0;                               // (a per-lane load of a uniform address: not waited for on the spot)
@@ -105,20 +112,22 @@ __device__ __forceinline__ void wave_items(const ConvParams &p, const PlanW &q, 
     // Copy i moves 16-byte place lane % 4 of staged pixel 16 i + lane / 4 (row by row, tw pixels each): off, relative to the
     // item's first pixel and the chunk's first channel.  Worked out once where registers allow: an item's copies are
     // issued back to back.
-    constexpr bool KEEP = PBW == 2 && NB < 3;
+    constexpr bool KEEP = STR == 2 || (PBW == 2 && NB < 3);
     struct Place { uint32_t off; int col, ch; };
     auto place_of = [&](int i, int ln) __attribute__((always_inline)) {
-        const uint32_t px = (uint32_t)(i * 16 + (ln >> 2));
-        const uint32_t row = fdiv(px, p.div_tw), col = px - row * p.tw;
-        const uint32_t piece = (uint32_t)(ln & 3) ^ place_key(px);
+        const uint32_t px = (uint32_t)(i * (64 / CV) + ln / CV);
+        const uint32_t row = fdiv(px, p.div_tw), slot = px - row * p.tw, even = (uint32_t)(p.tw + 1) >> 1;
+        const uint32_t col = STR == 1 ? slot : slot < even ? 2 * slot : 2 * (slot - even) + 1;
+        const uint32_t piece = (uint32_t)(ln & (CV - 1)) ^ place_key<STR>(px);
         return Place{((row * in_w + col) * p.Cin + piece * 8) * 2u, (int)col, (int)piece * 8};
     };
     uint32_t gd[KEEP ? kCopiesW : 1];
-    // rows of channels 32 c .. of an item -> the wave's buffer
+    constexpr int PK = PBW == 2 ? 0 : 1;             // which of the plan's copy counts
+    // rows of channels CC c .. of an item -> the wave's buffer
     auto stage = [&](const Item &c, int chunk) __attribute__((always_inline)) {
         const int r_lo = (int)fdiv((uint32_t)c.pass * PP, p.div_ow);
         const uint16_t *base = (const uint16_t *)p.in;
-        int x0 = 0, y0 = r_lo;
+        int x0 = 0, y0 = r_lo * STR;
         if (FUSED) {
             y0 += p.g_in.boffset_h + c.by * p.g_in.bstride_h;
             x0 = p.g_in.boffset_w + c.bx * p.g_in.bstride_w;
@@ -127,20 +136,20 @@ __device__ __forceinline__ void wave_items(const ConvParams &p, const PlanW &q, 
             base += (long long)c.b * p.th * p.tw * p.Cin;
         }
         // (rows outside the image are outside the descriptor: the offset wraps below zero above it)
-        const uint32_t origin = (uint32_t)((y0 * in_w + x0) * p.Cin + chunk * 32) * 2u;
+        const uint32_t origin = (uint32_t)((y0 * in_w + x0) * p.Cin + chunk * CC) * 2u;
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)in_bytes, (int)kBufWord3);
         if constexpr (KEEP) {
-            if (x0 >= 0 && x0 + p.tw <= in_w && chunk * 32 + 32 <= p.Cin) {              // no lane to leave out
+            if (x0 >= 0 && x0 + p.tw <= in_w && chunk * CC + CC <= p.Cin) {              // no lane to leave out
 #pragma unroll
                 for (int i = 0; i < kCopiesW; ++i)
-                    if (i < q.copies[0])
+                    if (i < q.copies[PK])
                         __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(buf_l + i * 1024), 16, (int)(origin + gd[i]), 0, 0, 0);
                 return;
             }
         }
-        for (int i = 0; i < q.copies[PBW == 2 ? 0 : 1]; ++i) {
+        for (int i = 0; i < q.copies[PK]; ++i) {
             const Place t = place_of(i, lane);
-            const bool ok = (uint32_t)(x0 + t.col) < (uint32_t)in_w && chunk * 32 + t.ch < p.Cin;
+            const bool ok = (uint32_t)(x0 + t.col) < (uint32_t)in_w && chunk * CC + t.ch < p.Cin;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(buf_l + i * 1024), 16, (int)(ok ? origin + t.off : kOutOfRange), 0, 0, 0);
         }
     };
@@ -157,7 +166,7 @@ __device__ __forceinline__ void wave_items(const ConvParams &p, const PlanW &q, 
     if constexpr (KEEP) {
 #pragma unroll
         for (int i = 0; i < kCopiesW; ++i) {
-            gd[i] = i < q.copies[0] ? place_of(i, lane).off : 0u;
+            gd[i] = i < q.copies[PK] ? place_of(i, lane).off : 0u;
             asm volatile("" : "+v"(gd[i]));          // opaque: kept as it is, not regrouped with the origins
         }
     }
@@ -183,7 +192,7 @@ __device__ __forceinline__ void wave_items(const ConvParams &p, const PlanW &q, 
             for (int pb = 0; pb < PBW; ++pb) {
                 const uint32_t px = min(p_lo + (uint32_t)(pb * 32 + m), (uint32_t)M - 1u);
                 const uint32_t i = fdiv(px, p.div_ow), j = px - i * p.ow;
-                xlin[pb] = (i - i_lo) * p.tw + j;
+                xlin[pb] = (i - i_lo) * STR * p.tw + j;
             }
             if (fresh) {
                 __builtin_amdgcn_s_waitcnt(0);
@@ -208,7 +217,7 @@ __device__ __forceinline__ void wave_items(const ConvParams &p, const PlanW &q, 
         __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): the chunk's rows are in LDS
         auto steps = [&](auto kst_tag) __attribute__((always_inline)) {
             constexpr int KST = decltype(kst_tag)::value, NS = 9 * KST;
-            const unsigned char *WL = lds + (chunk * 18 * NB + cur.cb0) * 1024 + lane * 16;
+            const unsigned char *WL = lds + (chunk * (STR == 2 ? 9 : 18) * NB + cur.cb0) * 1024 + lane * 16;
             uint4 xa[D + 1][CBW], xb[D + 1][PBW];
             uint32_t xl[PBW];
 #pragma unroll
@@ -222,8 +231,9 @@ __device__ __forceinline__ void wave_items(const ConvParams &p, const PlanW &q, 
                 for (int cb = 0; cb < CBW; ++cb) xa[slot][cb] = *(const uint4 *)(WL + (s * NB + cb) * 1024);
 #pragma unroll
                 for (int pb = 0; pb < PBW; ++pb) {
-                    const uint32_t lin = xl[pb] + (uint32_t)((tap / 3) * p.tw + tap % 3);
-                    xb[slot][pb] = *(const uint4 *)(buf + lin * 64 + (((uint32_t)(ks * 2 + g) ^ place_key(lin)) * 16));
+                    const uint32_t dx = STR == 1 ? tap % 3 : tap % 3 == 1 ? (uint32_t)(p.tw + 1) >> 1 : tap % 3 >> 1;
+                    const uint32_t lin = xl[pb] + (uint32_t)((tap / 3) * p.tw) + dx;
+                    xb[slot][pb] = *(const uint4 *)(buf + lin * (CC * 2) + (((uint32_t)(ks * 2 + g) ^ place_key<STR>(lin)) * 16));
                 }
             };
 #pragma unroll
@@ -240,7 +250,7 @@ __device__ __forceinline__ void wave_items(const ConvParams &p, const PlanW &q, 
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        if (2 * chunk + 1 < q.nks) steps(std::integral_constant<int, 2>{});
+        if (STR == 1 && 2 * chunk + 1 < q.nks) steps(std::integral_constant<int, 2>{});
         else steps(std::integral_constant<int, 1>{});
         if (++chunk < nchunks) {
             __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): every read of the buffer has been answered
@@ -355,7 +365,7 @@ __device__ __forceinline__ void wave_items(const ConvParams &p, const PlanW &q, 
     }
 }
 
-template <int DT, bool FUSED, bool ADD, int NB, int EPI>
+template <int DT, bool FUSED, bool ADD, int NB, int EPI, int STR>
 __global__ __launch_bounds__(64 * kWavesW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void conv_wave_kernel(ConvParams p, PlanW q) {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -375,7 +385,7 @@ void conv_wave_kernel(ConvParams p, PlanW q) {
     auto rounds = [&](int k) __attribute__((always_inline)) {
         return (fdiv(nact * q.div_item[k].d + wgs - 1, q.div_wgs) + 3) >> 2;
     };
-    const uint32_t c64 = rounds(0) * (16 * NB), c32 = NB > 1 ? rounds(1) * (NB == 2 ? 18u : 24u) : ~0u, c1 = rounds(2) * 14u;
+    const uint32_t c64 = STR == 2 ? ~0u : rounds(0) * (16 * NB), c32 = NB > 1 ? rounds(1) * (NB == 2 ? 18u : 24u) : ~0u, c1 = rounds(2) * 14u;
     const int kind = c64 <= c32 && c64 <= c1 ? 0 : c32 <= c1 ? 1 : 2;
     const uint32_t items = nact * q.div_item[kind].d;
     const uint32_t each = fdiv(items, q.div_wgs), extra = items - each * wgs;
@@ -389,11 +399,12 @@ void conv_wave_kernel(ConvParams p, PlanW q) {
     auto weights = [&]() __attribute__((always_inline)) {
     const int nblk = 9 * q.nks * NB;
     for (int b = wave; b < nblk; b += kWavesW) {
-        const int s = b / NB, cb = b - s * NB, c = s / 18, r = s - c * 18;
-        const bool full = 2 * c + 1 < q.nks;
+        const int s = b / NB, cb = b - s * NB;
+        const int c = STR == 2 ? s / 9 : s / 18, r = s - c * (STR == 2 ? 9 : 18);
+        const bool full = STR == 1 && 2 * c + 1 < q.nks;
         const int tap = full ? r >> 1 : r, ks = full ? r & 1 : 0;
         const uint32_t nbk = (uint32_t)(ng * NB + cb);
-        const uint32_t off = (nbk >> 1) * (uint32_t)q.ks16 * 2048u + (uint32_t)(tap * q.cin16 + 2 * c + ks) * 2048u + (nbk & 1u) * 1024u;
+        const uint32_t off = (nbk >> 1) * (uint32_t)q.ks16 * 2048u + (uint32_t)(tap * q.cin16 + (STR == 2 ? c : 2 * c + ks)) * 2048u + (nbk & 1u) * 1024u;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lds_void *)((lds_byte *)lds + b * 1024), 16, (int)(off + lane * 16), 0, 0, 0);
     }
     {
@@ -402,27 +413,29 @@ void conv_wave_kernel(ConvParams p, PlanW q) {
         if (i < NB * 32) bl[i] = (p.bias && o < p.Cout) ? p.bias[o] : 0.f;
     }
     };
-    if (kind == 0) {
-        wave_items<DT, FUSED, ADD, NB, EPI, NB, 2>(p, q, lds, start, end, ng, weights);
-        return;
-    }
-    if constexpr (NB > 1) {
-        if (kind == 1) {
-            wave_items<DT, FUSED, ADD, NB, EPI, NB, 1>(p, q, lds, start, end, ng, weights);
+    if constexpr (STR == 1) {
+        if (kind == 0) {
+            wave_items<DT, FUSED, ADD, NB, EPI, STR, NB, 2>(p, q, lds, start, end, ng, weights);
             return;
         }
     }
-    wave_items<DT, FUSED, ADD, NB, EPI, 1, 1>(p, q, lds, start, end, ng, weights);
+    if constexpr (NB > 1) {
+        if (kind == 1) {
+            wave_items<DT, FUSED, ADD, NB, EPI, STR, NB, 1>(p, q, lds, start, end, ng, weights);
+            return;
+        }
+    }
+    wave_items<DT, FUSED, ADD, NB, EPI, STR, 1, 1>(p, q, lds, start, end, ng, weights);
 }
 
 // ------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------
-template <int DT, bool FUSED, bool ADD, int EPI>
+template <int DT, bool FUSED, bool ADD, int EPI, int STR>
 static void launch_wave_nb(int nb, const ConvParams &p, const PlanW &q, int grid, size_t lds, hipStream_t s) {
 #define SBNET_LW(NB)                                                                                                      \
     do {                                                                                                                  \
-        auto kern = conv_wave_kernel<DT, FUSED, ADD, NB, EPI>;                                                            \
+        auto kern = conv_wave_kernel<DT, FUSED, ADD, NB, EPI, STR>;                                                            \
         (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);              \
         hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * kWavesW), lds, s, p, q);                                 \
     } while (0)
@@ -433,22 +446,29 @@ static void launch_wave_nb(int nb, const ConvParams &p, const PlanW &q, int grid
 }
 template <int DT>
 static void launch_wave(bool fused, ConvForm form, int nb, const ConvParams &p, const PlanW &q, int grid, size_t lds, hipStream_t s) {
-    if (form == ConvForm::own) launch_wave_nb<DT, true, false, kWaveOwn>(nb, p, q, grid, lds, s);
-    else if (form == ConvForm::mask) launch_wave_nb<DT, true, false, kWaveMask>(nb, p, q, grid, lds, s);
-    else if (fused && p.add) launch_wave_nb<DT, true, true, kWavePlain>(nb, p, q, grid, lds, s);
-    else if (fused) launch_wave_nb<DT, true, false, kWavePlain>(nb, p, q, grid, lds, s);
-    else launch_wave_nb<DT, false, false, kWavePlain>(nb, p, q, grid, lds, s);
+    if (form == ConvForm::own) launch_wave_nb<DT, true, false, kWaveOwn, 1>(nb, p, q, grid, lds, s);
+    else if (form == ConvForm::mask) launch_wave_nb<DT, true, false, kWaveMask, 1>(nb, p, q, grid, lds, s);
+#define SBNET_LWS(STR)                                                                                 \
+    do {                                                                                               \
+        if (fused && p.add) launch_wave_nb<DT, true, true, kWavePlain, STR>(nb, p, q, grid, lds, s);   \
+        else if (fused) launch_wave_nb<DT, true, false, kWavePlain, STR>(nb, p, q, grid, lds, s);      \
+        else launch_wave_nb<DT, false, false, kWavePlain, STR>(nb, p, q, grid, lds, s);                \
+    } while (0)
+    else if (p.sh == 2) SBNET_LWS(2);
+    else SBNET_LWS(1);
+#undef SBNET_LWS
 }
 
 bool conv_wave_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t s, sbnet_status *st, const char *who, ConvForm form) {
     if (dt != SBNET_BF16 && dt != SBNET_F16) return false;
-    if (p.kh != 3 || p.kw != 3 || p.sh != 1 || p.sw != 1 || p.Cin % 8 != 0 || p.Cout % 8 != 0) return false;
-    if (form == ConvForm::inside || (form != ConvForm::plain && (!fused || p.add))) return false;
+    if (p.kh != 3 || p.kw != 3 || p.sh != p.sw || (p.sh != 1 && p.sh != 2) || p.Cin % 8 != 0 || p.Cout % 8 != 0) return false;
+    if (form == ConvForm::inside || (form != ConvForm::plain && (!fused || p.add || p.sh != 1))) return false;
     // byte offsets inside one sample (fused) or one tile are kept in 32 bits and checked by the hardware
     // against a buffer descriptor of that size
     if ((fused ? (long long)p.H * p.W : (long long)p.th * p.tw) * p.Cin >= (1LL << 30)) return false;
     if ((fused ? (long long)p.Ho * p.Wo : (long long)p.oh * p.ow) * p.Cout >= (1LL << 30)) return false;
     const long long M = (long long)p.oh * p.ow;
+    const bool strided = p.sh == 2;
     PlanW q = {};
     const int CinP = (p.Cin + 31) / 32 * 32, blocks = (p.Cout + 31) / 32;
     q.nks = (p.Cin + 15) / 16;
@@ -464,9 +484,19 @@ bool conv_wave_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t 
         // input rows that pp consecutive output pixels can touch
         long long rows = (pp + p.ow - 1) / p.ow + ((pp % p.ow) ? 1 : 0);
         if (rows > p.oh) rows = p.oh;
-        rows += 2;
-        q.copies[v] = (int)((rows * p.tw * 4 + 63) / 64);
-        if (rows * p.tw > kCopiesW * 16) return false;
+        if (strided) {
+            if (v == 0) continue;                    // (items of 32 pixels only)
+            if (rows > 1 && ((rows - 2) * 2 + 3) * p.tw > kCopiesW * 32) return false;
+            long long most = 1;                      // (exactly: where an item begins in a row repeats after at most ow items)
+            for (long long k = 0; k < passes[1] && k < p.ow; ++k) {
+                const long long last = 32 * k + 31 < M ? 32 * k + 31 : M - 1, r = last / p.ow - 32 * k / p.ow + 1;
+                if (r > most) most = r;
+            }
+            rows = most;
+        }
+        rows = (rows - 1) * p.sh + 3;
+        q.copies[v] = (int)((rows * p.tw * (strided ? 2 : 4) + 63) / 64);
+        if (q.copies[v] > kCopiesW) return false;
         if (q.copies[v] * 1024LL > buf) buf = q.copies[v] * 1024LL;
     }
     if (buf < 32 * kOstPsW) buf = (32 * kOstPsW + 15) / 16 * 16;
@@ -479,15 +509,31 @@ bool conv_wave_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t 
     if (nb == 0) return false;
     q.ngroups = (blocks + nb - 1) / nb;
     if (q.ngroups > 2) return false;
+    // Stride 2: blocks' pixels (in 16 x 16 blocks of the list's bound) beyond which conv3 is as fast.  Up to 48 input channels here
+    // at any number (1600 x 1408, half of 2200 blocks of 16: 32 -> 64 28.9 us by conv3 and 26.9 here, 48 -> 96 48.6 and 43.2), but
+    // for rows so wide that an item stages more than 8 KB a chunk (800 x 704, 32 -> 64, blocks of 14, 60 % 12.4 and 11.4, all 17.0
+    // and 18.4).  From 64 channels a line of memory is fetched once for each of its four chunks, and long lists wait for that.
+    // 800 x 704 (550 blocks of 16): groups of 96, 64 -> 96, 10 x 10, 30 % 17.2 and 13.9, all 41.4 and 40.1, 16 x 16 18.3 and 12.5,
+    // 38.2 and 37.1, half of 1600 x 1408 64.2 and 71.3; small blocks of more than 64 channels, for which conv3 has no wide
+    // group, 64 -> 128, 8 x 8, all 53.3 and 36.7; 64 -> 64 on blocks that fill their items, 16 x 16, 5 % 9.1 and 6.1, 30 %
+    // 16.6 and 10.9, 60 % 21.7 and 22.4, all 40.1 and 35.2; else 12 x 12, 30 % 20.5 and 12.9, 60 % 22.8 and 26.4; blocks that fill their items badly, 10 x 10, 64 -> 128, 5 % 8.8 and 8.2, 15 % 10.9 and 11.4, 14 x 14
+    // 10.4 and 9.0, 12.6 and 12.6; two groups of 32, 96 -> 64, 14 x 14, 5 % 14.1 and 9.5, 15 % 14.3 and 15.4.
+    if (strided) {
+        const long long most = q.nks <= 3 ? (q.copies[1] > 8 ? 400 : 1LL << 40)
+                             : nb == 3 || (M <= 64 && blocks > 2) || (q.nks <= 4 && M >= 256 && M % 32 == 0) ? 600
+                             : nb == 1 && q.ngroups == 2 ? 40
+                             : M > 64 && passes[1] * 32 * 8 > M * 9 ? 60 : 180;
+        if (p.cap * M > most * 256) return false;
+    }
     // Two groups of 32, each of which stages the pixels again, while the list is not long: 400 x 352, 128 -> 64, blocks of 16,
     // 5 % active 9.2 us by conv3 and 7.1 here, 30 % 13.8 and 13.2, all 31.3 and 30.1; blocks of 8 47.3 and 30.9; 1600 x 1408,
     // half of all blocks of 16 181 and 207.
-    if (nb == 1 && q.ngroups == 2 && p.cap * M > 640 * 256) return false;
+    if (!strided && nb == 1 && q.ngroups == 2 && p.cap * M > 640 * 256) return false;
     // Groups of 96 beside conv3's wide items of 256 pixels: blocks of more than 256 pixels are even (24 x 24, 48 -> 80: 20 %
     // active 11.3 us there, 11.8 here, all 28.6 and 28.7), and so are those whose pixels no item size fits better than
     // theirs, with the last round the worse here (14 x 14: 5 % active 8.5 and 6.2, 20 % 11.2 and 10.6, 60 % 18.1 and 18.0, all
     // 754 blocks 23.2 and 25.8): there while the list's bound is two of their rounds.
-    if (nb == 3 && (M > 256 || (M > 192 && M < 256 && p.cap > 512))) return false;
+    if (!strided && nb == 3 && (M > 256 || (M > 192 && M < 256 && p.cap > 512))) return false;
     if ((long long)p.cap * passes[1] * nb >= (1LL << 31)) return false;
     q.div_item[0] = make_fastdiv((uint32_t)passes[0]);
     q.div_item[1] = make_fastdiv((uint32_t)passes[1]);

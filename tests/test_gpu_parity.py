@@ -1058,6 +1058,51 @@ def test_sparse_conv_groups_of_96_at_stride_1(bo, side, Cin, Cout, dtype, add):
 
 
 @pytest.mark.parametrize("bo,grid,ragged,Cin,Cout,dtype,add", [
+    (16, 16, 0, 64, 96, "bf16", False),   # groups of 96, four chunks of 16 channels
+    (16, 16, 7, 24, 64, "f16", True),     # half of the last chunk empty; ragged map
+    (12, 14, 5, 40, 72, "f16", False),    # 32 pixels begin inside a row; the last channel block partly empty
+    (8, 20, 0, 32, 32, "bf16", True),
+    (8, 20, 3, 64, 128, "f16", True),     # two groups of 64
+    (15, 12, 0, 48, 56, "bf16", False),   # odd rows
+    (5, 20, 3, 8, 8, "bf16", False),      # tiles smaller than an item
+    (23, 8, 9, 32, 40, "bf16", True),     # the widest rows of an item
+])
+def test_sparse_conv_strided_with_resident_weights(bo, grid, ragged, Cin, Cout, dtype, add):
+    """Stride-2 layers whose weights stay in LDS: items of 32 pixels by all channels of a group or by 32, by the count."""
+    step("sparse_conv stride 2, resident weights %s" % ((bo, grid, ragged, Cin, Cout, dtype, add),))
+    r = gen.rng_for(5, bo * 1000 + Cin + Cout + 1)
+    side, total = 2 * bo * grid - ragged, grid * grid
+    g_in, g_out, Ho, Wo = sb.geometry(side, side, 3, 2, bo)
+    assert (g_out.bcount_h, g_out.bcount_w) == (grid, grid)
+    x = gen.activations(r, (1, side, side, Cin), dtype)
+    w = gen.conv_weights(r, 3, 3, Cin, Cout, dtype)
+    b = gen.bias_vector(r, Cout, 0.5)
+    y0 = gen.activations(r, (1, Ho, Wo, Cout), dtype)
+    wp, d_b, d_x = sb.pack_weights(to_dev(w, dtype)), torch.from_numpy(b).cuda(), to_dev(x, dtype)
+    for n in (total, total * 2 // 5, 10, 1):
+        blocks = np.zeros(total, np.uint8)
+        blocks[r.permutation(total)[:n]] = 1
+        mask = np.kron(blocks.reshape(1, grid, grid), np.ones((1, bo, bo), np.uint8))[:, :Ho, :Wo].copy()
+        d_idx, d_cnt = sb.reduce_mask(torch.from_numpy(mask).cuda(), g_out)      # window = output block
+        idx = orc.reduce_mask(mask, ogeom(g_out))
+        assert len(idx) == n
+        ref = orc.sparse_conv_dense(x, idx, ogeom(g_out), w, b, y0, stride=2, relu=True, add=add)
+        bm = orc.block_mask(idx, ogeom(g_out), 1, Ho, Wo)
+        y = to_dev(y0, dtype)
+        sb.sparse_conv(d_x, d_idx, d_cnt, g_in, g_out, wp, d_b, y, stride=2, relu=True, add=add)
+        got = to_host(y)
+        assert_close(got, ref, CONV_TOL[dtype], "fused, %d blocks" % n)
+        assert np.array_equal(got[~bm], y0[~bm])
+        tiles = sb.sparse_gather(d_x, d_idx, d_cnt, g_in)
+        out = sb.conv_on_tiles(tiles, d_cnt, wp, d_b, stride=2, relu=True,
+                               out=torch.full((total, bo, bo, Cout), 7.0, dtype=d_x.dtype, device="cuda"))
+        assert bool((out[n:] == 7.0).all())                                      # tiles beyond the count are not written
+        y = to_dev(y0, dtype)
+        sb.sparse_scatter(out, d_idx, d_cnt, g_out, y, add=add)
+        assert_close(to_host(y), ref, CONV_TOL[dtype], "unfused, %d blocks" % n)
+
+
+@pytest.mark.parametrize("bo,grid,ragged,Cin,Cout,dtype,add", [
     (16, 16, 0, 48, 64, "bf16", False),   # a chunk of 32 channels and one of 16
     (16, 16, 7, 24, 96, "f16", True),     # groups of 96; one chunk, its last eight channels empty; ragged map
     (16, 16, 0, 64, 32, "bf16", True),    # groups of 32
