@@ -3,7 +3,7 @@
 // arXiv 1801.02108).
 //
 // The paper appends indices with a global atomic counter, which gives an arbitrary order.
-// Here the list is produced in lexicographic (n, by, bx) order without atomics, in two launches.
+// Here the list is produced in lexicographic (n, by, bx) order without atomics, in two launches (one for the smallest grids).
 // Grids of at most 65 536 blocks (every configuration of the paper's detector is far below):
 //   pass 1  rm_pool_blocks: one wavefront per block.  All loads of a window are issued at once (aligned
 //           4-byte words where the mask allows), the lanes' partial pools are combined with cross-lane
@@ -17,6 +17,7 @@
 //           byte and the row's number of active blocks;
 //   pass 2  rm_compact: one workgroup per block row: exclusive prefix over the row counts, then
 //           ballot + popcount compaction of the row's flags into the index list.
+// Up to 64 blocks of a u8 mask whose windows are 64 wavefront loads or less: one launch (rm_one_u8w).
 // The flag bytes of pass 1 are also what the fused consumers take (conv16.hip): they do the compaction
 // of pass 2 in their own prologue, which saves a launch where a launch is a third of the step.
 #include "common.h"
@@ -375,6 +376,74 @@ __global__ __launch_bounds__(kRmThreads) void rm_compact_flags(const uint8_t *__
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *count = base + wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
 }
 
+// Both passes in one launch of one workgroup, for grids so small that a launch is most of either pass.  A unit is one batch of
+// a block's window rows, one aligned word per lane as above; a wave has at most four and requests them together.  The units'
+// pools meet in LDS and wave 0 thresholds and compacts.  Bound by one memory round trip and the launch.
+constexpr int kOneWaves = 16, kOneEach = 4, kOneUnits = kOneWaves * kOneEach;
+template <int POOL>
+__global__ __launch_bounds__(64 * kOneWaves) void rm_one_u8w(const uint32_t *__restrict__ mask, int H, int W4, sbnet_geom g,
+                                                             BlockDivs dv, FastDiv batches, int total, int lp_shift, int cutoff,
+                                                             int32_t *__restrict__ indices, int32_t *__restrict__ count, int cap) {
+    __shared__ int pooled[kOneUnits];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int c = lane & ((1 << lp_shift) - 1), r = lane >> lp_shift, rows_per = 64 >> lp_shift;
+    const int units = total * (int)batches.d;
+    uint32_t q[kOneEach], keep[kOneEach];
+#pragma unroll
+    for (int u = 0; u < kOneEach; ++u) {
+        const int unit = wave + u * kOneWaves;
+        q[u] = keep[u] = 0u;
+        if (unit < units) {                                       // (uniform)
+            const int blk = (int)fdiv((uint32_t)unit, batches), r0 = (unit - blk * (int)batches.d) * rows_per;
+            const int n = (int)fdiv((uint32_t)blk, dv.per_sample);
+            const int rem = blk - n * g.bcount_h * g.bcount_w;
+            const int by = (int)fdiv((uint32_t)rem, dv.per_row), bx = rem - by * g.bcount_w;
+            const int y0 = g.boffset_h + by * g.bstride_h, x0 = g.boffset_w + bx * g.bstride_w;
+            const int yhi = min(y0 + g.bsize_h, H);
+            const int xlo = max(x0, 0), xhi = min(x0 + g.bsize_w, W4 * 4);
+            const int y = y0 + r0 + r, w = (xlo >> 2) + c;
+            // the row and the word are in the window and in the image, and the bytes of the word that are
+            if (y >= 0 && y < yhi && xhi > xlo && w <= (xhi - 1) >> 2) {
+                keep[u] = 0xffffffffu;
+                if (w == xlo >> 2) keep[u] &= 0xffffffffu << (8 * (xlo & 3));
+                if (w == (xhi - 1) >> 2) keep[u] &= 0xffffffffu >> (8 * (3 - ((xhi - 1) & 3)));
+                q[u] = mask[((size_t)n * H + y) * W4 + w];
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kOneEach; ++u) {
+        const uint32_t w = q[u] & keep[u];
+        int a;
+        if (POOL == SBNET_POOL_AVG) a = (int)__builtin_amdgcn_sad_u8(w, 0u, 0u);
+        else a = (int)max(max(w & 0xffu, (w >> 8) & 0xffu), max((w >> 16) & 0xffu, w >> 24));
+        a = wave_pool_nonneg<POOL>(a);
+        if (lane == 63) pooled[wave + u * kOneWaves] = a;
+    }
+    __syncthreads();
+    if (wave) return;
+    int a = 0;
+    if (lane < total) {
+        for (int k = 0; k < (int)batches.d; ++k) {
+            const int v = pooled[lane * (int)batches.d + k];
+            a = POOL == SBNET_POOL_AVG ? a + v : max(a, v);
+        }
+    }
+    const bool on = lane < total && a >= cutoff;
+    const unsigned long long ballot = __ballot(on);
+    const int pos = __popcll(ballot & ((1ull << lane) - 1ull));
+    if (on && pos < cap) {
+        const int n = (int)fdiv((uint32_t)lane, dv.per_sample);
+        const int rem = lane - n * g.bcount_h * g.bcount_w;
+        const int by = (int)fdiv((uint32_t)rem, dv.per_row);
+        indices[3 * pos + 0] = n;
+        indices[3 * pos + 1] = by;
+        indices[3 * pos + 2] = rem - by * g.bcount_w;
+    }
+    if (lane == 0) *count = __popcll(ballot);
+}
+
 }  // namespace sbnet
 
 using namespace sbnet;
@@ -412,6 +481,47 @@ BlockDivs block_divs(const sbnet_geom *g) {
     return dv;
 }
 
+// u8 masks in aligned words
+static bool word_path(const void *mask, sbnet_dtype mdt, int W) { return mdt == SBNET_U8 && (W % 4 == 0) && (((uintptr_t)mask) % 4 == 0); }
+
+// Smallest integer pool value v that counts as active: the decision everywhere is
+// (avg ? (double)v / area : (double)v) > (double)threshold, monotone in v, so it is a cutoff on v.
+static long long pool_cutoff(const sbnet_geom *g, sbnet_pool pool, double thr) {
+    const double area = (double)g->bsize_h * (double)g->bsize_w;
+    const long long vmax = pool == SBNET_POOL_AVG ? 255LL * g->bsize_h * g->bsize_w : 255LL;
+    auto active = [&](long long v) { return (pool == SBNET_POOL_AVG ? (double)v / area : (double)v) > thr; };
+    long long lo = 0, hi = vmax + 1;                          // active(hi) taken as true: hi = "never"
+    if (active(0)) hi = 0;
+    while (hi - lo > 1) {                                     // invariant: !active(lo), hi active or vmax + 1
+        const long long mid = lo + (hi - lo) / 2;
+        if (active(mid)) hi = mid; else lo = mid;
+    }
+    return hi;
+}
+
+// log2 of the lanes that a window row's words take: the most words it can touch, at most 64
+static int word_lanes_shift(const sbnet_geom *g) {
+    const int words_per_row = (g->bsize_w + 6) / 4;
+    int shift = 0;
+    while ((1 << shift) < words_per_row && shift < 6) ++shift;
+    return shift;
+}
+
+// One workgroup reads every window: up to kOneUnits wavefront loads, about 50 clocks each for the one address unit, which is
+// less than the launch it saves (64 x 64, 64 windows of 10 x 10: 4.4 us in two launches, 3.9 in one; 16 windows 4.3 and 2.8, both
+// replayed from a graph; issued call by call, with the layer that follows, 11.8 and 8.9).
+static bool one_launch(const void *mask, sbnet_dtype mdt, int N, int W, const sbnet_geom *g, sbnet_pool pool, double thr, int &batches,
+                       int &cutoff) {
+    const long long total = (long long)N * g->bcount_h * g->bcount_w;
+    if (total > 64 || !word_path(mask, mdt, W) || g->bsize_w > 250 || g->bsize_h > 64 * kOneUnits) return false;
+    const int rows_per = 64 >> word_lanes_shift(g);
+    batches = (g->bsize_h + rows_per - 1) / rows_per;
+    if (total * batches > kOneUnits) return false;
+    const long long c = pool_cutoff(g, pool, thr);
+    cutoff = (int)c;
+    return c <= 0x7fffffffLL;
+}
+
 // Pass 1 of the small-grid path: flags[blk] = 1 where block blk (lexicographic) is active, else 0, for all
 // N * bcount_h * bcount_w blocks; flags must hold that many bytes rounded up to 16.
 sbnet_status mask_to_flags(const char *who, const void *mask, sbnet_dtype mdt, int N, int H, int W,
@@ -424,22 +534,11 @@ sbnet_status mask_to_flags(const char *who, const void *mask, sbnet_dtype mdt, i
     const BlockDivs dv = block_divs(g);
     const double thr = (double)threshold;
     const dim3 grid((unsigned)((((total + 15) & ~15) + kRmThreads / 64 - 1) / (kRmThreads / 64)));   // one wave per flag byte, padding included
-    const bool words = mdt == SBNET_U8 && (W % 4 == 0) && (((uintptr_t)mask) % 4 == 0);
+    const bool words = word_path(mask, mdt, W);
     if (words) {
-        // Smallest integer pool value v that counts as active: the decision everywhere is
-        // (avg ? (double)v / area : (double)v) > (double)threshold, monotone in v, so it is a cutoff on v.
-        const double area = (double)g->bsize_h * (double)g->bsize_w;
-        const long long vmax = pool == SBNET_POOL_AVG ? 255LL * g->bsize_h * g->bsize_w : 255LL;
-        auto active = [&](long long v) { return (pool == SBNET_POOL_AVG ? (double)v / area : (double)v) > thr; };
-        long long lo = 0, hi = vmax + 1;                      // active(hi) taken as true: hi = "never"
-        if (active(0)) hi = 0;
-        while (hi - lo > 1) {                                 // invariant: !active(lo), hi active or vmax + 1
-            const long long mid = lo + (hi - lo) / 2;
-            if (active(mid)) hi = mid; else lo = mid;
-        }
+        const long long hi = pool_cutoff(g, pool, thr);
         if (hi <= 0x7fffffffLL) {
-            int words_per_row = (g->bsize_w + 6) / 4, lp_shift = 0;           // most words a window row can touch
-            while ((1 << lp_shift) < words_per_row && lp_shift < 6) ++lp_shift;
+            const int lp_shift = word_lanes_shift(g);
             if (pool == SBNET_POOL_MAX)
                 hipLaunchKernelGGL((rm_pool_blocks_u8w<SBNET_POOL_MAX>), grid, dim3(kRmThreads), 0, s, (const uint32_t *)mask, H,
                                    W / 4, *g, dv, total, lp_shift, (int)hi, flags);
@@ -498,6 +597,17 @@ static sbnet_status reduce_mask_launch(const void *mask, sbnet_dtype mdt, int N,
     if (st != SBNET_OK) return st;
     if (ws_bytes < sbnet_workspace_bytes(N, g)) return fail(SBNET_EINVAL, "sbnet_reduce_mask: workspace too small");
     hipStream_t s = (hipStream_t)stream;
+    int batches, cutoff;
+    if (one_launch(mask, mdt, N, W, g, pool, (double)threshold, batches, cutoff)) {
+        const int total = N * g->bcount_h * g->bcount_w;
+#define SBNET_RM_ONE(P)                                                                                                  \
+    hipLaunchKernelGGL((rm_one_u8w<P>), dim3(1), dim3(64 * kOneWaves), 0, s, (const uint32_t *)mask, H, W / 4, *g, block_divs(g), \
+                       make_fastdiv((uint32_t)batches), total, word_lanes_shift(g), cutoff, indices, count, cap)
+        if (pool == SBNET_POOL_MAX) SBNET_RM_ONE(SBNET_POOL_MAX);
+        else SBNET_RM_ONE(SBNET_POOL_AVG);
+#undef SBNET_RM_ONE
+        return launch_status("sbnet_reduce_mask(one launch)");
+    }
     if (mask_flag_path(N, g)) {
         uint8_t *flags = (uint8_t *)workspace;
         st = mask_to_flags("sbnet_reduce_mask(pool)", mask, mdt, N, H, W, g, pool, threshold, flags, s);

@@ -64,6 +64,27 @@ def test_reduce_mask_binary(H, W, bo, N, mdt):
         _reduce_case(mask, g_in, sb.POOL_AVG, 0.01, mdt)
 
 
+@pytest.mark.parametrize("N,H,W,geom", [
+    (1, 64, 64, (10, 10, 8, 8, -1, -1, 8, 8)),       # 64 windows of one load each: the most there are
+    (1, 64, 64, (18, 18, 16, 16, -1, -1, 4, 4)),     # three loads a window
+    (2, 40, 28, (7, 13, 9, 11, 2, -5, 4, 3)),        # words begin and end inside, gaps between the rows
+    (1, 300, 256, (256, 250, 40, 6, -8, -3, 1, 1)),  # 64 loads of 64 words: one window
+    (1, 300, 256, (257, 250, 40, 6, -8, -3, 1, 1)),  # one row more: two launches
+    (3, 8, 8, (4, 4, 4, 4, -6, 6, 4, 1)),            # windows outside the image
+    (1, 20, 12, (1, 1, 1, 1, 3, 5, 8, 7)),           # single pixels
+    (5, 16, 16, (6, 6, 4, 4, -1, -1, 13, 1)),        # 65 windows: two launches
+])
+def test_reduce_mask_of_few_blocks(N, H, W, geom):
+    """Up to 64 windows of up to 64 loads are pooled and listed by one workgroup."""
+    step("reduce_mask few blocks %s" % ((N, H, W, geom),))
+    r = gen.rng_for(1, sum(geom) + N)
+    g = sb.Geom(*geom)
+    for dens in (0.0, 0.01, 0.2, 1.0):
+        mask = (r.random((N, H, W)) < dens) * r.integers(1, 256, (N, H, W))
+        for pool, thr in ((sb.POOL_MAX, 0.0), (sb.POOL_MAX, 200.0), (sb.POOL_MAX, 255.0), (sb.POOL_MAX, -1.0), (sb.POOL_AVG, 0.0), (sb.POOL_AVG, 20.0)):
+            _reduce_case(mask, g, pool, thr, "u8")
+
+
 def test_reduce_mask_real_valued_max_and_avg():
     step("reduce_mask real-valued")
     r = gen.rng_for(1, 77)
