@@ -70,7 +70,7 @@ typedef struct {
        Lists whose bound costs at most one eighth more in 8 x 8 sub-tiles than one round of 16 x 16 ones run 8 x 8.
        Default 3; 0 = always 8 x 8; 1000 = always 16 x 16 where the block allows it. */
     int unit_small_item_cost_eighths;
-    /* LDS-tiled 3x3 convolution: cost of a 128-pixel work item in eighths of a 256-pixel one; the shape whose
+    /* LDS-tiled 3x3 convolution (layers whose weights do not stay in LDS): cost of a 128-pixel work item in eighths of a 256-pixel one; the shape whose
        cost-weighted rounds of work over 256 CUs are fewer is run.  Default 5; 0 = always 128-pixel items;
        1000 = always 256-pixel items. */
     int conv3_small_item_cost_eighths;
@@ -388,7 +388,8 @@ sbnet_status sbnet_conv_on_tiles_backward_data(const void *dout_tiles, sbnet_dty
  * F16), 16-byte aligned.  Products of BF16/F16 inputs are exact and summed in fp32; the tiles are
  * split over workgroups whose partial sums are added in a fixed order (no atomics: the same
  * inputs give the same bits).  3x3 and 1x1 kernels at stride 1 or 2 with channel counts that are
- * multiples of 8 (output tiles up to 32 columns; any tile for 1x1 at stride 1) run on the matrix
+ * multiples of 8 (output tiles up to 32 columns; wider ones too at stride 1: any for 1x1, up to about 120
+ * columns for 3x3) run on the matrix
  * cores, everything else in a plain kernel (correct, slow).  workspace: device, 16-byte aligned,
  * sbnet_conv_backward_weights_workspace_bytes(...) bytes (the partial sums); overwritten.
  */

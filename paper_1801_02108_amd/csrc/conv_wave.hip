@@ -517,13 +517,16 @@ bool conv_wave_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t 
     // 38.2 and 37.1, half of 1600 x 1408 64.2 and 71.3; small blocks of more than 64 channels, for which conv3 has no wide
     // group, 64 -> 128, 8 x 8, all 53.3 and 36.7; 64 -> 64 on blocks that fill their items, 16 x 16, 5 % 9.1 and 6.1, 30 %
     // 16.6 and 10.9, 60 % 21.7 and 22.4, all 40.1 and 35.2; else 12 x 12, 30 % 20.5 and 12.9, 60 % 22.8 and 26.4; blocks that fill their items badly, 10 x 10, 64 -> 128, 5 % 8.8 and 8.2, 15 % 10.9 and 11.4, 14 x 14
-    // 10.4 and 9.0, 12.6 and 12.6; two groups of 32, 96 -> 64, 14 x 14, 5 % 14.1 and 9.5, 15 % 14.3 and 15.4.
+    // 10.4 and 9.0, 12.6 and 12.6; two groups of 32, 96 -> 64, 14 x 14, 5 % 14.1 and 9.5, 15 % 14.3 and 15.4.  More than eight chunks
+    // one after the other, where conv3's items of 64 pixels fit the block as well: 200 x 176, 192 -> 32, 8 x 8, 5 % 11.4 and 9.5,
+    // 15 % 11.7 and 12.1, all 11.8 and 13.0.  110 KB of weights for a few small blocks: 200 x 176, 64 -> 96, 8 x 8, 30 % 7.3 and 7.5.
     if (strided) {
         const long long most = q.nks <= 3 ? (q.copies[1] > 8 ? 400 : 1LL << 40)
                              : nb == 3 || (M <= 64 && blocks > 2) || (q.nks <= 4 && M >= 256 && M % 32 == 0) ? 600
                              : nb == 1 && q.ngroups == 2 ? 40
                              : M > 64 && passes[1] * 32 * 8 > M * 9 ? 60 : 180;
-        if (p.cap * M > most * 256) return false;
+        if (p.cap * M > most * 256 || (q.nks > 8 && M <= 64)) return false;
+        if (nb == 3 && q.nks > 3 && M <= 64 && p.cap * M <= 64 * 256) return false;
     }
     // Two groups of 32, each of which stages the pixels again, while the list is not long: 400 x 352, 128 -> 64, blocks of 16,
     // 5 % active 9.2 us by conv3 and 7.1 here, 30 % 13.8 and 13.2, all 31.3 and 30.1; blocks of 8 47.3 and 30.9; 1600 x 1408,
@@ -542,7 +545,10 @@ bool conv_wave_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t 
     q.buf_bytes = (uint32_t)buf;
     q.bias_off = q.buf_off + kWavesW * q.buf_bytes;
     const size_t lds = q.bias_off + (size_t)nb * 128;
-    long long per_xcd = ((long long)p.cap * passes[1] * nb + 63) / 64;
+    // Two of the smallest items per workgroup on lists too short to fill the device: eight, one per wave, stood at one CU's address
+    // unit together (all active: 100 x 88, 32 -> 32, blocks of 8 5.2 -> 4.0 us, 64 -> 64 6.1 -> 5.5, stride 2 on 200 x 176, 128 -> 32,
+    // blocks of 16 12.3 -> 10.2), one is no faster than two.
+    long long per_xcd = ((long long)p.cap * passes[1] * nb + 15) / 16;
     if (per_xcd > 32 / q.ngroups) per_xcd = 32 / q.ngroups;
     q.per_xcd = (int)per_xcd;
     q.div_groups = make_fastdiv((uint32_t)q.ngroups);
