@@ -537,6 +537,9 @@ bool conv_wave_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t 
     // theirs, with the last round the worse here (14 x 14: 5 % active 8.5 and 6.2, 20 % 11.2 and 10.6, 60 % 18.1 and 18.0, all
     // 754 blocks 23.2 and 25.8): there while the list's bound is two of their rounds.
     if (!strided && nb == 3 && (M > 256 || (M > 192 && M < 256 && p.cap > 512))) return false;
+    // Long lists of tiles that conv3's items of 384 pixels fit better than six of 64: data gradient of 64 -> 64 on 16 x 16 blocks
+    // (18 x 18 results), 880 tiles 28.9 and 28.5 us, 1540 45.8 and 48.4, 2200 62.0 and 65.4.
+    if (!strided && nb == 2 && M > 256 && M <= 384 && p.cap * M > 1200 * 256) return false;
     if ((long long)p.cap * passes[1] * nb >= (1LL << 31)) return false;
     q.div_item[0] = make_fastdiv((uint32_t)passes[0]);
     q.div_item[1] = make_fastdiv((uint32_t)passes[1]);
