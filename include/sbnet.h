@@ -313,9 +313,10 @@ sbnet_status sbnet_block_flags(const void *mask, sbnet_dtype mask_dtype, int N, 
 
 /*
  * sbnet_sparse_conv fed by the block flags instead of the index list (Fig. 1 with the second half of
- * Sec. 3.1 moved into the consumer): the same y as sbnet_sparse_conv on the list those flags compact to,
- * and that list and its count are written to indices / count for later calls.  Where the convolution
- * kernel can take flags (3x3, stride 1, 16 x 16 output blocks, 32 or 64 input channels, bf16 / f16) every
+ * Sec. 3.1 moved into the consumer): the same y, bit for bit, as sbnet_sparse_conv with this cap on the
+ * list those flags compact to, and that list and its count are written to indices / count for later calls.  Where the convolution
+ * kernel can take flags (3x3, stride 1, 16 x 16 output blocks, 32 or 64 input channels, bf16 / f16, lists of 57 rows
+ * or more) and no other kernel is the faster one (from 65 output channels on, at some lengths of the list) every
  * workgroup compacts them in its prologue while its weights arrive, which saves reduce_mask's second
  * launch; every other shape compacts the flags in a launch of its own and runs sbnet_sparse_conv.
  * The block grid of g_in and g_out is the one the flags were made for; at most 65 536 blocks.  flags is

@@ -420,16 +420,21 @@ static bool direct_is_faster(const ConvParams &p, long long M) {
     return L <= 100 && p.Cout <= 16 && (L + 2) * p.Cout <= 160;
 }
 
-// Shapes of conv16.hip that conv_wave.hip serves better.  Up to 32 output channels half of conv16's matrix work is padding:
-// 800 x 704, blocks of 16, 64 -> 32, conv16 and conv_wave: 3 % active 6.5 and 5.0 us, 10 % (220 blocks, nearly a full round of
-// conv16) 6.7 and 7.1, 30 % 14.7 and 12.1, all 35.9 and 30.6.  More than 64: conv16 launches a persistent workgroup per CU and
-// group of 64, and the second group's wait for the first's whatever the count; 400 x 352, 64 -> 128: 5 % active 10.9 and 5.7 us,
-// 20 % 12.0 and 9.1, all 28.0 and 25.8; beyond 640 tiles of 16 x 16 it is even (800 x 704: 30 % 29.8 and 31.0, all 80 and 85),
-// and so it is where all of conv16's workgroups fit the device (64 -> 128, 110 tiles: 6.6 and 8.3).  33 to 64 channels: conv16's
-// item, a tile per workgroup, wins from about half a round on (64 -> 64, 220 blocks 7.4 and 9.3, 660 16.1 and 16.7, 2200 41 and 48).
-static bool wave_before_16(const ConvParams &p) {
+// Shapes of conv16.hip that conv_wave.hip serves better.  The two sum in different orders.
+// Up to 32 output channels half of conv16's matrix work is padding: 800 x 704, 64 -> 32, blocks of 32, conv16 and conv_wave: 3 % active
+// 6.2 and 5.1 us, 10 % 6.5 and 7.0, 30 % 15.0 and 12.4, all 37.7 and 34.4; data gradient with 32 -> 32 on 1000 tiles of 16 x 16 13.1 and
+// 9.3.  Not in the plain form on 16 x 16 blocks, for which conv16 takes the flags of a mask: a call from the mask or the flags is the
+// call from the list, bit for bit, and would lose more by a launch for the list than it gains (from the mask, 10 % active 9.7 and 12.5,
+// 32 -> 32 8.4 and 11.8, all 38.3 and 34.9 and, 400 x 352, 32 -> 32, 12.6 and 13.1).
+// More than 64: conv16 launches a persistent workgroup per CU and group of 64, and the second group's wait for the first's whatever
+// the count; 400 x 352, 64 -> 128: 5 % active 10.9 and 5.7 us, 20 % 12.0 and 9.1, all 28.0 and 25.8; beyond 640 tiles of 16 x 16 it is
+// even (800 x 704: 30 % 29.8 and 31.0, all 80 and 85), and so it is where all of conv16's workgroups fit the device (64 -> 128, 110
+// tiles: 6.6 and 8.3).  33 to 64 channels: conv16's item, a tile per workgroup, wins from about half a round on (64 -> 64, 220 blocks
+// 7.4 and 9.3, 660 16.1 and 16.7, 2200 41 and 48).
+static bool wave_before_16(const ConvParams &p, ConvForm form) {
     const long long tiles = (long long)p.cap * (p.oh / 16) * (p.ow / 16);
-    return p.Cout <= 32 || (p.Cout > 64 && tiles <= 640 && tiles * ((p.Cout + 63) / 64) > 256);
+    if (p.Cout <= 32) return form != ConvForm::plain || tiles != p.cap;
+    return p.Cout > 64 && tiles <= 640 && tiles * ((p.Cout + 63) / 64) > 256;
 }
 
 template <int DT, bool FUSED>
@@ -462,7 +467,7 @@ static sbnet_status run_conv(const char *who, sbnet_dtype dt, ConvParams &p, hip
 
     if (use_mfma(dt, p.Cin, p.Cout)) p.w32_offset = packed_elems(dt, p.kh, p.kw, p.Cin, p.Cout) / 2 / 8;
     sbnet_status st16 = SBNET_OK;
-    const bool takes16 = conv16_accepts(dt, FUSED, p), wave = !takes16 || wave_before_16(p);
+    const bool takes16 = conv16_accepts(dt, FUSED, p), wave = !takes16 || wave_before_16(p, form);
     if (form != ConvForm::plain) {
         if (wave && conv_wave_try(dt, FUSED, p, s, &st16, who, form)) return st16;
         if (!takes16 && conv3_try(dt, FUSED, p, s, &st16, who, form)) return st16;
@@ -807,7 +812,7 @@ extern "C" sbnet_status sbnet_sparse_conv_from_flags(const uint8_t *flags, const
         p.flags = flags;
         p.total_blocks = N * g_in->bcount_h * g_in->bcount_w;
         p.indices_out = indices; p.count_out = count;
-        fold = conv16_accepts(dtype, true, p) && !(Cout > 64 && wave_before_16(p));      // (up to 64 the launch saved is worth more)
+        fold = conv16_accepts(dtype, true, p) && !wave_before_16(p, ConvForm::plain);
     }
     if (!fold) {
         sbnet_status st = flags_to_indices(who, flags, N, g_in, indices, count, cap, s);

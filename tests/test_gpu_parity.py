@@ -925,6 +925,38 @@ def test_sparse_conv_from_mask(N, H, W, Cin, Cout, bo, dtype, add, dens, cap):
         assert_close(blk, ref, CONV_TOL[dtype], "from mask, tile %d" % k)
 
 
+@pytest.mark.parametrize("N,H,W,Cin,Cout,dtype,add", [
+    (1, 176, 160, 64, 32, "bf16", False),     # 110 blocks of up to 32 output channels: half of a 64-channel group
+    (1, 176, 160, 32, 32, "f16", True),
+    (1, 250, 170, 64, 24, "f16", False),      # ragged edges
+    (1, 176, 160, 64, 64, "bf16", False),
+    (1, 400, 352, 64, 128, "bf16", True),     # 550 blocks, two groups: the kernel that keeps the weights in LDS
+    (1, 400, 352, 64, 96, "f16", False),      # ... which does not take this width
+])
+def test_sparse_conv_from_flags_and_from_mask_are_the_list_call(N, H, W, Cin, Cout, dtype, add):
+    """One y, bit for bit, whether the convolution is given the mask, the flags or the list they compact to."""
+    step("flags, mask and list %s" % ((N, H, W, Cin, Cout, dtype, add),))
+    r = gen.rng_for(5, H * 10 + Cin + Cout)
+    g_in, g_out, Ho, Wo = sb.geometry(H, W, 3, 1, 16)
+    total = N * g_in.bcount_h * g_in.bcount_w
+    assert total >= 64
+    x = to_dev(gen.activations(r, (N, H, W, Cin), dtype), dtype)
+    y0 = to_dev(gen.activations(r, (N, Ho, Wo, Cout), dtype), dtype)
+    wp = sb.pack_weights(to_dev(gen.conv_weights(r, 3, 3, Cin, Cout, dtype), dtype))
+    b = torch.from_numpy(gen.bias_vector(r, Cout, 0.5)).cuda()
+    for dens in (0.0005, 1.0):
+        mask = torch.from_numpy((r.random((N, H, W)) < dens).astype(np.uint8)).cuda()
+        idx, cnt = sb.reduce_mask(mask, g_in)
+        assert sb.read_count(cnt, total) > 0
+        want = sb.sparse_conv(x, idx, cnt, g_in, g_out, wp, b, y0.clone(), relu=True, add=add)
+        i2, c2 = torch.full_like(idx, -3), torch.full_like(cnt, -3)
+        assert torch.equal(sb.sparse_conv_from_flags(sb.block_flags(mask, g_in), x, g_in, g_out, wp, b, y0.clone(), i2, c2,
+                                                     relu=True, add=add), want)
+        ws = torch.zeros((sb.workspace_bytes(N, g_in),), dtype=torch.uint8).cuda()
+        assert torch.equal(sb.sparse_conv_from_mask(mask, g_in, x, g_in, g_out, wp, b, y0.clone(), i2, c2, ws, relu=True, add=add),
+                           want)
+
+
 def _random_fused_shapes(n, seed):
     r = np.random.default_rng(seed)
     out = []
@@ -1126,7 +1158,8 @@ def test_sparse_conv_strided_with_resident_weights(bo, grid, ragged, Cin, Cout, 
 @pytest.mark.parametrize("bo,grid,ragged,Cin,Cout,dtype,add", [
     (16, 16, 0, 48, 64, "bf16", False),   # a chunk of 32 channels and one of 16
     (16, 16, 7, 24, 96, "f16", True),     # groups of 96; one chunk, its last eight channels empty; ragged map
-    (16, 16, 0, 64, 32, "bf16", True),    # groups of 32
+    (16, 16, 0, 64, 32, "bf16", True),    # blocks of 16 x 16: the kernel that takes flags
+    (32, 8, 0, 64, 32, "bf16", True),     # groups of 32
     (12, 16, 5, 40, 72, "f16", False),    # 64 pixels begin inside a row; the last channel block partly empty
     (8, 20, 0, 64, 128, "bf16", True),    # two groups of 64
     (15, 12, 0, 32, 128, "f16", False),
