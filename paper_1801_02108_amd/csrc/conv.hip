@@ -812,7 +812,7 @@ extern "C" sbnet_status sbnet_sparse_conv_from_flags(const uint8_t *flags, const
         p.flags = flags;
         p.total_blocks = N * g_in->bcount_h * g_in->bcount_w;
         p.indices_out = indices; p.count_out = count;
-        fold = conv16_accepts(dtype, true, p) && !wave_before_16(p, ConvForm::plain);
+        fold = conv16_accepts(dtype, true, p) && !(wave_before_16(p, ConvForm::plain) && conv_wave_accepts(dtype, true, p));
     }
     if (!fold) {
         sbnet_status st = flags_to_indices(who, flags, N, g_in, indices, count, cap, s);

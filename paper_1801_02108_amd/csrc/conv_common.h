@@ -174,6 +174,7 @@ enum class ConvForm {
 bool conv3_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t s, sbnet_status *st, const char *who,
                ConvForm form = ConvForm::plain);
 // conv_wave.hip: the same contract for 3x3 layers of stride 1 or 2 whose weights stay in LDS.
+bool conv_wave_accepts(sbnet_dtype dt, bool fused, const ConvParams &p);       // of the plain form
 bool conv_wave_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t s, sbnet_status *st, const char *who,
                    ConvForm form = ConvForm::plain);
 

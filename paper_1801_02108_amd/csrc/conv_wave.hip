@@ -459,7 +459,14 @@ static void launch_wave(bool fused, ConvForm form, int nb, const ConvParams &p, 
 #undef SBNET_LWS
 }
 
-bool conv_wave_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t s, sbnet_status *st, const char *who, ConvForm form) {
+struct LaunchW {
+    PlanW q;
+    int nb, grid;            // blocks of 32 output channels of a group; workgroups
+    size_t lds;
+};
+
+// Shape checks and launch shape; false where another kernel takes the call.
+static bool conv_wave_plan(sbnet_dtype dt, bool fused, const ConvParams &p, ConvForm form, LaunchW *l) {
     if (dt != SBNET_BF16 && dt != SBNET_F16) return false;
     if (p.kh != 3 || p.kw != 3 || p.sh != p.sw || (p.sh != 1 && p.sh != 2) || p.Cin % 8 != 0 || p.Cout % 8 != 0) return false;
     if (form == ConvForm::inside || (form != ConvForm::plain && (!fused || p.add || p.sh != 1))) return false;
@@ -469,7 +476,8 @@ bool conv_wave_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t 
     if ((fused ? (long long)p.Ho * p.Wo : (long long)p.oh * p.ow) * p.Cout >= (1LL << 30)) return false;
     const long long M = (long long)p.oh * p.ow;
     const bool strided = p.sh == 2;
-    PlanW q = {};
+    PlanW &q = l->q;
+    q = {};
     const int CinP = (p.Cin + 31) / 32 * 32, blocks = (p.Cout + 31) / 32;
     q.nks = (p.Cin + 15) / 16;
     q.cin16 = CinP / 16;
@@ -547,7 +555,7 @@ bool conv_wave_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t 
     q.buf_off = (uint32_t)(q.nks * 9 * nb * 1024);
     q.buf_bytes = (uint32_t)buf;
     q.bias_off = q.buf_off + kWavesW * q.buf_bytes;
-    const size_t lds = q.bias_off + (size_t)nb * 128;
+    l->lds = q.bias_off + (size_t)nb * 128;
     // Two of the smallest items per workgroup on lists too short to fill the device: eight, one per wave, stood at one CU's address
     // unit together (all active: 100 x 88, 32 -> 32, blocks of 8 5.2 -> 4.0 us, 64 -> 64 6.1 -> 5.5, stride 2 on 200 x 176, 128 -> 32,
     // blocks of 16 12.3 -> 10.2), one is no faster than two.
@@ -556,9 +564,21 @@ bool conv_wave_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t 
     q.per_xcd = (int)per_xcd;
     q.div_groups = make_fastdiv((uint32_t)q.ngroups);
     q.div_wgs = make_fastdiv((uint32_t)(8 * q.per_xcd));
-    const int grid = 8 * q.per_xcd * q.ngroups;
-    if (dt == SBNET_BF16) launch_wave<SBNET_BF16>(fused, form, nb, p, q, grid, lds, s);
-    else launch_wave<SBNET_F16>(fused, form, nb, p, q, grid, lds, s);
+    l->nb = nb;
+    l->grid = 8 * q.per_xcd * q.ngroups;
+    return true;
+}
+
+bool conv_wave_accepts(sbnet_dtype dt, bool fused, const ConvParams &p) {
+    LaunchW l;
+    return conv_wave_plan(dt, fused, p, ConvForm::plain, &l);
+}
+
+bool conv_wave_try(sbnet_dtype dt, bool fused, const ConvParams &p, hipStream_t s, sbnet_status *st, const char *who, ConvForm form) {
+    LaunchW l;
+    if (!conv_wave_plan(dt, fused, p, form, &l)) return false;
+    if (dt == SBNET_BF16) launch_wave<SBNET_BF16>(fused, form, l.nb, p, l.q, l.grid, l.lds, s);
+    else launch_wave<SBNET_F16>(fused, form, l.nb, p, l.q, l.grid, l.lds, s);
     *st = launch_status(who);
     return true;
 }

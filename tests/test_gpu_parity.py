@@ -957,6 +957,30 @@ def test_sparse_conv_from_flags_and_from_mask_are_the_list_call(N, H, W, Cin, Co
                            want)
 
 
+def _launches(fn):
+    """Kernel launches of fn(): the nodes of a graph that holds it."""
+    fn()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        fn()
+    n = ctypes.c_size_t()
+    assert sb.lib().hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("Cin,Cout,want", [(64, 64, 1), (64, 32, 1), (64, 96, 1), (64, 192, 1), (32, 256, 1),
+                                           (64, 128, 2), (32, 192, 2)])   # served by a kernel that needs the list
+def test_sparse_conv_from_flags_folds_the_compaction(Cin, Cout, want):
+    """One launch where the kernel that takes flags runs, also where another was asked first and refused."""
+    step("launches of from_flags %s" % ((Cin, Cout),))
+    g_in, g_out, Ho, Wo = sb.geometry(400, 352, 3, 1, 16)
+    x, y = (torch.zeros((1, 400, 352, c), dtype=torch.bfloat16, device="cuda") for c in (Cin, Cout))
+    wp = sb.pack_weights(torch.zeros((3, 3, Cin, Cout), dtype=torch.bfloat16, device="cuda"))
+    flags = sb.block_flags(torch.ones((1, 400, 352), dtype=torch.uint8, device="cuda"), g_in)
+    idx, cnt = torch.zeros((550, 3), dtype=torch.int32, device="cuda"), torch.zeros((1,), dtype=torch.int32, device="cuda")
+    assert _launches(lambda: sb.sparse_conv_from_flags(flags, x, g_in, g_out, wp, None, y, idx, cnt)) == want
+
+
 def _random_fused_shapes(n, seed):
     r = np.random.default_rng(seed)
     out = []
