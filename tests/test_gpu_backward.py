@@ -8,7 +8,7 @@ import torch
 import oracle as orc
 import paper_1801_02108_amd as sb
 from paper_1801_02108_amd import inputs as gen
-from util import CONV_TOL, TORCH_DT, assert_close, to_dev, to_host
+from util import CONV_TOL, TORCH_DT, assert_close, kernels, template_args, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -34,6 +34,10 @@ DGRAD_CASES = [
     (2, 11, 9, 6, 5, 3, 1, "bf16"),          # channel counts the matrix-core kernels do not take
     (1, 9, 9, 3, 7, 5, 1, "f16"),
     (2, 9, 11, 16, 16, 3, 3, "bf16"),        # stride 3
+    (3, 10, 10, 96, 48, 3, 1, "bf16"),       # groups of 96 with the weights in LDS
+    (3, 10, 10, 80, 40, 3, 1, "f16"),
+    (4, 18, 18, 200, 40, 3, 1, "f16"),       # weights that do not stay there
+    (2, 10, 10, 200, 40, 3, 1, "f16"),
 ]
 
 
@@ -67,7 +71,7 @@ WGRAD_CASES = [
     (6, 18, 18, 96, 192, 3, 1, "bf16"),      # several channel blocks
     (11, 10, 10, 40, 24, 3, 1, "bf16"),      # 8x8 blocks: half-filled matrix rows, ragged channel counts
     (4, 12, 15, 8, 16, 3, 1, "f16"),         # ragged tile: 10 x 13 outputs
-    (3, 34, 34, 16, 16, 3, 1, "bf16"),       # 32 x 32 outputs: two segments per row
+    (3, 34, 34, 16, 16, 3, 1, "bf16"),       # 32 x 32 outputs
     (3, 37, 41, 16, 8, 3, 2, "bf16"),        # stride 2 with two segments per row (18 x 20 outputs)
     (2, 21, 16, 8, 8, 3, 1, "bf16"),         # 19 output rows: the last stage is partly empty
     (3, 12, 20, 24, 16, 3, 1, "f32"),        # plain kernel
@@ -119,7 +123,10 @@ def test_conv_on_tiles_backward_weights(B, th, tw, Cin, Cout, k, s, dtype):
     (2, 2, 41, 37, 64, 32, 3, "f16"),      # tiles in slices, the last one short
     (2, 2, 3, 170, 8, 40, 3, "bf16"),      # a row or two to a slice
     (70, 70, 12, 12, 96, 96, 3, "bf16"),   # more tiles than splits of nine channel blocks
-    (30, 1100, 16, 16, 64, 64, 3, "bf16"), # a list bound that takes the kernel for long lists
+    (30, 1100, 16, 16, 64, 64, 3, "bf16"), # list bounds that take the kernel for long lists
+    (30, 1100, 16, 16, 64, 64, 3, "f16"),
+    (5, 260, 32, 32, 64, 64, 3, "bf16"),   # ... two segments a row
+    (4, 330, 30, 27, 40, 64, 3, "f16"),    # ... the second one partly empty, the last stage too
     (300, 300, 4, 4, 16, 16, 3, "f16"),    # fewer stages than splits
     (5, 9, 9, 15, 72, 64, 1, "f16"),       # runs of pixels that end inside a stage
     (64, 64, 16, 16, 64, 136, 1, "bf16"),
@@ -141,6 +148,8 @@ def test_weight_gradient_stages(B, cap, oh, ow, Cin, Cout, k, dtype):
         # products are exact in fp32, sums of n oh ow of them in any order
         assert_close(to_host(dw), want, 1e-4, "weight gradient, %d tiles" % n)
         assert torch.equal(dw, sb.conv_on_tiles_backward_weights(xd, gd, cnt, k))
+    name = kernels(lambda: sb.conv_on_tiles_backward_weights(xd, gd, cnt, k))[0]
+    assert ("wgrad_run" if k == 1 else "wgrad_mfma" if cap > 200 and oh > 4 else "wgrad_tile") in name
 
 
 def test_sparse_conv_gradients_end_to_end():
@@ -350,9 +359,39 @@ def test_residual_unit_backward_composed_from_single_calls(C, Cm, dens):
 ])
 def test_residual_unit_in_one_call_equals_single_calls(n, cap, bo, C, Cm, dtype):
     """Masks and zeroing in the epilogues of the convolutions, bias sums in one launch: the bits of the single calls."""
+    _unit_in_one_call(n, cap, bo, C, Cm, dtype)
+
+
+@pytest.mark.parametrize("n,cap,bo,C,Cm,dtype,kernel,args", [
+    # 3x3 layers of more channel groups than weights stay in LDS for: every item shape of the LDS-tiled kernel
+    (5, 7, 8, 64, 200, "bf16", "conv3", (32, 4, 2, 1, 3)),
+    (5, 7, 8, 64, 200, "f16", "conv3", (32, 4, 2, 1, 3)),
+    (2, 2, 4, 96, 200, "bf16", "conv3", (32, 2, 1, 1, 3)),
+    (2, 2, 4, 96, 200, "f16", "conv3", (32, 2, 1, 1, 3)),
+    (18, 20, 16, 64, 200, "bf16", "conv3", (32, 4, 2, 1, 6)),
+    (18, 20, 16, 64, 200, "f16", "conv3", (32, 4, 2, 1, 6)),
+    (36, 40, 16, 64, 200, "bf16", "conv3_pair", (32, 7, 32, 6, 3, 2, 2)),      # one round of 384-pixel items
+    (20, 40, 16, 64, 200, "bf16", "conv3_pair", (32, 7, 32, 6, 3, 2, 2)),      # one of 256-pixel ones
+    (36, 40, 16, 64, 200, "f16", "conv3_pair", (32, 7, 32, 6, 3, 2, 2)),
+    (12, 14, 24, 48, 200, "bf16", "conv3_pair", (32, 6, 32, 6, 2, 1, 2)),      # 256 pixels
+    (10, 14, 24, 48, 200, "f16", "conv3_pair", (32, 6, 32, 6, 2, 1, 2)),       # 128
+    # lists too long for the kernel that keeps the weights in LDS
+    (36, 1000, 16, 64, 64, "bf16", "conv3_pair", (32, 7, 32, 6, 3, 2, 2)),
+    (20, 24, 12, 64, 64, "f16", "conv_wave", (2, 2, 1)),                       # ... and that kernel, with groups of 64
+])
+def test_residual_unit_in_one_call_masks_in_every_kernel(n, cap, bo, C, Cm, dtype, kernel, args):
+    """The ReLU mask in the epilogue of the 3x3 data gradient, for every kernel and item shape that has one."""
+    backward = _unit_in_one_call(n, cap, bo, C, Cm, dtype)
+    of_3x3 = [k for k in kernels(backward) if kernel + "_kernel" in k]
+    dt = {"bf16": 1, "f16": 2}[dtype]
+    assert [template_args(k) for k in of_3x3] == [(dt, 1, 0, *args) if kernel == "conv_wave" else (dt, 1, 0, *args, 2)]
+
+
+def _unit_in_one_call(n, cap, bo, C, Cm, dtype):
     step("residual unit, one call %s" % ((n, cap, bo, C, Cm, dtype),))
     r = gen.rng_for(29, n * 100 + bo + C + Cm)
-    side, per = 20 * bo - 3, 20                     # blocks at the right and bottom edge reach outside the image
+    per = 20 if cap <= 400 else 32
+    side = per * bo - 3                             # blocks at the right and bottom edge reach outside the image
     g_in, g_out, _, _ = sb.geometry(side, side, 3, 1, bo)
     th = bo + 2
     cells = np.sort(r.permutation(per * per)[:cap])[::-1].copy()      # the last cells first: the edge is among the active
@@ -383,6 +422,7 @@ def test_residual_unit_in_one_call_equals_single_calls(n, cap, bo, C, Cm, dtype)
     assert torch.equal(one[0][:n], want[0][:n])
     for k in range(1, 7):
         assert torch.equal(one[k], want[k]), k
+    return lambda: sb.bottleneck_backward_on_tiles(tiles, t1, t2, d3, cnt, (q1, q2, q3))
 
 
 def test_residual_unit_backward_writes_over_its_incoming_gradient():

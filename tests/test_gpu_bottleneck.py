@@ -173,6 +173,22 @@ def test_unit_variants_around_the_lists_bound(C, Cm, dtype, preact, on_tiles, ca
         sb.set_tuning()
 
 
+@pytest.mark.parametrize("N,H,W,C,Cm,dtype,preact", [
+    (1, 48, 48, 64, 64, "f16", False), (1, 64, 48, 128, 32, "bf16", False), (2, 40, 40, 192, 48, "bf16", False),
+    (2, 48, 48, 256, 64, "bf16", False), (1, 48, 48, 96, 24, "f16", False),
+    (2, 48, 48, 256, 64, "bf16", True), (1, 40, 56, 128, 64, "f16", True)])
+def test_unit_in_16_pixel_sub_tiles(N, H, W, C, Cm, dtype, preact):
+    """Short lists launch the 8 x 8 variant alone: the 16 x 16 one, asked for, against the oracle."""
+    try:
+        sb.set_tuning(unit_small_item_cost_eighths=1000)
+        if preact:
+            test_preactivation_unit(N, H, W, C, 16, dtype)
+        else:
+            _unit_case(N, H, W, C, Cm, 16, dtype)
+    finally:
+        sb.set_tuning()
+
+
 @pytest.mark.parametrize("N,H,W,C,bo,dtype", [(2, 48, 48, 256, 16, "bf16"), (1, 40, 56, 128, 16, "f16"), (2, 40, 24, 256, 8, "bf16"),
                                               (1, 37, 29, 64, 8, "f16")])
 def test_preactivation_unit(N, H, W, C, bo, dtype):

@@ -10,7 +10,7 @@ import torch
 import oracle as orc
 import paper_1801_02108_amd as sb
 from paper_1801_02108_amd import inputs as gen
-from util import CONV_TOL, TORCH_DT, assert_close, round_like, to_dev, to_host
+from util import CONV_TOL, TORCH_DT, assert_close, kernels, round_like, template_args, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -930,6 +930,7 @@ def test_sparse_conv_from_mask(N, H, W, Cin, Cout, bo, dtype, add, dens, cap):
     (1, 176, 160, 32, 32, "f16", True),
     (1, 250, 170, 64, 24, "f16", False),      # ragged edges
     (1, 176, 160, 64, 64, "bf16", False),
+    (1, 176, 160, 32, 64, "bf16", False),
     (1, 400, 352, 64, 128, "bf16", True),     # 550 blocks, two groups: the kernel that keeps the weights in LDS
     (1, 400, 352, 64, 96, "f16", False),      # ... which does not take this width
 ])
@@ -957,17 +958,6 @@ def test_sparse_conv_from_flags_and_from_mask_are_the_list_call(N, H, W, Cin, Co
                            want)
 
 
-def _launches(fn):
-    """Kernel launches of fn(): the nodes of a graph that holds it."""
-    fn()
-    g = torch.cuda.CUDAGraph(keep_graph=True)
-    with torch.cuda.graph(g):
-        fn()
-    n = ctypes.c_size_t()
-    assert sb.lib().hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
-    return n.value
-
-
 @pytest.mark.parametrize("Cin,Cout,want", [(64, 64, 1), (64, 32, 1), (64, 96, 1), (64, 192, 1), (32, 256, 1),
                                            (64, 128, 2), (32, 192, 2)])   # served by a kernel that needs the list
 def test_sparse_conv_from_flags_folds_the_compaction(Cin, Cout, want):
@@ -978,7 +968,7 @@ def test_sparse_conv_from_flags_folds_the_compaction(Cin, Cout, want):
     wp = sb.pack_weights(torch.zeros((3, 3, Cin, Cout), dtype=torch.bfloat16, device="cuda"))
     flags = sb.block_flags(torch.ones((1, 400, 352), dtype=torch.uint8, device="cuda"), g_in)
     idx, cnt = torch.zeros((550, 3), dtype=torch.int32, device="cuda"), torch.zeros((1,), dtype=torch.int32, device="cuda")
-    assert _launches(lambda: sb.sparse_conv_from_flags(flags, x, g_in, g_out, wp, None, y, idx, cnt)) == want
+    assert len(kernels(lambda: sb.sparse_conv_from_flags(flags, x, g_in, g_out, wp, None, y, idx, cnt))) == want
 
 
 def _random_fused_shapes(n, seed):
@@ -1014,16 +1004,19 @@ def test_sparse_conv_random_shapes(N, H, W, Cin, Cout, s, bo, dtype, add):
     assert np.array_equal(got[~bm], y0[~bm])
 
 
-@pytest.mark.parametrize("H,W,bh,bw,Cin,Cout,dtype", [
+@pytest.mark.parametrize("H,W,bh,bw,Cin,Cout,dtype,kernel", [
     # sizes at which the 128-pixel items of all blocks outnumber the workgroups: below that the host plans no second shape
-    (110, 130, 18, 18, 96, 64, "bf16"),    # the 18x18 outputs of a data gradient on 16x16 blocks; blocks hang over the edge
-    (80, 120, 13, 28, 40, 72, "f16"),      # 364 pixels whose input rows only fit in 16-channel chunks
-    (120, 120, 19, 19, 32, 32, "bf16"),    # 361 pixels, one chunk
+    (110, 130, 18, 18, 96, 64, "bf16", "conv_wave"),       # the 18x18 outputs of a data gradient on 16x16 blocks; blocks hang over
+                                                           # the edge.  The weights fit LDS: no tile shapes, the tuning plays no part
+    (80, 120, 13, 28, 40, 72, "f16", "conv3_pair"),        # 364 pixels whose input rows only fit in 16-channel chunks
+    (120, 120, 19, 19, 32, 32, "bf16", "conv_wave"),       # 361 pixels, one chunk
+    (110, 130, 18, 18, 40, 200, "bf16", "conv3_pair"),     # more channel groups than weights stay in LDS for: 384 pixels in chunks of 32
+    (120, 120, 19, 19, 32, 200, "f16", "conv3_pair"),      # ... one chunk
 ])
 @pytest.mark.parametrize("choice", ["larger", "smaller", "by count"])
-def test_sparse_conv_blocks_of_257_to_384_pixels(H, W, bh, bw, Cin, Cout, dtype, choice):
-    """Blocks of 257 ... 384 output pixels have a tile shape of their own (one 384-pixel item per block) beside the
-    128-pixel one; the count picks on the device.  Both forced, and the default rule, against the oracle."""
+def test_sparse_conv_blocks_of_257_to_384_pixels(H, W, bh, bw, Cin, Cout, dtype, kernel, choice):
+    """Blocks of 257 ... 384 output pixels have a tile shape of their own in the LDS-tiled kernel (one 384-pixel item per block)
+    beside the 256-pixel one; the count picks on the device.  Both forced, and the default rule, against the oracle."""
     step("sparse_conv 384-pixel shape %s %s" % (choice, (H, W, bh, bw, Cin, Cout, dtype)))
     r = gen.rng_for(5, H * 100 + Cin + bh)
     g_in, g_out = sb.Geom(), sb.Geom()
@@ -1050,21 +1043,28 @@ def test_sparse_conv_blocks_of_257_to_384_pixels(H, W, bh, bw, Cin, Cout, dtype,
             got = to_host(y)
             assert_close(got, ref, CONV_TOL[dtype], "fused, %s shape" % choice)
             assert np.array_equal(got[~bm], y0[~bm])
+        d_x = to_dev(x, dtype)
+        name, = kernels(lambda: sb.sparse_conv(d_x, d_idx, d_cnt, g_in, g_out, wp, d_b, y, relu=True))
+        assert kernel + "_kernel" in name
+        assert kernel != "conv3_pair" or template_args(name)[7:9] == (3, 2)      # pixel blocks per wave: 384 and 256 pixels
     finally:
         sb.set_tuning()
 
 
-@pytest.mark.parametrize("H,W,Cin,Cout,dtype", [
-    (224, 224, 16, 96, "bf16"),      # groups of 96 output channels
-    (224, 200, 24, 128, "f16"),      # groups of 128; blocks hang over the right edge
-    (224, 224, 32, 256, "bf16"),     # two groups of 128, two chunks
-    (200, 224, 16, 384, "bf16"),     # three groups of 128
+@pytest.mark.parametrize("H,W,Cin,Cout,dtype,kernel,wide", [
+    (224, 224, 16, 96, "bf16", "conv_wave", None),     # the weights fit LDS: no groups of this kind
+    (224, 200, 24, 128, "f16", "conv_wave", None),     # blocks hang over the right edge
+    (224, 224, 32, 256, "bf16", "conv3_mixed", 4),     # two groups of 128, two chunks
+    (200, 224, 16, 384, "bf16", "conv3_mixed", 4),     # three groups of 128
+    (224, 224, 72, 96, "bf16", "conv3_mixed", 3),      # groups of 96; the last chunk half empty
+    (224, 200, 72, 96, "f16", "conv3_mixed", 3),       # blocks hang over the right edge
+    (224, 200, 24, 256, "f16", "conv3_mixed", 4),
 ])
 @pytest.mark.parametrize("add", [False, True])
-def test_sparse_conv_strided_wide_channel_groups(H, W, Cin, Cout, dtype, add):
-    """Stride-2 3x3 convolutions on 16x16 blocks whose output channels are a multiple of 96 or 128: one launch holds
-    128-pixel work items with groups of 96 / 128 channels and with groups of 64, and the count picks (wide from 96 work
-    items).  All 49 blocks active runs the wide items, a handful of blocks the 64-channel ones."""
+def test_sparse_conv_strided_wide_channel_groups(H, W, Cin, Cout, dtype, kernel, wide, add):
+    """Stride-2 3x3 convolutions on 16x16 blocks whose output channels are a multiple of 96 or 128 and whose weights do not
+    fit LDS: one launch holds 128-pixel work items with groups of 96 / 128 channels and with groups of 64, and the count
+    picks (wide from 96 work items).  All 49 blocks active runs the wide items, a handful of blocks the 64-channel ones."""
     step("sparse_conv strided, wide groups add=%s %s" % (add, (H, W, Cin, Cout, dtype)))
     r = gen.rng_for(5, H * 100 + Cin + Cout)
     N, s, bo = 1, 2, 16
@@ -1094,17 +1094,25 @@ def test_sparse_conv_strided_wide_channel_groups(H, W, Cin, Cout, dtype, add):
         y = to_dev(y0, dtype)
         sb.sparse_scatter(out, d_idx, d_cnt, g_out, y, add=add)
         assert_close(to_host(y), ref, CONV_TOL[dtype], "unfused, %d blocks" % len(idx))
+    d_x = to_dev(x, dtype)
+    for name in kernels(lambda: (sb.sparse_conv(d_x, d_idx, d_cnt, g_in, g_out, wp, d_b, y, stride=s, relu=True, add=add),
+                                 sb.conv_on_tiles(tiles, d_cnt, wp, d_b, stride=s, relu=True))):
+        assert kernel + "_kernel" in name and (wide is None or template_args(name)[3] == wide)
 
 
-@pytest.mark.parametrize("bo,side,Cin,Cout,dtype,add", [
-    (12, 140, 48, 80, "f16", False),     # ragged map; three chunks of 16 channels, 16 of 96 output channels empty
-    (16, 192, 96, 96, "bf16", True),     # six chunks, a full group of 96
-    (14, 168, 40, 72, "bf16", False),    # last chunk half filled, 24 output channels empty
-    (16, 190, 40, 288, "bf16", True),    # ragged map, three groups of 96
+@pytest.mark.parametrize("bo,side,Cin,Cout,dtype,add,rows,kernel", [
+    (12, 140, 48, 80, "f16", False, 144, "conv_wave"),      # ragged map; 16 of 96 output channels empty
+    (16, 192, 96, 96, "bf16", True, 144, "conv3_wide96"),   # six chunks, a full group of 96
+    (14, 168, 40, 72, "bf16", False, 144, "conv_wave"),     # last chunk half filled, 24 output channels empty
+    (16, 190, 40, 288, "bf16", True, 144, "conv3_wide96"),  # ragged map, three groups of 96
+    (14, 168, 40, 72, "bf16", False, 520, "conv3_wide96"),  # the list's bound takes the kernel for long lists: 24 channels empty
+    (14, 165, 40, 72, "f16", False, 520, "conv3_wide96"),   # ragged map
+    (12, 140, 48, 288, "f16", False, 144, "conv3_wide96"),  # three chunks of 16 channels, three groups
 ])
-def test_sparse_conv_groups_of_96_at_stride_1(bo, side, Cin, Cout, dtype, add):
-    """One launch holds 256-pixel items with groups of 96 channels, and items of 256 and 128 pixels with groups of 64.
-    On a grid of 144 blocks the count picks the wide items with all of them active, the others with 100 and with 20."""
+def test_sparse_conv_groups_of_96_at_stride_1(bo, side, Cin, Cout, dtype, add, rows, kernel):
+    """One launch of the LDS-tiled kernel holds 256-pixel items with groups of 96 channels, and items of 256 and 128 pixels with
+    groups of 64.  On a grid of 144 blocks the count picks the wide items with all of them active, the others with 100 and
+    with 20.  (Where the weights fit LDS another kernel has groups of 96 of its own.)"""
     step("sparse_conv stride 1, groups of 96 %s" % ((bo, side, Cin, Cout, dtype, add),))
     r = gen.rng_for(5, side * 100 + Cin + Cout)
     g_in, g_out, Ho, Wo = sb.geometry(side, side, 3, 1, bo)
@@ -1119,6 +1127,7 @@ def test_sparse_conv_groups_of_96_at_stride_1(bo, side, Cin, Cout, dtype, add):
         blocks[r.permutation(144)[:n]] = 1
         mask = np.kron(blocks.reshape(1, 12, 12), np.ones((1, bo, bo), np.uint8))[:, :side, :side].copy()
         d_idx, d_cnt = sb.reduce_mask(torch.from_numpy(mask).cuda(), g_out)      # window = output block
+        d_idx = torch.cat([d_idx, d_idx.new_zeros((rows - 144, 3))])             # rows beyond the count are not read
         idx = orc.reduce_mask(mask, ogeom(g_out))
         assert len(idx) == n
         ref = orc.sparse_conv_dense(x, idx, ogeom(g_out), w, b, y0, stride=1, relu=True, add=add)
@@ -1132,6 +1141,8 @@ def test_sparse_conv_groups_of_96_at_stride_1(bo, side, Cin, Cout, dtype, add):
         y = to_dev(y0, dtype)
         sb.sparse_scatter(out, d_idx, d_cnt, g_out, y, add=add)
         assert_close(to_host(y), ref, CONV_TOL[dtype], "unfused, %d blocks" % n)
+    name, = kernels(lambda: sb.sparse_conv(d_x, d_idx, d_cnt, g_in, g_out, wp, d_b, y, relu=True, add=add))
+    assert kernel + "_kernel" in name
 
 
 @pytest.mark.parametrize("bo,grid,ragged,Cin,Cout,dtype,add", [
@@ -1143,6 +1154,8 @@ def test_sparse_conv_groups_of_96_at_stride_1(bo, side, Cin, Cout, dtype, add):
     (15, 12, 0, 48, 56, "bf16", False),   # odd rows
     (5, 20, 3, 8, 8, "bf16", False),      # tiles smaller than an item
     (23, 8, 9, 32, 40, "bf16", True),     # the widest rows of an item
+    (8, 20, 0, 48, 32, "f16", False),
+    (16, 16, 5, 64, 96, "f16", True),
 ])
 def test_sparse_conv_strided_with_resident_weights(bo, grid, ragged, Cin, Cout, dtype, add):
     """Stride-2 layers whose weights stay in LDS: items of 32 pixels by all channels of a group or by 32, by the count."""
@@ -1177,12 +1190,15 @@ def test_sparse_conv_strided_with_resident_weights(bo, grid, ragged, Cin, Cout, 
         y = to_dev(y0, dtype)
         sb.sparse_scatter(out, d_idx, d_cnt, g_out, y, add=add)
         assert_close(to_host(y), ref, CONV_TOL[dtype], "unfused, %d blocks" % n)
+    for name in kernels(lambda: (sb.sparse_conv(d_x, d_idx, d_cnt, g_in, g_out, wp, d_b, y, stride=2, relu=True, add=add),
+                                 sb.conv_on_tiles(tiles, d_cnt, wp, d_b, stride=2, relu=True))):
+        assert "conv_wave_kernel" in name
 
 
 @pytest.mark.parametrize("bo,grid,ragged,Cin,Cout,dtype,add", [
     (16, 16, 0, 48, 64, "bf16", False),   # a chunk of 32 channels and one of 16
     (16, 16, 7, 24, 96, "f16", True),     # groups of 96; one chunk, its last eight channels empty; ragged map
-    (16, 16, 0, 64, 32, "bf16", True),    # blocks of 16 x 16: the kernel that takes flags
+    (16, 16, 0, 64, 32, "bf16", True),    # the one case that another kernel takes: the one for flags
     (32, 8, 0, 64, 32, "bf16", True),     # groups of 32
     (12, 16, 5, 40, 72, "f16", False),    # 64 pixels begin inside a row; the last channel block partly empty
     (8, 20, 0, 64, 128, "bf16", True),    # two groups of 64
@@ -1190,6 +1206,8 @@ def test_sparse_conv_strided_with_resident_weights(bo, grid, ragged, Cin, Cout, 
     (6, 20, 3, 8, 8, "bf16", False),      # tiles smaller than an item
     (24, 8, 9, 32, 40, "bf16", True),
     (30, 6, 0, 64, 64, "bf16", False),    # the widest rows of an item
+    (8, 20, 5, 64, 32, "f16", False),
+    (12, 16, 0, 48, 80, "bf16", True),
 ])
 def test_sparse_conv_with_resident_weights(bo, grid, ragged, Cin, Cout, dtype, add):
     """Layers whose weights stay in LDS: items of 64 or 32 pixels by all channels of a group, or of 32 by 32, by the count."""
@@ -1222,17 +1240,74 @@ def test_sparse_conv_with_resident_weights(bo, grid, ragged, Cin, Cout, dtype, a
         y = to_dev(y0, dtype)
         sb.sparse_scatter(out, d_idx, d_cnt, g_out, y, add=add)
         assert_close(to_host(y), ref, CONV_TOL[dtype], "unfused, %d blocks" % n)
+    for name in kernels(lambda: (sb.sparse_conv(d_x, d_idx, d_cnt, g_in, g_out, wp, d_b, y, relu=True, add=add),
+                                 sb.conv_on_tiles(tiles, d_cnt, wp, d_b, relu=True))):
+        assert ("conv16_kernel" if (bo, Cin, Cout) == (16, 64, 32) else "conv_wave_kernel") in name
+
+
+@pytest.mark.parametrize("bh,bw,gh,gw,s,Cin,Cout,dtype,add,kernel,args", [
+    # layers of more channel groups than weights stay in LDS for (40 or 16 -> 200), and blocks that no item of the wide groups fits
+    (8, 8, 6, 7, 1, 16, 200, "bf16", True, "conv3", (32, 2, 1, 1, 3)),            # one item of 64 pixels
+    (8, 8, 6, 7, 1, 40, 200, "f16", True, "conv3", (32, 2, 1, 1, 3)),
+    (8, 8, 6, 7, 2, 40, 200, "bf16", True, "conv3", (32, 2, 1, 1, 6)),            # ... with rows twice as wide
+    (7, 8, 6, 7, 2, 16, 200, "f16", False, "conv3", (32, 2, 1, 1, 6)),
+    (16, 16, 5, 6, 2, 40, 200, "bf16", False, "conv3", (16, 4, 2, 1, 5)),         # items of 128 pixels in 16-channel chunks
+    (16, 16, 5, 6, 2, 16, 200, "f16", True, "conv3", (16, 4, 2, 1, 5)),
+    (16, 24, 4, 5, 2, 40, 200, "f16", False, "conv3", (16, 4, 2, 1, 9)),
+    (24, 24, 4, 5, 1, 40, 200, "bf16", False, "conv3_pair", (32, 6, 32, 6, 2, 1, 2)),   # 256 pixels beside 128
+    (24, 23, 4, 5, 1, 16, 200, "f16", True, "conv3_pair", (32, 6, 32, 6, 2, 1, 2)),
+])
+def test_sparse_conv_item_shapes_of_the_lds_tiled_kernel(bh, bw, gh, gw, s, Cin, Cout, dtype, add, kernel, args):
+    """3x3 layers whose weights do not stay in LDS: every tile shape, both of a pair forced, fused and on tiles."""
+    step("sparse_conv item shapes %s" % ((bh, bw, gh, gw, s, Cin, Cout, dtype, add),))
+    r = gen.rng_for(5, bh * 1000 + bw * 10 + Cin + s)
+    Ho, Wo, total = bh * gh - 3, bw * gw - 2, gh * gw
+    H, W = Ho * s, Wo * s
+    g_in, g_out = sb.Geom(), sb.Geom()
+    ho, wo = ctypes.c_int(), ctypes.c_int()
+    assert sb.lib().sbnet_geometry(H, W, 3, 3, s, s, bh, bw, g_in, g_out, ho, wo) == 0
+    assert (ho.value, wo.value, g_out.bcount_h, g_out.bcount_w) == (Ho, Wo, gh, gw)
+    x = gen.activations(r, (1, H, W, Cin), dtype)
+    w = gen.conv_weights(r, 3, 3, Cin, Cout, dtype)
+    b = gen.bias_vector(r, Cout, 0.5)
+    y0 = gen.activations(r, (1, Ho, Wo, Cout), dtype)
+    wp, d_b, d_x = sb.pack_weights(to_dev(w, dtype)), torch.from_numpy(b).cuda(), to_dev(x, dtype)
+    try:
+        for n, cost in ((total, 100000), (total, 0), (2, None)):                 # the larger items, the smaller ones, the rule
+            sb.set_tuning(**({} if cost is None else {"conv3_small_item_cost_eighths": cost}))
+            cells = np.sort(r.permutation(total)[:n])
+            idx = np.stack([np.zeros(n), cells // gw, cells % gw], 1).astype(np.int32)
+            d_idx, d_cnt = dev_indices(idx, total)
+            ref = orc.sparse_conv_tiled(x, idx, ogeom(g_in), ogeom(g_out), w, b, y0, stride=s, relu=True, add=add)
+            bm = orc.block_mask(idx, ogeom(g_out), 1, Ho, Wo)
+            y = to_dev(y0, dtype)
+            sb.sparse_conv(d_x, d_idx, d_cnt, g_in, g_out, wp, d_b, y, stride=s, relu=True, add=add)
+            got = to_host(y)
+            assert_close(got, ref, CONV_TOL[dtype], "fused, %d blocks" % n)
+            assert np.array_equal(got[~bm], y0[~bm])
+            tiles = sb.sparse_gather(d_x, d_idx, d_cnt, g_in)
+            out = sb.conv_on_tiles(tiles, d_cnt, wp, d_b, stride=s, relu=True)
+            y = to_dev(y0, dtype)
+            sb.sparse_scatter(out, d_idx, d_cnt, g_out, y, add=add)
+            assert_close(to_host(y), ref, CONV_TOL[dtype], "unfused, %d blocks" % n)
+        names = kernels(lambda: (sb.sparse_conv(d_x, d_idx, d_cnt, g_in, g_out, wp, d_b, y, stride=s, relu=True, add=add),
+                                 sb.conv_on_tiles(tiles, d_cnt, wp, d_b, stride=s, relu=True)))
+        dt = {"bf16": 1, "f16": 2}[dtype]
+        assert [template_args(k) for k in names] == [(dt, 1, int(add), *args, 0), (dt, 0, 0, *args, 0)]
+        assert all(kernel + "_kernel" in k for k in names)
+    finally:
+        sb.set_tuning()
 
 
 @pytest.mark.parametrize("dens", [1.0, 0.35])
-@pytest.mark.parametrize("Cin", [32, 40])
-def test_sparse_conv_more_tiles_than_workgroups(dens, Cin):
-    """Persistent kernels: 342 tiles on at most 256 workgroups, so the double-buffered tile loop and its prefetch
-    run several iterations per workgroup.  Cin = 32: register-stationary kernel; Cin = 40: LDS-tiled kernel, which
-    launches its 256-pixel and its 128-pixel variant and lets the device-side count pick (above / below 256 items)."""
-    step("sparse_conv persistent loop dens=%s Cin=%d" % (dens, Cin))
+@pytest.mark.parametrize("Cin,Cout,kernel", [(32, 64, "conv16"), (40, 64, "conv_wave"), (16, 200, "conv3_pair")])
+def test_sparse_conv_more_tiles_than_workgroups(dens, Cin, Cout, kernel):
+    """Persistent kernels: 342 tiles on at most 256 workgroups, so the double-buffered tile loop and its prefetch run several
+    iterations per workgroup.  conv16: register-stationary kernel; conv_wave: the one that keeps its weights in LDS, runs of
+    items per wave; conv3_pair: LDS-tiled kernel, which holds its 256-pixel and its 128-pixel variant and lets the count pick."""
+    step("sparse_conv persistent loop dens=%s %d -> %d" % (dens, Cin, Cout))
     r = gen.rng_for(5, 999)
-    N, H, W, Cout, bo = 1, 288, 304, 64, 16
+    N, H, W, bo = 1, 288, 304, 16
     g_in, g_out, Ho, Wo = sb.geometry(H, W, 3, 1, bo)
     x = gen.activations(r, (N, H, W, Cin), "bf16")
     w = gen.conv_weights(r, 3, 3, Cin, Cout, "bf16")
@@ -1251,6 +1326,9 @@ def test_sparse_conv_more_tiles_than_workgroups(dens, Cin):
     assert_close(got, ref, CONV_TOL["bf16"], "persistent")
     bm = orc.block_mask(idx, ogeom(g_out), N, Ho, Wo)
     assert np.array_equal(got[~bm], y0[~bm])
+    d_x, wp = to_dev(x, "bf16"), sb.pack_weights(to_dev(w, "bf16"))
+    name, = kernels(lambda: sb.sparse_conv(d_x, d_idx, d_cnt, g_in, g_out, wp, None, y, add=True))
+    assert kernel + "_kernel" in name
 
 
 def test_config1_end_to_end():

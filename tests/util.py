@@ -1,4 +1,6 @@
 """Helpers shared by the GPU parity tests: host<->device marshalling and the tolerance rule."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -7,6 +9,41 @@ TORCH_DT = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
 # bf16 are the stated targets; fp16 (11-bit significand, unit roundoff 2^-11 = 4.9e-4, one
 # rounding of the output plus fp32 accumulation) gets 4e-3.
 CONV_TOL = {"f32": 1e-4, "bf16": 2e-2, "f16": 4e-3}
+
+
+class _KernelNode(ctypes.Structure):             # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
+def kernels(fn):
+    """The (mangled) names of the kernels that fn() launches, in order: the nodes of a graph that holds it."""
+    import paper_1801_02108_amd as sb
+    hip = sb.lib()
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+    fn()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        fn()
+    graph, n = ctypes.c_void_p(g.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    names = []
+    for node in nodes:
+        kind, node = ctypes.c_int(), ctypes.c_void_p(node)
+        assert hip.hipGraphNodeGetType(node, ctypes.byref(kind)) == 0 and kind.value == 0, "not a kernel"
+        q = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(node, ctypes.byref(q)) == 0
+        names.append(hip.hipKernelNameRefByPtr(ctypes.c_void_p(q.func), None).decode())
+    return names
+
+
+def template_args(name):
+    """The whole-number and boolean template arguments in a kernel's mangled name: _ZN5sbnet6kernelILi1ELb0EE... -> (1, 0)."""
+    import re
+    m = re.search(r"I((?:L[ib]\d+E)+)E", name)
+    return tuple(int(v) for v in re.findall(r"L[ib](\d+)E", m.group(1))) if m else ()
 
 
 def to_dev(a, dtype):
