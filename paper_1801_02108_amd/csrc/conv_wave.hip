@@ -1,6 +1,7 @@
 // 3x3 tile convolution of stride 1 or 2, bf16 / f16, for layers whose weights stay in LDS: all input channels by a group of 32, 64
-// or 96 output channels, at most about 100 KB (Sec. 3.2 and 3.4 of arXiv 1801.02108: the regular convolution between
-// gather and scatter; fused with both, and as the data gradient of a tile convolution).
+// or 96 output channels, at most 160 KB with eight waves' buffers of 2.5 to 12 KB and the bias (Sec. 3.2 and 3.4 of arXiv
+// 1801.02108: the regular convolution between gather and scatter; fused with both, and as the data gradient of a tile
+// convolution).
 //
 // conv3.hip stages a chunk of weights with every chunk of pixels and has its workgroup meet at a barrier per chunk.  Here
 // the weights are copied to LDS once for the life of the workgroup and every wave works by itself from then on:
@@ -22,9 +23,11 @@
 //   * Stride 2: items of 32 pixels (their rows are twice as many and twice as wide), chunks of 16 channels (so that 64 -> 96 keeps
 //     all its weights beside eight buffers), the even columns of a row before its odd ones.  conv3 -> this: 800 x 704 to
 //     400 x 352, blocks of 16, 64 -> 96, 5 % active 9.1 -> 7.4, 30 % 18.3 -> 12.5; 32 -> 32, all 17.6 -> 11.7.
-// What bounds it at many items: matrix steps 37 % of the time, LDS 34 %, the address unit (copies of 64-byte pieces, stores)
-// 40 %, vector instructions 39 %; with fewer than two items per wave the latency of an item and the copy of the weights.
-// The sum over (chunk of 32 channels, tap, 16 channels) runs in the order of conv3's 32-channel chunks: same bits.
+// What bounds it at many items (1600 x 1408, half of all blocks of 12, 64 -> 64, counters): matrix cores busy 38 % of the time,
+// LDS 44 (11 of them bank conflicts), the address unit (copies of 64-byte pieces, stores) 40, vector
+// instructions 41, beside each other; with fewer than two items per wave the latency of an item and the copy of the weights.
+// At stride 1 the sum over (chunk of 32 channels, tap, 16 channels) runs in the order of conv3's 32-channel chunks: same bits.  At
+// stride 2 it runs over (chunk of 16 channels, tap), conv3's order with 16-channel chunks.
 #include "conv_common.h"
 
 #include <type_traits>
@@ -517,22 +520,57 @@ static bool conv_wave_plan(sbnet_dtype dt, bool fused, const ConvParams &p, Conv
     if (nb == 0) return false;
     q.ngroups = (blocks + nb - 1) / nb;
     if (q.ngroups > 2) return false;
-    // Stride 2: blocks' pixels (in 16 x 16 blocks of the list's bound) beyond which conv3 is as fast.  Up to 48 input channels here
-    // at any number (1600 x 1408, half of 2200 blocks of 16: 32 -> 64 28.9 us by conv3 and 26.9 here, 48 -> 96 48.6 and 43.2), but
-    // for rows so wide that an item stages more than 8 KB a chunk (800 x 704, 32 -> 64, blocks of 14, 60 % 12.4 and 11.4, all 17.0
-    // and 18.4).  From 64 channels a line of memory is fetched once for each of its four chunks, and long lists wait for that.
-    // 800 x 704 (550 blocks of 16): groups of 96, 64 -> 96, 10 x 10, 30 % 17.2 and 13.9, all 41.4 and 40.1, 16 x 16 18.3 and 12.5,
-    // 38.2 and 37.1, half of 1600 x 1408 64.2 and 71.3; small blocks of more than 64 channels, for which conv3 has no wide
-    // group, 64 -> 128, 8 x 8, all 53.3 and 36.7; 64 -> 64 on blocks that fill their items, 16 x 16, 5 % 9.1 and 6.1, 30 %
-    // 16.6 and 10.9, 60 % 21.7 and 22.4, all 40.1 and 35.2; else 12 x 12, 30 % 20.5 and 12.9, 60 % 22.8 and 26.4; blocks that fill their items badly, 10 x 10, 64 -> 128, 5 % 8.8 and 8.2, 15 % 10.9 and 11.4, 14 x 14
-    // 10.4 and 9.0, 12.6 and 12.6; two groups of 32, 96 -> 64, 14 x 14, 5 % 14.1 and 9.5, 15 % 14.3 and 15.4.  More than eight chunks
-    // one after the other, where conv3's items of 64 pixels fit the block as well: 200 x 176, 192 -> 32, 8 x 8, 5 % 11.4 and 9.5,
-    // 15 % 11.7 and 12.1, all 11.8 and 13.0.  110 KB of weights for a few small blocks: 200 x 176, 64 -> 96, 8 x 8, 30 % 7.3 and 7.5.
+    // The longest list, in blocks of 256 pixels of its bound, that is served here (`most`).  At stride 2 a line of memory is
+    // fetched once for each of its chunks of 16 channels, and long lists, whose maps do not stay in the caches, wait for that:
+    // most layers lose from some length on where every block is active and win where few are.  What was measured on either side,
+    // us by conv3 and here at 5, 10, 30, 60, 100 % of the bound active unless named, or the change from conv3 to here in % at 10,
+    // 40, 70, 100 % (two maps in turn).  The lines of 40, 60 and 180 lie between the numbers of active blocks at which the curves
+    // of a list of 550 cross.
+    //   layer                                          most  blocks  figures
+    //   up to 48 channels (in %):
+    //     blocks of up to 64 pixels                      -   8 x 8: -30 to -50 at any length
+    //     8 KB a chunk, up to 256 pixels, 12 x 12:
+    //       33 to 48 -> 64                             600     600   -16 +3 +5 +10; 2000 -28 +15 +27 +30; 10000 +25 +38 +47 +53
+    //       33 to 48 -> 32 or 96                      1000    1000   -22 -6 +2 -6; 2000 -35 +6 +17 +25; 96: -16 -5 -1 -13; -35 +1 +15 +11
+    //       up to 32                                  1500    1500   32 -> 64 -38 +1 0 -6; 3000 -10 +4 +19 +12; 32 -> 32 -47 -13 -13 -19; 6000
+    //                                                                -11 +6 +12 +15; 24 -> 96 3000 -18 -14 +8 +13
+    //     others, groups of 64, 16 x 16               2000    2000   32 -> 64 -32 -8 -8 -3; 3000 -14 -4 +9 +11; 48 -> 64 -28 -16 -6 +1; 3000
+    //                                                                -8 -3 0 +8; 10000 -8 +5 +9 +11; 16 -> 128 -15 -3 +4 +3; 4000
+    //                                                                -16 +2 +6 +19; 24 x 24, 48 -> 64 -27 -13 -3 +5
+    //       10 x 10, which fill their items badly    1000    1000   48 -> 64 +1 +3 -2 -11; 2000 +4 +7 +11 +8
+    //     ... of 32                                   6000    6000   16 x 16, 48 -> 32 -26 -6 +1 +6; 10000 -15 -1 +3 +7
+    //       10 x 10                                  3000    3000   48 -> 32 -7 -3 0 -1; 4000 -6 +2 +8 +10
+    //     ... of 96                                     -    10000   16 x 16, 48 -> 96 -6 -3 -2 -3; 24 x 24 -39 -36 -34 -33
+    //     more than 8 KB a chunk, 14 x 14              400     550   32 -> 64 (us) 60 % 12.4 11.4, all 17.0 18.4
+    //   from 64 channels (us):
+    //   groups of 96: 64 -> 96, 16 x 16                 600    550   10.3 7.8, 13.3 9.9, 20.4 14.8, 27.3 25.9, 39.3 37.9
+    //                                                          600   9.5 7.6, 12.9 9.4, 20.0 15.3, 27.1 27.0, 39.5 41.4
+    //                                                          800   9.5 7.7, 13.2 10.3, 21.1 18.9, 34.7 33.3, 56.0 55.4
+    //                                                          1100  12.9 9.0, 13.7 12.3, 28.3 26.9, 49.3 48.3, 72.9 77.2
+    //                                                          2200  13.6 12.2, 21.0 17.1, 50.1 50.0, 86.0 92.4, 133 143
+    //   small blocks of more than 64 channels, for
+    //   which conv3 has no wide group: 64 -> 128, 8 x 8 600    550   all 53.3 36.7
+    //   64 channels, blocks that fill their items:
+    //   64 -> 64, 16 x 16                               600    550   5 % 9.1 6.1, 30 % 16.6 10.9, 60 % 21.7 22.4, all 40.1 35.2
+    //   two groups of 32: 96 -> 64, 14 x 14              40    550   5 % 14.1 9.5, 15 % 14.3 15.4
+    //   blocks that fill their items badly:              60    550   64 -> 128, 10 x 10, 5 % 8.8 8.2, 15 % 10.9 11.4; 14 x 14,
+    //                                                                10.4 9.0, 12.6 12.6
+    //   others: 64 -> 64, 12 x 12                       180    550   30 % 20.5 12.9, 60 % 22.8 26.4
+    // Not taken at any length: more than eight chunks one after the other, where conv3's items of 64 pixels fit the block as well
+    // (200 x 176, 192 -> 32, 8 x 8, 5 % 11.4 9.5, 15 % 11.7 12.1, all 11.8 13.0), and 110 KB of weights for a few small blocks (200 x
+    // 176, 64 -> 96, 8 x 8, 30 % 7.3 7.5).
+    const long long any = 1LL << 40;
     if (strided) {
-        const long long most = q.nks <= 3 ? (q.copies[1] > 8 ? 400 : 1LL << 40)
-                             : nb == 3 || (M <= 64 && blocks > 2) || (q.nks <= 4 && M >= 256 && M % 32 == 0) ? 600
-                             : nb == 1 && q.ngroups == 2 ? 40
-                             : M > 64 && passes[1] * 32 * 8 > M * 9 ? 60 : 180;
+        const bool bad_fit = M > 64 && passes[1] * 32 * 8 > M * 9;           // an eighth of the items is padding
+        long long most = 180;
+        if (q.nks <= 3) {
+            if (q.copies[1] > 8) most = 400;
+            else if (M <= 64) most = any;
+            else if (q.copies[1] > 6 && M < 256) most = q.nks < 3 ? 1500 : nb == 2 ? 600 : 1000;
+            else most = nb == 3 ? any : (nb == 2 ? 2000 : 6000) / (bad_fit ? 2 : 1);
+        } else if (nb == 3 || (M <= 64 && blocks > 2) || (q.nks <= 4 && M >= 256 && M % 32 == 0)) most = 600;
+        else if (nb == 1 && q.ngroups == 2) most = 40;
+        else if (bad_fit) most = 60;
         if (p.cap * M > most * 256 || (q.nks > 8 && M <= 64)) return false;
         if (nb == 3 && q.nks > 3 && M <= 64 && p.cap * M <= 64 * 256) return false;
     }
@@ -543,8 +581,22 @@ static bool conv_wave_plan(sbnet_dtype dt, bool fused, const ConvParams &p, Conv
     // Groups of 96 beside conv3's wide items of 256 pixels: blocks of more than 256 pixels are even (24 x 24, 48 -> 80: 20 %
     // active 11.3 us there, 11.8 here, all 28.6 and 28.7), and so are those whose pixels no item size fits better than
     // theirs, with the last round the worse here (14 x 14: 5 % active 8.5 and 6.2, 20 % 11.2 and 10.6, 60 % 18.1 and 18.0, all
-    // 754 blocks 23.2 and 25.8): there while the list's bound is two of their rounds.
+    // 754 blocks 23.2 and 25.8): there while the list's bound is two of their rounds.  14 x 14, 5, 30, 60, 100 % active, conv3
+    // and here: 48 -> 80, 512 blocks 7.9 6.1, 11.6 10.8, 18.1 14.1, 19.7 20.1, 754 8.4 6.1, 13.2 12.8, 19.2 19.4, 25.4 28.9, 2200 10.1
+    // 8.9, 26.1 25.6, 41.8 42.6, 61.6 61.6; 48 -> 96, 512 7.9 5.8, 10.7 9.4, 16.4 12.2, 17.4 16.1, 754 8.0 5.8, 11.2 10.5, 16.9 15.1,
+    // 23.3 21.9.
     if (!strided && nb == 3 && (M > 256 || (M > 192 && M < 256 && p.cap > 512))) return false;
+    // ... and from 33 channels on 256 pixels, where those items are full: change in % at 10, 40, 70, 100 % active, 16 x 16: 40 -> 80, 800
+    // blocks -14 -12 -6 -1, 1100 -16 +1 +21 +9, 2500 -8 +8 +13 +16; 48 -> 80 the same; 48 -> 96, 4000 -16 -3 -1 0, 6000 -21 -1 +11 +13.
+    // Up to 32 channels (24 -> 96), for which conv3 has no such groups, -11 to -25 at any length.
+    if (!strided && nb == 3 && M > 192 && p.Cin > 32 && p.cap * M > (p.Cout % 96 ? 800 : 4000) * 256) return false;
+    // Long lists of blocks whose pixels neither item fits: 64 -> 64 in units of 256 pixels, 15 x 15, 1000 -17 -14 -3 -5, 3000 -22 +5 +4
+    // +4; 14 x 14, 4000 -22 -1 0 +3, 6000 -8 +7 +11 +11; 48 -> 64 and 32 -> 64 -15 to +6 up to 10000.
+    if (!strided && nb == 2 && q.nks > 3 && M > 192 && M < 256 && p.cap * M > 3000 * 256) return false;
+    // Wide rows of one chunk, half of them or more outside the item and the map's lines written in two halves: on tiles, the same units,
+    // 35 x 35, 8 -> 64, 1000 -26 -14 -4 -2, 1500 -6 -10 0 +13, 2500 -1 +4 +18 +28; 33 x 33, 16 -> 128, 500 -28 -10 -29 -11, 1000 -3 -12 -1 +13, 1500
+    // -29 -3 +18 +23; 28 x 28, 2500 -20 +2 +15 +7.  From 17 channels on -1 to -28 at any length.
+    if (!strided && q.nks == 1 && nb == 2 && q.copies[0] > 10 && p.cap * M > 1000 / q.ngroups * 256) return false;
     // Long lists of tiles that conv3's items of 384 pixels fit better than six of 64: data gradient of 64 -> 64 on 16 x 16 blocks
     // (18 x 18 results), 880 tiles 28.9 and 28.5 us, 1540 45.8 and 48.4, 2200 62.0 and 65.4.
     if (!strided && nb == 2 && M > 256 && M <= 384 && p.cap * M > 1200 * 256) return false;

@@ -1299,6 +1299,32 @@ def test_sparse_conv_item_shapes_of_the_lds_tiled_kernel(bh, bw, gh, gw, s, Cin,
         sb.set_tuning()
 
 
+@pytest.mark.parametrize("bh,bw,s,Cin,Cout,most", [
+    # the longest list, in blocks of 256 pixels, of a layer whose weights stay in LDS
+    (10, 10, 2, 48, 64, 1000), (10, 10, 2, 48, 32, 3000), (33, 33, 1, 16, 128, 500),
+    (12, 12, 2, 48, 64, 600), (12, 12, 2, 48, 32, 1000), (12, 12, 2, 32, 64, 1500), (16, 16, 2, 32, 64, 2000), (24, 24, 2, 48, 64, 2000),
+    (16, 16, 2, 48, 32, 6000), (16, 16, 2, 48, 96, None), (8, 8, 2, 48, 64, None), (16, 16, 1, 40, 80, 800), (16, 16, 1, 48, 96, 4000),
+    (16, 16, 1, 24, 80, None), (15, 15, 1, 64, 64, 3000), (33, 33, 1, 16, 64, 1000), (33, 33, 1, 24, 64, None)])
+def test_sparse_conv_long_lists_leave_the_resident_weights(bh, bw, s, Cin, Cout, most):
+    """Up to the line the kernel that keeps its weights in LDS, past it the LDS-tiled one, and one result of either."""
+    step("long lists %s" % ((bh, bw, s, Cin, Cout, most),))
+    r = gen.rng_for(5, bh * 1000 + Cin + Cout + s)
+    H, W = 2 * bh * s, 2 * bw * s
+    g_in, g_out, Ho, Wo = sb.geometry(H, W, 3, s, bh)
+    x = gen.activations(r, (1, H, W, Cin), "bf16")
+    w = gen.conv_weights(r, 3, 3, Cin, Cout, "bf16")
+    idx = np.array([[0, 0, 0], [0, 1, 1]], np.int32)
+    ref = orc.sparse_conv_tiled(x, idx, ogeom(g_in), ogeom(g_out), w, None, np.zeros((1, Ho, Wo, Cout)), stride=s)
+    d_x, wp = to_dev(x, "bf16"), sb.pack_weights(to_dev(w, "bf16"))
+    rows = (most or 20000) * 256 // (bh * bw)
+    for cap in (rows, rows + 1):
+        d_idx, d_cnt = dev_indices(idx, cap)
+        y = torch.zeros((1, Ho, Wo, Cout), dtype=torch.bfloat16, device="cuda")
+        name, = kernels(lambda: sb.sparse_conv(d_x, d_idx, d_cnt, g_in, g_out, wp, None, y, stride=s))
+        assert ("conv_wave_kernel" in name) == (most is None or cap == rows), (cap, name)
+        assert_close(to_host(y), ref, CONV_TOL["bf16"], "list bound %d" % cap)
+
+
 @pytest.mark.parametrize("dens", [1.0, 0.35])
 @pytest.mark.parametrize("Cin,Cout,kernel", [(32, 64, "conv16"), (40, 64, "conv_wave"), (16, 200, "conv3_pair")])
 def test_sparse_conv_more_tiles_than_workgroups(dens, Cin, Cout, kernel):
