@@ -554,10 +554,11 @@ def run_tune(args):
         out["unit_subtiles"].append(res)
     # (strided layers with 96 / 256 ... output channels run 128-pixel items only and have no such choice)
     # the last entry has 18 x 18 blocks (324 output pixels, as in a data gradient on 16 x 16 blocks): its two items are
-    # 384 and 256 pixels, one or two per block, and a 256-pixel item is taken as 6/5 of the ratio below
-    for (H, W, Cin, Cout, s_, bo_) in ((400, 352, 96, 96, 1, 16), (400, 352, 96, 192, 2, 16), (200, 176, 192, 192, 1, 16),
-                                       (396, 360, 64, 64, 1, 18)):
-        x = torch.randn((1, H, W, Cin), device=dev).to(torch.bfloat16)
+    # 384 and 256 pixels, one or two per block, and a 256-pixel item is taken as 6/5 of the ratio below; three maps, because
+    # a list bound of up to 948 of these blocks runs the kernel that keeps its weights in LDS
+    for (N, H, W, Cin, Cout, s_, bo_) in ((1, 400, 352, 96, 96, 1, 16), (1, 400, 352, 96, 192, 2, 16), (1, 200, 176, 192, 192, 1, 16),
+                                          (3, 396, 360, 64, 64, 1, 18)):
+        x = torch.randn((N, H, W, Cin), device=dev).to(torch.bfloat16)
         w = torch.from_numpy(gen.conv_weights(r, 3, 3, Cin, Cout, "bf16")).to(torch.bfloat16).to(dev)
         res = kt.conv3_items(x, w, stride=s_, block=bo_, counts=(8, 16, 32, 64, 96, 128, 192, 256, 320, 384, 512))
         # what the default cost ratio would have picked at each count (rounds of work over 256 CUs)
@@ -570,7 +571,7 @@ def run_tune(args):
             rb, rs = (n * 1 * ngroups + 255) // 256, (n * 2 * ngroups + 255) // 256
             picks.append("larger" if rb * 8 <= rs * cost else "smaller")
         res["faster"] = ["larger" if f == "256" else "smaller" for f in res["faster"]]
-        res.update({"shape": "%dx%dx%d->%d s%d, block %d" % (H, W, Cin, Cout, s_, bo_), "items": "384 / 256" if bo_ == 18 else "256 / 128",
+        res.update({"shape": "%s%dx%dx%d->%d s%d, block %d" % ("" if N == 1 else "%dx" % N, H, W, Cin, Cout, s_, bo_), "items": "384 / 256" if bo_ == 18 else "256 / 128",
                     "ms_larger": [round(v, 5) for v in res.pop("ms256")], "ms_smaller": [round(v, 5) for v in res.pop("ms128")],
                     "default_picks": picks})
         out["conv3_items"].append(res)

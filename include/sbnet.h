@@ -67,12 +67,13 @@ typedef struct {
 typedef struct {
     /* residual unit: cost of an 8 x 8 sub-tile in eighths of a 16 x 16 one; the size whose cost-weighted rounds of
        work over 256 workgroups are fewer is run (8 x 8: four times the items, a shorter latency chain each).
-       Lists whose bound costs at most one eighth more in 8 x 8 sub-tiles than one round of 16 x 16 ones run 8 x 8.
+       Lists whose bound costs at most one eighth more in 8 x 8 sub-tiles than one round of 16 x 16 ones run 8 x 8
+       (with a pre-activation: at least one eighth less).
        Default 3; 0 = always 8 x 8; 1000 = always 16 x 16 where the block allows it. */
     int unit_small_item_cost_eighths;
-    /* LDS-tiled 3x3 convolution (layers whose weights do not stay in LDS): cost of a 128-pixel work item in eighths of a 256-pixel one; the shape whose
-       cost-weighted rounds of work over 256 CUs are fewer is run.  Default 5; 0 = always 128-pixel items;
-       1000 = always 256-pixel items. */
+    /* LDS-tiled 3x3 convolution (layers whose weights do not stay in LDS): cost of a 128-pixel work item in eighths of a
+       256-pixel one; the shape whose cost-weighted rounds of work over 256 CUs are fewer is run.  Default 5;
+       0 = always 128-pixel items; 1000 = always 256-pixel items. */
     int conv3_small_item_cost_eighths;
     /* weight gradient: splits of the tile list used = min(launch's, n, f * sqrt(n)) for n active tiles, f given
        here for 3x3 and for 1x1 kernels.  Defaults 8 and 16. */
@@ -314,8 +315,8 @@ sbnet_status sbnet_block_flags(const void *mask, sbnet_dtype mask_dtype, int N, 
 /*
  * sbnet_sparse_conv fed by the block flags instead of the index list (Fig. 1 with the second half of
  * Sec. 3.1 moved into the consumer): the same y, bit for bit, as sbnet_sparse_conv with this cap on the
- * list those flags compact to, and that list and its count are written to indices / count for later calls.  Where the convolution
- * kernel can take flags (3x3, stride 1, 16 x 16 output blocks, 32 or 64 input channels, bf16 / f16, lists of 57 rows
+ * list those flags compact to, and that list and its count are written to indices / count for later calls.
+ * Where the convolution kernel can take flags (3x3, stride 1, 16 x 16 output blocks, 32 or 64 input channels, bf16 / f16, lists of 57 rows
  * or more) and no other kernel is the faster one (from 65 output channels on, at some lengths of the list) every
  * workgroup compacts them in its prologue while its weights arrive, which saves reduce_mask's second
  * launch; every other shape compacts the flags in a launch of its own and runs sbnet_sparse_conv.
