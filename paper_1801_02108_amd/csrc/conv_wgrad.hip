@@ -18,7 +18,7 @@
 // 8 x 8: 440 26.0 -> 16.3; 32 -> 32, 12 x 12, 2200 tiles 50.8 -> 20.5; 96 -> 96, 16 x 16, 440 40.2 -> 33.2.  1x1: 256 -> 64 on 165 tiles of
 // 18 x 18 15.0 -> 11.4, on 550 26.3 -> 22.6; 96 -> 24 on 550 23.7 -> 13.0.
 //
-// wgrad_mfma (3x3 on long lists, 3x3 and 1x1 with a stride of 2; BF16/F16, channel counts multiples of 8): a workgroup owns 64 input by 64
+// wgrad_mfma (long lists, 3x3 and 1x1 with a stride of 2; BF16/F16, channel counts multiples of 8): a workgroup owns 64 input by 64
 // output channels, one 32x32 block per wave with one fp32 accumulator per tap (nine, or one).  Tiles pass through LDS a few output
 // rows at a time (a "stage"), stored channel-major so that a lane's matrix operand (8 consecutive pixels of one
 // channel) is one aligned 16-byte read:
@@ -664,6 +664,7 @@ struct WgradPlan {
     bool mfma;
     int kh, s, nseg, nsplit, ncb, nob, CinP, CoutP;
     bool flat;               // 1x1 at stride 1: the tile as one run of pixels
+    bool run;                // ... by wgrad_run
     bool tile;               // wgrad_tile, with t
     TilePlan t;
     size_t part_bytes;
@@ -731,6 +732,16 @@ bool plan_wgrad(sbnet_dtype dt, int cap, int th, int tw, int Cin, int kh, int kw
         const long long px16 = ow <= 16 ? (oh + 7LL) / 8 * 8 * 16 : (oh + 3LL) / 4 * 4 * 32, px8 = (long long)q->t.slices * q->t.R * q->t.gp;
         if (p32 * px8 * 10 >= p64 * 4 * px16 * 8 && (long long)cap * oh * ow * p64 > 1000 * 256) q->tile = false;
     }
+    const long long p64 = (long long)((Cin + 63) / 64) * ((Cout + 63) / 64), px = (long long)th * tw;
+    // 1x1: past these lengths, in tiles of 256 pixels, several channel blocks read their operands from memory again, and wgrad_mfma
+    // with its two workgroups per CU waits less.  us by it and by wgrad_run, 16 x 16, 40 % of the bound active and all: 64 -> 96, 3500
+    // tiles 26.7 23.8, 60.3 60.2, 5000 38.0 35.6, 80.7 88.0, 8800 59.2 62.3, 135 170; 256 -> 256, 2200 80.1 78.2, 189 181, 3500 118 120,
+    // 281 292, 8800 293 286, 698 766; 160 -> 160, 1760 50.6 33.3, 105 113, 3500 83.5 92.8, 191 221; 512 -> 512, 300 42.4 34.7, 99 100,
+    // 700 90.8 92.6, 212 230, 2200 265 296, 638 816; 384 -> 384, 700 73.7 58.5, 186 189, 1200 130 122, 310 366.  At a tenth active wgrad_run
+    // is 5 to 30 % the faster everywhere.  One channel block (64 -> 64 47.9 45.0, 106 99 at 8800) and tiles that leave a tenth of
+    // wgrad_mfma's stages of 128 pixels empty (18 x 18, 128 -> 128, 5500 84.4 69.1, 190 174): wgrad_run at any length.
+    const long long most1 = p64 > 16 ? 700 : p64 > 4 ? 3000 : 4000;
+    q->run = q->flat && !(p64 >= 2 && px * 10 >= (px + 127) / 128 * 128 * 9 && (long long)cap * px > most1 * 256);
     if (q->tile) {
         q->s = q->nseg = 1;
         q->ncb = (Cin + 31) / 32;
@@ -747,9 +758,9 @@ bool plan_wgrad(sbnet_dtype dt, int cap, int th, int tw, int Cin, int kh, int kw
         q->nob = (Cout + 63) / 64;
         q->CinP = q->ncb * 64;
         q->CoutP = q->nob * 64;
-        // one workgroup per CU for 3x3 (its two stages take 100 KB of LDS) and wgrad_run (its four 128 KB); two for strided 1x1
-        // (70 KB), whose stages hold little matrix work and wait on memory: the second workgroup's loads fill that wait
-        int ns = (kh == 1 && !q->flat ? 512 : 256) / (q->ncb * q->nob);
+        // one workgroup per CU for 3x3 (its two stages take 100 KB of LDS) and wgrad_run (its four 128 KB); two for 1x1
+        // otherwise (70 KB), whose stages hold little matrix work and wait on memory: the second workgroup's loads fill that wait
+        int ns = (kh == 1 && !q->run ? 512 : 256) / (q->ncb * q->nob);
         ns = ns / 8 * 8;                                   // splits of one channel block share an XCD's L2 with the others
         if (ns < 8) ns = 8;
         q->nsplit = ns;
@@ -779,7 +790,7 @@ void launch_mfma(const WgradParams &p, hipStream_t s) {
 
 template <int DT>
 void launch_mfma_dt(const WgradPlan &q, const WgradParams &p, hipStream_t s) {
-    if (q.kh == 1 && q.flat) {
+    if (q.run) {
         constexpr int bytes = kRunDepth * kRunStage;
         static_assert(bytes >= 4 * 4096 * 4 && bytes <= 160 * 1024, "the stages; the four waves' sums");
         (void)hipFuncSetAttribute((const void *)wgrad_run<DT>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
@@ -798,6 +809,8 @@ void launch_mfma_dt(const WgradPlan &q, const WgradParams &p, hipStream_t s) {
         else if (q.s == 1) launch_mfma<DT, 3, 1, 2>(p, s);
         else if (q.nseg == 1) launch_mfma<DT, 3, 2, 1>(p, s);
         else launch_mfma<DT, 3, 2, 2>(p, s);
+    } else if (q.flat) {
+        launch_mfma<DT, 1, 1, 1>(p, s);
     } else if (q.nseg == 1) {
         launch_mfma<DT, 1, 2, 1>(p, s);
     } else {
@@ -842,6 +855,12 @@ extern "C" sbnet_status sbnet_conv_on_tiles_backward_weights(const void *tiles_i
     p.split_factor = taps == 1 ? tune.wgrad_split_factor_1x1 : tune.wgrad_split_factor_3x3;
     p.x_tile_bytes = (uint32_t)((size_t)th * tw * Cin * 2);
     p.g_tile_bytes = (uint32_t)((size_t)p.oh * p.ow * Cout * 2);
+    if (q.mfma && q.flat && !q.run) {
+        // 1x1 at stride 1 pairs pixel with pixel, whatever the tile's shape: wgrad_mfma sees rows of 16 pixels
+        // (the tile sizes in bytes stay the true ones, so the pixels past the end of the last row read as zeros)
+        p.th = p.oh = (th * tw + 15) / 16;
+        p.tw = p.ow = 16;
+    }
     if (cap > 0) {
         if (q.mfma || q.tile) {
             if (dtype == SBNET_BF16) launch_mfma_dt<SBNET_BF16>(q, p, s);

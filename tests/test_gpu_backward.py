@@ -189,6 +189,36 @@ def test_sparse_conv_gradients_end_to_end():
         assert_close(to_host(dw), ref_dw, 2e-5, "sparse conv dL/dw")
 
 
+@pytest.mark.parametrize("oh,ow,Cin,Cout,k,dtype,most,kernel", [
+    # the longest list that the kernel takes which is faster on short ones
+    (16, 16, 64, 72, 1, "bf16", 4000, "wgrad_run"),
+    (31, 33, 136, 64, 1, "f16", 1000, "wgrad_run"),         # 1023 pixels: one short of a row of 16
+    (16, 16, 160, 160, 1, "bf16", 3000, "wgrad_run"),       # nine blocks of 64 x 64 channels
+    (16, 16, 264, 264, 1, "bf16", 700, "wgrad_run"),        # 25
+    (16, 16, 64, 64, 1, "bf16", None, "wgrad_run"),         # one block
+    (18, 18, 64, 72, 1, "bf16", None, "wgrad_run"),         # stages of 128 pixels would be a sixth padding
+    (16, 16, 64, 64, 3, "f16", 1000, "wgrad_tile"),
+    (24, 24, 64, 64, 3, "bf16", None, "wgrad_tile"),
+])
+def test_weight_gradient_kernel_by_list_bound(oh, ow, Cin, Cout, k, dtype, most, kernel):
+    step("weight gradient, list bound %s" % ((oh, ow, Cin, Cout, k, dtype, most),))
+    r = gen.rng_for(8, oh * 1000 + Cin + Cout + k)
+    B, rows = 5, most or 6000
+    x = gen.activations(r, (B, oh + k - 1, ow + k - 1, Cin), dtype)
+    g = gen.activations(r, (B, oh, ow, Cout), dtype)
+    xd = torch.zeros((rows + 1,) + x.shape[1:], dtype=TORCH_DT[dtype], device="cuda")
+    gd = torch.zeros((rows + 1,) + g.shape[1:], dtype=TORCH_DT[dtype], device="cuda")
+    xd[:B], gd[:B] = to_dev(x, dtype), to_dev(g, dtype)
+    cnt = torch.tensor([B], dtype=torch.int32).cuda()
+    dw = torch.empty((k, k, Cin, Cout), dtype=torch.float32).cuda()
+    want = orc.conv_valid_backward_weights(x, g, k, k)
+    for cap in (rows, rows + 1):
+        names = kernels(lambda: sb.conv_on_tiles_backward_weights(xd[:cap], gd[:cap], cnt, k, out=dw))
+        assert (kernel if most is None or cap == rows else "wgrad_mfma") in names[0], (cap, names)
+        # fp32 accumulation of exact products over B * oh * ow terms in a tree of partial sums
+        assert_close(to_host(dw), want, 2e-5, "list bound %d" % cap)
+
+
 @pytest.mark.parametrize("n,th,Cin,Cout,s", [(2200, 18, 64, 64, 1), (220, 18, 64, 64, 1), (550, 33, 64, 96, 2)])
 def test_gradients_at_full_size_sampled(n, th, Cin, Cout, s):
     """The tile counts and shapes bench.py times (all 2200 blocks and 10 % of them for the headline layer, the dense
