@@ -726,11 +726,14 @@ bool plan_wgrad(sbnet_dtype dt, int cap, int th, int tw, int Cin, int kh, int kw
         // results are two to four times as many bytes): us by it and by wgrad_tile, 440 tiles 24.7 and 20.4, 2200 49.6 and
         // 54.1; 128 -> 128, 165 tiles 27.5 and 25.6, 440 42.6 and 46.1; 256 -> 256, 60 tiles 37.7 and 37.7, 440 125 and 155.  The
         // line lies at 1000 tiles of 256 pixels by the number of 64 x 64 blocks.  Where more than a fifth of its work is
-        // padding wgrad_tile wins at any length (2200 tiles: 96 -> 96 147 and 116, 32 -> 32 46.7 and 24.0, 64 -> 64 of 8 x 8
-        // 35.2 and 22.7).
+        // padding wgrad_tile wins on lists up to four times as long (224 -> 224, 16 x 16, 110 tiles 47.6 and 48.8, at 44 of them
+        // 34.4 and 31.5; 440 130 and 143, 62.4 and 67.1; 2200 570 and 625), and where nearly a quarter is at any length (2200 tiles:
+        // 96 -> 96 147 and 116, 32 -> 32 46.7 and 24.0, 64 -> 64 of 8 x 8 35.2 and 22.7, of 24 x 24 142 and 135; 512 -> 512, 12 x 12,
+        // 2126 and 2112).
         const long long p64 = (long long)((Cin + 63) / 64) * ((Cout + 63) / 64), p32 = (long long)((Cin + 31) / 32) * ((Cout + 31) / 32);
         const long long px16 = ow <= 16 ? (oh + 7LL) / 8 * 8 * 16 : (oh + 3LL) / 4 * 4 * 32, px8 = (long long)q->t.slices * q->t.R * q->t.gp;
-        if (p32 * px8 * 10 >= p64 * 4 * px16 * 8 && (long long)cap * oh * ow * p64 > 1000 * 256) q->tile = false;
+        const long long work8 = p32 * px8 * 100, work16 = p64 * 4 * px16, most = work8 >= work16 * 80 ? 1000 : 4000;
+        if (work8 >= work16 * 76 && (long long)cap * oh * ow * p64 > most * 256) q->tile = false;
     }
     const long long p64 = (long long)((Cin + 63) / 64) * ((Cout + 63) / 64), px = (long long)th * tw;
     // 1x1: past these lengths, in tiles of 256 pixels, several channel blocks read their operands from memory again, and wgrad_mfma

@@ -197,6 +197,7 @@ def test_sparse_conv_gradients_end_to_end():
     (16, 16, 264, 264, 1, "bf16", 700, "wgrad_run"),        # 25
     (16, 16, 64, 64, 1, "bf16", None, "wgrad_run"),         # one block
     (18, 18, 64, 72, 1, "bf16", None, "wgrad_run"),         # stages of 128 pixels would be a sixth padding
+    (16, 16, 224, 224, 3, "bf16", 250, "wgrad_tile"),
     (16, 16, 64, 64, 3, "f16", 1000, "wgrad_tile"),
     (24, 24, 64, 64, 3, "bf16", None, "wgrad_tile"),
 ])
