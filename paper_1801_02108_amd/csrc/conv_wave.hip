@@ -24,8 +24,8 @@
 //     all its weights beside eight buffers), the even columns of a row before its odd ones.  conv3 -> this: 800 x 704 to
 //     400 x 352, blocks of 16, 64 -> 96, 5 % active 9.1 -> 7.4, 30 % 18.3 -> 12.5; 32 -> 32, all 17.6 -> 11.7.
 // What bounds it at many items (1600 x 1408, half of all blocks of 12, 64 -> 64, counters): matrix cores busy 38 % of the time,
-// LDS 44 (11 of them bank conflicts), the address unit (copies of 64-byte pieces, stores) 40, vector
-// instructions 41, beside each other; with fewer than two items per wave the latency of an item and the copy of the weights.
+// LDS 45 (11 of them bank conflicts), the address unit (copies of 64-byte pieces, stores) 41, vector
+// instructions 42, beside each other; with fewer than two items per wave the latency of an item and the copy of the weights.
 // At stride 1 the sum over (chunk of 32 channels, tap, 16 channels) runs in the order of conv3's 32-channel chunks: same bits.  At
 // stride 2 it runs over (chunk of 16 channels, tap), conv3's order with 16-channel chunks.
 #include "conv_common.h"
@@ -597,6 +597,14 @@ static bool conv_wave_plan(sbnet_dtype dt, bool fused, const ConvParams &p, Conv
     // 35 x 35, 8 -> 64, 1000 -26 -14 -4 -2, 1500 -6 -10 0 +13, 2500 -1 +4 +18 +28; 33 x 33, 16 -> 128, 500 -28 -10 -29 -11, 1000 -3 -12 -1 +13, 1500
     // -29 -3 +18 +23; 28 x 28, 2500 -20 +2 +15 +7.  From 17 channels on -1 to -28 at any length.
     if (!strided && q.nks == 1 && nb == 2 && q.copies[0] > 10 && p.cap * M > 1000 / q.ngroups * 256) return false;
+    // Output channels that do not fill their blocks, and little matrix work: the pieces of a line of memory are written apart (by two
+    // groups of workgroups, or by two blocks of which the last is 8 or 24 wide).  Change in % at 10, 40, 100 %, same units: 8 -> 120, 12 x 12, 600 -18 -17 -11, 1000 -24 -18 +22,
+    // 1500 -21 +6 +45, 2500 -31 +29 +62; 8 -> 104, 16 x 16, 600 -18 -5 -1, 1000 -19 -19 +12, 1500 -20 +1 +22; 24 -> 56, 16 x 16, 2200 -5 0
+    // +21, 5000 +7 +17 +22; 24 -> 104, 14 x 14, 1000 -9 +5 +25; 16 -> 112, 14 x 14, 1000 -26 -16 +22, 2500 -20 +22 +47; one group of 96: 16 -> 88,
+    // 12 x 12, 1000 -40 -12 -1, 2500 -16 +9 +12.  Wins still: 8 x 8 (24 -> 56, 2500 -8 -20 -25), blocks that are filled (24 -> 64, 16 x 16,
+    // 2200 -8 -20 -9; 16 -> 128, 20 x 20, 2500 -28 -19 -23) and from 33 input channels on (48 -> 104, 12 x 12, 2500 -24 -16 -16).
+    if (!strided && nb == 2 && q.nks <= 2 && (p.Cout % 16 || (p.Cout % 32 && q.ngroups == 2)) && M > 64 && p.cap * M > 800 * 256) return false;
+    if (!strided && nb == 3 && q.nks == 1 && p.Cout % 16 && M > 64 && p.cap * M > 1500 * 256) return false;
     // Long lists of tiles that conv3's items of 384 pixels fit better than six of 64: data gradient of 64 -> 64 on 16 x 16 blocks
     // (18 x 18 results), 880 tiles 28.9 and 28.5 us, 1540 45.8 and 48.4, 2200 62.0 and 65.4.
     if (!strided && nb == 2 && M > 256 && M <= 384 && p.cap * M > 1200 * 256) return false;

@@ -1304,7 +1304,9 @@ def test_sparse_conv_item_shapes_of_the_lds_tiled_kernel(bh, bw, gh, gw, s, Cin,
     (10, 10, 2, 48, 64, 1000), (10, 10, 2, 48, 32, 3000), (33, 33, 1, 16, 128, 500),
     (12, 12, 2, 48, 64, 600), (12, 12, 2, 48, 32, 1000), (12, 12, 2, 32, 64, 1500), (16, 16, 2, 32, 64, 2000), (24, 24, 2, 48, 64, 2000),
     (16, 16, 2, 48, 32, 6000), (16, 16, 2, 48, 96, None), (8, 8, 2, 48, 64, None), (16, 16, 1, 40, 80, 800), (16, 16, 1, 48, 96, 4000),
-    (16, 16, 1, 24, 80, None), (15, 15, 1, 64, 64, 3000), (33, 33, 1, 16, 64, 1000), (33, 33, 1, 24, 64, None)])
+    (16, 16, 1, 24, 80, None), (15, 15, 1, 64, 64, 3000), (33, 33, 1, 16, 64, 1000), (33, 33, 1, 24, 64, None),
+    (12, 12, 1, 8, 120, 800), (16, 16, 1, 24, 56, 800), (14, 14, 1, 16, 112, 800), (12, 12, 1, 16, 88, 1500),
+    (20, 20, 1, 16, 128, None), (16, 16, 1, 40, 56, None), (8, 8, 1, 24, 56, None)])
 def test_sparse_conv_long_lists_leave_the_resident_weights(bh, bw, s, Cin, Cout, most):
     """Up to the line the kernel that keeps its weights in LDS, past it the LDS-tiled one, and one result of either."""
     step("long lists %s" % ((bh, bw, s, Cin, Cout, most),))
