@@ -916,8 +916,8 @@ static sbnet_status bneck_entry(const char *who, bool fused, const void *in, voi
     // ones can win an eighth (one round against three: 8 eighths to 9) on lists near their bound and lose the launch on all
     // others, so only the 8 x 8 variant is launched.  192 blocks of 16 x 16, us with two launches -> with one: 64/16 at
     // 19 active blocks 8.4 -> 6.7, 128/32 at 115 12.2 -> 10.5, 256/64 at 58 11.6 -> 9.7, at 131 19.1 -> 18.2, at 173 18.9
-    // -> 19.2, at 192 19.3 -> 19.1; a bound of 168, 70 %, 90 % and all active 18.5 -> 16.1, 20.2 -> 21.0, 20.2 -> 21.9; a stage of six units (143 blocks, 36 active) 70.6 -> 62.7.  With a pre-activation an
-    // 8 x 8 item costs more than three eighths (256/64 at 192: 24.5 -> 25.8): there the line is two rounds, up to which
+    // -> 19.2, at 192 19.3 -> 19.1; a bound of 168, 70 %, 90 % and all active 18.5 -> 16.1, 20.2 -> 21.0, 20.2 -> 21.9;
+    // a stage of six units (143 blocks, 36 active) 70.6 -> 62.7.  With a pre-activation an 8 x 8 item costs more than three eighths (256/64 at 192: 24.5 -> 25.8): there the line is two rounds, up to which
     // 16 x 16 items never win.
     const int cost8 = tuning().unit_small_item_cost_eighths;
     const long long rounds8 = ((long long)cap * (p.oh / 8) * (p.ow / 8) + 255) / 256;
